@@ -3,24 +3,21 @@
 // of a small two-layer perceptron on the hidden state, the anchor flag f(h) > thr and the
 // per-anchor sponsor budget of TA-Learned (fixed B) or TA-LearnRank (scale * f(h)).
 //
-// The first layer is a [positions x d_model] x [d_model x m] contraction: bf16 MFMA
-// (v_mfma_f32_32x32x16_bf16), fp32 accumulation.  It is computed as W1 . h^T so that a lane
-// owns ONE position (a column of the accumulator tile) and 16 hidden units of each tile: GELU,
-// the product with W2 and the sum over the hidden units are then register arithmetic, followed
-// by one half-wave exchange.  A workgroup owns 256 consecutive positions and all m hidden
-// units; a wavefront owns 64 positions x (32 * HT) hidden units.  h and W1 stream through LDS
-// in slices of 32 input features (64 bytes per row), a ring of three buffers filled by direct
-// global->LDS loads two slices ahead, 16-byte chunks XOR-swizzled by row for conflict-free
-// fragment reads.  W1 is re-read by every workgroup (from the L2: it is at most 16 MB, 1 MB for the usual
-// d_model = 4096, m = 128); per workgroup that is m / positions of the bytes of h.
+// The first layer is a [positions x d_model] x [d_model x m] contraction on the matrix cores (bf16 MFMA,
+// fp32 accumulation).  It is computed as W1 . h^T, so that an accumulator tile has hidden units as rows and
+// positions as columns: GELU, the product with W2 and the sum over the hidden units then stay with one
+// position.  h and W1 stream through LDS, 64 input features (one 128-byte line per row) at a time, by direct
+// global->LDS loads ahead of their use, 16-byte chunks XOR-swizzled by row for conflict-free fragment reads.
+// Two forms (below), by the number of positions: one wavefront per share of the features for few positions,
+// shared slices for many.  W1 is re-read by every workgroup (from the L2: it is at most 16 MB, 1 MB for the
+// usual d_model = 4096, m = 128).
 //
-// The same kernel, in its second mode, is the embedding-based detector (Sec. 3.2 "Anchor detection",
+// The same kernels, in their second mode, are the embedding-based detector (Sec. 3.2 "Anchor detection",
 // third instantiation; TA-Fast-Embedding): W1 holds the anchor-concept embeddings, the contraction
 // gives every dot product x . c_e, the squared norms of both operands are summed from the very
 // fragments the MFMA consumes (v_dot2_f32_bf16), and the epilogue takes the largest cosine and
 // compares it with the threshold.
 #include <math.h>
-
 
 #include "ta_internal.h"
 #include "ta_score_common.h"
@@ -29,7 +26,7 @@ namespace ta {
 
 namespace {
 
-constexpr int DT_KS = 32;                        // input features per slice
+constexpr int DT_KS = 64;                        // input features per slice
 
 struct DetectArgs {
     const uint4* h;
@@ -93,15 +90,12 @@ __device__ __forceinline__ float add_squares(uint4 v, float acc)
 }
 
 enum { MODE_MLP = 0, MODE_COSINE = 1 };
-// Slice buffers of a workgroup.  Three (loads two slices ahead), except where two leave room for a third
-// resident workgroup per compute unit (24 KB buffers of the 128-unit detector: 881 us against 903), which
-// the long streams of the learned detector gain more from than from the deeper ring (the 256-unit
-// detector, one large workgroup per compute unit either way, loses 8 % with two).
-constexpr int detect_ring(int M, int MODE) { return (MODE == MODE_MLP && M == 128) ? 2 : 3; }
 
+// ---- shared form: the wavefronts of a workgroup share every slice ---------------------------------------
 // TW: wavefront rows over the positions (64 TW positions per workgroup); HT: 32-unit hidden tiles
-// per wavefront; MH: wavefront columns over the hidden units (m = 32 HT MH); MODE: which epilogue
-template <int TW, int HT, int MH, int MODE>
+// per wavefront; MH: wavefront columns over the hidden units (m = 32 HT MH); MODE: which epilogue; DT_RING: slice
+// buffers, loads run DT_RING - 1 slices ahead
+template <int TW, int HT, int MH, int MODE, int DT_RING>
 __global__ void __launch_bounds__(64 * TW * MH, 2)
 detect_kernel(DetectArgs a)
 {
@@ -109,14 +103,13 @@ detect_kernel(DetectArgs a)
     constexpr int THREADS = 64 * TW * MH;
     constexpr int M = 32 * HT * MH;
     constexpr int WAVES = TW * MH;
-    constexpr int NI_H = DT_TOKENS / 16;                   // 1 KB loads per slice: h (16 rows each)
-    constexpr int NI_W = M / 16;                           //                      W1
+    constexpr int NI_H = DT_TOKENS / 8;                    // 1 KB loads per slice: h (8 rows each)
+    constexpr int NI_W = M / 8;                            //                      W1
     constexpr int LH = NI_H / WAVES;                       // per wavefront
     constexpr int LW = (NI_W + WAVES - 1) / WAVES;         // (wraps: a few duplicate loads when M is small)
     constexpr int LPS = LH + LW;
-    constexpr int H_BYTES = DT_TOKENS * 64;                // bytes of the h part of a buffer
-    constexpr int BUF_BYTES = H_BYTES + M * 64;
-    constexpr int DT_RING = detect_ring(M, MODE);
+    constexpr int H_BYTES = DT_TOKENS * 128;               // bytes of the h part of a buffer
+    constexpr int BUF_BYTES = H_BYTES + M * 128;
 
     extern __shared__ uint4 s_buf[];                       // DT_RING buffers, then W2 as floats
     float* s_w2 = reinterpret_cast<float*>(reinterpret_cast<char*>(s_buf) + DT_RING * BUF_BYTES);
@@ -128,7 +121,7 @@ detect_kernel(DetectArgs a)
     const int c32 = lane & 31, hf = lane >> 5;
     const int tw = wave % TW, mh = wave / TW;              // position block of 64, hidden column
     const int64_t tile0 = (int64_t)blockIdx.x * DT_TOKENS;
-    const int nstages = a.dm / DT_KS;
+    const int nstages = (a.dm + DT_KS - 1) / DT_KS;        // (the last slice may be half)
 
     if constexpr (MODE == MODE_MLP)
         for (int j = tid; j < M; j += THREADS) s_w2[j] = bf16_bits_to_float(a.W2[j]);
@@ -140,33 +133,35 @@ detect_kernel(DetectArgs a)
 #pragma unroll
     for (int j = 0; j < LH; ++j) {
         const int ins = wave + WAVES * j;
-        const int row = ins * 16 + (lane >> 2);
+        const int row = ins * 8 + (lane >> 3);
         int64_t t = tile0 + row;
         t = t < a.total ? t : a.total - 1;                 // stay inside the tensor; never stored
-        const int chunk = (lane & 3) ^ ((row >> 2) & 3);
+        const int chunk = (lane & 7) ^ (row & 7);
         off_h[j] = (uint32_t)((t - tile0) * a.h_row_bytes + chunk * 16);
         ins_h[j] = ins;
     }
 #pragma unroll
     for (int j = 0; j < LW; ++j) {
         const int ins = (wave + WAVES * j) % NI_W;
-        const int row = ins * 16 + (lane >> 2);
-        const int chunk = (lane & 3) ^ ((row >> 2) & 3);
+        const int row = ins * 8 + (lane >> 3);
+        const int chunk = (lane & 7) ^ (row & 7);
         const int src_row = row < a.wrows ? row : a.wrows - 1;   // missing rows repeat the last one
         off_w[j] = (uint32_t)(src_row * a.dm * 2 + chunk * 16);
         ins_w[j] = ins;
     }
+    const uint32_t half_back = ((lane & 7) ^ (lane >> 3)) >= 4 ? 64u : 0u;   // half a slice: the second half repeats the first
     const char* hbase = reinterpret_cast<const char*>(a.h) + tile0 * a.h_row_bytes;
     const char* wbase = reinterpret_cast<const char*>(a.W1);
     const auto issue = [&](int s) {
         const uint32_t dst = lds0 + (uint32_t)(s % DT_RING) * BUF_BYTES;
         const char* hs = hbase + (size_t)s * (DT_KS * 2);
         const char* ws = wbase + (size_t)s * (DT_KS * 2);
+        const uint32_t back = s * DT_KS + 32 >= a.dm ? half_back : 0u;
 #pragma unroll
-        for (int j = 0; j < LH; ++j) dma16(hs, off_h[j], __builtin_amdgcn_readfirstlane(dst + ins_h[j] * 1024));
+        for (int j = 0; j < LH; ++j) dma16(hs, off_h[j] - back, __builtin_amdgcn_readfirstlane(dst + ins_h[j] * 1024));
 #pragma unroll
         for (int j = 0; j < LW; ++j)
-            dma16(ws, off_w[j], __builtin_amdgcn_readfirstlane(dst + H_BYTES + ins_w[j] * 1024));
+            dma16(ws, off_w[j] - back, __builtin_amdgcn_readfirstlane(dst + H_BYTES + ins_w[j] * 1024));
     };
     const auto wait_but = [](int k) {                      // at most k later slices outstanding
         switch (k) {
@@ -181,19 +176,19 @@ detect_kernel(DetectArgs a)
     for (int s = 0; s < DT_RING - 1; ++s)
         if (s < nstages) issue(s);
 
-    // fragment slots of this lane inside a buffer (16-byte units), for the two MFMA steps of a slice
-    int slot_h[2][2], slot_w[HT][2];
+    // fragment slots of this lane inside a buffer (16-byte units), for the four MFMA steps of a slice
+    int slot_h[2][4], slot_w[HT][4];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
+    for (int ks = 0; ks < 4; ++ks) {
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt) {
             const int row = 64 * tw + 32 * tt + c32;
-            slot_h[tt][ks] = row * 4 + ((2 * ks + hf) ^ ((row >> 2) & 3));
+            slot_h[tt][ks] = row * 8 + ((2 * ks + hf) ^ (row & 7));
         }
 #pragma unroll
         for (int ht = 0; ht < HT; ++ht) {
             const int row = 32 * (mh * HT + ht) + c32;
-            slot_w[ht][ks] = H_BYTES / 16 + row * 4 + ((2 * ks + hf) ^ ((row >> 2) & 3));
+            slot_w[ht][ks] = H_BYTES / 16 + row * 8 + ((2 * ks + hf) ^ (row & 7));
         }
     }
 
@@ -215,7 +210,8 @@ detect_kernel(DetectArgs a)
         if (s + DT_RING - 1 < nstages) issue(s + DT_RING - 1);
         const uint4* buf = s_buf + (size_t)(s % DT_RING) * (BUF_BYTES / 16);
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
+        for (int ks = 0; ks < 4; ++ks) {
+            if (ks == 2 && s * DT_KS + 32 >= a.dm) break;   // uniform
             uint4 hraw[2], wraw[HT];
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) hraw[tt] = buf[slot_h[tt][ks]];
@@ -341,31 +337,292 @@ detect_kernel(DetectArgs a)
     }
 }
 
-template <int TW, int HT, int MH, int MODE>
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// ---- split form: every wavefront contracts its own share of the features ------------------------------------
+// For few positions, and for few hidden units: no workgroup barrier and no shared slice in the loop.  A wavefront has
+// a ring of R steps of its own in LDS (64 features of the tile's positions and of all hidden rows, filled by direct
+// loads of whole 128-byte lines: with 64-byte pieces the same kernel took 24 instead of 19 us at 4096 positions and 128
+// units, and loading the operand fragments straight into registers, where neighbouring lanes lie in different rows,
+// 40 us), and the partial sums of the WV wavefronts meet once, in LDS, after the last step.
+// PT: 16-position tiles of a workgroup; NT: 16-unit tiles of the hidden layer (concepts); WV wavefronts, each of which
+// contracts every WV-th step of 64 features; R: steps in flight per wavefront
+template <int PT, int NT, int WV, int R>
+struct SplitShape {
+    static constexpr int POS = 16 * PT, M = 16 * NT, THREADS = 64 * WV;
+    static constexpr int STEP_UNITS = (PT + NT) * 128;     // 16-byte units of a step
+    static constexpr int RING_UNITS = WV * R * STEP_UNITS;
+    static constexpr int TILE_UNITS = WV * 4 * POS;        // partial sums of one tile of hidden units, every wavefront's
+    // tiles exchanged per round: as many as the ring's memory holds
+    static constexpr int CH = RING_UNITS >= NT * TILE_UNITS ? NT : (RING_UNITS >= NT / 2 * TILE_UNITS ? (NT + 1) / 2 : (NT + 3) / 4);
+    static constexpr int UNITS = RING_UNITS > CH * TILE_UNITS ? RING_UNITS : CH * TILE_UNITS;
+    static constexpr int LDS_BYTES = UNITS * 16 + (M + THREADS + WV * M + WV * POS) * 4;
+};
+
+template <int PT, int NT, int WV, int R, int MODE>
+__global__ void __launch_bounds__(64 * WV)
+detect_split_kernel(DetectArgs a)
+{
+    using S = SplitShape<PT, NT, WV, R>;
+    constexpr int POS = S::POS, M = S::M, THREADS = S::THREADS, LPS = 2 * (PT + NT);
+    static_assert((R - 1) * LPS <= 63, "vmcnt range");
+    extern __shared__ uint4 s_buf[];                       // step rings, then the partial sums
+    float* s_w = reinterpret_cast<float*>(s_buf + S::UNITS);   // output weights, or reciprocal norms of the concepts
+    float* s_part = s_w + M;
+    float* s_cc = s_part + THREADS;                        // cosine mode: squared norms per wavefront
+    float* s_xx = s_cc + WV * M;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, grp = lane >> 4;
+    const int64_t tile0 = (int64_t)blockIdx.x * POS;
+    const int nsteps = (a.dm + 63) >> 6;                   // (the last one may be half a step)
+    const int mine = nsteps > wave ? (nsteps - wave + WV - 1) / WV : 0;
+
+    // A load instruction brings 8 rows x 128 bytes (one line), eight neighbouring lanes per row, chunks XOR-swizzled by row
+    uint32_t off[LPS];
+    const int lrow = lane >> 3, lchunk = (lane & 7) ^ lrow;
+    const uint32_t half_back = lchunk >= 4 ? 64u : 0u;     // half a step: the second half repeats the first
+#pragma unroll
+    for (int p = 0; p < 2 * PT; ++p) {
+        int64_t t = tile0 + 8 * p + lrow;
+        t = t < a.total ? t : a.total - 1;                 // stay inside the tensor; never stored
+        off[p] = (uint32_t)((t - tile0) * a.h_row_bytes + lchunk * 16);
+    }
+#pragma unroll
+    for (int j = 0; j < 2 * NT; ++j) {
+        const int row = 8 * j + lrow;
+        off[2 * PT + j] = (uint32_t)((row < a.wrows ? row : a.wrows - 1) * a.dm * 2 + lchunk * 16);   // missing rows repeat the last one
+    }
+    const char* hbase = reinterpret_cast<const char*>(a.h) + tile0 * a.h_row_bytes;
+    const char* wbase = reinterpret_cast<const char*>(a.W1);
+    uint4* ring = s_buf + wave * (R * S::STEP_UNITS);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)ring;
+    const auto half = [&](int i) { return 64 * (wave + WV * i) + 32 >= a.dm; };
+    const auto issue = [&](int i) {
+        const uint32_t dst = lds0 + (uint32_t)(i % R) * (S::STEP_UNITS * 16);
+        const size_t at = (size_t)(wave + WV * i) * 128;
+        const uint32_t back = half(i) ? half_back : 0u;
+#pragma unroll
+        for (int j = 0; j < LPS; ++j)
+            dma16((j < 2 * PT ? hbase : wbase) + at, off[j] - back, __builtin_amdgcn_readfirstlane(dst + j * 1024));
+    };
+    // this lane's fragments inside a 2 KB tile of 16 rows
+    const int slot0 = r16 * 8 + (grp ^ (r16 & 7)), slot1 = r16 * 8 + ((4 + grp) ^ (r16 & 7));
+
+    f32x4 acc[PT][NT];
+#pragma unroll
+    for (int p = 0; p < PT; ++p)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[p][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    float xx[PT], cc[NT];                                  // cosine mode: squared norms, this lane's share
+#pragma unroll
+    for (int p = 0; p < PT; ++p) xx[p] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) cc[j] = 0.0f;
+
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+        if (i < mine) issue(i);
+    const auto step = [&](int i, bool more) {
+        const uint4* buf = ring + (i % R) * S::STEP_UNITS;
+        uint4 f[2][PT + NT];
+#pragma unroll
+        for (int j = 0; j < PT + NT; ++j) {
+            f[0][j] = buf[j * 128 + slot0];
+            f[1][j] = buf[j * 128 + slot1];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the fragments are in registers: the buffer is free
+        const bool whole = !half(i);
+        if (more) issue(i + R);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if (s == 1 && !whole) break;                   // uniform
+#pragma unroll
+            for (int j = 0; j < PT + NT; ++j) asm volatile("" : "+v"(f[s][j].x), "+v"(f[s][j].y), "+v"(f[s][j].z), "+v"(f[s][j].w));
+            if constexpr (MODE == MODE_COSINE) {
+#pragma unroll
+                for (int p = 0; p < PT; ++p) xx[p] = add_squares(f[s][p], xx[p]);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) cc[j] = add_squares(f[s][PT + j], cc[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int p = 0; p < PT; ++p)               // rows: hidden units of the tile, columns: positions
+                    acc[p][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(f[s][PT + j]), as_frag(f[s][p]), acc[p][j], 0, 0, 0);
+        }
+    };
+    int i = 0;
+    for (; i + R < mine; ++i) {
+        __builtin_amdgcn_s_waitcnt(vm_imm((R - 1) * LPS)); // step i is in; R - 1 later ones are on their way
+        asm volatile("" ::: "memory");
+        step(i, true);
+    }
+    __builtin_amdgcn_s_waitcnt(vm_imm(0));
+    asm volatile("" ::: "memory");
+    for (; i < mine; ++i) step(i, false);
+
+    __syncthreads();                                       // every wavefront is done with its ring
+    if constexpr (MODE == MODE_MLP)
+        for (int j = tid; j < M; j += THREADS) s_w[j] = bf16_bits_to_float(a.W2[j]);
+    // ---- the wavefronts' partial sums meet in LDS, CH tiles at a time; a thread owns one position and every
+    // (THREADS / POS)-th quad of hidden units of each round
+    if constexpr (MODE == MODE_COSINE) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            float c = cc[j];
+            c += __shfl_xor(c, 16);
+            c += __shfl_xor(c, 32);
+            if (grp == 0) s_cc[wave * M + 16 * j + r16] = c;
+        }
+#pragma unroll
+        for (int p = 0; p < PT; ++p) {
+            float x = xx[p];
+            x += __shfl_xor(x, 16);
+            x += __shfl_xor(x, 32);
+            if (grp == 0) s_xx[wave * POS + 16 * p + r16] = x;
+        }
+        __syncthreads();
+        for (int j = tid; j < M; j += THREADS) {
+            float c = 0.0f;
+#pragma unroll
+            for (int w = 0; w < WV; ++w) c += s_cc[w * M + j];
+            s_w[j] = c > 0.0f ? 1.0f / sqrtf(c) : 0.0f;
+        }
+    }
+    const int pos = tid % POS, q0 = tid / POS;
+    float part = MODE == MODE_COSINE ? -INFINITY : 0.0f;
+    float4* s_red = reinterpret_cast<float4*>(s_buf);      // [wave][quad of units][position]
+    constexpr int CH = S::CH;
+    static_assert(NT % CH == 0, "whole rounds");
+#pragma unroll
+    for (int j0 = 0; j0 < NT; j0 += CH) {
+        if (j0) __syncthreads();                           // the previous round has been read
+#pragma unroll
+        for (int j = 0; j < CH; ++j)
+#pragma unroll
+            for (int p = 0; p < PT; ++p) {
+                const f32x4 v = acc[p][j0 + j];
+                s_red[(wave * CH * 4 + 4 * j + grp) * POS + 16 * p + r16] = make_float4(v[0], v[1], v[2], v[3]);
+            }
+        __syncthreads();
+        for (int q = q0; q < 4 * CH; q += THREADS / POS) {
+            float4 z = s_red[q * POS + pos];
+#pragma unroll
+            for (int w = 1; w < WV; ++w) {
+                const float4 v = s_red[(w * CH * 4 + q) * POS + pos];
+                z.x += v.x; z.y += v.y; z.z += v.z; z.w += v.w;
+            }
+            const float4 wt = *reinterpret_cast<const float4*>(&s_w[16 * j0 + 4 * q]);
+            const float zs[4] = {z.x, z.y, z.z, z.w}, ws[4] = {wt.x, wt.y, wt.z, wt.w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if constexpr (MODE == MODE_MLP)
+                    part = fmaf(ws[c], 0.5f * zs[c] * (1.0f + erf_poly(zs[c] * 0.70710678118654752f)), part);
+                else
+                    part = fmaxf(part, zs[c] * ws[c]);
+            }
+        }
+    }
+    s_part[tid] = part;
+    __syncthreads();
+    if (tid >= POS) return;
+    const int64_t t = tile0 + tid;
+    if (t >= a.total) return;
+    float out = s_part[tid];
+#pragma unroll
+    for (int k = 1; k < THREADS / POS; ++k) out = MODE == MODE_COSINE ? fmaxf(out, s_part[k * POS + tid]) : out + s_part[k * POS + tid];
+    bool past = false;                                     // past the end of its sequence
+    if (a.seq_len) {
+        const int64_t b = t / a.n;
+        past = (int32_t)(t - b * a.n) >= a.seq_len[b];
+    }
+    if constexpr (MODE == MODE_MLP) {
+        const float conf = past ? 0.0f : 1.0f / (1.0f + expf(-out));
+        const bool is_anchor = conf > a.thr;
+        a.conf[t] = conf;
+        a.anchor[t] = is_anchor ? 1 : 0;
+        a.anchor_B[t] = is_anchor ? (a.rank ? a.scale * conf : a.B) : 0.0f;
+    } else {
+        float x2 = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WV; ++w) x2 += s_xx[w * POS + tid];
+        const float sim = past ? 0.0f : (x2 > 0.0f ? out / sqrtf(x2) : 0.0f);
+        a.conf[t] = sim;
+        a.anchor[t] = sim > a.thr ? 1 : 0;
+    }
+}
+
+template <int TW, int HT, int MH, int MODE, int RING>
 hipError_t launch_one(const DetectArgs& a, hipStream_t st)
 {
     constexpr int M = 32 * HT * MH;
     constexpr int DT_TOKENS = 64 * TW;
-    const size_t lds = (size_t)detect_ring(M, MODE) * (DT_TOKENS * 64 + M * 64) + (size_t)M * 4 + (size_t)(MH + 1) * DT_TOKENS * 4;
+    const size_t lds = (size_t)RING * (DT_TOKENS + M) * 128 + (size_t)M * 4 + (size_t)(MH + 1) * DT_TOKENS * 4;
     static DeviceOnce setup;                               // dynamic LDS above 64 KB needs the attribute (per instantiation)
     const hipError_t attr_err = setup.run([&](int) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_kernel<TW, HT, MH, MODE>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_kernel<TW, HT, MH, MODE, RING>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned blocks = (unsigned)((a.total + DT_TOKENS - 1) / DT_TOKENS);
-    hipLaunchKernelGGL((detect_kernel<TW, HT, MH, MODE>), dim3(blocks), dim3(64 * TW * MH), lds, st, a);
+    hipLaunchKernelGGL((detect_kernel<TW, HT, MH, MODE, RING>), dim3(blocks), dim3(64 * TW * MH), lds, st, a);
     return hipGetLastError();
 }
 
+template <int PT, int NT, int WV, int R, int MODE>
+hipError_t launch_split(const DetectArgs& a, hipStream_t st)
+{
+    using S = SplitShape<PT, NT, WV, R>;
+    static DeviceOnce setup;
+    const hipError_t attr_err = setup.run([&](int) {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES);
+    });
+    if (attr_err != hipSuccess) return attr_err;
+    const unsigned blocks = (unsigned)((a.total + S::POS - 1) / S::POS);
+    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
+    return hipGetLastError();
+}
+
+// Which form runs.  A workgroup of the split form streams all of W1 (1 MB at d_model 4096, 128 units) for its 16, 32 or
+// 64 positions, and the sum of these streams is what bounds it (about 12 TB/s over all L2s); a workgroup of the
+// shared form does so for 128 or 256 positions but needs many positions to fill the chip.  So: the smallest tile
+// that gives every compute unit at most one workgroup (16 positions up to 4096, 32 up to 8192), then 64 positions, and
+// the shared form where W1's traffic counts.  Measured at d_model 4096, in us, split / shared form (and before either,
+// 256 positions per workgroup and 64-byte slices):
+//   128 units:  4096 positions 19 (95);  8192: 28 / 47 (108);  16384: 38 / 49 (113);  32768: 72 / 70 (128);
+//               65536: 136 / 133 (153);  524288: 1018 / 863 (856)
+//   256 units:  4096: 31 (110);  8192: 42 / 64 (110);  16384: 75 / 65 (115);  32768: 147 / 82 (120);
+//               65536: 285 / 145 (153);  524288: 2220 / 1161 (1213)
+//   64 units:   4096: 13 (62);  16384: 31 (73);  262144: 420 (432)
+//   32 units:   4096: 11 (56);  16384: 29 (68);  262144: 380 (423)
+//   16 concepts (cosine): 8000 rows 13 (55);  128256 rows 174 = 6.0 TB/s (212)
 template <int MODE>
 hipError_t launch_width(const DetectArgs& a, hipStream_t st)
 {
+    const int64_t P = a.total;
+    if (MODE == MODE_COSINE && a.wrows <= 16) return launch_split<1, 1, 8, 2, MODE>(a, st);
     switch (a.m) {
-        case 32: return launch_one<4, 1, 1, MODE>(a, st);
-        case 64: return launch_one<4, 2, 1, MODE>(a, st);
-        case 128: return launch_one<4, 4, 1, MODE>(a, st);
-        default: return launch_one<4, 2, 4, MODE>(a, st);  // 256: sixteen wavefronts of 64 x 64
+        case 32:
+            if (P <= 4096) return launch_split<1, 2, 8, 2, MODE>(a, st);
+            if (P <= 8192) return launch_split<2, 2, 4, 2, MODE>(a, st);
+            return launch_split<4, 2, 8, 1, MODE>(a, st);
+        case 64:
+            if (P <= 4096) return launch_split<1, 4, 4, 3, MODE>(a, st);
+            if (P <= 8192) return launch_split<2, 4, 4, 2, MODE>(a, st);
+            return launch_split<4, 4, 4, 2, MODE>(a, st);
+        case 128:
+            if (P <= 4096) return launch_split<1, 8, 4, 2, MODE>(a, st);
+            if (P <= 8192) return launch_split<2, 8, 4, 1, MODE>(a, st);
+            if (P <= 24576) return launch_split<4, 8, 4, 1, MODE>(a, st);
+            return launch_one<2, 2, 2, MODE, 2>(a, st);
+        default:
+            if (P <= 4096) return launch_split<1, 16, 4, 1, MODE>(a, st);
+            if (P <= 8192) return launch_split<2, 16, 4, 1, MODE>(a, st);
+            if (P <= 32768) return launch_one<2, 2, 4, MODE, 3>(a, st);
+            return launch_one<4, 2, 4, MODE, 2>(a, st);
     }
 }
 

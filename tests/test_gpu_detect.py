@@ -101,6 +101,22 @@ def test_detect_tiny_inputs():
     assert not conf.any() and not anchor.any() and not anchor_B.any()
 
 
+@pytest.mark.parametrize("m", [32, 64, 128, 256])
+@pytest.mark.parametrize("n", [15, 4096, 4097, 8200, 24577, 32800])
+def test_detect_forms_at_their_limits(m, n):
+    # position counts on both sides of the lines between the kernel forms, ragged last tiles, half a feature slice left over
+    dm = 96 if n % 2 else 608
+    h, W1, W2 = wl.make_detector_inputs(1, n, dm, m, seed=wl.BASE_SEED + n, p_anchor=0.1, device=DEV, row_stride=dm + 8)
+    conf, anchor, anchor_B = ta.ta_detect_anchors(h, W1, W2, ta.Params(), 0.3, True, 2.0)
+    torch.cuda.synchronize()
+    rows = np.unique(np.clip(np.concatenate([np.arange(0, 40), np.arange(n // 2, n // 2 + 70), np.arange(n - 70, n)]), 0, n - 1))
+    at = _dev(rows)
+    ref = _conf_ref(h[:, at], W1, W2)
+    got = conf.cpu().numpy()
+    assert _close(got[:, rows], ref).all(), np.abs(got[:, rows] - ref).max()
+    _check_decisions(got[:, rows], ref, anchor.cpu().numpy()[:, rows], anchor_B.cpu().numpy()[:, rows], 0.3, True, 15.0, 2.0)
+
+
 def test_detect_rejects_unsupported_shapes():
     prm = ta.Params(n_sink=4, n_recent=4)
     h, W1, W2 = wl.make_detector_inputs(1, 64, 64, 32, device=DEV)

@@ -45,6 +45,16 @@ def test_largest_cosine_matches_oracle(E):
     assert sim.max() > 0.95 and np.all(np.abs(sim) <= 1.0 + 1e-5)
 
 
+@pytest.mark.parametrize("E", [16, 60, 128, 200])
+@pytest.mark.parametrize("V", [4097, 24600, 32800])
+def test_largest_cosine_forms_at_their_limits(E, V):
+    # row counts past the lines between the kernel forms, ragged last tiles, half a feature slice left over
+    x, C = wl.make_embedding_inputs(V, 96, E, seed=wl.BASE_SEED + E, p_near=0.2, device=DEV)
+    sim, anchor = ta.ta_embed_anchors(x[None], C, 0.6)
+    torch.cuda.synchronize()
+    _check(sim, anchor, x, C, 0.6)
+
+
 def test_wide_rows_strided_and_ragged_sequences():
     B, n, dm, E = 3, 300, 4096, 24
     x, C = wl.make_embedding_inputs(B * n, dm, E, p_near=0.1, device=DEV, row_stride=dm + 32)
