@@ -480,7 +480,7 @@ int32_t evict_pass(const int32_t* tok, const int32_t* seq_len,
         if (rc != TA_OK) return rc;
     }
     rc = hip_status(ta::launch_select(A, anchor, spons, vouch, seq_len, sel_layers, lay->batch, sel_hkv,
-                                      lay->n, K, *prm, idx, cnt, st));
+                                      lay->n, K, *prm, idx, cnt, st, true));
     if (rc != TA_OK) return rc;
     return hip_status(ta::launch_compact(Kin, Vin, idx, cnt, *lay, K, scored ? 0 : 1, Kout, Vout, pg, lptr, st));
 }

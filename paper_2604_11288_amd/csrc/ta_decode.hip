@@ -20,6 +20,7 @@
 #include <math.h>
 
 #include "ta_internal.h"
+#include "ta_wave.h"
 
 namespace ta {
 
@@ -257,55 +258,6 @@ __device__ __forceinline__ s16x4 hi_half(const uint4& v)
     union { uint2 u; s16x4 s; } c;
     c.u = make_uint2(v.z, v.w);
     return c.s;
-}
-
-// ---- cross-lane reductions on the data-parallel-primitive path (no LDS round trips) ----------
-// Steps: neighbours within quads, quads within a row of 16 by rotation, then the last lane of a row
-// broadcast to the next row(s); lane 63 ends up with the reduction over the wavefront.
-template <int CTRL>
-__device__ __forceinline__ int dpp_move(int v)
-{
-    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
-}
-#define TA_DPP_STEPS(STEP) STEP(0xb1) STEP(0x4e) STEP(0x124) STEP(0x128) STEP(0x142) STEP(0x143)
-
-__device__ __forceinline__ float wave_max_dpp(float v)
-{
-#define STEP(C) v = fmaxf(v, __int_as_float(dpp_move<C>(__float_as_int(v))));
-    TA_DPP_STEPS(STEP)
-#undef STEP
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-__device__ __forceinline__ float wave_sum_dpp(float v)
-{
-#define STEP(C) v += __int_as_float(dpp_move<C>(__float_as_int(v)));
-    TA_DPP_STEPS(STEP)
-#undef STEP
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-__device__ __forceinline__ int wave_sum_dpp(int v)
-{
-#define STEP(C) v += dpp_move<C>(v);
-    TA_DPP_STEPS(STEP)
-#undef STEP
-    return __builtin_amdgcn_readlane(v, 63);
-}
-__device__ __forceinline__ int wave_min_dpp(int v)
-{
-#define STEP(C) { const int o = dpp_move<C>(v); v = o < v ? o : v; }
-    TA_DPP_STEPS(STEP)
-#undef STEP
-    return __builtin_amdgcn_readlane(v, 63);
-}
-__device__ __forceinline__ unsigned long long wave_min_dpp(unsigned long long v)
-{
-#define STEP(C) { const unsigned lo = (unsigned)dpp_move<C>((int)(unsigned)v), hi = (unsigned)dpp_move<C>((int)(unsigned)(v >> 32)); \
-                  const unsigned long long o = ((unsigned long long)hi << 32) | lo; v = o < v ? o : v; }
-    TA_DPP_STEPS(STEP)
-#undef STEP
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, 63);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
-    return ((unsigned long long)hi << 32) | lo;
 }
 
 // One wavefront per unit, no workgroup barriers.  SMALL: at most SLOTS_PER_LANE * 64 slots, so a

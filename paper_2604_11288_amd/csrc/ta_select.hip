@@ -8,11 +8,12 @@
 // "boundary class" - and only inside it a rank threshold is needed:
 //   c2 + c1 <= K : classes 2 and 1 are kept whole, R = K - c2 - c1 slots go to class 0
 //   otherwise    : class 2 is kept whole, R = K - c2 slots go to class 1 (pool overflow)
-// The R-th largest (u, position) key of the boundary class is found with an
-// MSD radix select (8-bit digits) over order-preserving 32-bit images of u kept
-// in LDS, followed - only if several positions tie with the threshold u - by a
-// radix select over their positions.  The retained positions are then written
-// in ascending order with a ballot/popcount stream compaction.
+// Three kernels find the R-th largest (u, position) key of that class and write the retained positions in
+// ascending order, all over order-preserving 32-bit images of u:
+//   select_reg_kernel     rows whose keys fit the registers of a workgroup: one pass over the inputs, the
+//                         cut found by binning over the range of the keys and ranking one bin's members
+//   select_stream         long rows and many units: one pass with a list of candidates in LDS
+//   select_kernel         what neither takes: keys recomputed for every pass of an MSD radix select
 //
 // Options around the same selection (baselines and Sec. 3.3 as settings):
 //   pool_r       the scores are max-pooled over 2 pool_r + 1 positions before the utility
@@ -23,6 +24,7 @@
 //                mandatory competes for the main pool by (u, position) alone - two threshold
 //                searches instead of one
 #include "ta_internal.h"
+#include "ta_wave.h"
 
 namespace ta {
 
@@ -32,8 +34,6 @@ constexpr int SEL_THREADS = 1024;
 constexpr int SEL_WAVES = SEL_THREADS / 64;
 constexpr int HIST_COPIES = 16;               // privatised histograms, one per lane % 16
 constexpr int HIST_STRIDE = 257;              // odd stride: the same bin of different copies sits in different LDS banks
-constexpr int SEL_CACHE_MAX_N = 32768;        // keys cached in LDS up to this length
-constexpr int SEL_MAX_ROUNDS = SEL_CACHE_MAX_N / 4 / SEL_THREADS;   // rounds of SEL_THREADS quads in the longest cached row
 
 struct SelectArgs {
     const float* A;
@@ -49,6 +49,7 @@ struct SelectArgs {
     int32_t pool_r, k_protected;
     int32_t units, units_per_xcd;
     int32_t vec_ok;
+    int32_t plain_vouch;            // 1: vouchers of the match or the expansion (0 at every unsponsored position)
     int32_t n_sink, n_recent;
     float alpha, beta, gamma;
 };
@@ -150,19 +151,12 @@ struct Quad {
     uint8_t an[4];
 };
 
-// SEL_ROUNDS: 1 - cached rows of at most 4 * SEL_THREADS positions, a thread has one quad; SEL_MAX_ROUNDS - the longer
-// cached rows; 0 - rows that are not cached (any length)
-template <bool CACHED, bool CAPPED, int SEL_ROUNDS>
+// ---- form for what the others do not take (rows longer than SR_MAX_N with an option, or with a list that does not
+// fit): the keys are recomputed from the inputs in every pass -----------------------------------------------------
+template <bool CAPPED>
 __global__ void __launch_bounds__(SEL_THREADS)
 select_kernel(SelectArgs a)
 {
-    static_assert(CACHED ? (SEL_ROUNDS == 1 || SEL_ROUNDS == SEL_MAX_ROUNDS) : SEL_ROUNDS == 0, "instances");
-    constexpr int SEL_BATCH = SEL_ROUNDS == SEL_MAX_ROUNDS ? 2 : 1;   // quads of a thread whose loads are in flight together
-    // long cached rows, one threshold search over every cached key: the histogram of the first digit is taken while
-    // the keys are built, which saves a sweep over the cache (the histograms are cleared before the class count,
-    // whose reduction has a barrier)
-    constexpr bool FIRST_DIGIT_EARLY = CACHED && !CAPPED && SEL_ROUNDS > 1;
-    extern __shared__ uint32_t s_key[];                     // [roundup4(n)] when CACHED
     __shared__ uint32_t s_hist[HIST_COPIES][HIST_STRIDE];
     __shared__ uint32_t s_h[256];
     __shared__ int s_red[SEL_WAVES];
@@ -274,38 +268,15 @@ select_kernel(SelectArgs a)
         }
     };
 
-    // ---- class-1 population.  A thread's quads are taken SEL_BATCH at a time, all their loads issued
-    // before the first is used (a quad index past the end is clamped and its data ignored): with few units a
-    // workgroup has a compute unit to itself and nothing else hides a round trip.  The first batch's other
-    // operands are requested before the reduction so that their latency hides behind it.
-    Quad first[SEL_BATCH];
+    // ---- class-1 population
     int local = 0;
-    for (int32_t q0 = tid; q0 < nquads; q0 += SEL_BATCH * SEL_THREADS) {
-        uint8_t sp[SEL_BATCH][4];
+    for (int32_t q = tid; q < nquads; q += SEL_THREADS) {
+        uint8_t sp[4];
+        load_flags(spons, q, sp);
 #pragma unroll
-        for (int u = 0; u < SEL_BATCH; ++u) {
-            const int32_t q = q0 + u * SEL_THREADS;
-            load_flags(spons, q < nquads ? q : nquads - 1, sp[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < SEL_BATCH; ++u) {
-            const int32_t q = q0 + u * SEL_THREADS;
-            if (q0 == tid) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) first[u].sp[c] = sp[u][c];
-            }
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int32_t p = 4 * q + c;
-                local += (q < nquads && p >= ns && p < rs && sp[u][c]) ? 1 : 0;
-            }
-        }
-    }
-    if (CACHED && tid < nquads) {
-#pragma unroll
-        for (int u = 0; u < SEL_BATCH; ++u) {
-            const int32_t q = tid + u * SEL_THREADS;
-            load_rest(q < nquads ? q : nquads - 1, first[u]);
+        for (int c = 0; c < 4; ++c) {
+            const int32_t p = 4 * q + c;
+            local += (p >= ns && p < rs && sp[c]) ? 1 : 0;
         }
     }
     const int32_t c1 = block_sum(local, s_red);
@@ -339,55 +310,11 @@ select_kernel(SelectArgs a)
         for (int c = 0; c < 4; ++c) k[c] = key_of(4 * q + c, x.A[c], x.an[c], x.sp[c], x.v[c]);
     };
     auto keys_at = [&](int32_t q, uint32_t (&k)[4]) {
-        if (CACHED) {
-            const uint4 kk = *reinterpret_cast<const uint4*>(&s_key[4 * q]);
-            k[0] = kk.x; k[1] = kk.y; k[2] = kk.z; k[3] = kk.w;
-        } else {
-            Quad x;
-            load_flags(spons, q, x.sp);
-            load_rest(q, x);
-            quad_keys(q, x, k);
-        }
+        Quad x;
+        load_flags(spons, q, x.sp);
+        load_rest(q, x);
+        quad_keys(q, x, k);
     };
-
-    if (CACHED) {
-        for (int32_t q0 = tid; q0 < nquads; q0 += SEL_BATCH * SEL_THREADS) {
-            Quad x[SEL_BATCH];
-#pragma unroll
-            for (int u = 0; u < SEL_BATCH; ++u) {
-                const int32_t q = q0 + u * SEL_THREADS;
-                if (q0 == tid) x[u] = first[u];
-                else {
-                    load_flags(spons, q < nquads ? q : nquads - 1, x[u].sp);
-                    load_rest(q < nquads ? q : nquads - 1, x[u]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < SEL_BATCH; ++u) {
-                const int32_t q = q0 + u * SEL_THREADS;
-                if (q < nquads) {
-                    uint32_t k[4];
-                    quad_keys(q, x[u], k);
-                    *reinterpret_cast<uint4*>(&s_key[4 * q]) = make_uint4(k[0], k[1], k[2], k[3]);
-                    if constexpr (FIRST_DIGIT_EARLY) {       // the first pass's histogram, while the keys are at hand
-                        int prev = -1;
-                        uint32_t run = 0;
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            const int bin = k[c] != 0u ? (int)(k[c] >> 24) : -1;
-                            if (bin != prev) {
-                                if (prev >= 0) atomicAdd(&s_hist[lane & (HIST_COPIES - 1)][prev], run);
-                                prev = bin;
-                                run = 0;
-                            }
-                            ++run;
-                        }
-                        if (prev >= 0) atomicAdd(&s_hist[lane & (HIST_COPIES - 1)][prev], run);
-                    }
-                }
-            }
-        }
-    }
     __syncthreads();
 
     // ---- threshold search ------------------------------------------------
@@ -399,35 +326,15 @@ select_kernel(SelectArgs a)
         bool done = false;
         for (int pass = 0; pass < 4 && !done; ++pass) {
             const int shift = 24 - 8 * pass;
-            for (int32_t q = tid; q < nquads && !(FIRST_DIGIT_EARLY && pass == 0); q += SEL_THREADS) {
+            for (int32_t q = tid; q < nquads; q += SEL_THREADS) {
                 uint32_t k4[4];
                 keys_at(q, k4);
                 member(q, k4);
-                if constexpr (SEL_ROUNDS > 1) {
-                    // long rows: neighbouring positions mostly share a digit (the recency term moves slowly), and
-                    // equal digits in a row go into the histogram as one add
-                    int prev = -1;
-                    uint32_t run = 0;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const uint32_t k = k4[c];
-                        const bool in = k != 0u && (pass == 0 || (k >> (shift + 8)) == (prefix >> (shift + 8)));
-                        const int bin = in ? (int)((k >> shift) & 255u) : -1;
-                        if (bin != prev) {
-                            if (prev >= 0) atomicAdd(&s_hist[lane & (HIST_COPIES - 1)][prev], run);
-                            prev = bin;
-                            run = 0;
-                        }
-                        ++run;
-                    }
-                    if (prev >= 0) atomicAdd(&s_hist[lane & (HIST_COPIES - 1)][prev], run);
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const uint32_t k = k4[c];
-                        bool in = k != 0u && (pass == 0 || (k >> (shift + 8)) == (prefix >> (shift + 8)));
-                        if (in) atomicAdd(&s_hist[lane & (HIST_COPIES - 1)][(k >> shift) & 255u], 1u);
-                    }
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t k = k4[c];
+                    bool in = k != 0u && (pass == 0 || (k >> (shift + 8)) == (prefix >> (shift + 8)));
+                    if (in) atomicAdd(&s_hist[lane & (HIST_COPIES - 1)][(k >> shift) & 255u], 1u);
                 }
             }
             __syncthreads();
@@ -506,22 +413,14 @@ select_kernel(SelectArgs a)
         uint32_t keep = 0;
         uint8_t sp[4] = {0, 0, 0, 0};
         uint32_t k4[4] = {0u, 0u, 0u, 0u};
-        if (CACHED && !CAPPED) {
-            // no load: a key of 0 between the mandatory ranges is a position of the other class, which is
-            // sponsored exactly when the cut falls among the plain ones
-            keys_at(q, k4);
+        load_flags(spons, q, sp);
+        bool need_keys = false;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) sp[c] = (uint8_t)((k4[c] == 0u) == (bclass == 0) ? 1 : 0);
-        } else {
-            load_flags(spons, q, sp);
-            bool need_keys = false;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int32_t p = 4 * q + c;
-                need_keys = need_keys || (p >= ns && p < rs && (CAPPED || (sp[c] != 0) == (bclass == 1)));
-            }
-            if (need_keys) keys_at(q, k4);
+        for (int c = 0; c < 4; ++c) {
+            const int32_t p = 4 * q + c;
+            need_keys = need_keys || (p >= ns && p < rs && (CAPPED || (sp[c] != 0) == (bclass == 1)));
         }
+        if (need_keys) keys_at(q, k4);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const int32_t p = 4 * q + c;
@@ -548,96 +447,35 @@ select_kernel(SelectArgs a)
 
     // ---- ascending write-out -------------------------------------------------------------------
     int32_t base = 0;
-    if constexpr (CACHED && SEL_ROUNDS > 1) {
-        // Every round of SEL_THREADS quads at once (at most SEL_ROUNDS of them fit the key cache): a thread keeps
-        // the masks of its quads in one register, the rounds' counts are scanned two to a register, and ONE
-        // scan over the (round, wavefront) totals gives every wavefront its offsets - three barriers instead of
-        // two per round.
-        uint32_t masks = 0;
+    // one scan over per-quad counts per round of 4096 positions
+    for (int32_t q0 = 0; q0 < nquads; q0 += SEL_THREADS) {
+        const int32_t q = q0 + tid;
+        const uint32_t keep = q < nquads ? keep_of(q) : 0u;
+        const int mine = __popc(keep);
+        int incl = mine;
 #pragma unroll
-        for (int r = 0; r < SEL_ROUNDS; ++r) {
-            const int32_t q = r * SEL_THREADS + tid;
-            if (q < nquads) masks |= keep_of(q) << (4 * r);
-        }
-        uint32_t incl2[SEL_ROUNDS / 2];                      // inclusive counts within the wavefront, rounds 2j and 2j + 1
-#pragma unroll
-        for (int j = 0; j < SEL_ROUNDS / 2; ++j) {
-            uint32_t v = (uint32_t)__popc((masks >> (8 * j)) & 15u) | ((uint32_t)__popc((masks >> (8 * j + 4)) & 15u) << 16);
-            if (2 * j * SEL_THREADS < nquads) {              // uniform: rounds past the row's end hold nothing
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const uint32_t up = __shfl_up(v, o);
-                    if (lane >= o) v += up;                  // at most 256 per field: no carry between the halves
-                }
-            }
-            incl2[j] = v;
-        }
-        __syncthreads();                                     // s_h is free (the threshold search is over)
-        if (lane == 63) {
-#pragma unroll
-            for (int r = 0; r < SEL_ROUNDS; ++r) s_h[r * SEL_WAVES + wave] = (incl2[r >> 1] >> (16 * (r & 1))) & 0xFFFFu;
+        for (int o = 1; o < 64; o <<= 1) {
+            int up = __shfl_up(incl, o);
+            if (lane >= o) incl += up;
         }
         __syncthreads();
-        if (tid < 64) {                                      // exclusive scan of the SEL_ROUNDS * SEL_WAVES totals, two per lane
-            static_assert(SEL_ROUNDS * SEL_WAVES == 128, "two entries per lane of one wavefront");
-            const uint32_t t0 = s_h[2 * tid], t1 = s_h[2 * tid + 1];
-            uint32_t v = t0 + t1;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t up = __shfl_up(v, o);
-                if (tid >= o) v += up;
-            }
-            s_h[2 * tid] = v - t0 - t1;
-            s_h[2 * tid + 1] = v - t1;
-            if (tid == 63) s_h[SEL_ROUNDS * SEL_WAVES] = v;  // everything retained
-        }
+        if (lane == 63) s_red[wave] = incl;
         __syncthreads();
+        int woff = 0, total = 0;
+        for (int w = 0; w < SEL_WAVES; ++w) {
+            int c = s_red[w];
+            woff += (w < wave) ? c : 0;
+            total += c;
+        }
+        int32_t slot = base + woff + incl - mine;
 #pragma unroll
-        for (int r = 0; r < SEL_ROUNDS; ++r) {
-            const uint32_t keep = (masks >> (4 * r)) & 15u;
-            const int32_t q = r * SEL_THREADS + tid;
-            const uint32_t incl = (incl2[r >> 1] >> (16 * (r & 1))) & 0xFFFFu;
-            int32_t slot = (int32_t)(s_h[r * SEL_WAVES + wave] + incl) - __popc(keep);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (keep & (1u << c)) {
-                    if (slot < K) idx[slot] = 4 * q + c;
-                    ++slot;
-                }
+        for (int c = 0; c < 4; ++c) {
+            if (keep & (1u << c)) {
+                if (slot < K) idx[slot] = 4 * q + c;
+                ++slot;
             }
         }
-        base = (int32_t)s_h[SEL_ROUNDS * SEL_WAVES];
-    } else {
-        // one scan over per-quad counts per round of 4096 positions
-        for (int32_t q0 = 0; q0 < nquads; q0 += SEL_THREADS) {
-            const int32_t q = q0 + tid;
-            const uint32_t keep = q < nquads ? keep_of(q) : 0u;
-            const int mine = __popc(keep);
-            int incl = mine;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                int up = __shfl_up(incl, o);
-                if (lane >= o) incl += up;
-            }
-            __syncthreads();
-            if (lane == 63) s_red[wave] = incl;
-            __syncthreads();
-            int woff = 0, total = 0;
-            for (int w = 0; w < SEL_WAVES; ++w) {
-                int c = s_red[w];
-                woff += (w < wave) ? c : 0;
-                total += c;
-            }
-            int32_t slot = base + woff + incl - mine;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                if (keep & (1u << c)) {
-                    if (slot < K) idx[slot] = 4 * q + c;
-                    ++slot;
-                }
-            }
-            base += total;
-        }
+        base += total;
     }
     if (tid == 0) a.cnt[unit] = base < K ? base : K;
     if (a.margin) {                                          // uniform
@@ -665,6 +503,535 @@ select_kernel(SelectArgs a)
 }
 
 
+// ---- register form: rows of up to SR_MAX_N positions, one workgroup per unit ---------------------------------
+// A thread keeps the keys of its quads in registers (quad r * SR_THREADS + tid in round r), so every input is read
+// once, whatever class the cut falls in: the sponsored positions, the ranges of both classes' keys and the keys
+// themselves come out of one pass.  The cut is found by binning the boundary class's keys over the range they
+// really take (SR_BINS bins between the smallest and the largest: integers that order as the floats do, so an
+// outlier costs a few octaves of bins and not the resolution) and ranking the few members of the bin it falls
+// in against each other.
+constexpr int SR_THREADS = 1024;
+constexpr int SR_WAVES = SR_THREADS / 64;
+constexpr int SR_MAX_ROUNDS = 8;
+constexpr int SR_MAX_N = SR_MAX_ROUNDS * SR_THREADS * 4;
+constexpr int SR_BINS = 2048;
+constexpr int SR_CAND = 256;                                 // members of a bin that are ranked one against the other
+
+struct SelectRegLds {
+    uint32_t hist[32 * 65];                                  // bin b at (b % 32) * 65 + b / 32: 64 lanes read a row of it at once
+    uint32_t part[5][SR_WAVES];                              // per wavefront: sponsored count, key ranges of both classes
+    uint32_t edge[2][SR_WAVES];                              // per wavefront: smallest retained, largest evicted key
+    uint32_t totals[SR_MAX_ROUNDS * SR_WAVES];               // retained positions per round and wavefront
+    uint32_t cand[2 * SR_CAND + 4];                          // (position, key) pairs
+    uint32_t count;
+    struct { uint32_t bin, need, count, all, key, pos; } st;
+};
+
+// ---- quads of a row of n positions at any alignment (n % 4 != 0 puts the rows of a batch at odd places): one wide load
+// each, which the hardware takes at any byte address.  A quad that would reach past the row's end (the last one, n >= 4)
+// is loaded from the row's last four positions and moved down; what lies past the end is 0.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+__device__ __forceinline__ int32_t quad_start(int32_t p, int32_t n) { return p <= n - 4 ? p : n - 4; }
+__device__ __forceinline__ float4 load_quad_f(const float* row, int32_t start)
+{
+    const f32x4_any v = *reinterpret_cast<const f32x4_any*>(row + start);
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ uint32_t load_quad_b(const uint8_t* row, int32_t start)
+{
+    return *reinterpret_cast<const u32_any*>(row + start);
+}
+__device__ __forceinline__ float4 move_down(float4 v, int32_t by)         // by 0 .. 3 positions
+{
+    if (by & 1) v = make_float4(v.y, v.z, v.w, 0.0f);
+    if (by & 2) v = make_float4(v.z, v.w, 0.0f, 0.0f);
+    return v;
+}
+
+// a / n, correctly rounded, from y = RN(1 / n): two Newton corrections of the quotient with exact residuals
+__device__ __forceinline__ float div_by(float a, float n, float y)
+{
+    float q = a * y;
+    q = fmaf(fmaf(-q, n, a), y, q);
+    return fmaf(fmaf(-q, n, a), y, q);
+}
+
+template <int ROUNDS, bool CAPPED>
+__global__ void __launch_bounds__(SR_THREADS)
+select_reg_kernel(SelectArgs a)
+{
+    __shared__ __align__(16) SelectRegLds L;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    // Same block -> unit numbering as the score step (block b runs on XCD b mod 8, which
+    // scored the units [x * units_per_xcd, (x+1) * units_per_xcd)): A is then read from the
+    // L2 that holds it.
+    const int32_t unit = (int32_t)(blockIdx.x & 7u) * a.units_per_xcd + (int32_t)(blockIdx.x >> 3);
+    if (unit >= a.units) return;
+    const int32_t b = (unit / a.hkv) % a.batch;
+    const int32_t n = a.n;
+    int32_t K = a.K;                                         // capacity of an idx row; the budget unless a layer has its own
+    if (a.layer_K) {
+        int32_t lo = a.n_sink + a.n_recent;                  // the mandatory tokens must fit (validated: <= a.K)
+        lo = lo < 1 ? 1 : lo;
+        const int32_t kl = a.layer_K[unit / (a.batch * a.hkv)];
+        K = kl < lo ? lo : (kl > K ? K : kl);
+    }
+    int32_t nb = a.seq_len ? a.seq_len[b] : n;
+    nb = nb < 0 ? 0 : (nb > n ? n : nb);
+    int32_t* idx = a.idx + (size_t)unit * (size_t)a.K;
+
+    if (nb <= K) {                                           // nothing to evict
+        for (int32_t p = tid; p < nb; p += SR_THREADS) idx[p] = p;
+        if (tid == 0) {
+            a.cnt[unit] = nb;
+            if (a.margin) {
+                a.margin[2 * (size_t)unit] = INFINITY;
+                a.margin[2 * (size_t)unit + 1] = -INFINITY;
+            }
+        }
+        return;
+    }
+
+    const float* A = a.A ? a.A + (size_t)unit * (size_t)n : nullptr;
+    const size_t row = (size_t)b * (size_t)n;
+    const uint8_t* anchor = a.anchor + row;
+    const uint8_t* spons = a.spons + row;
+    const float* vouch = a.vouch + row;
+    const int32_t ns = a.n_sink < nb ? a.n_sink : nb;
+    int32_t rs = nb - a.n_recent;                            // recent window = [rs, nb)
+    rs = rs < ns ? ns : rs;
+    const int32_t c2 = ns + (nb - rs);
+    const int32_t nquads = (nb + 3) >> 2;
+    const bool use_A = (a.alpha != 0.0f);
+
+    for (int i = tid; i < 32 * 65; i += SR_THREADS) L.hist[i] = 0u;
+    if (tid == 0) L.count = 0u;
+
+    // ---- one pass over the inputs ------------------------------------------------------------------
+    // scores of a quad, max-pooled over [p - r, p + r] clipped to the sequence (r <= 4: the quad and its neighbours)
+    const auto load_pooled = [&](int32_t q, float (&out)[4]) {
+        float w[12];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int32_t p = 4 * (q - 1 + j);
+            if (p >= 0 && p + 3 < n) {
+                const float4 f = load_quad_f(A, p);
+                w[4 * j + 0] = f.x; w[4 * j + 1] = f.y; w[4 * j + 2] = f.z; w[4 * j + 3] = f.w;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (p + c >= nb) w[4 * j + c] = -INFINITY;
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w[4 * j + c] = (p + c >= 0 && p + c < nb) ? A[p + c] : -INFINITY;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float m = w[4 + c];
+#pragma unroll
+            for (int d = 1; d <= 4; ++d)
+                if (d <= a.pool_r) m = fmaxf(m, fmaxf(w[4 + c - d], w[4 + c + d]));
+            out[c] = (4 * q + c < nb) ? m : 0.0f;
+        }
+    };
+    uint32_t key[ROUNDS][4];                                 // order-preserving images of u
+    uint32_t mid = 0u, spm = 0u;                             // bits 4 r + c: between the mandatory ranges; and sponsored
+    uint32_t lo0 = 0xFFFFFFFFu, hi0 = 0u, lo1 = 0xFFFFFFFFu, hi1 = 0u;   // key ranges of the plain and of the sponsored positions
+    const float nf = (float)nb, inv = __fdiv_rn(1.0f, nf);
+    // Without an attention term the plain positions' utilities (no anchor, no voucher) rise with the position, so the last
+    // K - c2 positions before the recent window outrank or tie-break every plain one before them: those are not
+    // looked at again.  (The margin output wants the best of the evicted ones, the fixed partition ranks both classes.  Only
+    // for vouchers of the match or the expansion, which are 0 wherever the sponsor flag is.)
+    const int32_t plain_end = !CAPPED && !use_A && a.plain_vouch && a.beta >= 0.0f && a.gamma >= 0.0f && !a.margin ? rs - (K - c2) : 0;
+    const float g0 = __fmul_rn(a.gamma, 0.0f);
+    // The loads of BATCH rounds are issued together, unconditionally (a quad index past the
+    // end is clamped and its data masked): with few units nothing else hides a round trip.
+    constexpr int BATCH = ROUNDS < 4 ? ROUNDS : 4;
+#pragma unroll
+    for (int r0 = 0; r0 < ROUNDS; r0 += BATCH) {
+        if (r0 * SR_THREADS >= nquads) {                     // uniform: nothing of the row lies this far
+#pragma unroll
+            for (int r = r0; r < r0 + BATCH; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) key[r][c] = 0u;
+            continue;
+        }
+        uint32_t sp[BATCH], an[BATCH];
+        float4 v[BATCH], s[BATCH];
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int32_t q0 = (r0 + j) * SR_THREADS + tid;
+            const int32_t q = q0 < nquads ? q0 : nquads - 1;
+            s[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (n >= 4) {
+                const int32_t start = quad_start(4 * q, n);
+                sp[j] = load_quad_b(spons, start);
+                an[j] = load_quad_b(anchor, start);
+                v[j] = load_quad_f(vouch, start);
+                if (use_A && a.pool_r == 0) s[j] = load_quad_f(A, start);
+            } else {                                         // (a row of one to three positions)
+                float vv[4], ss[4];
+                sp[j] = an[j] = 0u;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const bool in = 4 * q + c < nb;
+                    sp[j] |= in && spons[4 * q + c] ? 1u << (8 * c) : 0u;
+                    an[j] |= in ? (uint32_t)anchor[4 * q + c] << (8 * c) : 0u;
+                    vv[c] = in ? vouch[4 * q + c] : 0.0f;
+                    ss[c] = in && use_A && a.pool_r == 0 ? A[4 * q + c] : 0.0f;
+                }
+                v[j] = make_float4(vv[0], vv[1], vv[2], vv[3]);
+                s[j] = make_float4(ss[0], ss[1], ss[2], ss[3]);
+            }
+            if (use_A && a.pool_r > 0) {
+                float ss[4];
+                load_pooled(q, ss);
+                s[j] = make_float4(ss[0], ss[1], ss[2], ss[3]);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < BATCH; ++j) {
+            const int r = r0 + j;
+            const int32_t q = r * SR_THREADS + tid;
+            if (n >= 4 && (n & 3)) {                         // uniform
+                const int32_t by = q < nquads ? 4 * q - quad_start(4 * q, n) : 0;
+                sp[j] >>= 8 * by;
+                an[j] >>= 8 * by;
+                v[j] = move_down(v[j], by);
+                if (a.pool_r == 0) s[j] = move_down(s[j], by);
+            }
+            const float Aq[4] = {s[j].x, s[j].y, s[j].z, s[j].w}, vq[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+            const bool no_flags = (sp[j] | an[j]) == 0u;
+            const bool plain = no_flags && 4 * q + 3 < plain_end && 4 * q >= ns &&
+                               ((__float_as_uint(vq[0]) | __float_as_uint(vq[1]) | __float_as_uint(vq[2]) | __float_as_uint(vq[3])) << 1) == 0u;
+            if (__ballot(!plain) == 0ull) {                  // a whole wavefront of positions that cannot be retained
+#pragma unroll
+                for (int c = 0; c < 4; ++c) key[r][c] = 0u;
+                continue;
+            }
+            if (__ballot(!(no_flags && 4 * q >= ns && 4 * q + 3 < rs)) == 0ull) {   // nothing but class 0
+                mid |= 15u << (4 * r);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float t = use_A ? __fmul_rn(a.alpha, Aq[c]) : 0.0f;
+                    t = __fadd_rn(t, __fmul_rn(a.beta, div_by((float)(4 * q + c + 1), nf, inv)));
+                    t = __fadd_rn(t, g0);
+                    t = __fadd_rn(t, vq[c]);
+                    const uint32_t k = ordered_bits(t);
+                    key[r][c] = k;
+                    lo0 = k < lo0 ? k : lo0;
+                    hi0 = k > hi0 ? k : hi0;
+                }
+                continue;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int32_t p = 4 * q + c;
+                float t = use_A ? __fmul_rn(a.alpha, Aq[c]) : 0.0f;
+                t = __fadd_rn(t, __fmul_rn(a.beta, div_by((float)(p + 1), nf, inv)));
+                t = __fadd_rn(t, __fmul_rn(a.gamma, (float)((an[j] >> (8 * c)) & 0xFFu)));
+                t = __fadd_rn(t, vq[c]);
+                const uint32_t k = ordered_bits(t);
+                key[r][c] = k;
+                const bool m = p >= ns && p < rs, sps = ((sp[j] >> (8 * c)) & 0xFFu) != 0u;
+                mid |= m ? 1u << (4 * r + c) : 0u;
+                spm |= m && sps ? 1u << (4 * r + c) : 0u;
+                lo0 = m && !sps && k < lo0 ? k : lo0;
+                hi0 = m && !sps && k > hi0 ? k : hi0;
+                lo1 = m && sps && k < lo1 ? k : lo1;
+                hi1 = m && sps && k > hi1 ? k : hi1;
+            }
+        }
+    }
+    {
+        const uint32_t c = wave_sum_dpp((uint32_t)__popc(spm));
+        lo0 = wave_min_dpp(lo0);
+        hi0 = wave_max_dpp(hi0);
+        lo1 = wave_min_dpp(lo1);
+        hi1 = wave_max_dpp(hi1);
+        if (lane == 0) {
+            L.part[0][wave] = c;
+            L.part[1][wave] = lo0;
+            L.part[2][wave] = hi0;
+            L.part[3][wave] = lo1;
+            L.part[4][wave] = hi1;
+        }
+    }
+    __syncthreads();
+    int32_t c1;
+    {
+        const int w = lane & (SR_WAVES - 1);
+        c1 = (int32_t)wave_sum_dpp(lane < SR_WAVES ? L.part[0][w] : 0u);
+        lo0 = wave_min_dpp(L.part[1][w]);
+        hi0 = wave_max_dpp(L.part[2][w]);
+        lo1 = wave_min_dpp(L.part[3][w]);
+        hi1 = wave_max_dpp(L.part[4][w]);
+    }
+    const int bclass = (c2 + c1 <= K) ? 0 : 1;
+    const int32_t R = bclass == 0 ? K - c2 - c1 : K - c2;    // slots for the boundary class
+    // fixed partition: P sponsored tokens are protected, M more slots go to the best of everything else
+    int32_t P = 0;
+    if (CAPPED) {
+        P = a.k_protected < c1 ? a.k_protected : c1;
+        P = P < K - c2 ? P : K - c2;
+    }
+    const int32_t M = K - c2 - P;
+
+    // ---- the cut: among the positions of `members` (bits as above; values val(r, c) in [lo, hi]), a position is in the
+    // top `need` iff value > T, or value == T and position >= Pt.  False: the cut falls among more than SR_CAND
+    // members that all have the value T, and `need` of these are wanted.  The histogram is clear on entry.
+    const auto search = [&](auto&& val, const uint32_t members, uint32_t lo, uint32_t hi, uint32_t& need, uint32_t& T,
+                            int32_t& Pt) -> bool {
+        for (bool first_level = true;; first_level = false) {
+            const uint32_t d = hi - lo;
+            const int shift = d < (uint32_t)SR_BINS ? 0 : 21 - __clz((int)d);    // d >> shift < SR_BINS
+            int prev = -1;                                   // equal bins in a row go into the histogram as one add
+            uint32_t run = 0;
+            const auto put = [&]() {
+                if (prev >= 0) atomicAdd(&L.hist[(prev & 31) * 65 + (prev >> 5)], run);
+            };
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                if (r * SR_THREADS >= nquads) break;         // uniform
+                if (__ballot((members >> (4 * r)) & 15u) == 0ull) continue;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t v = val(r, c);
+                    if (first_level) {                       // uniform; every member lies in [lo, hi]
+                        const int bin = ((members >> (4 * r + c)) & 1u) ? (int)((v - lo) >> shift) : -1;
+                        if (bin != prev) {
+                            put();
+                            prev = bin;
+                            run = 0;
+                        }
+                        ++run;
+                        continue;
+                    }
+                    const int bin = ((members >> (4 * r + c)) & 1u) && v >= lo && v <= hi ? (int)((v - lo) >> shift) : -1;
+                    if (bin != prev) {
+                        put();
+                        prev = bin;
+                        run = 0;
+                    }
+                    ++run;
+                }
+            }
+            put();
+            __syncthreads();
+            if (wave == 0) {
+                // lane l owns the bins 32 (63 - l) .. + 31: the scan over lanes runs downwards through the values
+                uint32_t mine = 0;
+#pragma unroll
+                for (int j = 0; j < 32; ++j) mine += L.hist[j * 65 + 63 - lane];
+                const uint32_t incl = wave_scan_dpp(mine);
+                const int first = __ffsll((long long)__ballot(incl >= need)) - 1;   // the lane whose bins hold the cut
+                const uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)(incl - mine), first);
+                // its 32 bins, one per lane, again from the largest down
+                const uint32_t h = lane < 32 ? L.hist[(31 - lane) * 65 + 63 - first] : 0u;
+                const uint32_t in2 = above + wave_scan_dpp(h);
+                const int at = __ffsll((long long)__ballot(in2 >= need)) - 1;
+                if (lane == at) {
+                    L.st.bin = (uint32_t)(32 * (63 - first) + 31 - at);
+                    L.st.need = need - (in2 - h);
+                    L.st.count = h;
+                    L.st.all = in2 == need ? 1u : 0u;
+                }
+            }
+            __syncthreads();
+            const uint32_t bin = L.st.bin, count = L.st.count, all = L.st.all;
+            need = L.st.need;
+            lo += bin << shift;
+            hi = hi - lo < (1u << shift) - 1u ? hi : lo + ((1u << shift) - 1u);
+            if (all) {                                       // everything from the bin's lower end up
+                T = lo - 1u;
+                Pt = 0x7FFFFFFF;
+                return true;
+            }
+            if (count <= (uint32_t)SR_CAND) {
+#pragma unroll
+                for (int r = 0; r < ROUNDS; ++r) {
+                    if (r * SR_THREADS >= nquads) break;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const uint32_t v = val(r, c);
+                        if (((members >> (4 * r + c)) & 1u) && v >= lo && v <= hi) {
+                            const uint32_t e = atomicAdd(&L.count, 1u);
+                            L.cand[2 * e] = (uint32_t)(4 * (r * SR_THREADS + tid) + c);
+                            L.cand[2 * e + 1] = v;
+                        }
+                    }
+                }
+                __syncthreads();
+                if (tid < (int)count) {
+                    const unsigned long long* pairs = reinterpret_cast<const unsigned long long*>(L.cand);
+                    const unsigned long long me = pairs[tid];
+                    uint32_t rank = 0;
+                    for (uint32_t e = 0; e < count; ++e) rank += pairs[e] > me ? 1u : 0u;
+                    if (rank == need - 1u) {
+                        L.st.key = (uint32_t)(me >> 32);
+                        L.st.pos = (uint32_t)me;
+                    }
+                }
+                if (tid == 0) L.count = 0u;
+                __syncthreads();
+                T = L.st.key;
+                Pt = (int32_t)L.st.pos;
+                return true;
+            }
+            __syncthreads();                                 // the state has been read
+            for (int i = tid; i < 32 * 65; i += SR_THREADS) L.hist[i] = 0u;
+            __syncthreads();
+            if (shift == 0) {
+                T = lo;
+                return false;
+            }
+        }
+    };
+    const auto find_threshold = [&](const uint32_t members, uint32_t lo, uint32_t hi, uint32_t want, uint32_t& T, int32_t& Pt) {
+        uint32_t need = want;
+        const auto keys = [&](int r, int c) { return key[r][c]; };
+        if (search(keys, members, lo, hi, need, T, Pt)) return;
+        // many positions share the key T: the `need` highest of them are kept
+        uint32_t same = 0u;
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) same |= key[r][c] == T ? 1u << (4 * r + c) : 0u;
+        uint32_t Tp = 0;
+        int32_t unused = 0;
+        const auto positions = [&](int r, int c) { return (uint32_t)(4 * (r * SR_THREADS + tid) + c); };
+        search(positions, members & same, 0u, (uint32_t)(nb - 1), need, Tp, unused);   // positions are unique: always found
+        Pt = unused == 0x7FFFFFFF ? (int32_t)Tp + 1 : (int32_t)Tp;
+    };
+
+    uint32_t T = 0xFFFFFFFFu;     // a position that competes is kept iff key > T, or key == T and p >= Pt
+    int32_t Pt = 0x7FFFFFFF;
+    uint32_t always = 0u, compete;                           // retained whatever the ranking says; ranked
+    if (!CAPPED) {
+        compete = bclass ? spm : (mid & ~spm);
+        always = bclass ? 0u : spm;
+        if (R > 0) find_threshold(compete, bclass ? lo1 : lo0, bclass ? hi1 : hi0, (uint32_t)R, T, Pt);
+    } else {
+        if (P == c1) always = spm;                           // every sponsored token is protected
+        else if (P > 0) {
+            uint32_t T1 = 0xFFFFFFFFu;
+            int32_t Pt1 = 0x7FFFFFFF;
+            find_threshold(spm, lo1, hi1, (uint32_t)P, T1, Pt1);
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int32_t p = 4 * (r * SR_THREADS + tid) + c;
+                    const bool prot = key[r][c] > T1 || (key[r][c] == T1 && p >= Pt1);
+                    always |= prot ? spm & (1u << (4 * r + c)) : 0u;
+                }
+            __syncthreads();
+            for (int i = tid; i < 32 * 65; i += SR_THREADS) L.hist[i] = 0u;
+            __syncthreads();
+        }
+        compete = mid & ~always;
+        if (M > 0) find_threshold(compete, lo0 < lo1 ? lo0 : lo1, hi0 > hi1 ? hi0 : hi1, (uint32_t)M, T, Pt);   // more candidates than M remain: nb > K
+    }
+
+    // ---- what is retained, in ascending order: the counts of all rounds are scanned at once, two rounds to a register
+    uint32_t keep = always;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        if (r * SR_THREADS >= nquads) break;                 // uniform
+        const int32_t q = r * SR_THREADS + tid;
+        if (__ballot((compete >> (4 * r)) & 15u)) {          // uniform
+            uint32_t above = 0u, level = 0u;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                above |= key[r][c] > T ? 1u << c : 0u;
+                level |= key[r][c] == T ? 1u << c : 0u;
+            }
+            if (level) {                                     // at the cut the position decides
+#pragma unroll
+                for (int c = 0; c < 4; ++c) above |= 4 * q + c >= Pt ? level & (1u << c) : 0u;
+            }
+            keep |= (above << (4 * r)) & compete;
+        }
+        if (4 * q < ns || 4 * q + 3 >= rs) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int32_t p = 4 * q + c;
+                keep |= p < nb && (p < ns || p >= rs) ? 1u << (4 * r + c) : 0u;
+            }
+        }
+    }
+    uint32_t kept_min = 0xFFFFFFFFu, gone_max = 0u;          // keys at the cut, over this thread's candidates
+    if (a.margin) {                                          // uniform
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t bit = 1u << (4 * r + c), k = key[r][c];
+                kept_min = (compete & keep & bit) && k < kept_min ? k : kept_min;
+                gone_max = (compete & ~keep & bit) && k > gone_max ? k : gone_max;
+            }
+    }
+    constexpr int PAIRS = (ROUNDS + 1) / 2;
+    uint32_t incl2[PAIRS];                                   // inclusive counts within the wavefront, rounds 2j and 2j + 1
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) {
+        uint32_t v = (uint32_t)__popc((keep >> (8 * j)) & 15u);
+        if (2 * j + 1 < ROUNDS) v |= (uint32_t)__popc((keep >> (8 * j + 4)) & 15u) << 16;
+        incl2[j] = wave_scan_dpp(v);                         // at most 256 per field: no carry between the halves
+    }
+    if (lane == 63) {
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) L.totals[r * SR_WAVES + wave] = (incl2[r >> 1] >> (16 * (r & 1))) & 0xFFFFu;
+    }
+    if (a.margin) {                                          // uniform
+        kept_min = wave_min_dpp(kept_min);
+        gone_max = wave_max_dpp(gone_max);
+        if (lane == 0) {
+            L.edge[0][wave] = kept_min;
+            L.edge[1][wave] = gone_max;
+        }
+    }
+    __syncthreads();
+    // every wavefront scans the ROUNDS * SR_WAVES totals for itself, two per lane
+    const uint32_t t0 = 2 * lane < ROUNDS * SR_WAVES ? L.totals[2 * lane] : 0u;
+    const uint32_t t1 = 2 * lane < ROUNDS * SR_WAVES ? L.totals[2 * lane + 1] : 0u;
+    const uint32_t after = wave_scan_dpp(t0 + t1);
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        if (r * SR_THREADS >= nquads) break;                 // uniform
+        const int e = r * SR_WAVES + wave;                   // uniform in the wavefront
+        const uint32_t upto = (uint32_t)__builtin_amdgcn_readlane((int)after, __builtin_amdgcn_readfirstlane(e >> 1));
+        const uint32_t odd = (uint32_t)__builtin_amdgcn_readlane((int)t1, __builtin_amdgcn_readfirstlane(e >> 1));
+        const uint32_t even = (uint32_t)__builtin_amdgcn_readlane((int)t0, __builtin_amdgcn_readfirstlane(e >> 1));
+        const uint32_t before = upto - odd - ((e & 1) ? 0u : even);
+        const uint32_t bits = (keep >> (4 * r)) & 15u;
+        if (__ballot(bits) == 0ull) continue;
+        const uint32_t incl = (incl2[r >> 1] >> (16 * (r & 1))) & 0xFFFFu;
+        int32_t slot = (int32_t)(before + incl) - __popc(bits);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            if (bits & (1u << c)) {
+                if (slot < K) idx[slot] = 4 * (r * SR_THREADS + tid) + c;
+                ++slot;
+            }
+        }
+    }
+    if (tid == 0) {
+        const int32_t total = (int32_t)__builtin_amdgcn_readlane((int)after, 63);
+        a.cnt[unit] = total < K ? total : K;
+        if (a.margin) {
+            for (int w = 0; w < SR_WAVES; ++w) {
+                kept_min = L.edge[0][w] < kept_min ? L.edge[0][w] : kept_min;
+                gone_max = L.edge[1][w] > gone_max ? L.edge[1][w] : gone_max;
+            }
+            a.margin[2 * (size_t)unit] = margin_value(kept_min);
+            a.margin[2 * (size_t)unit + 1] = margin_value(gone_max);
+        }
+    }
+}
+
 // ---- streaming form: every input is read once, whatever the length ----------------------------
 // One workgroup of four wavefronts per unit walks the sequence from its end in segments and keeps
 // the best candidates of the boundary class seen so far in LDS as (key, position) pairs.  A
@@ -678,49 +1045,36 @@ select_kernel(SelectArgs a)
 // bitmap of the sequence (bits of the mandatory positions, of the sponsored ones when they are
 // all kept, and of the final R candidates).
 constexpr int SS_THREADS = 256;
-constexpr int SS_WAVES = SS_THREADS / 64;
-#ifndef TA_SELECT_STREAM_QPT
-#define TA_SELECT_STREAM_QPT 1
-#endif
-#ifndef TA_SELECT_STREAM_SLACK
-#define TA_SELECT_STREAM_SLACK 256
-#endif
-constexpr int SS_QPT = TA_SELECT_STREAM_QPT;               // quads per thread and segment
-constexpr int SS_SLACK = TA_SELECT_STREAM_SLACK;           // list entries beyond R + one segment: new entries between two cuts
-constexpr int SS_SEG_QUADS = SS_THREADS * SS_QPT;
-constexpr int SS_SEG = SS_SEG_QUADS * 4;                   // positions per segment
-#ifndef TA_SELECT_STREAM_DEPTH
-#define TA_SELECT_STREAM_DEPTH 2
-#endif
-constexpr int SS_DEPTH = TA_SELECT_STREAM_DEPTH;           // segments whose operands are in flight
+constexpr int SS_BIG_THREADS = 1024;                       // few units with long rows: a workgroup has a compute unit to itself
+constexpr int SS_SLACK = 256;                              // list entries beyond R + one segment: new entries between two cuts
+constexpr int SS_DEPTH = 2;                                // segments whose operands are in flight
 constexpr int SS_HIST_COPIES = 4;
 constexpr int SS_MAX_PER_THREAD = 24;                      // list entries a thread holds while the list is compacted
 constexpr int SS_FEW_PER_THREAD = 10;                      // ... in the instance for short lists (budgets up to about 1300)
+constexpr int SS_BIG_PER_THREAD = 6;                       // ... in a workgroup of SS_BIG_THREADS
 constexpr int SS_MAX_CAP = SS_THREADS * SS_MAX_PER_THREAD;
 constexpr int SS_MAX_LDS = 144 * 1024;                     // dynamic LDS of a workgroup (list + bitmap)
-// Which form runs: the streaming form whenever the keys of a row do not fit the LDS cache of the
-// kernel above, and for shorter rows when there are enough units to fill the chip several times
-// (its workgroups are small and many fit a compute unit; measured on 16 384 ragged units of up to
-// 16 384 positions: 560 us against 1270).  With few units the latency of one workgroup counts, and
-// the cached kernel's is half as long (13 us against 25 for 256 units of 4096 positions).
-#ifndef TA_SELECT_STREAM_MIN_UNITS
-#define TA_SELECT_STREAM_MIN_UNITS 2048
-#endif
-constexpr int64_t SS_MIN_UNITS = TA_SELECT_STREAM_MIN_UNITS;
+// Which form runs: this one when a row does not fit the registers of the form above, and from 1024 units on, where its small
+// workgroups fill the chip (in us, register / streaming form: 512 units of up to 3001 positions 11 / 16, 256 of
+// 16 384 15 / 36, 1024 of 1000 17 / 15, 1024 of 32 768 102 / 78, 2048 of up to 16 384 94 / 65, 16 384 of up to
+// 2048 215 / 162).  Long rows: sixteen wavefronts per unit up to 512 units (512 of 65 537: 97 us against 118 with
+// four; 1024 of 40 001: 129 against 92).
+constexpr int64_t SS_MIN_UNITS = 1024;
+constexpr int64_t SS_BIG_MAX_UNITS = 512;
 
 struct StreamLds {
     uint32_t hist[SS_HIST_COPIES][HIST_STRIDE];
     uint32_t h[256];
-    int red[SS_WAVES];
+    int red[SS_BIG_THREADS / 64];
     RadixState state;
     uint32_t count;                                        // entries in the candidate list
 };
 
-// The same search as radix_pick, for a workgroup of SS_THREADS threads and SS_HIST_COPIES histograms.
+// The same search as radix_pick, for SS_HIST_COPIES histograms.
 __device__ __forceinline__ RadixState stream_pick(StreamLds& L, uint32_t need)
 {
     const int tid = threadIdx.x;
-    {
+    if (tid < 256) {
         uint32_t t = 0;
 #pragma unroll
         for (int c = 0; c < SS_HIST_COPIES; ++c) {
@@ -767,9 +1121,11 @@ __device__ __forceinline__ RadixState stream_pick(StreamLds& L, uint32_t need)
 
 // MARGIN: the keys turned away are tracked for the margin output (instances of their own: the default
 // ones keep their registers)
-template <int PER_THREAD, bool MARGIN>                     // cap <= SS_THREADS * PER_THREAD
+template <int THREADS, int PER_THREAD, bool MARGIN>        // cap <= THREADS * PER_THREAD
 __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t cap)
 {
+    constexpr int WAVES = THREADS / 64;
+    constexpr int SEG = THREADS * 4;                       // positions per segment
     extern __shared__ uint32_t s_dyn[];                    // [cap] keys, [cap] positions, [ceil(n / 32)] bitmap
     __shared__ StreamLds L;
     uint32_t* ckey = s_dyn;
@@ -793,7 +1149,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     nb = nb < 0 ? 0 : (nb > n ? n : nb);
     int32_t* idx = a.idx + (size_t)unit * (size_t)a.K;
     if (nb <= K) {                                         // nothing to evict
-        for (int32_t p = tid; p < nb; p += SS_THREADS) idx[p] = p;
+        for (int32_t p = tid; p < nb; p += THREADS) idx[p] = p;
         if (tid == 0) {
             a.cnt[unit] = nb;
             if (a.margin) {
@@ -813,7 +1169,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     int32_t rs = nb - a.n_recent;
     rs = rs < ns ? ns : rs;
     const int32_t c2 = ns + (nb - rs);
-    const int32_t nquads = (nb + 3) >> 2;                  // rows are padded to whole quads (n % 4 == 0)
+    const int32_t nquads = (nb + 3) >> 2;    
     const bool use_A = (a.alpha != 0.0f);
     const int32_t words = (nb + 31) >> 5;
 
@@ -826,34 +1182,34 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     const float* A_src = use_A ? A : vouch;                // no attention term: any readable row, the values are not used
     const auto load_quad = [&](int32_t q, Loaded& x) {
         q = q < 0 ? 0 : (q >= nquads ? nquads - 1 : q);
-        x.sp = *reinterpret_cast<const uint32_t*>(spons + 4 * q);
-        x.an = *reinterpret_cast<const uint32_t*>(anchor + 4 * q);
-        x.v = *reinterpret_cast<const float4*>(vouch + 4 * q);
-        x.A = *reinterpret_cast<const float4*>(A_src + 4 * q);
+        const int32_t start = quad_start(4 * q, n);        // n >= 4 (the launcher)
+        x.sp = load_quad_b(spons, start);
+        x.an = load_quad_b(anchor, start);
+        x.v = load_quad_f(vouch, start);
+        x.A = load_quad_f(A_src, start);
     };
 
     // the first segments' operands are requested before anything else: they travel while the sponsored
     // positions are counted
-    const int32_t nseg = (nquads + SS_SEG_QUADS - 1) / SS_SEG_QUADS;
-    Loaded ring[SS_DEPTH][SS_QPT];
+    const int32_t nseg = (nquads + THREADS - 1) / THREADS;
+    Loaded ring[SS_DEPTH];
 #pragma unroll
-    for (int d = 0; d < SS_DEPTH; ++d)
-#pragma unroll
-        for (int j = 0; j < SS_QPT; ++j) load_quad((nseg - 1 - d) * SS_SEG_QUADS + j * SS_THREADS + tid, ring[d][j]);
+    for (int d = 0; d < SS_DEPTH; ++d) load_quad((nseg - 1 - d) * THREADS + tid, ring[d]);
 
 
-    for (int i = tid; i < SS_HIST_COPIES * HIST_STRIDE; i += SS_THREADS) (&L.hist[0][0])[i] = 0;
-    for (int32_t i = tid; i < words; i += SS_THREADS) bitmap[i] = 0u;
+    for (int i = tid; i < SS_HIST_COPIES * HIST_STRIDE; i += THREADS) (&L.hist[0][0])[i] = 0;
+    for (int32_t i = tid; i < words; i += THREADS) bitmap[i] = 0u;
     if (tid == 0) L.count = 0u;
 
     // ---- sponsored positions outside the mandatory ranges (16 flags per load) -------------------
     int local = 0;
     {
-        const int32_t n16 = ((uintptr_t)spons & 15u) == 0 ? nb >> 4 : 0;     // (a row that is not 16-byte aligned: byte by byte)
-        const uint4* sp16 = reinterpret_cast<const uint4*>(spons);
-        for (int32_t i = tid; i < n16; i += SS_THREADS) {
-            const uint4 f = sp16[i];
-            const uint32_t w4[4] = {f.x, f.y, f.z, f.w};
+        const int32_t n16 = nb >> 4;
+        typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+        const u32x4_any* sp16 = reinterpret_cast<const u32x4_any*>(spons);
+        for (int32_t i = tid; i < n16; i += THREADS) {
+            const u32x4_any f = sp16[i];
+            const uint32_t w4[4] = {f[0], f[1], f[2], f[3]};
             const int32_t p0 = 16 * i;
             if (p0 >= ns && p0 + 15 < rs) {
 #pragma unroll
@@ -872,7 +1228,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
                 }
             }
         }
-        for (int32_t p = 16 * n16 + tid; p < nb; p += SS_THREADS) local += (p >= ns && p < rs && spons[p]) ? 1 : 0;
+        for (int32_t p = 16 * n16 + tid; p < nb; p += THREADS) local += (p >= ns && p < rs && spons[p]) ? 1 : 0;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) local += __shfl_xor(local, o);
@@ -880,14 +1236,14 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     __syncthreads();                                       // also: histograms, bitmap and count are cleared
     int32_t c1 = 0;
 #pragma unroll
-    for (int w = 0; w < SS_WAVES; ++w) c1 += L.red[w];
+    for (int w = 0; w < WAVES; ++w) c1 += L.red[w];
 
     const int bclass = (c2 + c1 <= K) ? 0 : 1;
     const int32_t R = bclass == 0 ? K - c2 - c1 : K - c2;  // slots of the boundary class (more members than that exist)
-    const float nf = (float)nb;
+    const float nf = (float)nb, inv = __fdiv_rn(1.0f, nf);
 
     auto key_of = [&](int32_t p, float Ap, uint32_t an, float v) -> uint32_t {
-        float r = __fdiv_rn((float)(p + 1), nf);
+        const float r = div_by((float)(p + 1), nf, inv);
         float t = use_A ? __fmul_rn(a.alpha, Ap) : 0.0f;
         t = __fadd_rn(t, __fmul_rn(a.beta, r));
         t = __fadd_rn(t, __fmul_rn(a.gamma, an ? 1.0f : 0.0f));
@@ -907,7 +1263,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
         bool done = false;
         for (int pass = 0; pass < 4 && !done; ++pass) {
             const int shift = 24 - 8 * pass;
-            for (uint32_t e = tid; e < m; e += SS_THREADS) {
+            for (uint32_t e = tid; e < m; e += THREADS) {
                 const uint32_t k = ckey[e];
                 const bool in = pass == 0 || (k >> (shift + 8)) == (prefix >> (shift + 8));
                 if (in) atomicAdd(&L.hist[lane & (SS_HIST_COPIES - 1)][(k >> shift) & 255u], 1u);
@@ -927,7 +1283,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
                 uint32_t pprefix = 0, pneed = need;
                 for (int pp = 0; pp < ppasses; ++pp) {
                     const int ps = 8 * (ppasses - 1 - pp);
-                    for (uint32_t e = tid; e < m; e += SS_THREADS) {
+                    for (uint32_t e = tid; e < m; e += THREADS) {
                         const uint32_t p = cpos[e];
                         const bool in = ckey[e] == Tn && (pp == 0 || (p >> (ps + 8)) == (pprefix >> (ps + 8)));
                         if (in) atomicAdd(&L.hist[lane & (SS_HIST_COPIES - 1)][(p >> ps) & 255u], 1u);
@@ -946,7 +1302,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
         uint32_t mk[PER_THREAD], mp[PER_THREAD];
 #pragma unroll
         for (int j = 0; j < PER_THREAD; ++j) {
-            const uint32_t e = (uint32_t)tid + (uint32_t)j * SS_THREADS;
+            const uint32_t e = (uint32_t)tid + (uint32_t)j * THREADS;
             mk[j] = e < m ? ckey[e] : 0u;
             mp[j] = e < m ? cpos[e] : 0u;
         }
@@ -954,7 +1310,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < PER_THREAD; ++j) {
-            if ((uint32_t)j * SS_THREADS >= m) continue;   // uniform: nothing of the list lies this far
+            if ((uint32_t)j * THREADS >= m) continue;   // uniform: nothing of the list lies this far
             const bool keep = mk[j] > Tn || (mk[j] == Tn && mk[j] != 0u && (int32_t)mp[j] >= Pn);
             if (MARGIN && !keep) gone_max = mk[j] > gone_max ? mk[j] : gone_max;   // (0 beyond the list's end)
             const unsigned long long bal = __ballot(keep);
@@ -980,55 +1336,55 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
 #pragma unroll
         for (int d = 0; d < SS_DEPTH; ++d) {
             const int32_t sg = top - d;
-            uint32_t keys[SS_QPT][4];
-            bool join[SS_QPT][4];
-            uint32_t always[SS_QPT];                       // bits of a quad that are retained whatever the ranking says
-#pragma unroll
-            for (int j = 0; j < SS_QPT; ++j) {
-                const Loaded& x = ring[d][j];
-                const int32_t q = sg * SS_SEG_QUADS + j * SS_THREADS + tid;
+            const int32_t q = sg * THREADS + tid;
+            uint32_t keys[4];
+            bool join[4];
+            uint32_t always = 0u;                          // bits of the quad that are retained whatever the ranking says
+            {
+                Loaded x = ring[d];
+                if (n & 3) {                               // uniform
+                    const int32_t by = q == nquads - 1 ? 4 * q - quad_start(4 * q, n) : 0;
+                    x.sp >>= 8 * by;
+                    x.an >>= 8 * by;
+                    x.v = move_down(x.v, by);
+                    x.A = move_down(x.A, by);
+                }
                 const float Aq[4] = {x.A.x, x.A.y, x.A.z, x.A.w};
                 const float vq[4] = {x.v.x, x.v.y, x.v.z, x.v.w};
-                always[j] = 0u;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const int32_t p = 4 * q + c;
                     const uint32_t sp = (x.sp >> (8 * c)) & 0xFFu, an = (x.an >> (8 * c)) & 0xFFu;
-                    keys[j][c] = 0u;
-                    join[j][c] = false;
+                    keys[c] = 0u;
+                    join[c] = false;
                     if (sg >= 0 && p < nb && q < nquads) {
-                        if (p < ns || p >= rs) always[j] |= 1u << c;
-                        else if ((sp != 0u) != (bclass == 1)) always[j] |= (sp != 0u) ? (1u << c) : 0u;   // class 1 above the boundary class, class 0 below it
+                        if (p < ns || p >= rs) always |= 1u << c;
+                        else if ((sp != 0u) != (bclass == 1)) always |= (sp != 0u) ? (1u << c) : 0u;   // class 1 above the boundary class, class 0 below it
                         else if (MARGIN || R > 0) {
-                            keys[j][c] = key_of(p, Aq[c], an, vq[c]);
-                            join[j][c] = R > 0 && (keys[j][c] > T || (keys[j][c] == T && p >= Pt));
-                            if (MARGIN && !join[j][c]) gone_max = keys[j][c] > gone_max ? keys[j][c] : gone_max;
+                            keys[c] = key_of(p, Aq[c], an, vq[c]);
+                            join[c] = R > 0 && (keys[c] > T || (keys[c] == T && p >= Pt));
+                            if (MARGIN && !join[c]) gone_max = keys[c] > gone_max ? keys[c] : gone_max;
                         }
                     }
                 }
             }
             // the segment SS_DEPTH further on takes over the registers (past the first segment: a clamped
             // address whose data nobody uses)
-#pragma unroll
-            for (int j = 0; j < SS_QPT; ++j) load_quad((sg - SS_DEPTH) * SS_SEG_QUADS + j * SS_THREADS + tid, ring[d][j]);
+            load_quad((sg - SS_DEPTH) * THREADS + tid, ring[d]);
             if (sg >= 0) {                                 // uniform
+                if (always) atomicOr(&bitmap[(4 * q) >> 5], always << ((4 * q) & 31));
 #pragma unroll
-                for (int j = 0; j < SS_QPT; ++j) {
-                    const int32_t q = sg * SS_SEG_QUADS + j * SS_THREADS + tid;
-                    if (always[j]) atomicOr(&bitmap[(4 * q) >> 5], always[j] << ((4 * q) & 31));
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const unsigned long long bal = __ballot(join[j][c]);
-                        if (bal) {                         // uniform
-                            uint32_t base = 0;
-                            if (lane == 0) base = atomicAdd(&L.count, (uint32_t)__popcll(bal));
-                            base = __shfl(base, 0);
-                            if (join[j][c]) {
-                                const uint32_t slot = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-                                if (slot < (uint32_t)cap) {    // holds by construction: the list is cut back before it could overflow
-                                    ckey[slot] = keys[j][c];
-                                    cpos[slot] = (uint32_t)(4 * q + c);
-                                }
+                for (int c = 0; c < 4; ++c) {
+                    const unsigned long long bal = __ballot(join[c]);
+                    if (bal) {                             // uniform
+                        uint32_t base = 0;
+                        if (lane == 0) base = atomicAdd(&L.count, (uint32_t)__popcll(bal));
+                        base = __shfl(base, 0);
+                        if (join[c]) {
+                            const uint32_t slot = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+                            if (slot < (uint32_t)cap) {    // holds by construction: the list is cut back before it could overflow
+                                ckey[slot] = keys[c];
+                                cpos[slot] = (uint32_t)(4 * q + c);
                             }
                         }
                     }
@@ -1039,7 +1395,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
                 // Cut back when the next segment might not fit, at the end (to exactly R), and once early: the
                 // first cut gives the threshold that keeps most later positions out of the list.
                 const bool early = T == 0u && m >= 2u * (uint32_t)R && m >= 512u;
-                if (R > 0 && ((sg > 0 && (m + (uint32_t)SS_SEG > (uint32_t)cap || early)) || (sg == 0 && m > (uint32_t)R))) shrink(m);
+                if (R > 0 && ((sg > 0 && (m + (uint32_t)SEG > (uint32_t)cap || early)) || (sg == 0 && m > (uint32_t)R))) shrink(m);
             }
         }
     }
@@ -1047,13 +1403,13 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     // ---- the final candidates join the bitmap; ascending write-out from it --------------------------
     {
         const uint32_t m = L.count;                        // == R (or 0)
-        for (uint32_t e = tid; e < m; e += SS_THREADS) {
+        for (uint32_t e = tid; e < m; e += THREADS) {
             const uint32_t p = cpos[e];
             atomicOr(&bitmap[p >> 5], 1u << (p & 31u));
         }
     }
     __syncthreads();
-    const int32_t wpt = (words + SS_THREADS - 1) / SS_THREADS;            // consecutive words per thread
+    const int32_t wpt = (words + THREADS - 1) / THREADS;            // consecutive words per thread
     const int32_t w0 = tid * wpt;
     int mine = 0;
     for (int32_t w = w0; w < w0 + wpt && w < words; ++w) mine += __popc(bitmap[w]);
@@ -1067,7 +1423,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     __syncthreads();
     int woff = 0, total = 0;
 #pragma unroll
-    for (int w = 0; w < SS_WAVES; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
         const int c = L.red[w];
         woff += (w < wave) ? c : 0;
         total += c;
@@ -1086,7 +1442,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     if (MARGIN) {
         uint32_t kept_min = 0xFFFFFFFFu;
         const uint32_t m = L.count;
-        for (uint32_t e = tid; e < m; e += SS_THREADS) kept_min = ckey[e] < kept_min ? ckey[e] : kept_min;
+        for (uint32_t e = tid; e < m; e += THREADS) kept_min = ckey[e] < kept_min ? ckey[e] : kept_min;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             const uint32_t lo = __shfl_xor(kept_min, o), hi = __shfl_xor(gone_max, o);
@@ -1096,14 +1452,14 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
         __syncthreads();                                   // the scan's partial sums have been read
         if (lane == 0) {
             L.h[wave] = kept_min;
-            L.h[SS_WAVES + wave] = gone_max;
+            L.h[WAVES + wave] = gone_max;
         }
         __syncthreads();
         if (tid == 0) {
 #pragma unroll
-            for (int w = 0; w < SS_WAVES; ++w) {
+            for (int w = 0; w < WAVES; ++w) {
                 kept_min = L.h[w] < kept_min ? L.h[w] : kept_min;
-                gone_max = L.h[SS_WAVES + w] > gone_max ? L.h[SS_WAVES + w] : gone_max;
+                gone_max = L.h[WAVES + w] > gone_max ? L.h[WAVES + w] : gone_max;
             }
             a.margin[2 * (size_t)unit] = margin_value(kept_min);
             a.margin[2 * (size_t)unit + 1] = margin_value(gone_max);
@@ -1117,25 +1473,39 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
 __global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
 select_stream_few_kernel(SelectArgs a, int32_t cap)
 {
-    select_stream<SS_FEW_PER_THREAD, false>(a, cap);
+    select_stream<SS_THREADS, SS_FEW_PER_THREAD, false>(a, cap);
 }
 
 __global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
 select_stream_few_margin_kernel(SelectArgs a, int32_t cap)
 {
-    select_stream<SS_FEW_PER_THREAD, true>(a, cap);
+    select_stream<SS_THREADS, SS_FEW_PER_THREAD, true>(a, cap);
 }
 
 __global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 select_stream_kernel(SelectArgs a, int32_t cap)
 {
-    select_stream<SS_MAX_PER_THREAD, false>(a, cap);
+    select_stream<SS_THREADS, SS_MAX_PER_THREAD, false>(a, cap);
 }
 
 __global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
 select_stream_margin_kernel(SelectArgs a, int32_t cap)
 {
-    select_stream<SS_MAX_PER_THREAD, true>(a, cap);
+    select_stream<SS_THREADS, SS_MAX_PER_THREAD, true>(a, cap);
+}
+
+// Few units with long rows: 256 of them have a compute unit each, where four wavefronts walk 1024 positions at a time
+// (256 rows of 131 072 positions: 203 us); sixteen walk 4096.
+__global__ void __launch_bounds__(SS_BIG_THREADS)
+select_stream_big_kernel(SelectArgs a, int32_t cap)
+{
+    select_stream<SS_BIG_THREADS, SS_BIG_PER_THREAD, false>(a, cap);
+}
+
+__global__ void __launch_bounds__(SS_BIG_THREADS)
+select_stream_big_margin_kernel(SelectArgs a, int32_t cap)
+{
+    select_stream<SS_BIG_THREADS, SS_BIG_PER_THREAD, true>(a, cap);
 }
 
 DeviceOnce g_setup;
@@ -1145,21 +1515,19 @@ DeviceOnce g_setup;
 hipError_t select_setup()
 {
     return g_setup.run([](int) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<true, false, SEL_MAX_ROUNDS>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           SEL_CACHE_MAX_N * (int)sizeof(uint32_t));
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<true, true, SEL_MAX_ROUNDS>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    SEL_CACHE_MAX_N * (int)sizeof(uint32_t));
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_few_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_few_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_few_margin_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_big_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_big_margin_kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
         if (e == hipSuccess)
             e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_margin_kernel),
@@ -1171,9 +1539,10 @@ hipError_t select_setup()
 hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* spons,
                          const float* vouch, const int32_t* seq_len,
                          int32_t layers, int32_t batch, int32_t hkv, int32_t n, int32_t K,
-                         const ta_params& prm, int32_t* idx, int32_t* cnt, hipStream_t st)
+                         const ta_params& prm, int32_t* idx, int32_t* cnt, hipStream_t st, bool own_vouchers)
 {
     SelectArgs a;
+    a.plain_vouch = own_vouchers ? 1 : 0;
     a.A = (prm.alpha != 0.0f) ? A : nullptr;
     a.anchor = anchor;
     a.spons = spons;
@@ -1201,34 +1570,35 @@ hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* s
                ((uintptr_t)vouch % 16 == 0) && (a.A == nullptr || (uintptr_t)a.A % 16 == 0);
     const unsigned blocks = 8u * (unsigned)a.units_per_xcd;
     const bool capped = prm.k_protected >= 0;
-    // The streaming form serves the plain (elastic, unpooled) selection on quad-aligned rows when
-    // its candidate list and the bitmap of the sequence fit the LDS of a workgroup.
-    if (!capped && a.pool_r == 0 && a.vec_ok && (n > SEL_CACHE_MAX_N || units >= SS_MIN_UNITS)) {
+    // The streaming form serves the plain (elastic, unpooled) selection when its candidate list and the bitmap of the
+    // sequence fit the LDS of a workgroup.
+    if (!capped && a.pool_r == 0 && n >= 4 && (n > SR_MAX_N || units >= SS_MIN_UNITS)) {
         const int64_t rmax = (int64_t)K - prm.n_sink - prm.n_recent;      // most slots the boundary class can have
-        int64_t cap = rmax + SS_SEG + SS_SLACK;
-        cap = (cap + SS_THREADS - 1) / SS_THREADS * SS_THREADS;
-        const int64_t lds = cap * 8 + ((int64_t)n + 31) / 32 * 4;
-        if (cap <= SS_MAX_CAP && lds <= SS_MAX_LDS) {
+        const auto list_cap = [&](int threads) { return (rmax + 4 * threads + SS_SLACK + threads - 1) / threads * threads; };
+        const auto lds_of = [&](int64_t cap) { return cap * 8 + ((int64_t)n + 31) / 32 * 4; };
+        const int64_t big_cap = list_cap(SS_BIG_THREADS), cap = list_cap(SS_THREADS);
+        const bool big = units <= SS_BIG_MAX_UNITS && big_cap <= SS_BIG_THREADS * SS_BIG_PER_THREAD && lds_of(big_cap) <= SS_MAX_LDS;
+        if (big || (cap <= SS_MAX_CAP && lds_of(cap) <= SS_MAX_LDS)) {
             const hipError_t attr_err = select_setup();
             if (attr_err != hipSuccess) return attr_err;
             const bool few = cap <= SS_THREADS * SS_FEW_PER_THREAD;
-            auto kernel = few ? (a.margin ? select_stream_few_margin_kernel : select_stream_few_kernel)
+            auto kernel = big ? (a.margin ? select_stream_big_margin_kernel : select_stream_big_kernel)
+                        : few ? (a.margin ? select_stream_few_margin_kernel : select_stream_few_kernel)
                               : (a.margin ? select_stream_margin_kernel : select_stream_kernel);
-            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(SS_THREADS), (size_t)lds, st, a, (int32_t)cap);
+            const int64_t c = big ? big_cap : cap;
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(big ? SS_BIG_THREADS : SS_THREADS), (size_t)lds_of(c), st, a, (int32_t)c);
             return hipGetLastError();
         }
     }
-    if (n <= SEL_CACHE_MAX_N) {
-        const hipError_t attr_err = select_setup();
-        if (attr_err != hipSuccess) return attr_err;
-        const size_t lds = (size_t)((n + 3) / 4 * 4) * sizeof(uint32_t);
-        const bool one_round = n <= 4 * SEL_THREADS;         // 16 KB of keys: within the default dynamic LDS limit
-        auto kernel = capped ? (one_round ? select_kernel<true, true, 1> : select_kernel<true, true, SEL_MAX_ROUNDS>)
-                             : (one_round ? select_kernel<true, false, 1> : select_kernel<true, false, SEL_MAX_ROUNDS>);
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(SEL_THREADS), lds, st, a);
+    if (n <= SR_MAX_N) {
+        auto kernel = capped ? (n <= 4 * SR_THREADS ? select_reg_kernel<1, true> : n <= 8 * SR_THREADS ? select_reg_kernel<2, true>
+                                : n <= 16 * SR_THREADS ? select_reg_kernel<4, true> : select_reg_kernel<8, true>)
+                             : (n <= 4 * SR_THREADS ? select_reg_kernel<1, false> : n <= 8 * SR_THREADS ? select_reg_kernel<2, false>
+                                : n <= 16 * SR_THREADS ? select_reg_kernel<4, false> : select_reg_kernel<8, false>);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(SR_THREADS), 0, st, a);
     } else {
-        if (capped) hipLaunchKernelGGL((select_kernel<false, true, 0>), dim3(blocks), dim3(SEL_THREADS), 0, st, a);
-        else hipLaunchKernelGGL((select_kernel<false, false, 0>), dim3(blocks), dim3(SEL_THREADS), 0, st, a);
+        if (capped) hipLaunchKernelGGL(select_kernel<true>, dim3(blocks), dim3(SEL_THREADS), 0, st, a);
+        else hipLaunchKernelGGL(select_kernel<false>, dim3(blocks), dim3(SEL_THREADS), 0, st, a);
     }
     return hipGetLastError();
 }

@@ -112,3 +112,73 @@ def test_streaming_select_per_layer_budgets():
 ])
 def test_streaming_select_long_rows(n, K, mode):
     _check(1, 2, 3, n, K, 4, 128, mode, planted=40)
+
+
+@pytest.mark.parametrize("n,K,ns,nr,mode", [
+    (2, 1, 0, 1, "uniform"), (3, 2, 1, 1, "zeros"), (5, 4, 0, 0, "ties"), (37, 9, 4, 4, "uniform"),   # rows of less than a quad and a few
+    (1023, 300, 4, 4, "ties"),           # rows of a batch at every alignment
+    (4095, 64, 4, 4, "uniform"), (4096, 4000, 4, 4, "zeros"), (4097, 1024, 4, 4, "early"),              # one round of quads and one position more
+    (8193, 2000, 0, 64, "ties"), (16385, 512, 4, 4, "uniform"), (32767, 16, 4, 4, "zeros"), (32768, 1024, 4, 128, "uniform"),
+    (33001, 700, 4, 4, "uniform"),       # streaming form, rows at odd addresses
+])
+def test_register_select_at_its_limits(n, K, ns, nr, mode):
+    _check(1, 3, 2, n, K, ns, nr, mode, planted=3 if n > 300 else 0)
+
+
+@pytest.mark.parametrize("n,layers", [(1337, 64), (2050, 64)])
+def test_streaming_select_rows_at_odd_addresses(n, layers):
+    _check(layers, 4, 4, n, 120, 4, 8, "uniform", ragged=(100, n), sample=150)     # 1024 units
+
+
+@pytest.mark.parametrize("spread", [1e-30, 1.0, 1e30])
+def test_register_select_with_outliers_and_crowded_bins(spread):
+    # nearly all keys in one bin of the first level (a few values far away), then exact ties among thousands
+    rng = np.random.default_rng(7)
+    n, K = 12000, 900
+    A = (1.0 + rng.integers(0, 4, (1, 1, 4, n)) * 1e-6).astype(np.float32)
+    A[0, 0, :, rng.integers(0, n, 5)] = spread
+    A[0, 0, 1, 100:200] = -spread
+    A[0, 0, 2] = np.float32(0.25)
+    zero8, zerof = np.zeros((1, n), np.uint8), np.zeros((1, n), np.float32)
+    prm = ta.Params(n_sink=2, n_recent=3, beta=0.0)
+    idx, cnt = ta.ta_select(_dev(A), _dev(zero8), _dev(zero8), _dev(zerof), K, prm, 1, 4)
+    idx = idx.cpu().numpy()
+    for h in range(4):
+        ref = ora.select(A[0, 0, h], zero8[0], zero8[0], zerof[0], K, 2, 3, alpha=1.0, beta=0.0, gamma=0.3)
+        assert np.array_equal(idx[0, 0, h], ref)
+
+
+@pytest.mark.parametrize("n,K", [(900, 40), (4097, 256), (20001, 512), (32768, 512), (40002, 512)])
+@pytest.mark.parametrize("vouchers", ["sponsored", "any", "negative"])
+def test_attention_free_select_with_any_vouchers(n, K, vouchers):
+    # anchors and vouchers anywhere, on unsponsored positions too; negative vouchers turn the recency order round
+    rng = np.random.default_rng(n + K)
+    anchor = (rng.random((2, n)) < 0.004).astype(np.uint8)
+    spons = (rng.random((2, n)) < 0.004).astype(np.uint8)
+    vouch = np.where(spons != 0, rng.random((2, n)) * 9, 0.0).astype(np.float32)
+    if vouchers == "any":
+        vouch += np.where(rng.random((2, n)) < 0.002, 0.7, 0.0).astype(np.float32)
+    if vouchers == "negative":
+        vouch[1] -= np.where(rng.random(n) < 0.9, 0.9, 0.0).astype(np.float32)
+    prm = ta.Params(n_sink=4, n_recent=8, alpha=0.0)
+    idx, cnt = ta.ta_select(None, _dev(anchor), _dev(spons), _dev(vouch), K, prm, 1, 1)
+    idx = idx.cpu().numpy()
+    for b in range(2):
+        ref = ora.select(None, anchor[b], spons[b], vouch[b], K, 4, 8, alpha=0.0)
+        assert np.array_equal(idx[0, b, 0], ref)
+
+
+@pytest.mark.parametrize("n,K,planted,beta,gamma", [(900, 40, 3, 0.5, 0.3), (4097, 256, 12, 0.5, 0.3), (20001, 512, 200, 0.5, 0.3),
+                                                    (20001, 64, 200, 0.5, 0.3), (32768, 512, 30, 0.0, 0.0), (32767, 512, 30, 0.5, -0.4),
+                                                    (9000, 512, 30, -0.5, 0.3)])
+def test_attention_free_pass_skips_nothing_that_counts(n, K, planted, beta, gamma):
+    # the pass does not rank plain positions that cannot be retained; anchors early in the sequence can be
+    w, td, seqs = _inputs(n, 2, planted, (n // 2, n), 3)
+    kv = torch.zeros((1, 2, 1, n, 128), dtype=torch.bfloat16, device=DEV)
+    prm = ta.Params(n_sink=4, n_recent=8, alpha=0.0, beta=beta, gamma=gamma)
+    plan = ta.ta_evict(_dev(td.tok), td.tab_ids, td.tab_len, None, kv, kv.clone(), K, prm, seq_len=_dev(td.seq_len))
+    idx, cnt = plan.idx.cpu().numpy(), plan.cnt.cpu().numpy()
+    for b in range(2):
+        a, s, v = seqs[b]
+        ref = ora.select(None, a, s, v, K, 4, 8, alpha=0.0, beta=beta, gamma=gamma)
+        assert cnt[b] == len(ref) and np.array_equal(idx[b, :len(ref)], ref)
