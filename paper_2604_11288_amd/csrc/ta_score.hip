@@ -407,32 +407,58 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t][ks], kf[ks], acc[t], 0, 0, 0);
             }
     };
+    // online update of a row tile's statistics from its accumulators (the exact running maximum)
+    const auto online = [&](f32x16& acc, int t, auto masked_tag) {
+        constexpr bool MASKED = decltype(masked_tag)::value;
+        float tmax = acc[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, acc[i]);
+        const float mnew = fmaxf(m_run[t], tmax * sc);
+        const float mref = (MASKED && mnew == -INFINITY) ? 0.0f : mnew;   // every key hidden so far
+        float sum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum += fast_exp2(fmaf(acc[i], sc, -mref));
+        z_run[t] = z_run[t] * fast_exp2(m_run[t] - mref) + sum;
+        m_run[t] = mnew;
+    };
     // reduction of the accumulators of stage s; MASKED: some key of the stage is hidden from some row
     const auto reduce = [&](int s, f32x16 (&acc)[ROW_TILES], auto masked_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         const int32_t tile_key0 = key_lo + stage_pos(s) * STAGE_KEYS + 32 * kt;
         float colsum = 0.0f;
+        if constexpr (!COLSUM && !MASKED) {
+            // The reference of a row's exponents does not have to be the maximum: any logit the row has had keeps Z at 1 or
+            // more, and fp32 holds sums far above it.  So a stage only sums against the reference it finds (no maximum,
+            // no rescaling); one whose sum passes 2^64 - the first of the chunk, whose reference is -inf, and any
+            // with a logit 64 octaves above the reference - is reduced again with the maximum.
+            float sum[ROW_TILES];
+            bool small = true;
+#pragma unroll
+            for (int t = 0; t < ROW_TILES; ++t) {
+                sum[t] = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum[t] += fast_exp2(fmaf(acc[t][i], sc, -m_run[t]));
+                small = small && sum[t] < 1.8446744e19f;
+            }
+            if (__ballot(!small) == 0ull) {                // uniform
+#pragma unroll
+                for (int t = 0; t < ROW_TILES; ++t) z_run[t] += sum[t];
+            } else {
+#pragma unroll
+                for (int t = 0; t < ROW_TILES; ++t) online(acc[t], t, masked_tag);
+            }
+            return;
+        }
 #pragma unroll
         for (int t = 0; t < ROW_TILES; ++t) {
             if constexpr (!COLSUM) {
-                if constexpr (MASKED) {
-                    const int32_t lim = my_lim[t];
+                const int32_t lim = my_lim[t];
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int32_t key = tile_key0 + 8 * (i >> 2) + 4 * hf + (i & 3);
-                        acc[t][i] = key <= lim ? acc[t][i] : -INFINITY;
-                    }
+                for (int i = 0; i < 16; ++i) {
+                    const int32_t key = tile_key0 + 8 * (i >> 2) + 4 * hf + (i & 3);
+                    acc[t][i] = key <= lim ? acc[t][i] : -INFINITY;
                 }
-                float tmax = acc[t][0];
-#pragma unroll
-                for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, acc[t][i]);
-                const float mnew = fmaxf(m_run[t], tmax * sc);
-                const float mref = (MASKED && mnew == -INFINITY) ? 0.0f : mnew;   // every key hidden so far
-                float sum = 0.0f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) sum += fast_exp2(fmaf(acc[t][i], sc, -mref));
-                z_run[t] = z_run[t] * fast_exp2(m_run[t] - mref) + sum;
-                m_run[t] = mnew;
+                online(acc[t], t, masked_tag);
             } else {
                 if constexpr (!MASKED) {
 #pragma unroll

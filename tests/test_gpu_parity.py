@@ -232,6 +232,23 @@ def test_score_long_context_chunking():
     _check_score(w)
 
 
+@pytest.mark.parametrize("hq,window,n", [(4, 32, 3000), (8, 32, 2500)])
+@pytest.mark.parametrize("order", [1, -1, 0])
+def test_score_rows_whose_logits_pass_any_reference(hq, window, n, order):
+    # logits from -700 to 700 along the sequence (rising, falling, shuffled): the statistics sweep sums against a logit
+    # that a later stage exceeds by hundreds of octaves, or that the rest of the row never reaches again
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + order)
+    t = torch.linspace(-8, 8, n, device=DEV)
+    t = t.flip(0) if order < 0 else (t[torch.randperm(n, generator=g, device=DEV)] if order == 0 else t)
+    K = (t[:, None] + 0.05 * torch.randn((n, 128), generator=g, device=DEV)).to(torch.bfloat16)[None, None, None]
+    Q = (8.0 + 0.5 * torch.randn((1, 1, hq, window, 128), generator=g, device=DEV)).to(torch.bfloat16)
+    A = ta.ta_score(Q, K, ta.Params())
+    ref = ora.score(wl.bf16_bits(Q[0, 0]), wl.bf16_bits(K[0, 0, 0]))
+    got = A[0, 0, 0].cpu().numpy()
+    assert np.isfinite(got).all() and _score_close(got, ref)
+
+
 # --------------------------------------------------------------------------
 # step 4
 # --------------------------------------------------------------------------
