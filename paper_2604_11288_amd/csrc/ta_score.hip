@@ -285,52 +285,67 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     // load is issued: these are ordinary loads, and waiting for them later would also wait for
     // every direct load issued in between).  Chunks are added in index order, four loads in flight.
     if constexpr (COLSUM) {
-        for (int lr = tid; lr < GROUP_ROWS * RG; lr += THREADS) {
-            const int32_t r = row_base + lr;
-            float c = INFINITY;
-            int32_t lim = -1;
-            if (r < a.rows && a.lse) {
+        constexpr int ROWS = GROUP_ROWS * RG, PARTS = THREADS / ROWS;
+        static_assert(PARTS == 2, "two threads per row");
+        const int lr = tid % ROWS, part = tid / ROWS;
+        const int32_t r = row_base + lr;
+        float c = INFINITY;
+        int32_t lim = -1;
+        if (r < a.rows) {
+            const int32_t h = r / W, w = r - h * W;
+            lim = a.causal ? nb - W + w : nb - 1;
+            if (a.lse) {
                 // the row's normaliser comes from the prefill attention kernel: c = lse * log2(e)
-                const int32_t h = r / W, w = r - h * W;
                 const float v = a.lse[(((size_t)l * a.batch + b) * ((size_t)a.hkv * a.G) + (size_t)(g * a.G + h)) * W + w];
                 if (v > -INFINITY) c = v * 1.4426950408889634f;
-                lim = a.causal ? nb - W + w : nb - 1;
-            } else if (r < a.rows) {
-                const float2* st = reinterpret_cast<const float2*>(a.ws) + ((size_t)unit * a.nchunks * a.rows_pad + r);
-                const size_t step = (size_t)a.rows_pad;
-                const int last_ch = a.nchunks - 1;
-                float2 first[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) first[j] = st[(size_t)(j < last_ch ? j : last_ch) * step];
-                float mstar = first[0].x;
-#pragma unroll
-                for (int j = 1; j < 4; ++j) mstar = fmaxf(mstar, first[j].x);
-                for (int ch0 = 4; ch0 < a.nchunks; ch0 += 4) {
-                    float2 more[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) more[j] = st[(size_t)(ch0 + j < last_ch ? ch0 + j : last_ch) * step];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) mstar = fmaxf(mstar, more[j].x);
-                }
-                float Z = 0.0f;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (j <= last_ch && first[j].y > 0.0f) Z += first[j].y * fast_exp2(first[j].x - mstar);
-                for (int ch0 = 4; ch0 < a.nchunks; ch0 += 4) {
-                    float2 more[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) more[j] = st[(size_t)(ch0 + j < last_ch ? ch0 + j : last_ch) * step];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (ch0 + j <= last_ch && more[j].y > 0.0f) Z += more[j].y * fast_exp2(more[j].x - mstar);
-                }
-                if (Z > 0.0f) c = mstar + log2f(Z);
-                const int32_t h = r / W, w = r - h * W;
-                lim = a.causal ? nb - W + w : nb - 1;
             }
+        }
+        if (!a.lse) {                                      // uniform
+            // Two threads per row, each with half of the chunks, up to eight loads in flight: at most two round trips however
+            // many chunks there are (at most 32), so that few units can be cut into many.
+            float2* s_mz = reinterpret_cast<float2*>(&s_k[0][0]);          // (the stage ring is not in use yet)
+            const int32_t half = (a.nchunks + 1) >> 1, ch0 = part * half;
+            const float2* st = reinterpret_cast<const float2*>(a.ws) + ((size_t)unit * a.nchunks * a.rows_pad + (r < a.rows_pad ? r : 0));
+            float m = -INFINITY, Z = 0.0f;
+            const auto merge = [&](auto count_tag, int32_t first) {
+                constexpr int COUNT = decltype(count_tag)::value;
+                float2 v[COUNT];
+#pragma unroll
+                for (int j = 0; j < COUNT; ++j) {
+                    const int32_t ch = ch0 + first + j;
+                    v[j] = st[(size_t)(ch < a.nchunks ? ch : a.nchunks - 1) * a.rows_pad];
+                }
+                float mm = m;
+#pragma unroll
+                for (int j = 0; j < COUNT; ++j)
+                    if (first + j < half && ch0 + first + j < a.nchunks) mm = fmaxf(mm, v[j].x);
+                const float ref = mm > -INFINITY ? mm : 0.0f;
+                Z *= fast_exp2(m - ref);
+#pragma unroll
+                for (int j = 0; j < COUNT; ++j)
+                    if (first + j < half && ch0 + first + j < a.nchunks && v[j].y > 0.0f) Z += v[j].y * fast_exp2(v[j].x - ref);
+                m = mm;
+            };
+            if (half <= 2) merge(std::integral_constant<int, 2>{}, 0);
+            else
+                for (int32_t first = 0; first < half; first += 8) merge(std::integral_constant<int, 8>{}, first);
+            if (part == 1) s_mz[lr] = make_float2(m, Z);
+            __syncthreads();
+            if (part == 0) {
+                const float2 o = s_mz[lr];
+                const float mm = fmaxf(m, o.x);
+                if (mm > -INFINITY) {
+                    const float z = Z * fast_exp2(m - mm) + o.y * fast_exp2(o.x - mm);
+                    if (z > 0.0f) c = mm + log2f(z);
+                }
+            }
+            if (r >= a.rows) c = INFINITY;
+        }
+        if (part == 0) {
             s_c[lr] = c;
             s_lim[lr] = lim;
         }
+        __syncthreads();                                   // the ring's memory is free again, the constants are in LDS
     }
 
     // The compiler waits for ordinary loads with a count that knows nothing of the direct loads
@@ -351,7 +366,6 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 
     float cst[ROW_TILES][16];
     if constexpr (COLSUM) {
-        __syncthreads();                                   // per-row constants are in LDS
 #pragma unroll
         for (int t = 0; t < ROW_TILES; ++t)
 #pragma unroll
@@ -711,16 +725,27 @@ ScorePlan make_plan(const ta_layout& lay)
     ScorePlan p;
     p.rows = (lay.hq / lay.hkv) * lay.window;
     p.rows_pad = padded_rows(p.rows);
-    // Chunks as long as possible (the per-workgroup prologue - Q fragments, first stages,
-    // statistics merge - is amortised over the chunk) while the grid still offers about two
-    // workgroups per compute unit; never more than 32 chunks per unit.
+    // Chunks per unit: the count whose fullest compute unit is done first.  A workgroup costs its stages plus the
+    // prologue (Q fragments, first stages, statistics merge) and epilogue, about SETUP stages' time; a compute unit that
+    // gets k of them costs k times that, and one workgroup of four wavefronts alone (rows_pad 128) does not quite
+    // fill it.  At most 32 chunks per unit, of at least two stages.  (Two workgroups per compute unit at any price, chunks of
+    // at least 512 keys, were the rule before.  Score step in us, before / now: 8 units of 4096 keys, 128 rows 22 / 19, 256
+    // rows 32 / 23; 64 units of 4096 keys 39 / 36; 192 units of 8192 keys, 256 rows 316 / 281: 576 workgroups on 256
+    // compute units that hold one each became 768.)
     p.units = (int64_t)lay.layers * lay.batch * lay.hkv;
-    const int64_t want_blocks = 2 * (int64_t)compute_units();
-    int64_t per_unit = (want_blocks + p.units - 1) / p.units;            // chunks per unit we would like
-    per_unit = per_unit < 1 ? 1 : (per_unit > 32 ? 32 : per_unit);
-    int64_t ck = ((lay.n + per_unit - 1) / per_unit + STAGE_KEYS - 1) / STAGE_KEYS * STAGE_KEYS;
-    if (ck < 512) ck = 512;
-    while (ck * 32 < lay.n) ck += STAGE_KEYS;
+    const int64_t cus = compute_units(), stages = (lay.n + STAGE_KEYS - 1) / STAGE_KEYS;
+    constexpr int64_t SETUP = 6, ALONE = 115;              // stages; per cent
+    int64_t best = -1, ck = 0;
+    for (int64_t c = 1; c <= 32 && (c == 1 || stages >= 2 * c); ++c) {
+        const int64_t per_chunk = (stages + c - 1) / c;
+        if (per_chunk * 32 < stages) continue;
+        const int64_t k = (p.units * ((stages + per_chunk - 1) / per_chunk) + cus - 1) / cus;
+        const int64_t cost = k * (per_chunk + SETUP) * (k == 1 && p.rows_pad == 128 ? ALONE : 100);
+        if (best < 0 || cost < best) {
+            best = cost;
+            ck = per_chunk * STAGE_KEYS;
+        }
+    }
     p.chunk_keys = (int32_t)ck;
     p.nchunks = (lay.n + p.chunk_keys - 1) / p.chunk_keys;
     return p;

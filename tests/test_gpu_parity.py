@@ -249,6 +249,14 @@ def test_score_rows_whose_logits_pass_any_reference(hq, window, n, order):
     assert np.isfinite(got).all() and _score_close(got, ref)
 
 
+@pytest.mark.parametrize("n", [65, 129, 2049, 4096, 4160, 20000])
+def test_score_one_unit_in_many_chunks(n):
+    # few units: up to 32 chunks of two stages or more, whose statistics two threads per row merge
+    for hq in (4, 8):
+        w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=1, batch=1, n=n, hq=hq, hkv=1, window=32)
+        _check_score(w)
+
+
 # --------------------------------------------------------------------------
 # step 4
 # --------------------------------------------------------------------------
