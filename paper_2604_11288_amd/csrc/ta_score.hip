@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "ta_match_device.h"
+#include "ta_order.h"
 #include "ta_score_common.h"
 
 namespace ta {
@@ -154,17 +155,16 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     const int c32 = lane & 31, hf = lane >> 5;
     const int rg = wave % RG, kt = wave / RG;              // row group, key tile of the stage
 
-    // XCD x = block % 8 runs the units [x * units_per_xcd, (x+1) * units_per_xcd)
     const int32_t seq_in_xcd = (int32_t)(blockIdx.x >> 3);
-    const int32_t unit_in_xcd = seq_in_xcd / a.nchunks;
-    const int32_t chunk = seq_in_xcd - unit_in_xcd * a.nchunks;
-    const int32_t unit = (int32_t)(blockIdx.x & 7u) * a.units_per_xcd + unit_in_xcd;
-    if (unit >= a.units) return;
+    int32_t chunk;
+    const int32_t place = place_of(blockIdx.x, a.nchunks, chunk);
+    if (place >= a.units) return;
+    const int32_t unit = __builtin_amdgcn_readfirstlane(unit_at(place, a.seq_len, a.batch, a.hkv, a.units));
     const int32_t g = unit % a.hkv;
     const int32_t b = (unit / a.hkv) % a.batch;
     const int32_t l = unit / (a.hkv * a.batch);
     const int32_t n = a.n, W = a.W;
-    int32_t nb = a.seq_len ? a.seq_len[b] : n;
+    int32_t nb = a.seq_len ? __builtin_amdgcn_readfirstlane(a.seq_len[b]) : n;   // (in a scalar register: it is part of every stage's address)
     nb = nb < 0 ? 0 : (nb > n ? n : nb);
 
     const int32_t key_lo = chunk * a.chunk_keys;
@@ -681,8 +681,7 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, hipStr
     // One launch per sweep over all units.  (Splitting the units into cache-sized groups
     // so that sweep 2 re-reads its keys from the last-level cache was measured slower.)
     a.units = (int32_t)units;
-    a.units_per_xcd = (int32_t)((units + 7) / 8);
-    const unsigned blocks = (unsigned)(8ll * a.units_per_xcd * a.nchunks);
+    const unsigned blocks = (unsigned)(8ll * ((units + 7) / 8) * a.nchunks);
     if (a.lse)                                             // the row normalisers are given: column sums alone
         return launch_sweep<RG, RT, true>(a, blocks, rider, st);
     const hipError_t e = launch_sweep<RG, RT, false>(a, blocks, rider, st);

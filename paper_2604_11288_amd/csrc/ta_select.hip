@@ -24,6 +24,7 @@
 //                mandatory competes for the main pool by (u, position) alone - two threshold
 //                searches instead of one
 #include "ta_internal.h"
+#include "ta_order.h"
 #include "ta_wave.h"
 
 namespace ta {
@@ -47,7 +48,7 @@ struct SelectArgs {
     float* margin;                  // [units][2] or null: smallest retained / largest evicted u of the class the cut falls in
     int32_t batch, hkv, n, K;
     int32_t pool_r, k_protected;
-    int32_t units, units_per_xcd;
+    int32_t units;
     int32_t vec_ok;
     int32_t plain_vouch;            // 1: vouchers of the match or the expansion (0 at every unsponsored position)
     int32_t n_sink, n_recent;
@@ -164,11 +165,10 @@ select_kernel(SelectArgs a)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    // Same block -> unit numbering as the score step (block b runs on XCD b mod 8, which
-    // scored the units [x * units_per_xcd, (x+1) * units_per_xcd)): A is then read from the
-    // L2 that holds it.
-    const int32_t unit = (int32_t)(blockIdx.x & 7u) * a.units_per_xcd + (int32_t)(blockIdx.x >> 3);
-    if (unit >= a.units) return;
+    // Same block -> unit order as the score step: A is then read from the L2 that holds it.
+    const int32_t place = (int32_t)blockIdx.x;
+    if (place >= a.units) return;
+    const int32_t unit = __builtin_amdgcn_readfirstlane(unit_at(place, a.seq_len, a.batch, a.hkv, a.units));
     const int32_t b = (unit / a.hkv) % a.batch;
     const int32_t n = a.n;
     int32_t K = a.K;                                         // capacity of an idx row; the budget unless a layer has its own
@@ -564,11 +564,10 @@ select_reg_kernel(SelectArgs a)
     __shared__ __align__(16) SelectRegLds L;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    // Same block -> unit numbering as the score step (block b runs on XCD b mod 8, which
-    // scored the units [x * units_per_xcd, (x+1) * units_per_xcd)): A is then read from the
-    // L2 that holds it.
-    const int32_t unit = (int32_t)(blockIdx.x & 7u) * a.units_per_xcd + (int32_t)(blockIdx.x >> 3);
-    if (unit >= a.units) return;
+    // Same block -> unit order as the score step: A is then read from the L2 that holds it.
+    const int32_t place = (int32_t)blockIdx.x;
+    if (place >= a.units) return;
+    const int32_t unit = __builtin_amdgcn_readfirstlane(unit_at(place, a.seq_len, a.batch, a.hkv, a.units));
     const int32_t b = (unit / a.hkv) % a.batch;
     const int32_t n = a.n;
     int32_t K = a.K;                                         // capacity of an idx row; the budget unless a layer has its own
@@ -1134,8 +1133,9 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int32_t unit = (int32_t)(blockIdx.x & 7u) * a.units_per_xcd + (int32_t)(blockIdx.x >> 3);
-    if (unit >= a.units) return;
+    const int32_t place = (int32_t)blockIdx.x;
+    if (place >= a.units) return;
+    const int32_t unit = __builtin_amdgcn_readfirstlane(unit_at(place, a.seq_len, a.batch, a.hkv, a.units));
     const int32_t b = (unit / a.hkv) % a.batch;
     const int32_t n = a.n;
     int32_t K = a.K;
@@ -1565,10 +1565,9 @@ hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* s
     a.gamma = prm.gamma;
     const int64_t units = (int64_t)layers * batch * hkv;
     a.units = (int32_t)units;
-    a.units_per_xcd = (int32_t)((units + 7) / 8);
     a.vec_ok = (n % 4 == 0) && ((uintptr_t)anchor % 4 == 0) && ((uintptr_t)spons % 4 == 0) &&
                ((uintptr_t)vouch % 16 == 0) && (a.A == nullptr || (uintptr_t)a.A % 16 == 0);
-    const unsigned blocks = 8u * (unsigned)a.units_per_xcd;
+    const unsigned blocks = (unsigned)units;
     const bool capped = prm.k_protected >= 0;
     // The streaming form serves the plain (elastic, unpooled) selection when its candidate list and the bitmap of the
     // sequence fit the LDS of a workgroup.

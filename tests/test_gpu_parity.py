@@ -249,6 +249,24 @@ def test_score_rows_whose_logits_pass_any_reference(hq, window, n, order):
     assert np.isfinite(got).all() and _score_close(got, ref)
 
 
+@pytest.mark.parametrize("batch,layers,hkv", [(2, 1, 1), (3, 2, 3), (64, 1, 1), (65, 1, 2)])
+def test_score_and_select_order_of_ragged_sequences(batch, layers, hkv):
+    # units are taken by falling sequence length (up to 64 sequences); equal lengths, empty and full ones among them
+    w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=layers, batch=batch, n=300, hq=4 * hkv, hkv=hkv, window=8)
+    lens = np.random.default_rng(batch).choice([0, 9, 64, 130, 131, 299, 300], size=batch).astype(np.int32)
+    _check_score(w, seq_len=lens)
+    A = torch.rand((layers, batch, hkv, 300), device=DEV)
+    flags, zero = torch.zeros((batch, 300), dtype=torch.uint8, device=DEV), torch.zeros((batch, 300), device=DEV)
+    idx, cnt = ta.ta_select(A, flags, flags, zero, 40, ta.Params(n_sink=2, n_recent=3), layers, hkv, seq_len=_dev(lens))
+    for l in range(layers):
+        for b in range(batch):
+            for h in range(hkv):
+                nb = int(lens[b])
+                z8, zf = np.zeros(nb, np.uint8), np.zeros(nb, np.float32)
+                ref = ora.select(A[l, b, h, :nb].cpu().numpy(), z8, z8, zf, 40, 2, 3) if nb else np.zeros(0, np.int32)
+                assert int(cnt[l, b, h]) == min(40, nb) and np.array_equal(idx[l, b, h, :min(40, nb)].cpu().numpy(), ref[:min(40, nb)])
+
+
 @pytest.mark.parametrize("n", [65, 129, 2049, 4096, 4160, 20000])
 def test_score_one_unit_in_many_chunks(n):
     # few units: up to 32 chunks of two stages or more, whose statistics two threads per row merge
