@@ -181,19 +181,29 @@ decode_seq_vouch_kernel(ta_decode_state st, const int32_t* new_tok, DecodeTable 
     if (p > len_old) return;                               // positions 0 .. len_old exist after the append
     const uint8_t* anchor = st.anchor + row;
     const float* budget = st.budget + row;
+    // the flags of the L positions before p, eight requested at a time (one after the other, each behind the test of the
+    // one before, cost a round trip per position: 3.9 us for a launch of 17 workgroups); bit k - 1: position p - k
+    unsigned long long near = 0ull;
+    for (int k0 = 1; k0 <= a.L; k0 += 8) {                 // uniform
+        uint8_t f[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) f[j] = anchor[p >= k0 + j ? p - k0 - j : 0];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (f[j] && p >= k0 + j && k0 + j <= a.L) near |= 1ull << (k0 + j - 1);
+    }
+    const uint8_t own = anchor[p < len_old ? p : 0];
+    const uint8_t sp = near != 0ull ? 1 : 0;
     float v = 0.0f;
-    uint8_t sp = 0;
-    for (int k = 1; k <= a.L; ++k) {
-        const int32_t i = p - k;
-        if (i >= 0 && anchor[i]) {
-            v = __fadd_rn(v, __fmul_rn(budget[i], a.pw[k]));
-            sp = 1;
-        }
+    while (near) {                                         // increasing distance, as in the fixed-order sum
+        const int k = __ffsll((long long)near);
+        near &= near - 1ull;
+        v = __fadd_rn(v, __fmul_rn(budget[p - k], a.pw[k]));
     }
     st.vouch[row + p] = v;
     // bit 0: sponsored; bit 1: the position is an anchor itself (the new position's flag travels in
     // `stepped`: it is being written by another workgroup of this launch)
-    st.spons[row + p] = sp | (p < len_old && anchor[p] ? 2 : 0);
+    st.spons[row + p] = sp | (p < len_old && own ? 2 : 0);
 }
 
 // Trailing workgroups of the unit launch: budget decay of 256 positions each, and the new length.
@@ -536,26 +546,55 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         // wavefronts: each takes every WAVES-th head (a head's reduction runs in one wavefront, in the
         // single wavefront's order) and the results are exchanged through LDS.
         const auto mine = [&](int h) { return h < G && (WAVES == 1 || h % WAVES == wave); };
+        if (SMALL) {
+            // a head's logits in registers, all requested at once (a loop over the slots, one LDS round trip per 64 of them and
+            // pass, took 4.2 of the 18.7 us of a unit of 1025 slots); lanes past the last slot add exp2(-inf) = 0
+            constexpr int NV = WAVES * SPL;
+            const auto one_head = [&](int h, float& m, float& inv) {
+                float lg[NV];
 #pragma unroll
-        for (int h = 0; h < GH; ++h) m_h[h] = -INFINITY;
-        for (int s = lane; s < slots; s += 64) {
+                for (int j = 0; j < NV; ++j) {
+                    const int s = lane + 64 * j;
+                    const float x = s_w[h * wstride + (s < slots ? s : slots - 1)];
+                    lg[j] = s < slots ? x : -INFINITY;
+                }
+                m = lg[0];
+#pragma unroll
+                for (int j = 1; j < NV; ++j) m = fmaxf(m, lg[j]);
+                m = wave_max_dpp(m);
+                float z = 0.0f;
+#pragma unroll
+                for (int j = 0; j < NV; ++j) z += __builtin_amdgcn_exp2f(lg[j] - m);
+                inv = __builtin_amdgcn_rcpf(wave_sum_dpp(z));
+            };
+#pragma unroll
+            for (int h = 0; h < GH; ++h) {
+                m_h[h] = -INFINITY;
+                inv_h[h] = 0.0f;
+                if (mine(h)) one_head(h, m_h[h], inv_h[h]);
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < GH; ++h) m_h[h] = -INFINITY;
+            for (int s = lane; s < slots; s += 64) {
+#pragma unroll
+                for (int h = 0; h < GH; ++h)
+                    if (mine(h)) m_h[h] = fmaxf(m_h[h], s_w[h * wstride + s]);
+            }
 #pragma unroll
             for (int h = 0; h < GH; ++h)
-                if (mine(h)) m_h[h] = fmaxf(m_h[h], s_w[h * wstride + s]);
+                if (mine(h)) m_h[h] = wave_max_dpp(m_h[h]);
+            float z_h[GH];
+#pragma unroll
+            for (int h = 0; h < GH; ++h) z_h[h] = 0.0f;
+            for (int s = lane; s < slots; s += 64) {
+#pragma unroll
+                for (int h = 0; h < GH; ++h)
+                    if (mine(h)) z_h[h] += __builtin_amdgcn_exp2f(s_w[h * wstride + s] - m_h[h]);
+            }
+#pragma unroll
+            for (int h = 0; h < GH; ++h) inv_h[h] = mine(h) ? __builtin_amdgcn_rcpf(wave_sum_dpp(z_h[h])) : 0.0f;
         }
-#pragma unroll
-        for (int h = 0; h < GH; ++h)
-            if (mine(h)) m_h[h] = wave_max_dpp(m_h[h]);
-        float z_h[GH];
-#pragma unroll
-        for (int h = 0; h < GH; ++h) z_h[h] = 0.0f;
-        for (int s = lane; s < slots; s += 64) {
-#pragma unroll
-            for (int h = 0; h < GH; ++h)
-                if (mine(h)) z_h[h] += __builtin_amdgcn_exp2f(s_w[h * wstride + s] - m_h[h]);
-        }
-#pragma unroll
-        for (int h = 0; h < GH; ++h) inv_h[h] = mine(h) ? __builtin_amdgcn_rcpf(wave_sum_dpp(z_h[h])) : 0.0f;
         if (WAVES > 1) {
             static_assert(WAVES == 1 || GH <= 16, "the exchange area holds 16 heads");
             float* s_stat = reinterpret_cast<float*>(s_x) + 32;            // [0..16): maxima, [16..32): reciprocal sums
