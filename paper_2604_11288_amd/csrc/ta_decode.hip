@@ -55,22 +55,42 @@ __device__ __forceinline__ int32_t clamp_page(const SlotPages& pg, int32_t page)
 }
 
 // ---- state initialisation -----------------------------------------------------
-__global__ void decode_init_seq_kernel(ta_decode_state st, const int32_t* tok, const int32_t* seq_len, int32_t n,
-                                       const uint8_t* anchor, const float* anchor_B, float B)
+constexpr int INIT_ITERS = 4;
+constexpr int INIT_ROWS = DU_THREADS / 16 * INIT_ITERS;    // cache slots per workgroup
+
+struct InitArgs {
+    const int32_t* tok;
+    const int32_t* seq_len;
+    const uint8_t* anchor;
+    const float* anchor_B;
+    const float* A;
+    const int32_t* idx;
+    const int32_t* cnt;
+    const uint4* Kout;
+    const uint4* Vout;
+    int64_t rows;                                          // units * slots
+    int64_t row_blocks;                                    // workgroups of slots; those behind them fill the per-sequence arrays
+    int32_t n;
+    float B;
+};
+
+// Per-sequence arrays of 256 positions.
+__device__ __forceinline__ void init_sequence(const ta_decode_state& st, const InitArgs& a, int32_t r)
 {
-    const int b = blockIdx.y;
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    int32_t nb = seq_len ? seq_len[b] : n;
-    nb = nb < 0 ? 0 : (nb > n ? n : nb);
+    const int32_t tiles = (st.cap + DU_THREADS - 1) / DU_THREADS;
+    const int b = r / tiles;
+    const int p = (r - b * tiles) * DU_THREADS + (int)threadIdx.x;
+    int32_t nb = a.seq_len ? a.seq_len[b] : a.n;
+    nb = nb < 0 ? 0 : (nb > a.n ? a.n : nb);
     if (p == 0) st.len[b] = nb;
     if (p >= st.cap) return;
     const size_t o = (size_t)b * st.cap + p;
     if (p < nb) {
-        const size_t i = (size_t)b * n + p;
-        const uint8_t a = anchor[i];
-        st.tok[o] = tok[i];
-        st.anchor[o] = a;
-        st.budget[o] = a ? (anchor_B ? anchor_B[i] : B) : 0.0f;
+        const size_t i = (size_t)b * a.n + p;
+        const uint8_t an = a.anchor[i];
+        st.tok[o] = a.tok[i];
+        st.anchor[o] = an;
+        st.budget[o] = an ? (a.anchor_B ? a.anchor_B[i] : a.B) : 0.0f;
     } else {
         st.tok[o] = 0;
         st.anchor[o] = 0;
@@ -78,60 +98,75 @@ __global__ void decode_init_seq_kernel(ta_decode_state st, const int32_t* tok, c
     }
 }
 
+// INIT_ROWS consecutive slots of the flat [units][slots] order per workgroup, 16 lanes per row, all loads of a lane (four
+// rows of K and V) before its first store, like the compaction: bound by HBM.  (One workgroup per unit with one row in flight per
+// lane: 65 us for 256 units of 1025 slots, 843 us for 16 384 of 257.)
 template <bool PAGED>
 __global__ void __launch_bounds__(DU_THREADS)
-decode_init_unit_kernel(ta_decode_state st, int32_t n, const float* A, const int32_t* idx, const int32_t* cnt,
-                        const uint4* Kout, const uint4* Vout, SlotPages pg)
+decode_init_kernel(ta_decode_state st, InitArgs a, SlotPages pg)
 {
-    const int unit = blockIdx.x;
-    const int slots = st.K + 1;
-    int32_t c = cnt[unit];
-    c = c < 0 ? 0 : (c > st.K ? st.K : c);
-    for (int s = threadIdx.x; s < slots; s += DU_THREADS) {
-        int32_t p = -1;
-        float a = 0.0f;
-        if (s < c) {
-            p = idx[(size_t)unit * st.K + s];
-            p = p < 0 ? 0 : (p >= n ? n - 1 : p);
-            if (A) a = A[(size_t)unit * n + p];
-        }
-        st.pos[(size_t)unit * slots + s] = p;
-        st.A[(size_t)unit * slots + s] = a;
-    }
-    if (!Kout) return;                                     // paged state whose rows are in place already
-    const uint4 zero = make_uint4(0, 0, 0, 0);
-    if (PAGED) {
-        const int g = unit % st.hkv;
-        const int b = (unit / st.hkv) % st.batch;
-        const int l = unit / (st.hkv * st.batch);
-        uint4* Kc = reinterpret_cast<uint4*>(st.Kc) + l * pg.s_layer + g * pg.s_head;
-        uint4* Vc = reinterpret_cast<uint4*>(st.Vc) + l * pg.s_layer + g * pg.s_head;
-        for (int i = threadIdx.x; i < slots * 16; i += DU_THREADS) {
-            const int s = i >> 4;
-            const int32_t j = page_index(pg, s);
-            const int32_t page = clamp_page(pg, pg.table[(size_t)b * pg.max_pages + j]);
-            const int64_t at = (int64_t)page * pg.s_page + (int64_t)(s - j * pg.page_size) * pg.s_slot + (i & 15);
-            uint4 kv = zero, vv = zero;                        // (a conditional expression on the structs goes through scratch memory)
-            if (s < c) {
-                kv = Kout[(size_t)unit * st.K * 16 + i];
-                vv = Vout[(size_t)unit * st.K * 16 + i];
-            }
-            Kc[at] = kv;
-            Vc[at] = vv;
-        }
+    if ((int64_t)blockIdx.x >= a.row_blocks) {
+        init_sequence(st, a, (int32_t)((int64_t)blockIdx.x - a.row_blocks));
         return;
     }
-    uint4* Kc = reinterpret_cast<uint4*>(st.Kc) + (size_t)unit * slots * 16;
-    uint4* Vc = reinterpret_cast<uint4*>(st.Vc) + (size_t)unit * slots * 16;
-    for (int i = threadIdx.x; i < slots * 16; i += DU_THREADS) {
-        const int s = i >> 4;
-        uint4 kv = zero, vv = zero;
-        if (s < c) {
-            kv = Kout[(size_t)unit * st.K * 16 + i];
-            vv = Vout[(size_t)unit * st.K * 16 + i];
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int32_t slots = st.K + 1;
+    const int64_t row0 = (int64_t)blockIdx.x * INIT_ROWS;
+    const int64_t unit0 = row0 / slots;                    // uniform
+    const int32_t slot0 = (int32_t)(row0 - unit0 * slots);
+    const int lane16 = threadIdx.x & 15, rsub = threadIdx.x >> 4;
+    int64_t from[INIT_ITERS], to[INIT_ITERS];
+    bool live[INIT_ITERS], kept[INIT_ITERS];
+#pragma unroll
+    for (int i = 0; i < INIT_ITERS; ++i) {
+        const int32_t off = 16 * i + rsub;
+        const int32_t du = (slot0 + off) / slots;
+        live[i] = row0 + off < a.rows;
+        const int32_t unit = (int32_t)(live[i] ? unit0 + du : unit0);
+        const int32_t s = live[i] ? slot0 + off - du * slots : slot0;
+        int32_t c = a.cnt[unit];
+        c = c < 0 ? 0 : (c > st.K ? st.K : c);
+        kept[i] = s < c;
+        const int32_t sr = s < st.K ? s : st.K - 1;        // a readable row; the spare slot is zeroed
+        from[i] = ((int64_t)unit * st.K + sr) * 16 + lane16;
+        if (PAGED) {
+            const int g = unit % st.hkv;
+            const int b = (unit / st.hkv) % st.batch;
+            const int l = unit / (st.hkv * st.batch);
+            const int32_t j = page_index(pg, s);
+            const int32_t page = clamp_page(pg, pg.table[(size_t)b * pg.max_pages + j]);
+            to[i] = l * pg.s_layer + g * pg.s_head + (int64_t)page * pg.s_page + (int64_t)(s - j * pg.page_size) * pg.s_slot + lane16;
+        } else {
+            to[i] = ((int64_t)unit * slots + s) * 16 + lane16;
         }
-        Kc[i] = kv;
-        Vc[i] = vv;
+        if (lane16 == 0 && live[i]) {
+            int32_t p = -1;
+            float at = 0.0f;
+            if (kept[i]) {
+                p = a.idx[(size_t)unit * st.K + s];
+                p = p < 0 ? 0 : (p >= a.n ? a.n - 1 : p);
+                if (a.A) at = a.A[(size_t)unit * a.n + p];
+            }
+            st.pos[(size_t)unit * slots + s] = p;
+            st.A[(size_t)unit * slots + s] = at;
+        }
+    }
+    if (!a.Kout) return;                                   // paged state whose rows are in place already
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    const u32x4 *Kin = reinterpret_cast<const u32x4*>(a.Kout), *Vin = reinterpret_cast<const u32x4*>(a.Vout);
+    u32x4 *Kc = reinterpret_cast<u32x4*>(st.Kc), *Vc = reinterpret_cast<u32x4*>(st.Vc);
+    u32x4 kv[INIT_ITERS], vv[INIT_ITERS];
+#pragma unroll
+    for (int i = 0; i < INIT_ITERS; ++i) {
+        kv[i] = __builtin_nontemporal_load(&Kin[from[i]]);
+        vv[i] = __builtin_nontemporal_load(&Vin[from[i]]);
+    }
+#pragma unroll
+    for (int i = 0; i < INIT_ITERS; ++i) {
+        if (live[i]) {
+            __builtin_nontemporal_store(kept[i] ? kv[i] : zero, &Kc[to[i]]);
+            __builtin_nontemporal_store(kept[i] ? vv[i] : zero, &Vc[to[i]]);
+        }
     }
 }
 
@@ -144,45 +179,52 @@ struct VouchArgs {
 };
 
 // Sequence part of a step, one launch: every workgroup reads the old length (nobody writes it here),
-// the first wavefront of a sequence's first workgroup appends the token, tests the table at the new
+// a sequence's last workgroup appends the token, tests the table at the new
 // position and publishes the new length in `stepped` (0: the sequence is at capacity and is left
-// alone); all workgroups compute the vouchers of their positions, which depend on earlier positions
+// alone); the others compute the vouchers of their positions, which depend on earlier positions
 // only and so not on anything the append writes.
 __global__ void __launch_bounds__(256)
 decode_seq_vouch_kernel(ta_decode_state st, const int32_t* new_tok, DecodeTable tab, VouchArgs a)
 {
     const int b = blockIdx.y;
-    const int32_t len_old = st.len[b];
-    if (len_old < 0 || len_old >= st.cap) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) st.stepped[b] = 0;
-        return;
-    }
     const size_t row = (size_t)b * st.cap;
-    if (blockIdx.x == 0 && threadIdx.x < 64) {
+    if (blockIdx.x == gridDim.x - 1) {                     // the append: one wavefront
+        const int e = (int)threadIdx.x;
+        if (e >= 64) return;
+        // (the launch's table lies in host memory: requested together with the length, not behind it)
+        const int32_t len_old = st.len[b], t0 = new_tok[b];
+        int32_t rid[TA_MAX_GRAM];
+#pragma unroll
+        for (int k = 0; k < TA_MAX_GRAM; ++k) rid[k] = tab.rid[e][k];
+        const int32_t gram = e < tab.E ? tab.len[e] : 0;
+        if (len_old < 0 || len_old >= st.cap) {
+            if (e == 0) st.stepped[b] = 0;
+            return;
+        }
         const int32_t p = len_old;
         int32_t* tok = st.tok + row;
-        const int32_t t0 = new_tok[b];
-        const int e = threadIdx.x;
-        bool hit = false;
-        if (e < tab.E && t0 == tab.rid[e][0]) {
-            const int32_t len = tab.len[e];
-            hit = p - len + 1 >= 0;
-            for (int k = 1; k < len && hit; ++k) hit = tok[p - k] == tab.rid[e][k];
-        }
+        bool hit = gram > 0 && t0 == rid[0] && p - gram + 1 >= 0;
+        int32_t before[TA_MAX_GRAM];
+#pragma unroll
+        for (int k = 1; k < TA_MAX_GRAM; ++k) before[k] = tok[p >= k ? p - k : 0];
+#pragma unroll
+        for (int k = 1; k < TA_MAX_GRAM; ++k) hit = hit && (k >= gram || before[k] == rid[k]);
         const bool any = __ballot(hit) != 0ull;
-        if (threadIdx.x == 0) {
+        if (e == 0) {
             tok[p] = t0;
             st.anchor[row + p] = any ? 1 : 0;
             st.budget[row + p] = any ? tab.B : 0.0f;
             st.stepped[b] = (p + 1) | (any ? (1 << 30) : 0);   // new length; bit 30: the new token is an anchor
         }
+        return;
     }
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p > len_old) return;                               // positions 0 .. len_old exist after the append
+    if (p >= st.cap) return;
     const uint8_t* anchor = st.anchor + row;
     const float* budget = st.budget + row;
-    // the flags of the L positions before p, eight requested at a time (one after the other, each behind the test of the
-    // one before, cost a round trip per position: 3.9 us for a launch of 17 workgroups); bit k - 1: position p - k
+    // the flags of the L positions before p, eight requested at a time, with the length; bit k - 1: position p - k
+    const int32_t len_old = st.len[b];
+    const uint8_t own = anchor[p];
     unsigned long long near = 0ull;
     for (int k0 = 1; k0 <= a.L; k0 += 8) {                 // uniform
         uint8_t f[8];
@@ -192,7 +234,7 @@ decode_seq_vouch_kernel(ta_decode_state st, const int32_t* new_tok, DecodeTable 
         for (int j = 0; j < 8; ++j)
             if (f[j] && p >= k0 + j && k0 + j <= a.L) near |= 1ull << (k0 + j - 1);
     }
-    const uint8_t own = anchor[p < len_old ? p : 0];
+    if (len_old >= st.cap || p > len_old) return;          // at capacity; positions 0 .. len_old exist after the append
     const uint8_t sp = near != 0ull ? 1 : 0;
     float v = 0.0f;
     while (near) {                                         // increasing distance, as in the fixed-order sum
@@ -832,16 +874,25 @@ hipError_t launch_decode_init(const ta_decode_state& st, const int32_t* tok, con
                               const int32_t* idx, const int32_t* cnt, const void* Kout, const void* Vout,
                               float B, hipStream_t s)
 {
-    dim3 g1((unsigned)((st.cap + 255) / 256), (unsigned)st.batch);
-    hipLaunchKernelGGL(decode_init_seq_kernel, g1, dim3(256), 0, s, st, tok, seq_len, n, anchor, anchor_B, B);
-    const unsigned units = (unsigned)(st.layers * st.batch * st.hkv);
+    InitArgs a;
+    a.tok = tok;
+    a.seq_len = seq_len;
+    a.anchor = anchor;
+    a.anchor_B = anchor_B;
+    a.A = A;
+    a.idx = idx;
+    a.cnt = cnt;
+    a.Kout = (const uint4*)Kout;
+    a.Vout = (const uint4*)Vout;
+    a.rows = (int64_t)st.layers * st.batch * st.hkv * (st.K + 1);
+    a.row_blocks = (a.rows + INIT_ROWS - 1) / INIT_ROWS;
+    a.n = n;
+    a.B = B;
+    const int64_t grid = a.row_blocks + (int64_t)((st.cap + DU_THREADS - 1) / DU_THREADS) * st.batch;
+    if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
     const SlotPages pg = slot_pages(st);
-    if (st.pages)
-        hipLaunchKernelGGL(decode_init_unit_kernel<true>, dim3(units), dim3(DU_THREADS), 0, s, st, n, A, idx, cnt,
-                           (const uint4*)Kout, (const uint4*)Vout, pg);
-    else
-        hipLaunchKernelGGL(decode_init_unit_kernel<false>, dim3(units), dim3(DU_THREADS), 0, s, st, n, A, idx, cnt,
-                           (const uint4*)Kout, (const uint4*)Vout, pg);
+    if (st.pages) hipLaunchKernelGGL(decode_init_kernel<true>, dim3((unsigned)grid), dim3(DU_THREADS), 0, s, st, a, pg);
+    else hipLaunchKernelGGL(decode_init_kernel<false>, dim3((unsigned)grid), dim3(DU_THREADS), 0, s, st, a, pg);
     return hipGetLastError();
 }
 
@@ -860,7 +911,7 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
     va.L = prm.span_L;
     for (int k = 0; k <= TA_MAX_SPAN; ++k) va.pw[k] = tab.pw[k];
     const unsigned tiles = (unsigned)((st.cap + 255) / 256);            // 256 positions per workgroup
-    hipLaunchKernelGGL(decode_seq_vouch_kernel, dim3(tiles, (unsigned)st.batch), dim3(256), 0, s, st, new_tok, dt, va);
+    hipLaunchKernelGGL(decode_seq_vouch_kernel, dim3(tiles + 1, (unsigned)st.batch), dim3(256), 0, s, st, new_tok, dt, va);
 
     UnitArgs a;
     a.q_new = (const uint4*)q_new;
