@@ -155,7 +155,9 @@ typedef struct ta_layout {
 
 /* Bytes of DEVICE scratch that ta_score / ta_evict need for this layout (0 when
  * no attention term is computed).  The workspace holds per-chunk softmax row
- * statistics; its contents are meaningless between calls. */
+ * statistics; its contents are meaningless between calls.  A larger workspace is used where
+ * it helps: layouts of few units are then cut into more chunks (up to 32 per unit, i.e. 32 *
+ * units * 8 bytes * the rows of a unit rounded up to 128, 256 or 512). */
 size_t ta_workspace_bytes(const ta_layout *lay, const ta_params *prm);
 
 /*

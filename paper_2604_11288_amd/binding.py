@@ -230,6 +230,15 @@ def ta_workspace_bytes(lay: CLayout, params: Params) -> int:
     return int(lib().ta_workspace_bytes(ctypes.byref(lay), ctypes.byref(cp)))
 
 
+def _workspace(lay: CLayout, params: Params) -> int:
+    """Bytes to allocate for a scored pass: what it needs, or - up to 8 MiB - what lets the score step cut few units into its
+    largest number of chunks (32 per unit, two floats per row)."""
+    need = ta_workspace_bytes(lay, params)
+    rows = lay.hq // lay.hkv * lay.window
+    most = 32 * lay.layers * lay.batch * lay.hkv * 8 * (128 if rows <= 128 else 256 if rows <= 256 else 512)
+    return max(need, min(most, 8 << 20), 16)
+
+
 def ta_match_anchors(tok, tab_ids, tab_len, params: Params, seq_len=None, anchor_B=None,
                      out=None, stream=None):
     """Steps 1+2.  tok int32 [B][n] (device).  Returns (anchor u8, spons u8, vouch f32), each [B][n]."""
@@ -332,9 +341,8 @@ def ta_score(Q, K, params: Params, seq_len=None, A=None, ws=None, stream=None):
     lay = layout_of(K, Q)
     if A is None:
         A = torch.empty((lay.layers, lay.batch, lay.hkv, lay.n), dtype=torch.float32, device=K.device)
-    need = ta_workspace_bytes(lay, replace(params, alpha=1.0))   # sized as for a scored pass
     if ws is None:
-        ws = torch.empty(max(need, 16), dtype=torch.uint8, device=K.device)
+        ws = torch.empty(_workspace(lay, replace(params, alpha=1.0)), dtype=torch.uint8, device=K.device)   # sized as for a scored pass
     cp = params.c()
     rc = lib().ta_score(_ptr(Q), _ptr(K), ctypes.byref(lay), _ptr(seq_len), ctypes.byref(cp),
                         _ptr(A), _ptr(ws), ws.numel() * ws.element_size(), _stream(stream))
@@ -397,8 +405,7 @@ def ta_score_paged(Q, paged: PagedKV, params: Params, seq_len=None, lse=None, A=
     if ws is None and lse is None:
         dense = CLayout.from_buffer_copy(lay)
         dense.kv_stride[3] = lay.d
-        need = ta_workspace_bytes(dense, replace(params, alpha=1.0))
-        ws = torch.empty(max(need, 16), dtype=torch.uint8, device=Q.device)
+        ws = torch.empty(_workspace(dense, replace(params, alpha=1.0)), dtype=torch.uint8, device=Q.device)
     cp = params.c()
     rc = lib().ta_score_paged(_ptr(Q), _ptr(paged.Kpool), ctypes.byref(pg), ctypes.byref(lay), _ptr(seq_len),
                               ctypes.byref(cp), _ptr(lse), _ptr(A), _ptr(ws),
@@ -510,8 +517,8 @@ class EvictPlan:
             if paged is not None:                                # workspace size depends on the sizes only
                 sized = CLayout.from_buffer_copy(lay)
                 sized.kv_stride[3] = lay.d
-            nbytes = ta_workspace_bytes(sized, params) if lse is None else 0
-            self.ws = None if static_scratch else torch.empty(max(nbytes, 16), dtype=torch.uint8, device=dev)
+            nbytes = _workspace(sized, params) if lse is None else 16
+            self.ws = None if static_scratch else torch.empty(nbytes, dtype=torch.uint8, device=dev)
             if lse is not None:
                 assert lse.dtype == torch.float32 and lse.is_contiguous()
                 assert tuple(lse.shape) == (lay.layers, B, lay.hq, lay.window)
@@ -654,7 +661,7 @@ class LayerEvictPlan:
             if paged is not None:                                # workspace size depends on the sizes only
                 sized = CLayout.from_buffer_copy(lay)
                 sized.kv_stride[3] = lay.d
-            nbytes = (0 if lse is not None else (ta_workspace_bytes(sized, params) + 255) // 256 * 256) + TA_LAYER_WS_BYTES
+            nbytes = (0 if lse is not None else (_workspace(sized, params) + 255) // 256 * 256) + TA_LAYER_WS_BYTES
             if lse is not None:
                 assert lse.dtype == torch.float32 and lse.is_contiguous()
                 assert tuple(lse.shape) == (layers, B, lay.hq, lay.window)

@@ -314,7 +314,7 @@ int32_t ta_score(const void* Q, const void* K, const ta_layout* lay, const int32
 {
     int32_t rc = check_score(Q, K, lay, prm, A, ws, ws_bytes);
     if (rc != TA_OK) return rc;
-    return hip_status(ta::launch_score(Q, K, *lay, seq_len, prm->causal, A, (float*)ws, nullptr, nullptr, nullptr,
+    return hip_status(ta::launch_score(Q, K, *lay, seq_len, prm->causal, A, (float*)ws, ws_bytes, nullptr, nullptr, nullptr,
                                        nullptr, (hipStream_t)stream));
 }
 
@@ -328,7 +328,7 @@ int32_t ta_score_lse(const void* Q, const void* K, const ta_layout* lay, const i
     if (!Q || !K || !A || !lse) return TA_ERR_NULL;
     if (!aligned16(Q) || !aligned16(K)) return TA_ERR_ALIGN;
     if (ta::score_grid_blocks(*lay) > 0x7FFFFFFFll) return TA_ERR_SHAPE;
-    return hip_status(ta::launch_score(Q, K, *lay, seq_len, prm->causal, A, nullptr, lse, nullptr, nullptr,
+    return hip_status(ta::launch_score(Q, K, *lay, seq_len, prm->causal, A, nullptr, 0, lse, nullptr, nullptr,
                                        nullptr, (hipStream_t)stream));
 }
 
@@ -455,14 +455,16 @@ int32_t evict_pass(const int32_t* tok, const int32_t* seq_len,
     if (rc != TA_OK) return rc;
     rc = check_compact(Kin, Vin, idx, cnt, lay, K, Kout, Vout);
     if (rc != TA_OK) return rc;
-    // the table of per-layer addresses goes to the workspace, behind what the score step uses of it
+    // the table of per-layer addresses goes to the end of the workspace, behind what the score step may use of it
     ta::LayerPtrs* lptr = nullptr;
+    size_t stats_bytes = ws_bytes;
     if (lp) {
         static_assert(sizeof(ta::LayerPtrs) <= TA_LAYER_WS_BYTES, "table must fit its share of the workspace");
-        const size_t table_off = ((scored && !lse ? workspace_bytes(lay) : 0) + 255) & ~(size_t)255;
-        if (!ws || ws_bytes < table_off + TA_LAYER_WS_BYTES) return TA_ERR_WORKSPACE;
+        const size_t need = ((scored && !lse ? workspace_bytes(lay) : 0) + 255) & ~(size_t)255;
+        if (!ws || ws_bytes < need + TA_LAYER_WS_BYTES) return TA_ERR_WORKSPACE;
         if (!aligned16(ws)) return TA_ERR_ALIGN;
-        lptr = reinterpret_cast<ta::LayerPtrs*>(static_cast<char*>(ws) + table_off);
+        stats_bytes = (ws_bytes - TA_LAYER_WS_BYTES) & ~(size_t)255;
+        lptr = reinterpret_cast<ta::LayerPtrs*>(static_cast<char*>(ws) + stats_bytes);
     }
 
     hipStream_t st = (hipStream_t)stream;
@@ -473,7 +475,7 @@ int32_t evict_pass(const int32_t* tok, const int32_t* seq_len,
     if (scored) {
         // the match rides along with the first sweep over the keys (one launch fewer in front of them)
         const ta::MatchRider rider = {tok, anchor_B, prm->allow, anchor, spons, vouch, &tab};
-        rc = hip_status(ta::launch_score(Q, Kin, *lay, seq_len, prm->causal, A, (float*)ws, lse, &rider, pg, lptr, st));
+        rc = hip_status(ta::launch_score(Q, Kin, *lay, seq_len, prm->causal, A, (float*)ws, stats_bytes, lse, &rider, pg, lptr, st));
         if (rc != TA_OK) return rc;
     } else {
         rc = hip_status(ta::launch_match(tok, seq_len, lay->batch, lay->n, tab, anchor_B, prm->allow, anchor, spons, vouch, st));
@@ -506,7 +508,7 @@ int32_t ta_score_paged(const void* Q, const void* Kpool, const ta_paged_kv* pg, 
         rc = check_score(Q, Kpool, &dense, prm, A, ws, ws_bytes);
         if (rc != TA_OK) return rc;
     }
-    return hip_status(ta::launch_score(Q, Kpool, dense, seq_len, prm->causal, A, (float*)ws, lse, nullptr, pg,
+    return hip_status(ta::launch_score(Q, Kpool, dense, seq_len, prm->causal, A, (float*)ws, ws_bytes, lse, nullptr, pg,
                                        nullptr, (hipStream_t)stream));
 }
 

@@ -98,7 +98,8 @@ struct LayerPtrs {
 hipError_t launch_layer_table(const LayerPtrs& host_table, LayerPtrs* dev_table, int32_t layers, hipStream_t st);
 
 // ---- score ------------------------------------------------------------------
-// Scratch bytes and grid size of the score step for a validated layout.
+// Scratch bytes the score step needs, and its largest grid, for a validated layout.  launch_score uses what ws_bytes gives it
+// beyond that where more chunks are faster.
 size_t score_workspace_bytes(const ta_layout& lay);
 int64_t score_grid_blocks(const ta_layout& lay);
 // With `rider` set, the match + voucher expansion of all sequences runs as trailing workgroups
@@ -108,7 +109,7 @@ int64_t score_grid_blocks(const ta_layout& lay);
 // `pg` != null: K is a paged pool addressed through pg->block_table (lay.kv_stride unused).
 // `lp` != null: Q and K of layer l start at lp->Q[l], lp->K[l] (Q, K and the layer strides unused).
 hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, const int32_t* seq_len,
-                        int causal, float* A, float* ws, const float* lse, const MatchRider* rider,
+                        int causal, float* A, float* ws, size_t ws_bytes, const float* lse, const MatchRider* rider,
                         const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st);
 
 // ---- select -----------------------------------------------------------------

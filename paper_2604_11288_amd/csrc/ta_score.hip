@@ -719,33 +719,49 @@ struct ScorePlan {
     int64_t units;
 };
 
-ScorePlan make_plan(const ta_layout& lay)
+// The plan whose statistics ta_workspace_bytes makes room for: chunks as long as possible while the grid still offers about
+// two workgroups per compute unit, at least 512 keys, never more than 32 per unit.
+ScorePlan base_plan(const ta_layout& lay)
 {
     ScorePlan p;
     p.rows = (lay.hq / lay.hkv) * lay.window;
     p.rows_pad = padded_rows(p.rows);
-    // Chunks per unit: the count whose fullest compute unit is done first.  A workgroup costs its stages plus the
-    // prologue (Q fragments, first stages, statistics merge) and epilogue, about SETUP stages' time; a compute unit that
-    // gets k of them costs k times that, and one workgroup of four wavefronts alone (rows_pad 128) does not quite
-    // fill it.  At most 32 chunks per unit, of at least two stages.  (Two workgroups per compute unit at any price, chunks of
-    // at least 512 keys, were the rule before.  Score step in us, before / now: 8 units of 4096 keys, 128 rows 22 / 19, 256
-    // rows 32 / 23; 64 units of 4096 keys 39 / 36; 192 units of 8192 keys, 256 rows 316 / 281: 576 workgroups on 256
-    // compute units that hold one each became 768.)
     p.units = (int64_t)lay.layers * lay.batch * lay.hkv;
-    const int64_t cus = compute_units(), stages = (lay.n + STAGE_KEYS - 1) / STAGE_KEYS;
+    const int64_t want_blocks = 2 * (int64_t)compute_units();
+    int64_t per_unit = (want_blocks + p.units - 1) / p.units;            // chunks per unit we would like
+    per_unit = per_unit < 1 ? 1 : (per_unit > 32 ? 32 : per_unit);
+    int64_t ck = ((lay.n + per_unit - 1) / per_unit + STAGE_KEYS - 1) / STAGE_KEYS * STAGE_KEYS;
+    if (ck < 512) ck = 512;
+    while (ck * 32 < lay.n) ck += STAGE_KEYS;
+    p.chunk_keys = (int32_t)ck;
+    p.nchunks = (lay.n + p.chunk_keys - 1) / p.chunk_keys;
+    return p;
+}
+
+int64_t stats_bytes(const ScorePlan& p, int64_t nchunks) { return p.units * nchunks * p.rows_pad * 2 * (int64_t)sizeof(float); }
+
+// The plan that runs, given `room` bytes for the statistics (at least the base plan's): the chunk count whose fullest compute
+// unit is done first.  A workgroup costs its stages plus the prologue (Q fragments, first stages, statistics merge) and
+// epilogue, about SETUP stages' time; a compute unit that gets k of them costs k times that, and one workgroup of four
+// wavefronts alone (rows_pad 128) does not quite fill it.  At most 32 chunks per unit, of at least two stages.  (Score step in
+// us, base plan / this one: 8 units of 4096 keys, 128 rows 22 / 19, 256 rows 32 / 23; 64 units of 4096 keys 39 / 36; 192
+// units of 8192 keys, 256 rows 316 / 281: 576 workgroups on 256 compute units that hold one each become 768.)
+ScorePlan make_plan(const ta_layout& lay, int64_t room)
+{
+    ScorePlan p = base_plan(lay);
     constexpr int64_t SETUP = 6, ALONE = 115;              // stages; per cent
-    int64_t best = -1, ck = 0;
+    const int64_t cus = compute_units(), stages = (lay.n + STAGE_KEYS - 1) / STAGE_KEYS;
+    int64_t best = -1;
     for (int64_t c = 1; c <= 32 && (c == 1 || stages >= 2 * c); ++c) {
-        const int64_t per_chunk = (stages + c - 1) / c;
-        if (per_chunk * 32 < stages) continue;
-        const int64_t k = (p.units * ((stages + per_chunk - 1) / per_chunk) + cus - 1) / cus;
+        const int64_t per_chunk = (stages + c - 1) / c, chunks = (stages + per_chunk - 1) / per_chunk;
+        if (chunks > p.nchunks && stats_bytes(p, chunks) > room) break;
+        const int64_t k = (p.units * chunks + cus - 1) / cus;
         const int64_t cost = k * (per_chunk + SETUP) * (k == 1 && p.rows_pad == 128 ? ALONE : 100);
         if (best < 0 || cost < best) {
             best = cost;
-            ck = per_chunk * STAGE_KEYS;
+            p.chunk_keys = (int32_t)(per_chunk * STAGE_KEYS);
         }
     }
-    p.chunk_keys = (int32_t)ck;
     p.nchunks = (lay.n + p.chunk_keys - 1) / p.chunk_keys;
     return p;
 }
@@ -754,22 +770,22 @@ ScorePlan make_plan(const ta_layout& lay)
 
 size_t score_workspace_bytes(const ta_layout& lay)
 {
-    const ScorePlan p = make_plan(lay);
-    // per-chunk row statistics (m, Z)
-    return (size_t)p.units * p.nchunks * p.rows_pad * 2 * sizeof(float);
+    const ScorePlan p = base_plan(lay);
+    return (size_t)stats_bytes(p, p.nchunks);              // per-chunk row statistics (m, Z)
 }
 
 int64_t score_grid_blocks(const ta_layout& lay)
 {
-    const ScorePlan p = make_plan(lay);
-    return 8 * ((p.units + 7) / 8) * p.nchunks;
+    const ScorePlan p = make_plan(lay, INT64_MAX);
+    const int64_t base = base_plan(lay).nchunks;
+    return 8 * ((p.units + 7) / 8) * (p.nchunks > base ? p.nchunks : base);
 }
 
 hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, const int32_t* seq_len,
-                        int causal, float* A, float* ws, const float* lse, const MatchRider* rider,
+                        int causal, float* A, float* ws, size_t ws_bytes, const float* lse, const MatchRider* rider,
                         const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st)
 {
-    const ScorePlan p = make_plan(lay);
+    const ScorePlan p = make_plan(lay, lse ? INT64_MAX : (int64_t)ws_bytes);
     ScoreArgs a;
     a.Ql = lp ? reinterpret_cast<const uint4* const*>(&lp->Q[0]) : nullptr;
     a.Kl = lp ? reinterpret_cast<const uint4* const*>(&lp->K[0]) : nullptr;
