@@ -93,7 +93,20 @@ class Params:
     allow: Optional[torch.Tensor] = None         # device uint8 [B][n]: allowlist of positions
     margin: Optional[torch.Tensor] = None        # device float [units][2] (out): margin of every unit's cut
 
+    def __setattr__(self, name, value):
+        self.__dict__[name] = value
+        self.__dict__["_c"] = None
+
     def c(self) -> CParams:
+        """The ABI's struct: the same one until a field is assigned (a struct that names tensors is built anew)."""
+        if self.__dict__.get("_c") is not None:
+            return self._c
+        c = self._build_c()
+        if self.layer_K is None and self.allow is None and self.margin is None:
+            self.__dict__["_c"] = c
+        return c
+
+    def _build_c(self) -> CParams:
         for t, dt in ((self.layer_K, torch.int32), (self.allow, torch.uint8), (self.margin, torch.float32)):
             assert t is None or (t.dtype == dt and t.is_contiguous())
         return CParams(self.n_sink, self.n_recent, self.span_L, self.sponsor_B, self.rho,
@@ -183,12 +196,21 @@ def ta_init():
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# torch.cuda.current_stream() builds a Stream object (3 us, as long as a kernel launch); the raw handle of the current
+# device's current stream takes a tenth of that
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _get_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_get_device())
 
 
 def _check(rc, where):
@@ -197,14 +219,23 @@ def _check(rc, where):
 
 
 def _table(tab_ids, tab_len):
-    """Host copies of the anchor table in the ABI's [E][TA_MAX_GRAM] / [E] int32 form."""
-    tab_len = np.ascontiguousarray(np.asarray(tab_len, dtype=np.int32))
+    """Host copies of the anchor table in the ABI's [E][TA_MAX_GRAM] / [E] int32 form (arrays that already have it as they are)."""
+    tab_len = np.ascontiguousarray(tab_len, dtype=np.int32)
     E = int(tab_len.shape[0])
+    if (E and type(tab_ids) is np.ndarray and tab_ids.dtype == np.int32 and tab_ids.shape == (E, TA_MAX_GRAM)
+            and tab_ids.flags.c_contiguous):
+        return tab_ids, tab_len, E
     ids = np.full((max(E, 1), TA_MAX_GRAM), -1, np.int32)
     if E:
         src = np.asarray(tab_ids, dtype=np.int32).reshape(E, -1)
         ids[:E, :min(src.shape[1], TA_MAX_GRAM)] = src[:, :TA_MAX_GRAM]
     return ids, tab_len, E
+
+
+def _host(a: np.ndarray):
+    """A small host array for an argument that the call only reads: ctypes passes the bytes' address, and building them
+    takes a tenth of what ndarray.ctypes takes."""
+    return a.tobytes()
 
 
 def layout_of(K: torch.Tensor, Q: Optional[torch.Tensor] = None, window: Optional[int] = None) -> CLayout:
@@ -252,7 +283,7 @@ def ta_match_anchors(tok, tab_ids, tab_len, params: Params, seq_len=None, anchor
     else:
         anchor, spons, vouch = out
     cp = params.c()
-    rc = lib().ta_match_anchors(_ptr(tok), _ptr(seq_len), B, n, ids.ctypes.data, lens.ctypes.data, E,
+    rc = lib().ta_match_anchors(_ptr(tok), _ptr(seq_len), B, n, _host(ids), _host(lens), E,
                                 _ptr(anchor_B), ctypes.byref(cp), _ptr(anchor), _ptr(spons), _ptr(vouch),
                                 _stream(stream))
     _check(rc, "ta_match_anchors")
@@ -479,7 +510,24 @@ def ta_compact(Kin, Vin, idx, cnt, K: int, idx_shared: bool = False, out=None, s
     return Kout, Vout
 
 
-class EvictPlan:
+class _Plan:
+    """run(): the C call with arguments marshalled when the plan is first run (and again after an attribute was assigned)."""
+
+    def __setattr__(self, name, value):
+        self.__dict__[name] = value
+        self.__dict__["_call"] = None
+
+    def run(self, stream=None):
+        call = self._call
+        if call is None:
+            call = self.__dict__["_call"] = self._marshal()
+        rc = call[0](*call[2], _stream(stream))
+        if rc != TA_OK:
+            raise TaError(rc, call[1])
+        return self
+
+
+class EvictPlan(_Plan):
     """Pre-allocated outputs and marshalled arguments of one ta_evict configuration.
 
     run() only performs the C call, so it can sit inside a timed loop.
@@ -531,42 +579,21 @@ class EvictPlan:
         self.Vout = torch.zeros(shape, dtype=torch.bfloat16, device=dev)
         self._cp = params.c()
 
-    def run(self, stream=None):
-        ws_bytes = 0 if self.ws is None else self.ws.numel()
+    def _marshal(self):
+        """(function, its name, arguments but the stream) of this configuration."""
+        head = (_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data, self.E, _ptr(self.anchor_B),
+                _ptr(self.Q), _ptr(self.Kin), _ptr(self.Vin))
+        sizes = (ctypes.byref(self.lay), ctypes.byref(self._cp), self.K)
+        outs = (_ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch), _ptr(self.A), _ptr(self.idx), _ptr(self.cnt),
+                _ptr(self.Kout), _ptr(self.Vout))
+        ws = (_ptr(self.ws), 0 if self.ws is None else self.ws.numel())
         if self.paged is not None:
-            rc = lib().ta_evict_paged(_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data,
-                                      self.E, _ptr(self.anchor_B), _ptr(self.Q), _ptr(self.Kin), _ptr(self.Vin),
-                                      ctypes.byref(self._pg), _ptr(self.lse), ctypes.byref(self.lay),
-                                      ctypes.byref(self._cp), self.K,
-                                      _ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch), _ptr(self.A),
-                                      _ptr(self.idx), _ptr(self.cnt), _ptr(self.Kout), _ptr(self.Vout),
-                                      _ptr(self.ws), ws_bytes, _stream(stream))
-            _check(rc, "ta_evict_paged")
-            return self
+            return lib().ta_evict_paged, "ta_evict_paged", head + (ctypes.byref(self._pg), _ptr(self.lse)) + sizes + outs + ws
         if self.lse is not None:
-            rc = lib().ta_evict_lse(_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data,
-                                    self.E, _ptr(self.anchor_B), _ptr(self.Q), _ptr(self.Kin), _ptr(self.Vin),
-                                    _ptr(self.lse), ctypes.byref(self.lay), ctypes.byref(self._cp), self.K,
-                                    _ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch), _ptr(self.A),
-                                    _ptr(self.idx), _ptr(self.cnt), _ptr(self.Kout), _ptr(self.Vout), _stream(stream))
-            _check(rc, "ta_evict_lse")
-            return self
+            return lib().ta_evict_lse, "ta_evict_lse", head + (_ptr(self.lse),) + sizes + outs
         if self.static_scratch:
-            rc = lib().ta_evict_static(_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data,
-                                       self.E, _ptr(self.anchor_B), _ptr(self.Q), _ptr(self.Kin), _ptr(self.Vin),
-                                       ctypes.byref(self.lay), ctypes.byref(self._cp), self.K,
-                                       _ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch), _ptr(self.A),
-                                       _ptr(self.idx), _ptr(self.cnt), _ptr(self.Kout), _ptr(self.Vout), _stream(stream))
-            _check(rc, "ta_evict_static")
-            return self
-        rc = lib().ta_evict(_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data,
-                            self.E, _ptr(self.anchor_B), _ptr(self.Q), _ptr(self.Kin), _ptr(self.Vin),
-                            ctypes.byref(self.lay), ctypes.byref(self._cp), self.K,
-                            _ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch), _ptr(self.A),
-                            _ptr(self.idx), _ptr(self.cnt), _ptr(self.Kout), _ptr(self.Vout),
-                            _ptr(self.ws), ws_bytes, _stream(stream))
-        _check(rc, "ta_evict")
-        return self
+            return lib().ta_evict_static, "ta_evict_static", head + sizes + outs
+        return lib().ta_evict, "ta_evict", head + sizes + outs + ws
 
 
 def ta_evict(tok, tab_ids, tab_len, Q, Kin, Vin, K: int, params: Params, seq_len=None, anchor_B=None,
@@ -599,7 +626,7 @@ class CLayerPtrs(ctypes.Structure):
                 ("Kout", ctypes.c_void_p), ("Vout", ctypes.c_void_p)]
 
 
-class LayerEvictPlan:
+class LayerEvictPlan(_Plan):
     """ta_evict_layers on caches kept as one tensor per layer.
 
     Q_layers: list of bf16 [B][Hq][W][d] (or None when params.alpha == 0); K_layers, V_layers: lists
@@ -680,25 +707,15 @@ class LayerEvictPlan:
         self._lp = CLayerPtrs(*[addr(a) for a in self._tables])
         self._cp = params.c()
 
-    def run(self, stream=None):
-        ws_bytes = self.ws.numel()
+    def _marshal(self):
+        head = (_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data, self.E, _ptr(self.anchor_B),
+                ctypes.byref(self._lp))
+        tail = (ctypes.byref(self.lay), ctypes.byref(self._cp), self.K, _ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch),
+                _ptr(self.A), _ptr(self.idx), _ptr(self.cnt), _ptr(self.ws), self.ws.numel())
         if self.paged is not None:
-            rc = lib().ta_evict_layers_paged(_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data,
-                                             self.lens.ctypes.data, self.E, _ptr(self.anchor_B), ctypes.byref(self._lp),
-                                             ctypes.byref(self._pg), _ptr(self.lse), ctypes.byref(self.lay),
-                                             ctypes.byref(self._cp), self.K,
-                                             _ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch), _ptr(self.A),
-                                             _ptr(self.idx), _ptr(self.cnt), _ptr(self.ws), ws_bytes, _stream(stream))
-            _check(rc, "ta_evict_layers_paged")
-            return self
+            return lib().ta_evict_layers_paged, "ta_evict_layers_paged", head + (ctypes.byref(self._pg), _ptr(self.lse)) + tail
         assert self.lse is None, "row log-sum-exps are taken by the paged form only"
-        rc = lib().ta_evict_layers(_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data,
-                                   self.E, _ptr(self.anchor_B), ctypes.byref(self._lp), ctypes.byref(self.lay),
-                                   ctypes.byref(self._cp), self.K,
-                                   _ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch), _ptr(self.A),
-                                   _ptr(self.idx), _ptr(self.cnt), _ptr(self.ws), ws_bytes, _stream(stream))
-        _check(rc, "ta_evict_layers")
-        return self
+        return lib().ta_evict_layers, "ta_evict_layers", head + tail
 
 
 def ta_evict_layers_paged(tok, tab_ids, tab_len, Q_layers, Kpool_layers, Vpool_layers, paged: "PagedKV", K: int,
@@ -740,7 +757,17 @@ class DecodeState:
         self.A = torch.zeros((layers, batch, hkv, K + 1), dtype=torch.float32, device=dev)
         self.stepped = torch.zeros((batch,), dtype=i32, device=dev)
 
+    def __setattr__(self, name, value):
+        self.__dict__[name] = value
+        self.__dict__["_c"] = None
+
     def c(self) -> CDecodeState:
+        """The ABI's struct: the same one until an attribute is assigned."""
+        if self._c is None:
+            self.__dict__["_c"] = self._build_c()
+        return self._c
+
+    def _build_c(self) -> CDecodeState:
         return CDecodeState(self.layers, self.batch, self.hq, self.hkv, self.d, self.K, self.cap,
                             self.tok.data_ptr(), self.len.data_ptr(), self.anchor.data_ptr(),
                             self.budget.data_ptr(), self.vouch.data_ptr(), self.spons.data_ptr(),
@@ -766,7 +793,7 @@ def ta_decode_step(state: DecodeState, new_tok, q_new, k_new, v_new, tab_ids, ta
     ids, lens, E = _table(tab_ids, tab_len)
     cs, cp = state.c(), params.c()
     rc = lib().ta_decode_step(ctypes.byref(cs), _ptr(new_tok), _ptr(q_new), _ptr(k_new), _ptr(v_new),
-                              ids.ctypes.data, lens.ctypes.data, E, ctypes.byref(cp), _ptr(evicted),
+                              _host(ids), _host(lens), E, ctypes.byref(cp), _ptr(evicted),
                               _stream(stream))
     _check(rc, "ta_decode_step")
     return evicted
