@@ -1118,9 +1118,10 @@ __device__ __forceinline__ RadixState stream_pick(StreamLds& L, uint32_t need)
     return L.state;
 }
 
-// MARGIN: the keys turned away are tracked for the margin output (instances of their own: the default
+// MARGIN: the keys turned away are tracked for the margin output; OPTS: max-pooled scores and the fixed partition, which walks
+// the sequence a second time when it has to find the protected tokens first (instances of their own: the default
 // ones keep their registers)
-template <int THREADS, int PER_THREAD, bool MARGIN>        // cap <= THREADS * PER_THREAD
+template <int THREADS, int PER_THREAD, bool MARGIN, bool OPTS>        // cap <= THREADS * PER_THREAD
 __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t cap)
 {
     constexpr int WAVES = THREADS / 64;
@@ -1176,6 +1177,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     struct Loaded {
         float4 A, v;
         uint32_t sp, an;
+        float4 before[OPTS ? 1 : 0], after[OPTS ? 1 : 0];  // the neighbouring quads of A, for the max-pool
     };
     // unconditional loads (the quad index is clamped into the row, the caller masks what lies outside):
     // straight-line loads let the compiler wait for exactly the segment it needs
@@ -1187,6 +1189,12 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
         x.an = load_quad_b(anchor, start);
         x.v = load_quad_f(vouch, start);
         x.A = load_quad_f(A_src, start);
+        if constexpr (OPTS) {
+            if (a.pool_r > 0) {                            // uniform
+                x.before[0] = load_quad_f(A_src, 4 * (q > 0 ? q - 1 : 0));
+                x.after[0] = load_quad_f(A_src, quad_start(4 * q + 4, n));
+            }
+        }
     };
 
     // the first segments' operands are requested before anything else: they travel while the sponsored
@@ -1239,7 +1247,16 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     for (int w = 0; w < WAVES; ++w) c1 += L.red[w];
 
     const int bclass = (c2 + c1 <= K) ? 0 : 1;
-    const int32_t R = bclass == 0 ? K - c2 - c1 : K - c2;  // slots of the boundary class (more members than that exist)
+    int32_t R = bclass == 0 ? K - c2 - c1 : K - c2;        // slots of the boundary class (more members than that exist)
+    // fixed partition: P sponsored tokens are protected, K - c2 - P more slots go to the best of everything else
+    const bool capped = OPTS && a.k_protected >= 0;
+    int32_t P = 0;
+    if (capped) {
+        P = a.k_protected < c1 ? a.k_protected : c1;
+        P = P < K - c2 ? P : K - c2;
+    }
+    uint32_t T1 = 0xFFFFFFFFu;                             // a sponsored position is protected iff key > T1, or key == T1 and p >= Pt1
+    int32_t Pt1 = 0x7FFFFFFF;
     const float nf = (float)nb, inv = __fdiv_rn(1.0f, nf);
 
     auto key_of = [&](int32_t p, float Ap, uint32_t an, float v) -> uint32_t {
@@ -1332,70 +1349,123 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
 
     // ---- the walk, from the last segment to the first; the operands of SS_DEPTH segments are in flight
     // (a segment is worked on in about a microsecond, a round trip under load takes several)
-    for (int32_t top = nseg - 1; top >= 0; top -= SS_DEPTH) {
-#pragma unroll
-        for (int d = 0; d < SS_DEPTH; ++d) {
-            const int32_t sg = top - d;
-            const int32_t q = sg * THREADS + tid;
-            uint32_t keys[4];
-            bool join[4];
-            uint32_t always = 0u;                          // bits of the quad that are retained whatever the ranking says
-            {
-                Loaded x = ring[d];
-                if (n & 3) {                               // uniform
-                    const int32_t by = q == nquads - 1 ? 4 * q - quad_start(4 * q, n) : 0;
-                    x.sp >>= 8 * by;
-                    x.an >>= 8 * by;
-                    x.v = move_down(x.v, by);
-                    x.A = move_down(x.A, by);
+    for (int pool = OPTS ? 0 : 1; pool < 2; ++pool) {
+        const bool protect = pool == 0;
+        if constexpr (OPTS) {
+            if (protect && !(capped && P > 0 && P < c1)) continue;         // uniform: nothing to find
+            if (capped) R = protect ? P : K - c2 - P;
+            if (!protect && capped && P > 0 && P < c1) {                   // the first walk's list is the protected pool
+                T1 = T;
+                Pt1 = Pt;
+                const uint32_t m = L.count;
+                for (uint32_t e = tid; e < m; e += THREADS) {
+                    const uint32_t p = cpos[e];
+                    atomicOr(&bitmap[p >> 5], 1u << (p & 31u));
                 }
-                const float Aq[4] = {x.A.x, x.A.y, x.A.z, x.A.w};
-                const float vq[4] = {x.v.x, x.v.y, x.v.z, x.v.w};
+                __syncthreads();
+                if (tid == 0) L.count = 0u;
+                T = 0u;
+                Pt = 0x7FFFFFFF;
+                gone_max = 0u;
+                __syncthreads();
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const int32_t p = 4 * q + c;
-                    const uint32_t sp = (x.sp >> (8 * c)) & 0xFFu, an = (x.an >> (8 * c)) & 0xFFu;
-                    keys[c] = 0u;
-                    join[c] = false;
-                    if (sg >= 0 && p < nb && q < nquads) {
-                        if (p < ns || p >= rs) always |= 1u << c;
-                        else if ((sp != 0u) != (bclass == 1)) always |= (sp != 0u) ? (1u << c) : 0u;   // class 1 above the boundary class, class 0 below it
-                        else if (MARGIN || R > 0) {
-                            keys[c] = key_of(p, Aq[c], an, vq[c]);
-                            join[c] = R > 0 && (keys[c] > T || (keys[c] == T && p >= Pt));
-                            if (MARGIN && !join[c]) gone_max = keys[c] > gone_max ? keys[c] : gone_max;
+                for (int d = 0; d < SS_DEPTH; ++d) load_quad((nseg - 1 - d) * THREADS + tid, ring[d]);
+            }
+        }
+        for (int32_t top = nseg - 1; top >= 0; top -= SS_DEPTH) {
+#pragma unroll
+            for (int d = 0; d < SS_DEPTH; ++d) {
+                const int32_t sg = top - d;
+                const int32_t q = sg * THREADS + tid;
+                uint32_t keys[4];
+                bool join[4];
+                uint32_t always = 0u;                          // bits of the quad that are retained whatever the ranking says
+                {
+                    Loaded x = ring[d];
+                    if (n & 3) {                               // uniform
+                        const int32_t by = q == nquads - 1 ? 4 * q - quad_start(4 * q, n) : 0;
+                        x.sp >>= 8 * by;
+                        x.an >>= 8 * by;
+                        x.v = move_down(x.v, by);
+                        x.A = move_down(x.A, by);
+                    }
+                    float Aq[4] = {x.A.x, x.A.y, x.A.z, x.A.w};
+                    if constexpr (OPTS) {
+                        if (a.pool_r > 0) {                    // uniform; window clipped to [0, nb)
+                            const int32_t p4 = 4 * q + 4, by4 = p4 < n ? p4 - quad_start(p4, n) : 0;
+                            const float4 after = move_down(x.after[0], by4);
+                            float w12[12] = {x.before[0].x, x.before[0].y, x.before[0].z, x.before[0].w, Aq[0], Aq[1], Aq[2], Aq[3],
+                                             after.x, after.y, after.z, after.w};
+#pragma unroll
+                            for (int j = 0; j < 12; ++j)
+                                if (4 * q - 4 + j < 0 || 4 * q - 4 + j >= nb) w12[j] = -INFINITY;
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                float m = w12[4 + c];
+#pragma unroll
+                                for (int e = 1; e <= 4; ++e)
+                                    if (e <= a.pool_r) m = fmaxf(m, fmaxf(w12[4 + c - e], w12[4 + c + e]));
+                                Aq[c] = m;
+                            }
                         }
                     }
-                }
-            }
-            // the segment SS_DEPTH further on takes over the registers (past the first segment: a clamped
-            // address whose data nobody uses)
-            load_quad((sg - SS_DEPTH) * THREADS + tid, ring[d]);
-            if (sg >= 0) {                                 // uniform
-                if (always) atomicOr(&bitmap[(4 * q) >> 5], always << ((4 * q) & 31));
+                    const float vq[4] = {x.v.x, x.v.y, x.v.z, x.v.w};
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const unsigned long long bal = __ballot(join[c]);
-                    if (bal) {                             // uniform
-                        uint32_t base = 0;
-                        if (lane == 0) base = atomicAdd(&L.count, (uint32_t)__popcll(bal));
-                        base = __shfl(base, 0);
-                        if (join[c]) {
-                            const uint32_t slot = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
-                            if (slot < (uint32_t)cap) {    // holds by construction: the list is cut back before it could overflow
-                                ckey[slot] = keys[c];
-                                cpos[slot] = (uint32_t)(4 * q + c);
+                    for (int c = 0; c < 4; ++c) {
+                        const int32_t p = 4 * q + c;
+                        const uint32_t sp = (x.sp >> (8 * c)) & 0xFFu, an = (x.an >> (8 * c)) & 0xFFu;
+                        keys[c] = 0u;
+                        join[c] = false;
+                        if (sg >= 0 && p < nb && q < nquads) {
+                            if (p < ns || p >= rs) always |= 1u << c;
+                            else if (capped) {
+                                keys[c] = key_of(p, Aq[c], an, vq[c]);
+                                bool member = sp != 0u;        // first walk: the protected pool
+                                if (!protect) {
+                                    const bool prot = sp != 0u && (P == c1 || keys[c] > T1 || (keys[c] == T1 && p >= Pt1));
+                                    member = !prot;
+                                    always |= prot && P == c1 ? 1u << c : 0u;
+                                }
+                                join[c] = member && R > 0 && (keys[c] > T || (keys[c] == T && p >= Pt));
+                                if (MARGIN && member && !join[c]) gone_max = keys[c] > gone_max ? keys[c] : gone_max;
+                            } else if ((sp != 0u) != (bclass == 1)) always |= (sp != 0u) ? (1u << c) : 0u;   // class 1 above the boundary class, class 0 below it
+                            else if (MARGIN || R > 0) {
+                                keys[c] = key_of(p, Aq[c], an, vq[c]);
+                                join[c] = R > 0 && (keys[c] > T || (keys[c] == T && p >= Pt));
+                                if (MARGIN && !join[c]) gone_max = keys[c] > gone_max ? keys[c] : gone_max;
                             }
                         }
                     }
                 }
-                __syncthreads();                           // the segment's entries are in the list
-                const uint32_t m = L.count;
-                __syncthreads();                           // every thread has read the count before anyone adds to it again
-                // Cut back when the next segment might not fit, at the end (to exactly R), and once early: the
-                // first cut gives the threshold that keeps most later positions out of the list.
-                const bool early = T == 0u && m >= 2u * (uint32_t)R && m >= 512u;
-                if (R > 0 && ((sg > 0 && (m + (uint32_t)SEG > (uint32_t)cap || early)) || (sg == 0 && m > (uint32_t)R))) shrink(m);
+                // the segment SS_DEPTH further on takes over the registers (past the first segment: a clamped
+                // address whose data nobody uses)
+                load_quad((sg - SS_DEPTH) * THREADS + tid, ring[d]);
+                if (sg >= 0) {                                 // uniform
+                    if (always) atomicOr(&bitmap[(4 * q) >> 5], always << ((4 * q) & 31));
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const unsigned long long bal = __ballot(join[c]);
+                        if (bal) {                             // uniform
+                            uint32_t base = 0;
+                            if (lane == 0) base = atomicAdd(&L.count, (uint32_t)__popcll(bal));
+                            base = __shfl(base, 0);
+                            if (join[c]) {
+                                const uint32_t slot = base + (uint32_t)__popcll(bal & ((1ull << lane) - 1ull));
+                                if (slot < (uint32_t)cap) {    // holds by construction: the list is cut back before it could overflow
+                                    ckey[slot] = keys[c];
+                                    cpos[slot] = (uint32_t)(4 * q + c);
+                                }
+                            }
+                        }
+                    }
+                    __syncthreads();                           // the segment's entries are in the list
+                    const uint32_t m = L.count;
+                    __syncthreads();                           // every thread has read the count before anyone adds to it again
+                    // Cut back when the next segment might not fit, at the end (to exactly R), and once early: the
+                    // first cut gives the threshold that keeps most later positions out of the list.
+                    const bool early = T == 0u && m >= 2u * (uint32_t)R && m >= 512u;
+                    if (R > 0 && ((sg > 0 && (m + (uint32_t)SEG > (uint32_t)cap || early)) || (sg == 0 && m > (uint32_t)R))) shrink(m);
+                }
             }
         }
     }
@@ -1439,7 +1509,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
         }
     }
     if (tid == 0) a.cnt[unit] = total < K ? total : K;
-    if (MARGIN) {
+    if (MARGIN && a.margin) {                              // uniform
         uint32_t kept_min = 0xFFFFFFFFu;
         const uint32_t m = L.count;
         for (uint32_t e = tid; e < m; e += THREADS) kept_min = ckey[e] < kept_min ? ckey[e] : kept_min;
@@ -1467,46 +1537,31 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
     }
 }
 
-// Short candidate lists (budgets up to about 1300): six wavefronts per SIMD, which the many short units
-// of a ragged batch need to hide their round trips (two registers go to scratch for it).  Long lists keep
-// the registers.
-__global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
-select_stream_few_kernel(SelectArgs a, int32_t cap)
-{
-    select_stream<SS_THREADS, SS_FEW_PER_THREAD, false>(a, cap);
-}
-
-__global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
-select_stream_few_margin_kernel(SelectArgs a, int32_t cap)
-{
-    select_stream<SS_THREADS, SS_FEW_PER_THREAD, true>(a, cap);
-}
-
-__global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
+// WPE: wavefronts per SIMD.  Short candidate lists (budgets up to about 1300): six, which the many short units of a ragged
+// batch need to hide their round trips (two registers go to scratch for it); long lists keep the registers.
+template <int PER_THREAD, int WPE, bool MARGIN, bool OPTS>
+__global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(WPE)))
 select_stream_kernel(SelectArgs a, int32_t cap)
 {
-    select_stream<SS_THREADS, SS_MAX_PER_THREAD, false>(a, cap);
-}
-
-__global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(4)))
-select_stream_margin_kernel(SelectArgs a, int32_t cap)
-{
-    select_stream<SS_THREADS, SS_MAX_PER_THREAD, true>(a, cap);
+    select_stream<SS_THREADS, PER_THREAD, MARGIN, OPTS>(a, cap);
 }
 
 // Few units with long rows: 256 of them have a compute unit each, where four wavefronts walk 1024 positions at a time
-// (256 rows of 131 072 positions: 203 us); sixteen walk 4096.
+// (256 rows of 131 072 positions: 203 us); sixteen walk 4096 (89 us).
+template <bool MARGIN, bool OPTS>
 __global__ void __launch_bounds__(SS_BIG_THREADS)
 select_stream_big_kernel(SelectArgs a, int32_t cap)
 {
-    select_stream<SS_BIG_THREADS, SS_BIG_PER_THREAD, false>(a, cap);
+    select_stream<SS_BIG_THREADS, SS_BIG_PER_THREAD, MARGIN, OPTS>(a, cap);
 }
 
-__global__ void __launch_bounds__(SS_BIG_THREADS)
-select_stream_big_margin_kernel(SelectArgs a, int32_t cap)
-{
-    select_stream<SS_BIG_THREADS, SS_BIG_PER_THREAD, true>(a, cap);
-}
+typedef void (*StreamKernel)(SelectArgs, int32_t);
+// [margin]; the instances with options track the margin too
+constexpr StreamKernel STREAM_FEW[2] = {select_stream_kernel<SS_FEW_PER_THREAD, 6, false, false>, select_stream_kernel<SS_FEW_PER_THREAD, 6, true, false>};
+constexpr StreamKernel STREAM_LONG[2] = {select_stream_kernel<SS_MAX_PER_THREAD, 4, false, false>, select_stream_kernel<SS_MAX_PER_THREAD, 4, true, false>};
+constexpr StreamKernel STREAM_BIG[2] = {select_stream_big_kernel<false, false>, select_stream_big_kernel<true, false>};
+constexpr StreamKernel STREAM_OPTS = select_stream_kernel<SS_MAX_PER_THREAD, 3, true, true>;
+constexpr StreamKernel STREAM_BIG_OPTS = select_stream_big_kernel<true, true>;
 
 DeviceOnce g_setup;
 
@@ -1515,23 +1570,10 @@ DeviceOnce g_setup;
 hipError_t select_setup()
 {
     return g_setup.run([](int) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_few_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_few_margin_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_big_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_big_margin_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_stream_margin_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
+        hipError_t e = hipSuccess;
+        for (StreamKernel k : {STREAM_FEW[0], STREAM_FEW[1], STREAM_LONG[0], STREAM_LONG[1], STREAM_BIG[0], STREAM_BIG[1], STREAM_OPTS, STREAM_BIG_OPTS})
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, SS_MAX_LDS);
         return e;
     });
 }
@@ -1569,9 +1611,10 @@ hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* s
                ((uintptr_t)vouch % 16 == 0) && (a.A == nullptr || (uintptr_t)a.A % 16 == 0);
     const unsigned blocks = (unsigned)units;
     const bool capped = prm.k_protected >= 0;
-    // The streaming form serves the plain (elastic, unpooled) selection when its candidate list and the bitmap of the
-    // sequence fit the LDS of a workgroup.
-    if (!capped && a.pool_r == 0 && n >= 4 && (n > SR_MAX_N || units >= SS_MIN_UNITS)) {
+    // The streaming form serves the selection when its candidate list and the bitmap of the sequence fit the LDS of a
+    // workgroup (with options only rows that the register form cannot hold).
+    const bool opts = capped || a.pool_r > 0;
+    if (n >= 4 && (n > SR_MAX_N || (units >= SS_MIN_UNITS && !opts))) {
         const int64_t rmax = (int64_t)K - prm.n_sink - prm.n_recent;      // most slots the boundary class can have
         const auto list_cap = [&](int threads) { return (rmax + 4 * threads + SS_SLACK + threads - 1) / threads * threads; };
         const auto lds_of = [&](int64_t cap) { return cap * 8 + ((int64_t)n + 31) / 32 * 4; };
@@ -1581,9 +1624,8 @@ hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* s
             const hipError_t attr_err = select_setup();
             if (attr_err != hipSuccess) return attr_err;
             const bool few = cap <= SS_THREADS * SS_FEW_PER_THREAD;
-            auto kernel = big ? (a.margin ? select_stream_big_margin_kernel : select_stream_big_kernel)
-                        : few ? (a.margin ? select_stream_few_margin_kernel : select_stream_few_kernel)
-                              : (a.margin ? select_stream_margin_kernel : select_stream_kernel);
+            const int m = a.margin ? 1 : 0;
+            const StreamKernel kernel = opts ? (big ? STREAM_BIG_OPTS : STREAM_OPTS) : big ? STREAM_BIG[m] : few ? STREAM_FEW[m] : STREAM_LONG[m];
             const int64_t c = big ? big_cap : cap;
             hipLaunchKernelGGL(kernel, dim3(blocks), dim3(big ? SS_BIG_THREADS : SS_THREADS), (size_t)lds_of(c), st, a, (int32_t)c);
             return hipGetLastError();

@@ -66,6 +66,25 @@ def test_select_with_max_pooled_scores(n, ragged, pool_k, mode):
     assert differs > 0                        # the pooling does change the selection
 
 
+@pytest.mark.parametrize("n,K,pool_k,kp", [
+    (33003, 400, 9, 150), (33003, 3000, 5, 20), (33001, 3000, 1, 400), (40002, 64, 3, 10 ** 6), (32770, 6500, 7, 30),   # rows at odd addresses, both
+])                                                                                                                     # workgroup sizes, a list that does not fit
+def test_long_rows_with_pooling_and_partition(n, K, pool_k, kp):
+    w = wl.scaled(wl.CONFIGS["c2_full_model"], n=n, batch=3, planted=60, ragged=(n - 500, n))
+    td = wl.make_tokens(w, clean=False)
+    A = _scores(np.random.default_rng(n + K), (1, 3, 1, n), "heavy")
+    prm = _prm(w, pool_k=pool_k, k_protected=kp)
+    seq = _dev(td.seq_len)
+    anchor, spons, vouch = ta.ta_match_anchors(_dev(td.tok), td.tab_ids, td.tab_len, prm, seq_len=seq)
+    idx, cnt = ta.ta_select(_dev(A), anchor, spons, vouch, K, prm, 1, 1, seq_len=seq)
+    idx, cnt = idx.cpu().numpy(), cnt.cpu().numpy()
+    for b in range(3):
+        nb = int(td.seq_len[b])
+        a, s, v = ora.evict_sequence(td.tok[b, :nb], td.tab_ids, td.tab_len)
+        ref = ora.select_partition(ora.maxpool(A[0, b, 0, :nb], pool_k), a, s, v, K, kp, w.n_sink, w.n_recent)
+        assert cnt[0, b, 0] == len(ref) and np.array_equal(idx[0, b, 0, :len(ref)], ref)
+
+
 @pytest.mark.parametrize("n,K,planted,mode,ragged", [
     (4096, 16, 4, "heavy", None),             # the paper's K = 16: 24 sponsored tokens, pools of 0..8
     (4096, 64, 8, "heavy", None),
