@@ -603,15 +603,21 @@ template <int MODE>
 hipError_t launch_width(const DetectArgs& a, hipStream_t st)
 {
     const int64_t P = a.total;
-    if (MODE == MODE_COSINE && a.wrows <= 16) return launch_split<1, 1, 8, 2, MODE>(a, st);
+    // Rows of few steps: fewer wavefronts, so that each has several steps of its own to keep in flight (d_model 1024: 93388 rows
+    // and 16 concepts 28 us with four wavefronts, 37 with eight; 131072 positions, 32 units 52 / 56, 64 units 58 with two
+    // wavefronts, 68 with four; d_model 2048: 70 / 76, 100 / 108, 108 / 124).
+    const bool narrow = a.dm <= 2048;
+    if (MODE == MODE_COSINE && a.wrows <= 16) return narrow ? launch_split<2, 1, 4, 2, MODE>(a, st) : launch_split<1, 1, 8, 2, MODE>(a, st);
     switch (a.m) {
         case 32:
             if (P <= 4096) return launch_split<1, 2, 8, 2, MODE>(a, st);
             if (P <= 8192) return launch_split<2, 2, 4, 2, MODE>(a, st);
+            if (narrow && P > 24576) return launch_split<2, 2, 4, 2, MODE>(a, st);
             return launch_split<4, 2, 8, 1, MODE>(a, st);
         case 64:
             if (P <= 4096) return launch_split<1, 4, 4, 3, MODE>(a, st);
             if (P <= 8192) return launch_split<2, 4, 4, 2, MODE>(a, st);
+            if (narrow && P > 24576) return launch_split<4, 4, 2, 2, MODE>(a, st);
             return launch_split<4, 4, 4, 2, MODE>(a, st);
         case 128:
             if (P <= 4096) return launch_split<1, 8, 4, 2, MODE>(a, st);
