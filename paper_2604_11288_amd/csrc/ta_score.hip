@@ -46,7 +46,8 @@ constexpr int STAGE_KEYS = 64;
 constexpr int STAGE_UNITS = STAGE_KEYS * 16;     // 16-byte units per stage (256 B per key)
 // Stage buffers per workgroup; loads run that many minus one stages ahead.  (Eight buffers for
 // the wider workgroups, which have a compute unit to themselves, were measured: no gain.)
-constexpr int ring_of(int) { return 4; }
+// Three for units of at most 64 rows: 48 KB, so that three such workgroups share a compute unit.
+constexpr int ring_of(int rg) { return rg == 1 ? 3 : 4; }
 // the widest workgroup: 64 * MAX_RG rows at a time (more row groups leave too few registers per lane)
 constexpr int MAX_RG = 4;
 
@@ -652,22 +653,26 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 template <int RG, int RT, bool COLSUM>
 hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
 {
-    if (rider && a.table) {
-        // paged keys: the match runs as a launch of its own in front of the sweep
+    if (rider && (a.table || RG == 1)) {
+        // paged keys, workgroups narrower than a match tile: the match runs as a launch of its own in front of the sweep
         const hipError_t e = launch_match(rider->tok, a.seq_len, a.batch, a.n, *rider->tab, rider->anchor_B, rider->allow,
                                           rider->anchor, rider->spons, rider->vouch, st);
         if (e != hipSuccess) return e;
         rider = nullptr;
     }
-    if (rider) {
-        RiderArgs r;
-        r.m = make_match_args(rider->tok, a.seq_len, a.batch, a.n, rider->anchor_B, rider->allow, rider->anchor, rider->spons,
-                              rider->vouch);
-        r.tab = *rider->tab;
-        r.score_blocks = blocks;
-        const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
-        hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
-    } else if (a.table) {
+    if constexpr (RG > 1) {
+        if (rider) {
+            RiderArgs r;
+            r.m = make_match_args(rider->tok, a.seq_len, a.batch, a.n, rider->anchor_B, rider->allow, rider->anchor, rider->spons,
+                                  rider->vouch);
+            r.tab = *rider->tab;
+            r.score_blocks = blocks;
+            const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
+            hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            return hipGetLastError();
+        }
+    }
+    if (a.table) {
         hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true>), dim3(blocks), dim3(128 * RG), 0, st, a);
     } else {
         hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false>), dim3(blocks), dim3(128 * RG), 0, st, a);
@@ -781,6 +786,12 @@ int64_t score_grid_blocks(const ta_layout& lay)
     return 8 * ((p.units + 7) / 8) * (p.nchunks > base ? p.nchunks : base);
 }
 
+// Units of at most 64 rows: two wavefronts per workgroup instead of four of which two work on padding (score step, two sweeps,
+// us: 256 units of 4096 keys 104 -> 95, of 16384 keys 387 -> 369, of 40000 keys 481 -> 463; 8 units of 4096 keys 13.6 -> 13.2).
+// Such a workgroup cannot take a match tile along, so where there is one to take, the keys have to be many enough (256 MB) for
+// the gain to pay for a launch of its own, some 5 us.
+constexpr int64_t NARROW_KEYS = int64_t(1) << 20;
+
 hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, const int32_t* seq_len,
                         int causal, float* A, float* ws, size_t ws_bytes, const float* lse, const MatchRider* rider,
                         const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st)
@@ -833,7 +844,9 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
     switch (a.rows_pad) {
         // two 32-row tiles per wavefront (one tile per wavefront with twice the wavefronts - four
         // per SIMD instead of two - was measured: same time at 128 rows, 5 % slower at 256)
-        case 128: return launch_rg<2, 2>(a, p.units, rider, st);
+        case 128:
+            if (p.rows <= 64 && (!rider || a.table || p.units * lay.n >= NARROW_KEYS)) return launch_rg<1, 2>(a, p.units, rider, st);
+            return launch_rg<2, 2>(a, p.units, rider, st);
         case 256: return launch_rg<4, 2>(a, p.units, rider, st);
         default: return launch_rg<4, 2>(a, p.units, rider, st);   // 512 rows: two passes of 256 (eight row groups
                                                                   // at once leave 128 registers per lane: spills, 3x slower)

@@ -488,6 +488,12 @@ def test_evict_c2_dirty_tokens():
     _check_evict(w, 256, clean=False, layers=1, units=[(0, 0, 1), (0, 0, 4)])
 
 
+@pytest.mark.parametrize("n", [4095, 4096])
+def test_evict_narrow_units_beside_the_line_of_their_own_match_launch(n):
+    w = wl.scaled(wl.CONFIGS["c2_full_model"], layers=32, batch=1, n=n, window=16)
+    _check_evict(w, 128, units=[(0, 0, 0), (17, 0, 3), (31, 0, 7)])
+
+
 def test_evict_c3_ta_fast_scaled():
     w = wl.scaled(wl.CONFIGS["c3_ta_fast"], layers=2, batch=3, n=32768)
     _check_evict(w, 512, units=[(0, 0, 0), (1, 2, 7), (0, 1, 3)])
