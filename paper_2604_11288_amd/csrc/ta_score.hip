@@ -158,8 +158,12 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 
     const int32_t seq_in_xcd = (int32_t)(blockIdx.x >> 3);
     int32_t chunk;
-    const int32_t place = place_of(blockIdx.x, a.nchunks, chunk);
+    int32_t place = place_of(blockIdx.x, a.nchunks, chunk);
     if (place >= a.units) return;
+    if (COLSUM && a.backwards) {
+        place = a.units - 1 - place;
+        chunk = a.nchunks - 1 - chunk;
+    }
     const int32_t unit = __builtin_amdgcn_readfirstlane(unit_at(place, a.seq_len, a.batch, a.hkv, a.units));
     const int32_t g = unit % a.hkv;
     const int32_t b = (unit / a.hkv) % a.batch;
@@ -650,6 +654,20 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     }
 }
 
+int compute_units()
+{
+    static std::atomic<int> cached{0};                     // callers on several threads may race to fill it
+    int cu = cached.load(std::memory_order_relaxed);
+    if (cu == 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cu < 1)
+            cu = 256;                                      // MI355X
+        cached.store(cu, std::memory_order_relaxed);
+    }
+    return cu;
+}
+
 template <int RG, int RT, bool COLSUM>
 hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
 {
@@ -687,6 +705,13 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, hipStr
     // so that sweep 2 re-reads its keys from the last-level cache was measured slower.)
     a.units = (int32_t)units;
     const unsigned blocks = (unsigned)(8ll * ((units + 7) / 8) * a.nchunks);
+    // More workgroups than run at once: the second sweep takes them in the opposite order, so that it begins with the keys that
+    // the first has read last and that the last-level cache (256 MB) still holds.  (Two sweeps, 128 rows, us: 512 units of 2048
+    // keys 115 -> 107, 1024 of 2048 224 -> 211, 1024 of 4096 419 -> 410, ragged 1024 of 1500..3001 249 -> 233; 256 rows, 192
+    // units of 8192 keys 283 -> 271.)  Where all run at once the stages of each do that already, and the ragged ones should
+    // keep the longest first (512 of 1500..3001: 126 -> 129).
+    constexpr int64_t RESIDENT = RG == 1 ? 3 : (RG == 2 ? 2 : 1);       // workgroups per compute unit, by their stage rings
+    a.backwards = !a.lse && blocks > RESIDENT * compute_units();
     if (a.lse)                                             // the row normalisers are given: column sums alone
         return launch_sweep<RG, RT, true>(a, blocks, rider, st);
     const hipError_t e = launch_sweep<RG, RT, false>(a, blocks, rider, st);
@@ -703,20 +728,6 @@ int32_t padded_rows(int32_t rows)
     if (rows <= 128) return 128;
     if (rows <= 256) return 256;
     return 512;
-}
-
-int compute_units()
-{
-    static std::atomic<int> cached{0};                     // callers on several threads may race to fill it
-    int cu = cached.load(std::memory_order_relaxed);
-    if (cu == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cu < 1)
-            cu = 256;                                      // MI355X
-        cached.store(cu, std::memory_order_relaxed);
-    }
-    return cu;
 }
 
 struct ScorePlan {

@@ -27,6 +27,7 @@ struct ScoreArgs {
     int32_t chunk_keys, nchunks;
     int32_t units;
     int32_t causal;
+    int32_t backwards;                 // sweep 2 takes the units and chunks in the opposite order
     float scale_log2;                  // log2(e) / sqrt(d)
     // one tensor per layer: DEVICE tables of per-layer base addresses (layer l starts at Ql[l], Kl[l]
     // instead of Q + l*q_sl, K + l*k_sl), or null

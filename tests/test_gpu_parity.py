@@ -275,6 +275,17 @@ def test_score_one_unit_in_many_chunks(n):
         _check_score(w)
 
 
+@pytest.mark.parametrize("window,layers,batch", [(16, 4, 97), (13, 5, 60), (32, 3, 90), (32, 4, 60), (64, 2, 70)])
+def test_score_more_workgroups_than_run_at_once(window, layers, batch):
+    # the second sweep takes units and chunks in the opposite order; 64 rows and fewer have workgroups of their own.  Some
+    # lengths take the order of ragged sequences (up to 64 of them)
+    w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=layers, batch=batch, n=333, hq=8, hkv=2, window=window)
+    units = [(l, b, g) for l in (0, layers - 1) for b in (0, 1, batch // 2, batch - 1) for g in (0, 1)]
+    _check_score(w, units=units)
+    lens = np.random.default_rng(batch).integers(0, 334, size=batch).astype(np.int32)
+    _check_score(w, seq_len=lens, units=units)
+
+
 # --------------------------------------------------------------------------
 # step 4
 # --------------------------------------------------------------------------
