@@ -494,7 +494,10 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
             }
         }
         if constexpr (COLSUM) {
-            colsum += __shfl_xor(colsum, 32);
+            {
+                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(colsum), __float_as_uint(colsum), false, false);
+                colsum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+            }
             if (hf == 0) s_part[s & 1][rg][32 * kt + c32] = colsum;
         }
     };
