@@ -43,13 +43,16 @@ namespace ta {
 namespace {
 
 constexpr int STAGE_KEYS = 64;
+constexpr int MAX_CHUNKS = 32;                   // of a unit
 constexpr int STAGE_UNITS = STAGE_KEYS * 16;     // 16-byte units per stage (256 B per key)
 // Stage buffers per workgroup; loads run that many minus one stages ahead.  (Eight buffers for
 // the wider workgroups, which have a compute unit to themselves, were measured: no gain.)
 // Three for units of at most 64 rows: 48 KB, so that three such workgroups share a compute unit.
 constexpr int ring_of(int rg) { return rg == 1 ? 3 : 4; }
-// the widest workgroup: 64 * MAX_RG rows at a time (more row groups leave too few registers per lane)
-constexpr int MAX_RG = 4;
+// Where the query rows of a workgroup pass through on their way to the registers: the last buffers of the ring, or, where
+// they would fill the whole of it, buffers of their own behind the stages that are requested with them.
+constexpr int q_stage(int rg) { return rg == 4 ? ring_of(rg) - 1 : ring_of(rg) - rg; }
+constexpr int lds_stages(int rg) { return q_stage(rg) + rg > ring_of(rg) ? q_stage(rg) + rg : ring_of(rg); }
 
 // Direct global->LDS load of 16 bytes per lane: lane i reads 16 bytes at base + off (base
 // wave-uniform, off per lane) and its data lands at lds_base + 16*i (lds_base wave-uniform,
@@ -62,6 +65,15 @@ __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, u
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                  :
                  : "s"(lds_base), "v"(off), "s"(base)
+                 : "memory", "m0");
+}
+
+// the same from an address of each lane's own
+__device__ __forceinline__ void load_to_lds_16(const uint4* from, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(lds_base), "v"(from)
                  : "memory", "m0");
 }
 
@@ -78,20 +90,21 @@ struct RiderArgs {
 };
 
 // RG row groups of RT 32-row MFMA tiles each per workgroup; 2 * RG wavefronts.
-// row_base: first of the 64 * RG rows this call works on (units with more rows take several calls)
+// row_base: first of the 64 * RG rows this call works on (units with more rows than the widest workgroup's 256 take several
+// calls; more row groups would leave too few registers per lane)
 template <int RG, int RT, bool COLSUM, bool PAGED>
 __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], int32_t row_base);
 
 // one tile per wavefront: four wavefronts per SIMD (at most 128 registers each)
-template <int RG, int RT, bool COLSUM, bool PAGED>
+template <int RG, int RT, bool COLSUM, bool PAGED, bool PASSES>
 __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_kernel(ScoreArgs a)
 {
-    __shared__ uint4 s_k[ring_of(RG)][STAGE_UNITS];        // 16 KB per stage
+    __shared__ uint4 s_k[lds_stages(RG)][STAGE_UNITS];        // 16 KB per stage
     // a workgroup holds 64 * RG rows at a time; a unit with more rows is done in passes over its chunk
     // (the keys of the later passes come from the L2; their column sums are added to the first pass's)
-    if constexpr (RG < MAX_RG) {
-        score_body<RG, RT, COLSUM, PAGED>(a, s_k, 0);      // these kernels only get units that fit one pass
+    if constexpr (!PASSES) {
+        score_body<RG, RT, COLSUM, PAGED>(a, s_k, 0);
     } else {
         for (int32_t row_base = 0; row_base < a.rows_pad; row_base += 64 * RG) {
             if (row_base > 0) __syncthreads();             // the previous pass is done with the LDS
@@ -100,12 +113,12 @@ score_kernel(ScoreArgs a)
     }
 }
 
-template <int RG, int RT, bool COLSUM>
+template <int RG, int RT, bool COLSUM, bool PASSES>
 __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_match_kernel(ScoreArgs a, RiderArgs r)
 {
-    __shared__ uint4 s_k[ring_of(RG)][STAGE_UNITS];
-    static_assert(sizeof(MatchLds) <= sizeof(uint4) * ring_of(RG) * STAGE_UNITS, "match tile must fit the stage ring");
+    __shared__ uint4 s_k[lds_stages(RG)][STAGE_UNITS];
+    static_assert(sizeof(MatchLds) <= sizeof(uint4) * lds_stages(RG) * STAGE_UNITS, "match tile must fit the stage ring");
     if (blockIdx.x >= r.score_blocks) {
         if (threadIdx.x >= MATCH_THREADS) return;          // a tile is the work of four wavefronts
         const uint32_t t = blockIdx.x - r.score_blocks;
@@ -113,7 +126,7 @@ score_match_kernel(ScoreArgs a, RiderArgs r)
                           (int)threadIdx.x, *reinterpret_cast<MatchLds*>(&s_k[0][0]));
         return;
     }
-    if constexpr (RG < MAX_RG) {
+    if constexpr (!PASSES) {
         score_body<RG, RT, COLSUM, false>(a, s_k, 0);
     } else {
         for (int32_t row_base = 0; row_base < a.rows_pad; row_base += 64 * RG) {
@@ -158,16 +171,17 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 
     const int32_t seq_in_xcd = (int32_t)(blockIdx.x >> 3);
     int32_t chunk;
-    int32_t place = place_of(blockIdx.x, a.nchunks, chunk);
+    int32_t place = place_of(blockIdx.x, a.nchunks, a.by_chunks, chunk);
     if (place >= a.units) return;
     if (COLSUM && a.backwards) {
         place = a.units - 1 - place;
         chunk = a.nchunks - 1 - chunk;
     }
     const int32_t unit = __builtin_amdgcn_readfirstlane(unit_at(place, a.seq_len, a.batch, a.hkv, a.units));
-    const int32_t g = unit % a.hkv;
-    const int32_t b = (unit / a.hkv) % a.batch;
-    const int32_t l = unit / (a.hkv * a.batch);
+    const int32_t pair = (int32_t)divide((uint32_t)unit, a.by_hkv);
+    const int32_t g = unit - pair * a.hkv;
+    const int32_t l = (int32_t)divide((uint32_t)pair, a.by_batch);
+    const int32_t b = pair - l * a.batch;
     const int32_t n = a.n, W = a.W;
     int32_t nb = a.seq_len ? __builtin_amdgcn_readfirstlane(a.seq_len[b]) : n;   // (in a scalar register: it is part of every stage's address)
     nb = nb < 0 ? 0 : (nb > n ? n : nb);
@@ -266,25 +280,33 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
             }
         }
     };
-    // ---- Q fragments of this wavefront's 64 rows (registers, whole chunk) -----------
-    const uint4* qlayer = a.Ql ? uniform_global_ptr(a.Ql[l]) : a.Q + l * a.q_sl;
-    bf16x8 qf[ROW_TILES][8];
+    // ---- Q and the first stages of K are requested together: one round trip to memory brings both.  Q passes through LDS in
+    // the layout of a K stage per 64 rows (whole rows of 256 bytes per 16 lanes; loaded straight into the registers, 32 rows
+    // of 32 bytes per instruction and the same rows by both key tiles' wavefronts, they took 2 us of the 7 of a launch of
+    // two-stage chunks).  Rows past the last one repeat it: their column sums' constant is inf, their statistics are not read.
+    // (Both sweeps, with the statistics of all chunks in one round trip and the scalar divisions, us: 8 units of 4096 keys
+    // 15.4 -> 11.9; 32 units of 333 keys, 256 rows 20.2 -> 13.5; 192 units of 8192 keys, 256 rows 270 -> 257.)
+    constexpr int QS = q_stage(RG), FIRST = QS < RING - 1 ? QS : RING - 1;     // stages of K that are requested with Q
+    constexpr int QPW = 64 * RG / 4 / WAVES;                                    // direct loads of Q per wavefront
+    const uint4* qunit = (a.Ql ? uniform_global_ptr(a.Ql[l]) : a.Q + l * a.q_sl) + b * a.q_sb + (int64_t)(g * a.G) * a.q_sh;
+    const auto head_of = [&](int32_t r) { return (int32_t)(((uint32_t)r * a.inv_W) >> 20); };
+#pragma unroll
+    for (int j = 0; j < QPW; ++j) {
+        const int row = (wave + WAVES * j) * 4 + (lane >> 4);
+        int32_t r = row_base + row;
+        r = r < a.rows ? r : a.rows - 1;
+        const int32_t h = head_of(r);
+        load_to_lds_16(qunit + h * a.q_sh + (r - h * W) * 16 + ((lane & 15) ^ (row & 15)), lds_wave + QS * (STAGE_UNITS * 16u) + WAVES * j * 1024u);
+    }
+    if constexpr (PAGED) asm volatile("" ::"v"(my_page) : "memory");
+#pragma unroll
+    for (int s = 0; s < FIRST; ++s)
+        if (s < nstages) stage_issue(s);
     int32_t my_lim[ROW_TILES];                             // sweep 1: last visible key of this lane's row
 #pragma unroll
     for (int t = 0; t < ROW_TILES; ++t) {
         const int32_t r = row_base + GROUP_ROWS * rg + 32 * t + c32;
-        int32_t lim = -1;
-        if (r < a.rows) {
-            const int32_t h = r / W, w = r - h * W;
-            const uint4* qrow = qlayer + b * a.q_sb + (int64_t)(g * a.G + h) * a.q_sh + (int64_t)w * 16;
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) qf[t][ks] = as_frag(qrow[2 * ks + hf]);
-            lim = a.causal ? nb - W + w : nb - 1;
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) qf[t][ks] = as_frag(make_uint4(0, 0, 0, 0));
-        }
-        my_lim[t] = lim;
+        my_lim[t] = r >= a.rows ? -1 : (a.causal ? nb - W + (r - head_of(r) * W) : nb - 1);
     }
     // ---- sweep 2: merge the chunk statistics of a row into its constant (before any direct
     // load is issued: these are ordinary loads, and waiting for them later would also wait for
@@ -297,7 +319,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         float c = INFINITY;
         int32_t lim = -1;
         if (r < a.rows) {
-            const int32_t h = r / W, w = r - h * W;
+            const int32_t h = head_of(r), w = r - h * W;
             lim = a.causal ? nb - W + w : nb - 1;
             if (a.lse) {
                 // the row's normaliser comes from the prefill attention kernel: c = lse * log2(e)
@@ -306,34 +328,33 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
             }
         }
         if (!a.lse) {                                      // uniform
-            // Two threads per row, each with half of the chunks, up to eight loads in flight: at most two round trips however
-            // many chunks there are (at most 32), so that few units can be cut into many.
-            float2* s_mz = reinterpret_cast<float2*>(&s_k[0][0]);          // (the stage ring is not in use yet)
+            // Two threads per row, each with half of the chunks, all loads in flight: one round trip however many chunks
+            // there are, so that few units can be cut into many.
+            static_assert(sizeof(s_part) >= sizeof(float2) * ROWS, "the second halves pass through the partial sums' memory");
+            float2* s_mz = reinterpret_cast<float2*>(&s_part[0][0][0]);
             const int32_t half = (a.nchunks + 1) >> 1, ch0 = part * half;
             const float2* st = reinterpret_cast<const float2*>(a.ws) + ((size_t)unit * a.nchunks * a.rows_pad + (r < a.rows_pad ? r : 0));
             float m = -INFINITY, Z = 0.0f;
-            const auto merge = [&](auto count_tag, int32_t first) {
+            const auto merge = [&](auto count_tag) {
                 constexpr int COUNT = decltype(count_tag)::value;
                 float2 v[COUNT];
 #pragma unroll
                 for (int j = 0; j < COUNT; ++j) {
-                    const int32_t ch = ch0 + first + j;
+                    const int32_t ch = ch0 + j;
                     v[j] = st[(size_t)(ch < a.nchunks ? ch : a.nchunks - 1) * a.rows_pad];
                 }
-                float mm = m;
 #pragma unroll
                 for (int j = 0; j < COUNT; ++j)
-                    if (first + j < half && ch0 + first + j < a.nchunks) mm = fmaxf(mm, v[j].x);
-                const float ref = mm > -INFINITY ? mm : 0.0f;
-                Z *= fast_exp2(m - ref);
+                    if (j < half && ch0 + j < a.nchunks) m = fmaxf(m, v[j].x);
+                const float ref = m > -INFINITY ? m : 0.0f;
 #pragma unroll
                 for (int j = 0; j < COUNT; ++j)
-                    if (first + j < half && ch0 + first + j < a.nchunks && v[j].y > 0.0f) Z += v[j].y * fast_exp2(v[j].x - ref);
-                m = mm;
+                    if (j < half && ch0 + j < a.nchunks && v[j].y > 0.0f) Z += v[j].y * fast_exp2(v[j].x - ref);
             };
-            if (half <= 2) merge(std::integral_constant<int, 2>{}, 0);
-            else
-                for (int32_t first = 0; first < half; first += 8) merge(std::integral_constant<int, 8>{}, first);
+            static_assert(MAX_CHUNKS <= 32, "cases below");
+            if (half <= 2) merge(std::integral_constant<int, 2>{});
+            else if (half <= 8) merge(std::integral_constant<int, 8>{});
+            else merge(std::integral_constant<int, 16>{});
             if (part == 1) s_mz[lr] = make_float2(m, Z);
             __syncthreads();
             if (part == 0) {
@@ -350,24 +371,20 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
             s_c[lr] = c;
             s_lim[lr] = lim;
         }
-        __syncthreads();                                   // the ring's memory is free again, the constants are in LDS
     }
 
-    // The compiler waits for ordinary loads with a count that knows nothing of the direct loads
-    // below: a wait placed after them would also wait for every stage in flight.  Using the
-    // fragments here puts that wait before the first direct load is issued.
-    if constexpr (PAGED) asm volatile("" ::"v"(my_page) : "memory");
+    // ---- Q and stage 0 are in (loads complete in issue order; with sweep 2, waiting for the statistics has waited for both)
+    {
+        const int later = nstages - 1;
+        wait_but(later < FIRST - 1 ? (later < 0 ? 0 : later) : FIRST - 1);
+    }
+    __syncthreads();
+    bf16x8 qf[ROW_TILES][8];
 #pragma unroll
     for (int t = 0; t < ROW_TILES; ++t)
-        asm volatile("" ::"v"(qf[t][0]), "v"(qf[t][1]), "v"(qf[t][2]), "v"(qf[t][3]), "v"(qf[t][4]), "v"(qf[t][5]),
-                     "v"(qf[t][6]), "v"(qf[t][7])
-                     : "memory");
-
-    // ---- first stages of K; the loop starts as soon as stage 0 is in ---------------------
 #pragma unroll
-    for (int s = 0; s < RING - 1; ++s)
-        if (s < nstages) stage_issue(s);
-    wait_but(nstages - 1 < RING - 2 ? nstages - 1 : RING - 2);          // stage 0 is in
+        for (int ks = 0; ks < 8; ++ks)
+            qf[t][ks] = as_frag(s_k[QS + rg][(32 * t + c32) * 16 + ((2 * ks + hf) ^ (c32 & 15))]);
 
     float cst[ROW_TILES][16];
     if constexpr (COLSUM) {
@@ -389,9 +406,16 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) kslot[ks] = krow * 16 + ((2 * ks + hf) ^ (krow & 15));
 
-    // Every wavefront has waited for its own part of stage 0 above; the only loads in flight
-    // from here on are the direct loads of later stages.
+    // every wavefront has its rows: their buffers take the stages that are still missing of the first RING - 1
+#pragma unroll
+    for (int t = 0; t < ROW_TILES; ++t)
+        asm volatile("" ::"v"(qf[t][0]), "v"(qf[t][1]), "v"(qf[t][2]), "v"(qf[t][3]), "v"(qf[t][4]), "v"(qf[t][5]),
+                     "v"(qf[t][6]), "v"(qf[t][7])
+                     : "memory");
     __syncthreads();
+#pragma unroll
+    for (int s = FIRST; s < RING - 1; ++s)
+        if (s < nstages) stage_issue(s);
 
     // ---- main loop, software pipelined over stages -------------------------------------
     // Iteration s issues the MFMAs of stage s while the vector ALUs reduce the
@@ -671,7 +695,7 @@ int compute_units()
     return cu;
 }
 
-template <int RG, int RT, bool COLSUM>
+template <int RG, int RT, bool COLSUM, bool PASSES>
 hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
 {
     if (rider && (a.table || RG == 1)) {
@@ -689,19 +713,19 @@ hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* r
             r.tab = *rider->tab;
             r.score_blocks = blocks;
             const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
-            hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, PASSES>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
             return hipGetLastError();
         }
     }
     if (a.table) {
-        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true>), dim3(blocks), dim3(128 * RG), 0, st, a);
+        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true, PASSES>), dim3(blocks), dim3(128 * RG), 0, st, a);
     } else {
-        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false>), dim3(blocks), dim3(128 * RG), 0, st, a);
+        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false, PASSES>), dim3(blocks), dim3(128 * RG), 0, st, a);
     }
     return hipGetLastError();
 }
 
-template <int RG, int RT>
+template <int RG, int RT, bool PASSES = false>
 hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, hipStream_t st)
 {
     // One launch per sweep over all units.  (Splitting the units into cache-sized groups
@@ -716,10 +740,10 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, hipStr
     constexpr int64_t RESIDENT = RG == 1 ? 3 : (RG == 2 ? 2 : 1);       // workgroups per compute unit, by their stage rings
     a.backwards = !a.lse && blocks > RESIDENT * compute_units();
     if (a.lse)                                             // the row normalisers are given: column sums alone
-        return launch_sweep<RG, RT, true>(a, blocks, rider, st);
-    const hipError_t e = launch_sweep<RG, RT, false>(a, blocks, rider, st);
+        return launch_sweep<RG, RT, true, PASSES>(a, blocks, rider, st);
+    const hipError_t e = launch_sweep<RG, RT, false, PASSES>(a, blocks, rider, st);
     if (e != hipSuccess) return e;
-    return launch_sweep<RG, RT, true>(a, blocks, nullptr, st);
+    return launch_sweep<RG, RT, true, PASSES>(a, blocks, nullptr, st);
 }
 
 }  // namespace
@@ -748,10 +772,10 @@ ScorePlan base_plan(const ta_layout& lay)
     p.units = (int64_t)lay.layers * lay.batch * lay.hkv;
     const int64_t want_blocks = 2 * (int64_t)compute_units();
     int64_t per_unit = (want_blocks + p.units - 1) / p.units;            // chunks per unit we would like
-    per_unit = per_unit < 1 ? 1 : (per_unit > 32 ? 32 : per_unit);
+    per_unit = per_unit < 1 ? 1 : (per_unit > MAX_CHUNKS ? MAX_CHUNKS : per_unit);
     int64_t ck = ((lay.n + per_unit - 1) / per_unit + STAGE_KEYS - 1) / STAGE_KEYS * STAGE_KEYS;
     if (ck < 512) ck = 512;
-    while (ck * 32 < lay.n) ck += STAGE_KEYS;
+    while (ck * MAX_CHUNKS < lay.n) ck += STAGE_KEYS;
     p.chunk_keys = (int32_t)ck;
     p.nchunks = (lay.n + p.chunk_keys - 1) / p.chunk_keys;
     return p;
@@ -771,7 +795,7 @@ ScorePlan make_plan(const ta_layout& lay, int64_t room)
     constexpr int64_t SETUP = 6, ALONE = 115;              // stages; per cent
     const int64_t cus = compute_units(), stages = (lay.n + STAGE_KEYS - 1) / STAGE_KEYS;
     int64_t best = -1;
-    for (int64_t c = 1; c <= 32 && (c == 1 || stages >= 2 * c); ++c) {
+    for (int64_t c = 1; c <= MAX_CHUNKS && (c == 1 || stages >= 2 * c); ++c) {
         const int64_t per_chunk = (stages + c - 1) / c, chunks = (stages + per_chunk - 1) / per_chunk;
         if (chunks > p.nchunks && stats_bytes(p, chunks) > room) break;
         const int64_t k = (p.units * chunks + cus - 1) / cus;
@@ -848,6 +872,10 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
     a.hkv = lay.hkv;
     a.G = lay.hq / lay.hkv;
     a.W = lay.window;
+    a.inv_W = (1u << 20) / (uint32_t)lay.window + 1;
+    a.by_chunks = divider((uint32_t)p.nchunks);
+    a.by_hkv = divider((uint32_t)lay.hkv);
+    a.by_batch = divider((uint32_t)lay.batch);
     a.n = lay.n;
     a.rows = p.rows;
     a.rows_pad = p.rows_pad;
@@ -862,8 +890,9 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
             if (p.rows <= 64 && (!rider || a.table || p.units * lay.n >= NARROW_KEYS)) return launch_rg<1, 2>(a, p.units, rider, st);
             return launch_rg<2, 2>(a, p.units, rider, st);
         case 256: return launch_rg<4, 2>(a, p.units, rider, st);
-        default: return launch_rg<4, 2>(a, p.units, rider, st);   // 512 rows: two passes of 256 (eight row groups
-                                                                  // at once leave 128 registers per lane: spills, 3x slower)
+        // 512 rows: two passes of 256 (eight row groups at once leave 128 registers per lane: spills, 3x slower), in kernels of
+        // their own: the pass loop costs the column sums' main loop the registers that keep its two pipes busy (1.5 %)
+        default: return launch_rg<4, 2, true>(a, p.units, rider, st);
     }
 }
 

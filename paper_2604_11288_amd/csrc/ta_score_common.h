@@ -1,6 +1,7 @@
 // Types and launch arguments of the score kernels.
 #pragma once
 #include "ta_internal.h"
+#include "ta_order.h"
 
 namespace ta {
 
@@ -25,6 +26,8 @@ struct ScoreArgs {
     int32_t batch, hkv, G, W, n;
     int32_t rows, rows_pad;            // M = G*W and M rounded up to 64*RG
     int32_t chunk_keys, nchunks;
+    uint32_t inv_W;                    // (row * inv_W) >> 20 = row / W for rows below 512
+    Divider by_chunks, by_hkv, by_batch;
     int32_t units;
     int32_t causal;
     int32_t backwards;                 // sweep 2 takes the units and chunks in the opposite order
