@@ -4,7 +4,7 @@
 #include <math.h>
 #include <string.h>
 
-#include "ta_internal.h"
+#include "ta_gather.h"
 
 // Scratch of ta_evict_static: per-chunk softmax row statistics of the score step.  Host code
 // never uses this name as an address (it is a host-side stand-in): the device address is looked
@@ -481,9 +481,12 @@ int32_t evict_pass(const int32_t* tok, const int32_t* seq_len,
         rc = hip_status(ta::launch_match(tok, seq_len, lay->batch, lay->n, tab, anchor_B, prm->allow, anchor, spons, vouch, st));
         if (rc != TA_OK) return rc;
     }
+    // where every unit has a retained set of its own, the workgroup that selects it may move its rows as well
+    const ta::CompactArgs job = ta::make_compact_args(Kin, Vin, idx, cnt, *lay, K, scored ? 0 : 1, Kout, Vout, pg, lptr, nullptr);
+    bool gathered = false;
     rc = hip_status(ta::launch_select(A, anchor, spons, vouch, seq_len, sel_layers, lay->batch, sel_hkv,
-                                      lay->n, K, *prm, idx, cnt, st, true));
-    if (rc != TA_OK) return rc;
+                                      lay->n, K, *prm, idx, cnt, st, true, scored ? &job : nullptr, &gathered));
+    if (rc != TA_OK || gathered) return rc;
     return hip_status(ta::launch_compact(Kin, Vin, idx, cnt, *lay, K, scored ? 0 : 1, Kout, Vout, pg, lptr, st));
 }
 

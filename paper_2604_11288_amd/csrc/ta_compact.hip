@@ -7,52 +7,16 @@
 // workgroup takes ROWS_PER_BLOCK consecutive output rows of one unit and issues
 // all of its loads (K and V) before the first store to keep many requests in
 // flight per lane.
-#include "ta_internal.h"
+#include "ta_gather.h"
 
 namespace ta {
 
 namespace {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int COMPACT_THREADS = 256;
 constexpr int ROWS_PER_ITER = COMPACT_THREADS / 16;     // 16 rows per pass over the block
 constexpr int COMPACT_ITERS = 4;
 constexpr int ROWS_PER_BLOCK = ROWS_PER_ITER * COMPACT_ITERS;
-
-struct CompactArgs {
-    const uint4* Kin;
-    const uint4* Vin;
-    const int32_t* idx;
-    const int32_t* cnt;
-    uint4* Kout;
-    uint4* Vout;
-    int64_t s_layer, s_batch, s_head, s_pos;   // input strides in 16-byte units
-    int32_t batch, hkv, n, K;
-    int32_t idx_shared;
-    int32_t blocks_per_unit;
-    // paged input: rows are addressed through the block table (s_batch unused, s_page per page)
-    const int32_t* table;
-    int64_t s_page;
-    int32_t page_size, max_pages, num_pages;
-    // one tensor per layer: DEVICE tables; layer l reads Kin_l[l], Vin_l[l] and writes Kout_l[l], Vout_l[l]
-    const uint4* const* Kin_l;
-    const uint4* const* Vin_l;
-    uint4* const* Kout_l;
-    uint4* const* Vout_l;
-    // paged output: row r of a unit goes to slot r of its sequence's pages in the destination pools
-    const int32_t* d_table;
-    int64_t d_layer, d_page, d_pos, d_head;    // destination strides in 16-byte units
-    int32_t d_page_size, d_max_pages, d_num_pages;
-};
-
-// marks a pointer read from a device table as a global address (else it is accessed with flat instructions)
-template <typename T>
-__device__ __forceinline__ T* global_ptr(T* p)
-{
-    typedef __attribute__((address_space(1))) T* gp;
-    return (T*)(gp)(uintptr_t)p;
-}
 
 template <bool PAGED, bool LAYERED, bool DST_PAGED = false>
 __global__ void __launch_bounds__(COMPACT_THREADS)
@@ -67,7 +31,6 @@ compact_kernel(CompactArgs a)
     int32_t cnt = a.cnt[sel];
     cnt = cnt > a.K ? a.K : cnt;
     const int32_t* idx = a.idx + (size_t)sel * (size_t)a.K;
-    const int64_t in_base = (LAYERED ? 0 : l * a.s_layer) + (PAGED ? 0 : b * a.s_batch) + h * a.s_head;
     const int64_t out_base = (int64_t)(LAYERED ? unit - l * a.hkv * a.batch : unit) * a.K * 16;
 
     const int lane16 = threadIdx.x & 15;
@@ -75,17 +38,12 @@ compact_kernel(CompactArgs a)
     if (blk * ROWS_PER_BLOCK >= cnt) return;              // whole block past the retained rows
     // named registers (not an indexed array) so the loads stay in VGPRs
     const int32_t row0 = blk * ROWS_PER_BLOCK + rsub;
+    const RowSource<PAGED, LAYERED> rows(a, l, b, h, lane16);
     auto src = [&](int32_t r) -> int64_t {
         r = r < cnt ? r : cnt - 1;                          // tail lanes re-read the last row, store nothing
         int32_t p = idx[r];
         p = p < 0 ? 0 : (p >= a.n ? a.n - 1 : p);
-        if (PAGED) {
-            const int32_t slot = p / a.page_size;
-            int32_t page = a.table[(size_t)b * a.max_pages + slot];
-            page = page < 0 ? 0 : (page >= a.num_pages ? a.num_pages - 1 : page);
-            return in_base + (int64_t)page * a.s_page + (int64_t)(p - slot * a.page_size) * a.s_pos + lane16;
-        }
-        return in_base + (int64_t)p * a.s_pos + lane16;
+        return rows(p);
     };
     static_assert(COMPACT_ITERS == 4, "loads below are written out four times");
     const int64_t o0 = src(row0), o1 = src(row0 + ROWS_PER_ITER);
@@ -166,10 +124,9 @@ hipError_t launch_layer_table(const LayerPtrs& host_table, LayerPtrs* dev_table,
     return hipGetLastError();
 }
 
-hipError_t launch_compact(const void* Kin, const void* Vin, const int32_t* idx, const int32_t* cnt,
-                          const ta_layout& lay, int32_t K, int32_t idx_shared,
-                          void* Kout, void* Vout, const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st,
-                          const ta_paged_kv* dst_pg)
+CompactArgs make_compact_args(const void* Kin, const void* Vin, const int32_t* idx, const int32_t* cnt, const ta_layout& lay, int32_t K,
+                              int32_t idx_shared, void* Kout, void* Vout, const ta_paged_kv* pg, const LayerPtrs* lp,
+                              const ta_paged_kv* dst_pg)
 {
     CompactArgs a;
     a.d_table = dst_pg ? dst_pg->block_table : nullptr;
@@ -215,6 +172,15 @@ hipError_t launch_compact(const void* Kin, const void* Vin, const int32_t* idx, 
     a.K = K;
     a.idx_shared = idx_shared;
     a.blocks_per_unit = (K + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
+    return a;
+}
+
+hipError_t launch_compact(const void* Kin, const void* Vin, const int32_t* idx, const int32_t* cnt,
+                          const ta_layout& lay, int32_t K, int32_t idx_shared,
+                          void* Kout, void* Vout, const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st,
+                          const ta_paged_kv* dst_pg)
+{
+    const CompactArgs a = make_compact_args(Kin, Vin, idx, cnt, lay, K, idx_shared, Kout, Vout, pg, lp, dst_pg);
     int64_t units = (int64_t)lay.layers * lay.batch * lay.hkv;
     int64_t blocks = units * a.blocks_per_unit;
     const dim3 grid((unsigned)blocks), block(COMPACT_THREADS);

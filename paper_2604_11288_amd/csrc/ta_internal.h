@@ -114,10 +114,13 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
 
 // ---- select -----------------------------------------------------------------
 // `own_vouchers`: spons and vouch were written by launch_match or launch_expand (vouch is 0 wherever spons is).
+// `job`: the gather that follows, of the same units; *gathered says whether the selection has done it as well.
+struct CompactArgs;
 hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* spons,
                          const float* vouch, const int32_t* seq_len,
                          int32_t layers, int32_t batch, int32_t hkv, int32_t n, int32_t K,
-                         const ta_params& prm, int32_t* idx, int32_t* cnt, hipStream_t st, bool own_vouchers = false);
+                         const ta_params& prm, int32_t* idx, int32_t* cnt, hipStream_t st, bool own_vouchers = false,
+                         const CompactArgs* job = nullptr, bool* gathered = nullptr);
 
 // ---- compact ----------------------------------------------------------------
 // `lp` != null: layer l reads lp->K[l], lp->V[l] and writes lp->Kout[l], lp->Vout[l].

@@ -23,7 +23,9 @@
 //                takes the k_protected best sponsored tokens, everything else that is not
 //                mandatory competes for the main pool by (u, position) alone - two threshold
 //                searches instead of one
-#include "ta_internal.h"
+#include <type_traits>
+
+#include "ta_gather.h"
 #include "ta_order.h"
 #include "ta_wave.h"
 
@@ -517,8 +519,17 @@ constexpr int SR_MAX_N = SR_MAX_ROUNDS * SR_THREADS * 4;
 constexpr int SR_BINS = 2048;
 constexpr int SR_CAND = 256;                                 // members of a bin that are ranked one against the other
 
+// Rows moved by the workgroup that selects them: one launch fewer, some 2 us, but a workgroup moves no more than one compute
+// unit can.  So budgets up to 256 (a layer's 8 units of 4096 positions, whole pass in us, launch of its own / here: 16 rows 23.1 /
+// 20.6, 128 rows 25.2 / 22.9, 256 rows 24.7 / 23.6, but 512 rows 25.0 / 27.5), and any where the units are about as many as
+// the compute units (256 units of 4096 positions, 1024 rows 146.2 / 144.4; 192 of 8192 194.8 / 192.7; 128 of 4096 82.3 / 88.2).
+// With more units than that the launch of its own spreads the rows better (512 of up to 3001 positions, 64 rows 133.4 / 136.0).
+constexpr int SR_GATHER_MAX_K = 2048;                      // the list passes through the histogram's memory
+constexpr int SR_GATHER_FEW_K = 256;
+constexpr int SR_GATHER_MIN_UNITS = 192, SR_GATHER_MAX_UNITS = 256;
+
 struct SelectRegLds {
-    uint32_t hist[32 * 65];                                  // bin b at (b % 32) * 65 + b / 32: 64 lanes read a row of it at once
+    uint32_t hist[32 * 65];                                  // bin b at (b % 32) * 65 + b / 32: 64 lanes read a row of it at once; then the list to gather
     uint32_t part[5][SR_WAVES];                              // per wavefront: sponsored count, key ranges of both classes
     uint32_t edge[2][SR_WAVES];                              // per wavefront: smallest retained, largest evicted key
     uint32_t totals[SR_MAX_ROUNDS * SR_WAVES];               // retained positions per round and wavefront
@@ -557,9 +568,11 @@ __device__ __forceinline__ float div_by(float a, float n, float y)
     return fmaf(fmaf(-q, n, a), y, q);
 }
 
-template <int ROUNDS, bool CAPPED>
+static_assert(sizeof(SelectRegLds::hist) >= sizeof(uint32_t) * SR_GATHER_MAX_K, "the list to gather");
+
+template <int ROUNDS, bool CAPPED, int GATHER>
 __global__ void __launch_bounds__(SR_THREADS)
-select_reg_kernel(SelectArgs a)
+select_reg_kernel(SelectArgs a, std::conditional_t<GATHER != GATHER_NONE, CompactArgs, int> g)
 {
     __shared__ __align__(16) SelectRegLds L;
     const int tid = threadIdx.x;
@@ -582,13 +595,20 @@ select_reg_kernel(SelectArgs a)
     int32_t* idx = a.idx + (size_t)unit * (size_t)a.K;
 
     if (nb <= K) {                                           // nothing to evict
-        for (int32_t p = tid; p < nb; p += SR_THREADS) idx[p] = p;
+        for (int32_t p = tid; p < nb; p += SR_THREADS) {
+            idx[p] = p;
+            if constexpr (GATHER != GATHER_NONE) L.hist[p] = (uint32_t)p;
+        }
         if (tid == 0) {
             a.cnt[unit] = nb;
             if (a.margin) {
                 a.margin[2 * (size_t)unit] = INFINITY;
                 a.margin[2 * (size_t)unit + 1] = -INFINITY;
             }
+        }
+        if constexpr (GATHER != GATHER_NONE) {
+            __syncthreads();
+            gather_rows<SR_THREADS, GATHER>(g, unit, nb, L.hist, tid);
         }
         return;
     }
@@ -1012,7 +1032,10 @@ select_reg_kernel(SelectArgs a)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             if (bits & (1u << c)) {
-                if (slot < K) idx[slot] = 4 * (r * SR_THREADS + tid) + c;
+                if (slot < K) {
+                    idx[slot] = 4 * (r * SR_THREADS + tid) + c;
+                    if constexpr (GATHER != GATHER_NONE) L.hist[slot] = (uint32_t)(4 * (r * SR_THREADS + tid) + c);
+                }
                 ++slot;
             }
         }
@@ -1028,6 +1051,12 @@ select_reg_kernel(SelectArgs a)
             a.margin[2 * (size_t)unit] = margin_value(kept_min);
             a.margin[2 * (size_t)unit + 1] = margin_value(gone_max);
         }
+    }
+    if constexpr (GATHER != GATHER_NONE) {
+        // the positions lie in the histogram's memory, which the search has left behind
+        const int32_t total = (int32_t)__builtin_amdgcn_readlane((int)after, 63);
+        __syncthreads();
+        gather_rows<SR_THREADS, GATHER>(g, unit, total < K ? total : K, L.hist, tid);
     }
 }
 
@@ -1581,8 +1610,10 @@ hipError_t select_setup()
 hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* spons,
                          const float* vouch, const int32_t* seq_len,
                          int32_t layers, int32_t batch, int32_t hkv, int32_t n, int32_t K,
-                         const ta_params& prm, int32_t* idx, int32_t* cnt, hipStream_t st, bool own_vouchers)
+                         const ta_params& prm, int32_t* idx, int32_t* cnt, hipStream_t st, bool own_vouchers, const CompactArgs* job,
+                         bool* gathered)
 {
+    if (gathered) *gathered = false;
     SelectArgs a;
     a.plain_vouch = own_vouchers ? 1 : 0;
     a.A = (prm.alpha != 0.0f) ? A : nullptr;
@@ -1632,11 +1663,22 @@ hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* s
         }
     }
     if (n <= SR_MAX_N) {
-        auto kernel = capped ? (n <= 4 * SR_THREADS ? select_reg_kernel<1, true> : n <= 8 * SR_THREADS ? select_reg_kernel<2, true>
-                                : n <= 16 * SR_THREADS ? select_reg_kernel<4, true> : select_reg_kernel<8, true>)
-                             : (n <= 4 * SR_THREADS ? select_reg_kernel<1, false> : n <= 8 * SR_THREADS ? select_reg_kernel<2, false>
-                                : n <= 16 * SR_THREADS ? select_reg_kernel<4, false> : select_reg_kernel<8, false>);
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(SR_THREADS), 0, st, a);
+        const auto run = [&](auto capped_tag, auto kind_tag, auto g) {
+            constexpr bool CAPPED = decltype(capped_tag)::value;
+            constexpr int KIND = decltype(kind_tag)::value;
+            auto kernel = n <= 4 * SR_THREADS ? select_reg_kernel<1, CAPPED, KIND> : n <= 8 * SR_THREADS ? select_reg_kernel<2, CAPPED, KIND>
+                          : n <= 16 * SR_THREADS ? select_reg_kernel<4, CAPPED, KIND> : select_reg_kernel<8, CAPPED, KIND>;
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(SR_THREADS), 0, st, a, g);
+        };
+        const std::false_type plain{};
+        const bool fits = job && !capped && !(job->table && job->Kin_l) && units <= SR_GATHER_MAX_UNITS && K <= (units >= SR_GATHER_MIN_UNITS ? SR_GATHER_MAX_K : SR_GATHER_FEW_K);
+        if (fits) {
+            *gathered = true;
+            if (job->table) run(plain, std::integral_constant<int, GATHER_PAGED>{}, *job);
+            else if (job->Kin_l) run(plain, std::integral_constant<int, GATHER_LAYERED>{}, *job);
+            else run(plain, std::integral_constant<int, GATHER_DENSE>{}, *job);
+        } else if (capped) run(std::true_type{}, std::integral_constant<int, GATHER_NONE>{}, 0);
+        else run(plain, std::integral_constant<int, GATHER_NONE>{}, 0);
     } else {
         if (capped) hipLaunchKernelGGL(select_kernel<true>, dim3(blocks), dim3(SEL_THREADS), 0, st, a);
         else hipLaunchKernelGGL(select_kernel<false>, dim3(blocks), dim3(SEL_THREADS), 0, st, a);

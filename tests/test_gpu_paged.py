@@ -135,3 +135,34 @@ def test_whole_pass_over_a_paged_cache_equals_the_dense_pass(with_lse, alpha):
     if alpha != 0.0:
         assert torch.equal(dense.A, pg.A)
     assert int(pg.cnt.min()) > 0 and pg.Kout.abs().sum() > 0
+
+
+@pytest.mark.parametrize("form", ["dense", "paged", "layers"])
+@pytest.mark.parametrize("layers,n,K,lens", [
+    (1, 700, 1, None), (1, 700, 256, (700, 0, 255, 256)), (1, 700, 257, (700, 300, 257, 258)), (12, 300, 256, None), (47, 300, 257, (300, 40, 1, 299)),
+    (48, 300, 257, (300, 40, 1, 299)), (64, 300, 200, (300, 201, 200, 199)), (65, 300, 200, None), (48, 4500, 2048, None), (48, 4500, 2049, None),
+])
+def test_rows_moved_by_the_selecting_workgroup(form, layers, n, K, lens):
+    # budgets and unit counts on both sides of the lines up to which the selection moves the rows itself; 4 units per layer
+    batch, hkv = (4, 1) if lens else (1, 4)
+    w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=layers, batch=batch, n=n, hq=2 * hkv, hkv=hkv, window=4)
+    td = wl.make_tokens(w)
+    Q, Kc, Vc = wl.make_qkv(w, device=DEV)
+    seq = None if lens is None else torch.tensor(lens, dtype=torch.int32, device=DEV)
+    prm = ta.Params(n_sink=1 if K > 1 else 0, n_recent=1 if K > 2 else 0)
+    tok = torch.from_numpy(td.tok).to(DEV)
+    if form == "paged":
+        Kp, Vp, table, num_pages, strides = wl.make_paged(Kc, Vc, 64)
+        paged = ta.PagedKV(Kp, Vp, table, 64, num_pages, strides, layers, batch, hkv, n)
+        plan = ta.EvictPlan(tok, td.tab_ids, td.tab_len, Q, None, None, K, prm, seq_len=seq, paged=paged)
+    elif form == "layers":
+        plan = ta.LayerEvictPlan(tok, td.tab_ids, td.tab_len, list(Q), list(Kc), list(Vc), K, prm, seq_len=seq)
+    else:
+        plan = ta.EvictPlan(tok, td.tab_ids, td.tab_len, Q, Kc, Vc, K, prm, seq_len=seq)
+    plan.run()
+    idx, cnt = ta.ta_select(plan.A, plan.anchor, plan.spons, plan.vouch, K, prm, layers, hkv, seq_len=seq)
+    Ko, Vo = ta.ta_compact(Kc, Vc, idx, cnt, K)
+    live = torch.arange(K, device=DEV) < cnt[..., None]
+    assert torch.equal(plan.cnt, cnt) and torch.equal(plan.idx[live], idx[live])
+    got = [torch.stack(list(t)) if form == "layers" else t for t in (plan.Kout, plan.Vout)]
+    assert torch.equal(got[0][live], Ko[live]) and torch.equal(got[1][live], Vo[live])
