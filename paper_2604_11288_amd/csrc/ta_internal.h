@@ -108,9 +108,10 @@ int64_t score_grid_blocks(const ta_layout& lay);
 // column-sum sweep runs and ws is not used.
 // `pg` != null: K is a paged pool addressed through pg->block_table (lay.kv_stride unused).
 // `lp` != null: Q and K of layer l start at lp->Q[l], lp->K[l] (Q, K and the layer strides unused).
+// `gathered`: key rows per unit that the pass will read again right after.
 hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, const int32_t* seq_len,
                         int causal, float* A, float* ws, size_t ws_bytes, const float* lse, const MatchRider* rider,
-                        const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st);
+                        const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st, int32_t gathered = 0);
 
 // ---- select -----------------------------------------------------------------
 // `own_vouchers`: spons and vouch were written by launch_match or launch_expand (vouch is 0 wherever spons is).

@@ -60,12 +60,20 @@ constexpr int lds_stages(int rg) { return q_stage(rg) + rg > ring_of(rg) ? q_sta
 // every later LDS read wait for ALL outstanding direct loads, which would serialise the stage
 // pipeline; the waits for these loads are explicit below.  Extra outstanding loads only make
 // the compiler's own vmcnt waits more conservative.
+// STREAM: with the non-temporal hint, for what will not be read again soon.
+template <bool STREAM>
 __device__ __forceinline__ void load_to_lds_16(const void* base, uint32_t off, uint32_t lds_base)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_base), "v"(off), "s"(base)
-                 : "memory", "m0");
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(lds_base), "v"(off), "s"(base)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(lds_base), "v"(off), "s"(base)
+                     : "memory", "m0");
 }
 
 // the same from an address of each lane's own
@@ -92,11 +100,11 @@ struct RiderArgs {
 // RG row groups of RT 32-row MFMA tiles each per workgroup; 2 * RG wavefronts.
 // row_base: first of the 64 * RG rows this call works on (units with more rows than the widest workgroup's 256 take several
 // calls; more row groups would leave too few registers per lane)
-template <int RG, int RT, bool COLSUM, bool PAGED>
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM>
 __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], int32_t row_base);
 
 // one tile per wavefront: four wavefronts per SIMD (at most 128 registers each)
-template <int RG, int RT, bool COLSUM, bool PAGED, bool PASSES>
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool PASSES>
 __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_kernel(ScoreArgs a)
 {
@@ -104,16 +112,16 @@ score_kernel(ScoreArgs a)
     // a workgroup holds 64 * RG rows at a time; a unit with more rows is done in passes over its chunk
     // (the keys of the later passes come from the L2; their column sums are added to the first pass's)
     if constexpr (!PASSES) {
-        score_body<RG, RT, COLSUM, PAGED>(a, s_k, 0);
+        score_body<RG, RT, COLSUM, PAGED, STREAM>(a, s_k, 0);
     } else {
         for (int32_t row_base = 0; row_base < a.rows_pad; row_base += 64 * RG) {
             if (row_base > 0) __syncthreads();             // the previous pass is done with the LDS
-            score_body<RG, RT, COLSUM, PAGED>(a, s_k, row_base);
+            score_body<RG, RT, COLSUM, PAGED, STREAM>(a, s_k, row_base);
         }
     }
 }
 
-template <int RG, int RT, bool COLSUM, bool PASSES>
+template <int RG, int RT, bool COLSUM, bool STREAM, bool PASSES>
 __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_match_kernel(ScoreArgs a, RiderArgs r)
 {
@@ -127,16 +135,16 @@ score_match_kernel(ScoreArgs a, RiderArgs r)
         return;
     }
     if constexpr (!PASSES) {
-        score_body<RG, RT, COLSUM, false>(a, s_k, 0);
+        score_body<RG, RT, COLSUM, false, STREAM>(a, s_k, 0);
     } else {
         for (int32_t row_base = 0; row_base < a.rows_pad; row_base += 64 * RG) {
             if (row_base > 0) __syncthreads();
-            score_body<RG, RT, COLSUM, false>(a, s_k, row_base);
+            score_body<RG, RT, COLSUM, false, STREAM>(a, s_k, row_base);
         }
     }
 }
 
-template <int RG, int RT, bool COLSUM, bool PAGED>
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM>
 __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], const int32_t row_base)
 {
     constexpr int ROW_TILES = RT;
@@ -262,13 +270,19 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         const int row = (wave + WAVES * j) * 4 + (lane >> 4);
         lane_off[j] = (uint32_t)(row * a.k_sp + ((lane & 15) ^ (row & 15))) * 16u;
     }
+    // STREAM: with the streaming hint; in the first sweep up to this stage only, those from it on are for the last-level cache
+    const int keep_from = STREAM && !COLSUM && place < a.keep_place ? (int)(((uint64_t)nstages * (uint64_t)a.keep_stage) >> 10) : 0;
     auto stage_issue = [&](int s) {
         const int32_t key0 = key_lo + stage_pos(s) * STAGE_KEYS;
         const uint4* sbase = stage_base(key0);
         const uint32_t dst = lds_wave + (uint32_t)(s % RING) * (STAGE_UNITS * 16u);
-        if (key0 + STAGE_KEYS <= n) {
+        const bool whole = key0 + STAGE_KEYS <= n;
+        if (whole && (!STREAM || (!COLSUM && s >= keep_from))) {
 #pragma unroll
-            for (int j = 0; j < LPS; ++j) load_to_lds_16(sbase, lane_off[j], dst + WAVES * j * 1024u);
+            for (int j = 0; j < LPS; ++j) load_to_lds_16<false>(sbase, lane_off[j], dst + WAVES * j * 1024u);
+        } else if (whole) {
+#pragma unroll
+            for (int j = 0; j < LPS; ++j) load_to_lds_16<true>(sbase, lane_off[j], dst + WAVES * j * 1024u);
         } else {
 #pragma unroll
             for (int j = 0; j < LPS; ++j) {
@@ -276,7 +290,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                 const int32_t last = n - 1 - key0;         // stay inside the tensor; masked later
                 const int32_t rclamp = row > last ? last : row;
                 const uint32_t off = (uint32_t)(rclamp * a.k_sp + ((lane & 15) ^ (row & 15))) * 16u;
-                load_to_lds_16(sbase, off, dst + WAVES * j * 1024u);
+                load_to_lds_16<false>(sbase, off, dst + WAVES * j * 1024u);
             }
         }
     };
@@ -695,7 +709,7 @@ int compute_units()
     return cu;
 }
 
-template <int RG, int RT, bool COLSUM, bool PASSES>
+template <int RG, int RT, bool COLSUM, bool STREAM, bool PASSES>
 hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
 {
     if (rider && (a.table || RG == 1)) {
@@ -713,20 +727,20 @@ hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* r
             r.tab = *rider->tab;
             r.score_blocks = blocks;
             const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
-            hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, PASSES>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, STREAM, PASSES>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
             return hipGetLastError();
         }
     }
     if (a.table) {
-        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true, PASSES>), dim3(blocks), dim3(128 * RG), 0, st, a);
+        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true, STREAM, PASSES>), dim3(blocks), dim3(128 * RG), 0, st, a);
     } else {
-        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false, PASSES>), dim3(blocks), dim3(128 * RG), 0, st, a);
+        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false, STREAM, PASSES>), dim3(blocks), dim3(128 * RG), 0, st, a);
     }
     return hipGetLastError();
 }
 
 template <int RG, int RT, bool PASSES = false>
-hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, hipStream_t st)
+hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_t gathered, hipStream_t st)
 {
     // One launch per sweep over all units.  (Splitting the units into cache-sized groups
     // so that sweep 2 re-reads its keys from the last-level cache was measured slower.)
@@ -738,12 +752,34 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, hipStr
     // units of 8192 keys 283 -> 271.)  Where all run at once the stages of each do that already, and the ragged ones should
     // keep the longest first (512 of 1500..3001: 126 -> 129).
     constexpr int64_t RESIDENT = RG == 1 ? 3 : (RG == 2 ? 2 : 1);       // workgroups per compute unit, by their stage rings
-    a.backwards = !a.lse && blocks > RESIDENT * compute_units();
-    if (a.lse)                                             // the row normalisers are given: column sums alone
-        return launch_sweep<RG, RT, true, PASSES>(a, blocks, rider, st);
-    const hipError_t e = launch_sweep<RG, RT, false, PASSES>(a, blocks, rider, st);
+    const bool rounds = blocks > RESIDENT * compute_units();
+    a.backwards = !a.lse && rounds;
+    // Keys that will not be read again are loaded with the streaming hint, which leaves less to evict: those of the only or the
+    // second sweep, and in the first all but the last LLC_BYTES, which the second will begin with - of the last units or, where all
+    // run at once, of the last stages of each.  (Two sweeps, 128 rows, us: 256 units of 16 384 keys 396 -> 379, ragged 2048 of
+    // 2048..16384 1815 -> 1739, ragged 1024 of 1500..3001 238 -> 228; one sweep: 256 units of 4096 keys 59 -> 52, of 16 384
+    // 208 -> 195.  Streaming both sweeps of 256 units of 4096 keys: 5 % slower.)  Not below SMALL_BYTES, where the keys may
+    // be in the caches (64 units of 4096 keys 31 -> 33), and not the first sweep of 256 rows, which is bound by arithmetic
+    // and loses more to the test than it gains; passes over a chunk's rows read its keys several times.  Where an eighth of the
+    // keys or more is gathered next and the cache holds a good part of them, the second sweep leaves them there (evict pass
+    // over 256 units of 4096 keys, 1024 rows 152 -> 147).
+    constexpr int64_t LLC_BYTES = int64_t(256) << 20, SMALL_BYTES = int64_t(128) << 20;
+    const int64_t bytes = units * a.n * 256;
+    const bool stream = !PASSES && bytes > SMALL_BYTES && !(gathered >= a.n / 8 && bytes <= 2 * LLC_BYTES);
+    const auto column_sums = [&](const MatchRider* with) {
+        if (stream) return launch_sweep<RG, RT, true, !PASSES, PASSES>(a, blocks, with, st);
+        return launch_sweep<RG, RT, true, false, PASSES>(a, blocks, with, st);
+    };
+    if (a.lse) return column_sums(rider);                  // the row normalisers are given: column sums alone
+    a.keep_place = 0x7FFFFFFF;
+    a.keep_stage = 1024;
+    if (rounds) a.keep_place = (int32_t)(units - units * LLC_BYTES / bytes);
+    else a.keep_stage = (int32_t)(1024 - 1024 * LLC_BYTES / bytes);
+    constexpr bool FIRST = RG < 4;
+    const hipError_t e = FIRST && bytes > LLC_BYTES ? launch_sweep<RG, RT, false, FIRST, PASSES>(a, blocks, rider, st)
+                                                    : launch_sweep<RG, RT, false, false, PASSES>(a, blocks, rider, st);
     if (e != hipSuccess) return e;
-    return launch_sweep<RG, RT, true, PASSES>(a, blocks, nullptr, st);
+    return column_sums(nullptr);
 }
 
 }  // namespace
@@ -832,7 +868,7 @@ constexpr int64_t NARROW_KEYS = int64_t(1) << 20;
 
 hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, const int32_t* seq_len,
                         int causal, float* A, float* ws, size_t ws_bytes, const float* lse, const MatchRider* rider,
-                        const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st)
+                        const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st, int32_t gathered)
 {
     const ScorePlan p = make_plan(lay, lse ? INT64_MAX : (int64_t)ws_bytes);
     ScoreArgs a;
@@ -887,12 +923,12 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
         // two 32-row tiles per wavefront (one tile per wavefront with twice the wavefronts - four
         // per SIMD instead of two - was measured: same time at 128 rows, 5 % slower at 256)
         case 128:
-            if (p.rows <= 64 && (!rider || a.table || p.units * lay.n >= NARROW_KEYS)) return launch_rg<1, 2>(a, p.units, rider, st);
-            return launch_rg<2, 2>(a, p.units, rider, st);
-        case 256: return launch_rg<4, 2>(a, p.units, rider, st);
+            if (p.rows <= 64 && (!rider || a.table || p.units * lay.n >= NARROW_KEYS)) return launch_rg<1, 2>(a, p.units, rider, gathered, st);
+            return launch_rg<2, 2>(a, p.units, rider, gathered, st);
+        case 256: return launch_rg<4, 2>(a, p.units, rider, gathered, st);
         // 512 rows: two passes of 256 (eight row groups at once leave 128 registers per lane: spills, 3x slower), in kernels of
         // their own: the pass loop costs the column sums' main loop the registers that keep its two pipes busy (1.5 %)
-        default: return launch_rg<4, 2, true>(a, p.units, rider, st);
+        default: return launch_rg<4, 2, true>(a, p.units, rider, gathered, st);
     }
 }
 
