@@ -293,8 +293,6 @@ __device__ __forceinline__ uint32_t ordered_bits(float u)
     return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
 }
 
-constexpr int SLOTS_PER_LANE = 5;                          // budgets up to 5 * 64 - 1 keep a lane's slots in registers
-
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -312,17 +310,17 @@ __device__ __forceinline__ s16x4 hi_half(const uint4& v)
     return c.s;
 }
 
-// One wavefront per unit, no workgroup barriers.  SMALL: at most SLOTS_PER_LANE * 64 slots, so a
+// One wavefront per unit, no workgroup barriers.  SMALL: at most SPL * 64 slots, so a
 // lane's slots (position, voucher, flags, accumulated attention) stay in its registers from the
 // first round trip to the ranking and nothing loops over slots.
 // DT_RING: 16-row key tiles in flight per wavefront.
-// WAVES > 1 (few units with many slots: one wavefront per unit would leave most of the chip idle, stream its
-// keys one tile after the other and loop over its slots): WAVES wavefronts share a unit.  Each keeps its
-// SLOTS_PER_LANE * 64 slots in registers like the SMALL form and streams every WAVES-th key tile; the slot
+// WAVES > 1 (one wavefront would stream a unit's keys one tile after the other and loop over its slots):
+// WAVES wavefronts share a unit.  Each keeps its
+// SPL * 64 slots in registers like the SMALL form and streams every WAVES-th key tile; the slot
 // table, the logits and three small exchanges go through LDS (three workgroup barriers).  Every logit, every
 // softmax statistic (each wavefront reduces all of them, in the single wavefront's order) and every slot's
 // key is computed by the same instructions as in the single-wavefront form: the two give the same bits.
-template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES>
+template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES, int SPL>
 __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& pg)
 {
     extern __shared__ float s_dyn[];
@@ -345,7 +343,6 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     float* A = st.A + (size_t)unit * slots;
     uint4* Kc = reinterpret_cast<uint4*>(st.Kc) + (PAGED ? l * pg.s_layer + g * pg.s_head : (int64_t)unit * slots * 16);
     uint4* Vc = reinterpret_cast<uint4*>(st.Vc) + (PAGED ? l * pg.s_layer + g * pg.s_head : (int64_t)unit * slots * 16);
-    constexpr int SPL = SLOTS_PER_LANE;                            // slots per lane that one round trip covers
     const int sbase = wave * (SPL * 64);                           // first slot of this wavefront's share
 
     // Everything that does not depend on loaded data is requested first, in the order it is needed
@@ -740,55 +737,58 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     if (wave == 0 && lane == 0 && a.evicted) a.evicted[unit] = evict_pos;
 }
 
-// Dense slots: three tiles in flight at four wavefronts per SIMD (124 registers).  Paged slots need
-// more registers for their addresses: four tiles in flight at three wavefronts per SIMD instead of
-// spilling.  The same number of key bytes is in flight per SIMD either way.
-template <int GH, bool SCORED, bool SMALL>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
+// How a unit's slots are spread: over `waves` wavefronts with `spl` slots per lane in registers; spl 0: one wavefront that
+// loops over its slots.
+struct UnitForm {
+    int waves, spl;
+};
+constexpr int LOOP_SPL = 5;                                // slots per lane and round trip of that loop
+
+// Which one, with an attention term.  A wavefront waits for its tiles, so what counts is how many wavefronts stream at once;
+// where units are many, their barriers and their LDS do: from 257 slots on, and with up to two sequences' units at any
+// budget worth ranking, shared is ahead (us per step, one wavefront / this form: 257 slots, 256 units 14.9 / 11.0, 1024 units
+// 23.0 / 19.4, 4096 units 63.7 / 55, 16 384 units 225 / 201; 129 slots, 4096 units 36.6 / 34.6; 65 slots, 4096 units 22.1 /
+// 24.5; 701 slots, 1024 units 48.1 / 38; 1501 slots, 2048 units 198 / 125).  More wavefronts with fewer slots per lane where
+// a budget leaves the choice (1025 slots, 256 units: four wavefronts 20.4, eight 19.3; 601 slots: 14.9, 15.3).
+static_assert(TA_MAX_DECODE_K + 1 <= 8 * 4 * 64, "the widest form");
+constexpr int FEW_UNITS = 512;
+UnitForm unit_form(bool scored, int slots, int64_t units)
+{
+    if (!scored) return {1, slots <= LOOP_SPL * 64 ? LOOP_SPL : 0};
+    if (units > FEW_UNITS && slots <= 112) return {1, 2};
+    if (units > FEW_UNITS && slots <= 256) return {2, 2};
+    if (slots <= 512) return {4, 2};
+    if (slots <= 768) return {4, 3};
+    if (slots <= 1536) return {8, 3};
+    return {8, 4};                                         // at most 2048 slots; {1, 0} where the LDS does not hold the logits as well
+}
+
+// Key tiles in flight: two per wavefront where wavefronts share a unit - enough with all that then share a compute unit, and the
+// registers let more of them do so (six, us per step: 1025 slots, 256 units 21.0 -> 19.8, 1024 units 56.6 -> 52.7; 1501
+// slots, 1024 units 94.4 -> 75.4).  One wavefront per unit: three at four wavefronts per SIMD; paged slots need
+// more registers for their addresses: four at three wavefronts per SIMD instead of spilling.
+template <int GH, bool PAGED, bool SCORED, bool SMALL, int WAVES, int SPL>
+__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu((WAVES > 1 ? 2 : PAGED ? 3 : 4))))
 decode_unit_kernel(ta_decode_state st, UnitArgs a, SlotPages pg)
 {
-    decode_unit<GH, false, SCORED, SMALL, 3, 1>(st, a, pg);
+    decode_unit<GH, PAGED, SCORED, SMALL, (WAVES > 1 ? 2 : PAGED ? 4 : 3), WAVES, SPL>(st, a, pg);
 }
 
-template <int GH, bool SCORED, bool SMALL>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3)))
-decode_unit_paged_kernel(ta_decode_state st, UnitArgs a, SlotPages pg)
-{
-    decode_unit<GH, true, SCORED, SMALL, 4, 1>(st, a, pg);
-}
+using UnitKernel = void (*)(ta_decode_state, UnitArgs, SlotPages);
 
-// More slots than one wavefront's registers hold: four wavefronts per unit (up to 1280 slots) or eight (up to 2560),
-// each with SLOTS_PER_LANE * 64 of the slots.  Six key tiles in flight per wavefront (seven with paged slots) in two
-// wavefronts' worth of registers per SIMD.
-constexpr int DU_WIDE = 4;
-constexpr int DU_WIDER = 8;
-constexpr int DU_WIDE_RING = 6;
-// When: measured against one wavefront per unit on 32 x batch x 8 units.  From about 700 slots on the shared form is
-// ahead at every unit count (1025 slots: 24 against 44 us per step at 256 units, 198 against 220 us at 4096, 386
-// against 412 us at 8192 - the single wavefront has to loop over its slots there); below that it is ahead up to
-// about 640 units (513 slots: 18 against 27 us at 256 units, level at 768, behind from 1024 on).
-#ifndef TA_DECODE_WIDE_MAX_UNITS
-#define TA_DECODE_WIDE_MAX_UNITS 640
-#endif
-constexpr int DU_WIDE_MAX_UNITS = TA_DECODE_WIDE_MAX_UNITS;   // (0: never)
-constexpr int DU_WIDE_ALWAYS_SLOTS = 704;
-// Eight wavefronts (1281 to 2560 slots): 2048 slots: 37 against 74 us at 256 units, 140 against 173 us at 1024, 509
-// against 538 us at 4096; 1501 slots: 32 against 57 us at 256 units, but 207 against 183 us at 2048.
-constexpr int DU_WIDER_MAX_UNITS = 1024;
-constexpr int DU_WIDER_ALWAYS_SLOTS = 1792;
-
-template <int GH, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
-decode_unit_wide_kernel(ta_decode_state st, UnitArgs a, SlotPages pg)
+template <int GH, bool PAGED>
+UnitKernel unit_kernel(bool scored, UnitForm f)
 {
-    decode_unit<GH, false, true, true, DU_WIDE_RING, WAVES>(st, a, pg);
-}
-
-template <int GH, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2)))
-decode_unit_paged_wide_kernel(ta_decode_state st, UnitArgs a, SlotPages pg)
-{
-    decode_unit<GH, true, true, true, DU_WIDE_RING + 1, WAVES>(st, a, pg);
+    if (!scored) return f.spl ? decode_unit_kernel<GH, PAGED, false, true, 1, LOOP_SPL> : decode_unit_kernel<GH, PAGED, false, false, 1, LOOP_SPL>;
+    switch (f.waves * 8 + f.spl) {
+        case 1 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 1, 2>;
+        case 2 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 2, 2>;
+        case 4 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 4, 2>;
+        case 4 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 4, 3>;
+        case 8 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 8, 3>;
+        case 8 * 8 + 4: return decode_unit_kernel<GH, PAGED, true, true, 8, 4>;
+        default: return decode_unit_kernel<GH, PAGED, true, false, 1, LOOP_SPL>;
+    }
 }
 
 DeviceOnce g_setup;
@@ -820,41 +820,21 @@ template <int GH>
 hipError_t unit_attributes()
 {
     // dynamic LDS above 64 KB (large budgets with an attention term) needs the attribute
-    const void* fns[] = {reinterpret_cast<const void*>(&decode_unit_kernel<GH, true, true>),
-                         reinterpret_cast<const void*>(&decode_unit_kernel<GH, true, false>),
-                         reinterpret_cast<const void*>(&decode_unit_paged_kernel<GH, true, true>),
-                         reinterpret_cast<const void*>(&decode_unit_paged_kernel<GH, true, false>),
-                         reinterpret_cast<const void*>(&decode_unit_wide_kernel<GH, DU_WIDE>),
-                         reinterpret_cast<const void*>(&decode_unit_paged_wide_kernel<GH, DU_WIDE>),
-                         reinterpret_cast<const void*>(&decode_unit_wide_kernel<GH, DU_WIDER>),
-                         reinterpret_cast<const void*>(&decode_unit_paged_wide_kernel<GH, DU_WIDER>)};
     hipError_t e = hipSuccess;
-    for (const void* fn : fns)
-        if (e == hipSuccess) e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    for (const UnitForm f : {UnitForm{1, 2}, UnitForm{2, 2}, UnitForm{4, 2}, UnitForm{4, 3}, UnitForm{8, 3}, UnitForm{8, 4}, UnitForm{1, 0}})
+        for (const UnitKernel k : {unit_kernel<GH, false>(true, f), unit_kernel<GH, true>(true, f)})
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     return e;
 }
 
 template <int GH>
-void launch_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& pg, unsigned grid, size_t lds, int waves,
+void launch_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& pg, unsigned grid, size_t lds, UnitForm f,
                  hipStream_t s)
 {
-    const bool scored = a.alpha != 0.0f, small = st.K + 1 <= SLOTS_PER_LANE * 64;
-    if (waves > 1) {                                       // several wavefronts per unit
-        auto kernel = st.pages ? (waves == DU_WIDE ? decode_unit_paged_wide_kernel<GH, DU_WIDE> : decode_unit_paged_wide_kernel<GH, DU_WIDER>)
-                               : (waves == DU_WIDE ? decode_unit_wide_kernel<GH, DU_WIDE> : decode_unit_wide_kernel<GH, DU_WIDER>);
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), lds, s, st, a, pg);
-        return;
-    }
-#define TA_LAUNCH_UNIT(KERNEL, S, M) \
-    hipLaunchKernelGGL((KERNEL<GH, S, M>), dim3(grid), dim3(64), lds, s, st, a, pg)
-    if (st.pages) {
-        if (scored) { if (small) TA_LAUNCH_UNIT(decode_unit_paged_kernel, true, true); else TA_LAUNCH_UNIT(decode_unit_paged_kernel, true, false); }
-        else { if (small) TA_LAUNCH_UNIT(decode_unit_paged_kernel, false, true); else TA_LAUNCH_UNIT(decode_unit_paged_kernel, false, false); }
-    } else {
-        if (scored) { if (small) TA_LAUNCH_UNIT(decode_unit_kernel, true, true); else TA_LAUNCH_UNIT(decode_unit_kernel, true, false); }
-        else { if (small) TA_LAUNCH_UNIT(decode_unit_kernel, false, true); else TA_LAUNCH_UNIT(decode_unit_kernel, false, false); }
-    }
-#undef TA_LAUNCH_UNIT
+    const bool scored = a.alpha != 0.0f;
+    const UnitKernel kernel = st.pages ? unit_kernel<GH, true>(scored, f) : unit_kernel<GH, false>(scored, f);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * f.waves), lds, s, st, a, pg);
 }
 
 }  // namespace
@@ -934,18 +914,9 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
     const size_t page_list = st.pages ? (size_t)((slots - 1) / pg.page_size + 1) : 0;      // the pages of the unit's slots
     // per wavefront a key tile and the new key row; several wavefronts: 64 words more
     const auto scored_floats = [&](int waves) { return wstride + (1024 + 64) * (size_t)waves + (waves > 1 ? 64 : 0) + (size_t)G * wstride; };
-    // several wavefronts per unit when the slots do not fit one wavefront's registers (but do fit those of four or
-    // eight) and either are many or the units are few
-    int waves = 1;
-    if (prm.alpha != 0.0f && slots > SLOTS_PER_LANE * 64 && DU_WIDE_MAX_UNITS > 0) {
-        if (slots <= DU_WIDE * SLOTS_PER_LANE * 64) {
-            if (units <= (unsigned)DU_WIDE_MAX_UNITS || slots > DU_WIDE_ALWAYS_SLOTS) waves = DU_WIDE;
-        } else if (slots <= DU_WIDER * SLOTS_PER_LANE * 64) {
-            if (units <= (unsigned)DU_WIDER_MAX_UNITS || slots > DU_WIDER_ALWAYS_SLOTS) waves = DU_WIDER;
-        }
-    }
-    if (waves > 1 && (scored_floats(waves) + page_list) * sizeof(float) > 160 * 1024) waves = 1;
-    size_t lds_floats = prm.alpha != 0.0f ? scored_floats(waves) : wstride;
+    UnitForm form = unit_form(prm.alpha != 0.0f, slots, units);
+    if (form.waves > 1 && (scored_floats(form.waves) + page_list) * sizeof(float) > 160 * 1024) form = {1, 0};
+    size_t lds_floats = prm.alpha != 0.0f ? scored_floats(form.waves) : wstride;
     a.pg_off = (int32_t)lds_floats;
     a.units = (int32_t)units;
     a.decay = prm.budget_decay;
@@ -957,9 +928,9 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
     // the units, then one workgroup per 256 positions for the budget decay
     const uint64_t grid = (uint64_t)units + (uint64_t)tiles * (uint64_t)st.batch;
     if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    if (G <= 4) launch_unit<4>(st, a, pg, (unsigned)grid, lds, waves, s);
-    else if (G <= 8) launch_unit<8>(st, a, pg, (unsigned)grid, lds, waves, s);
-    else launch_unit<MAX_GROUP>(st, a, pg, (unsigned)grid, lds, waves, s);
+    if (G <= 4) launch_unit<4>(st, a, pg, (unsigned)grid, lds, form, s);
+    else if (G <= 8) launch_unit<8>(st, a, pg, (unsigned)grid, lds, form, s);
+    else launch_unit<MAX_GROUP>(st, a, pg, (unsigned)grid, lds, form, s);
     return hipGetLastError();
 }
 

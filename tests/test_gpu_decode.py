@@ -387,3 +387,13 @@ def test_several_wavefronts_per_unit_give_the_single_wavefronts_bits(paged, K, b
     for x1, xb in zip(*states):
         assert _same_bits(x1, xb)
     assert (states[0][4] >= 0).any()                      # slots were evicted on the way
+
+
+@pytest.mark.parametrize("paged", [None, (16, False)])
+@pytest.mark.parametrize("K,batch", [(127, 2), (128, 2), (511, 2), (512, 2), (767, 2), (768, 2), (1535, 2), (1536, 2), (2047, 2),
+                                     (111, 130), (112, 130), (255, 130), (256, 130)])
+def test_decode_at_the_edges_of_the_unit_forms(K, batch, paged):
+    # K + 1 slots on both sides of what each spread over wavefronts and registers holds; a cache that is not full at first
+    w = wl.scaled(wl.CONFIGS["c5_agentic_prefill"], layers=1, batch=batch, n=K + 20, hq=8, hkv=4, window=8, planted=2, ragged=(K - 2, K + 20))
+    ev, _ = _run_decode(w, K=K, steps=4, p_anchor=0.1, paged=paged)
+    assert ev > 0
