@@ -32,7 +32,9 @@ expand_mask_kernel(MatchArgs a, MatchTable tab)
 {
     constexpr int WORDS = (MATCH_TILE + MATCH_MARGIN) / 32 + 2;
     __shared__ uint32_t s_bits[WORDS];
+    __shared__ float s_pw[TA_MAX_SPAN + 1];
     const int tid = (int)threadIdx.x;
+    const float pw = tab.pw[tid <= TA_MAX_SPAN ? tid : 0];   // (in host memory: requested first)
     const int32_t tile = (int32_t)blockIdx.x, b = (int32_t)blockIdx.y;
     const int32_t n = a.n;
     int32_t nb = a.seq_len ? a.seq_len[b] : n;
@@ -41,6 +43,7 @@ expand_mask_kernel(MatchArgs a, MatchTable tab)
     const uint8_t* flags = a.anchor + (size_t)b * (size_t)n;
     const uint8_t* allow = a.allow ? a.allow + (size_t)b * (size_t)n : nullptr;
     if (tid < WORDS) s_bits[tid] = 0u;
+    if (tid <= TA_MAX_SPAN) s_pw[tid] = pw;
     __syncthreads();
     for (int g = tid; g < (MATCH_TILE + MATCH_MARGIN) / 4; g += MATCH_THREADS) {
         const int32_t q0 = first + 4 * g;
@@ -63,7 +66,7 @@ expand_mask_kernel(MatchArgs a, MatchTable tab)
         if (nib) atomicOr(&s_bits[(4 * g) >> 5], nib << ((4 * g) & 31));
     }
     __syncthreads();
-    expand_tile(a, tab, tile, b, tid, s_bits, false);
+    expand_tile(a, tab, tile, b, tid, s_bits, s_pw, false);
 }
 
 // Anchor flags by token ID (embedding-based detection evaluated once per vocabulary entry).
