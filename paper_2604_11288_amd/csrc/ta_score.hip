@@ -194,11 +194,23 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     int32_t nb = a.seq_len ? __builtin_amdgcn_readfirstlane(a.seq_len[b]) : n;   // (in a scalar register: it is part of every stage's address)
     nb = nb < 0 ? 0 : (nb > n ? n : nb);
 
-    const int32_t key_lo = chunk * a.chunk_keys;
-    int32_t key_hi = key_lo + a.chunk_keys;
+    // The chunks divide the sequence's own length, so that a short one is spread over as many workgroups as a long one (cut
+    // where the longest is, the last chunks of the others were empty and the rest no shorter.  Whole pass, us: 80 units of
+    // 5000..20000 keys 95 -> 64; 192 of them, 256 rows 506 -> 404; 176 units of 1090..8720 keys 146 -> 124).
+    const int32_t seq_stages = (nb + STAGE_KEYS - 1) / STAGE_KEYS;
+    const int32_t chunk_keys = (int32_t)divide((uint32_t)(seq_stages + a.nchunks - 1), a.by_chunks) * STAGE_KEYS;
+    const int32_t key_lo = chunk * chunk_keys;
+    int32_t key_hi = key_lo + chunk_keys;
     key_hi = key_hi > n ? n : key_hi;
-    // keys at or past the end of a ragged sequence are visible to no row: their stages are not
-    // streamed at all (their column sums are written as zeros at the end)
+    // Keys past the end of a ragged sequence are visible to no row: the stages behind it are not streamed at all; their
+    // column sums are zeros, an equal share of which every chunk writes.
+    const auto zero_share = [&]() {
+        const int32_t from = seq_stages * STAGE_KEYS;
+        if (from >= n) return;
+        const int32_t share = (int32_t)divide((uint32_t)(n - from + a.nchunks - 1), a.by_chunks);
+        const int32_t first = from + chunk * share, last = n - first < share ? n : first + share;
+        for (int32_t key = first + (int32_t)threadIdx.x; key < last; key += THREADS) a.A[(size_t)unit * n + key] = 0.0f;
+    };
     const int32_t key_end = key_hi < nb ? key_hi : nb;
     const int nstages = key_end > key_lo ? (key_end - key_lo + STAGE_KEYS - 1) / STAGE_KEYS : 0;
     // keys <= min_lim are visible to every live row of a full window
@@ -213,7 +225,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                 st[r * 2 + 1] = 0.0f;
             }
         } else {
-            for (int32_t key = key_lo + tid; key < key_hi; key += THREADS) a.A[(size_t)unit * n + key] = 0.0f;
+            zero_share();
         }
         return;
     }
@@ -652,8 +664,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     if constexpr (COLSUM) {
         __syncthreads();
         flush_pending();
-        for (int32_t key = key_lo + nstages * STAGE_KEYS + tid; key < key_hi; key += THREADS)
-            a.A[(size_t)unit * n + key] = 0.0f;
+        if (row_base == 0) zero_share();
     }
 
     if constexpr (!COLSUM) {
@@ -915,7 +926,6 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
     a.n = lay.n;
     a.rows = p.rows;
     a.rows_pad = p.rows_pad;
-    a.chunk_keys = p.chunk_keys;
     a.nchunks = p.nchunks;
     a.causal = causal;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)lay.d));

@@ -25,7 +25,7 @@ struct ScoreArgs {
     int32_t k_sp;                      // K position stride in 16-byte units (n * k_sp < 2^31)
     int32_t batch, hkv, G, W, n;
     int32_t rows, rows_pad;            // M = G*W and M rounded up to 64*RG
-    int32_t chunk_keys, nchunks;
+    int32_t nchunks;
     uint32_t inv_W;                    // (row * inv_W) >> 20 = row / W for rows below 512
     Divider by_chunks, by_hkv, by_batch;
     int32_t units;

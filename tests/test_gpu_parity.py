@@ -275,6 +275,13 @@ def test_score_one_unit_in_many_chunks(n):
         _check_score(w)
 
 
+@pytest.mark.parametrize("n,hq", [(3000, 4), (4096, 8), (2047, 16), (130, 4)])
+def test_score_chunks_of_each_sequences_own_length(n, hq):
+    # many chunks per unit, divided by the sequence's length: less than a stage, fewer stages than chunks, all of them
+    w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=1, batch=9, n=n, hq=hq, hkv=1, window=32)
+    _check_score(w, seq_len=[n, 1, 63, 64, 65, n - 1, n // 2, 0, n - n % 64])
+
+
 @pytest.mark.parametrize("window,layers,batch", [(16, 4, 97), (13, 5, 60), (32, 3, 90), (32, 4, 60), (64, 2, 70)])
 def test_score_more_workgroups_than_run_at_once(window, layers, batch):
     # the second sweep takes units and chunks in the opposite order; 64 rows and fewer have workgroups of their own.  Some
