@@ -6,6 +6,7 @@ stream.  There is no CPU fallback: a missing library or a failing call raises.
 """
 import ctypes
 import os
+from array import array
 from dataclasses import dataclass, replace
 from typing import Optional
 
@@ -510,27 +511,35 @@ def ta_compact(Kin, Vin, idx, cnt, K: int, idx_shared: bool = False, out=None, s
     return Kout, Vout
 
 
-class _Plan:
-    """run(): the C call with arguments marshalled when the plan is first run (and again after an attribute was assigned)."""
+def _ptrs(*tensors):
+    return [None if t is None else t.data_ptr() for t in tensors]
 
-    def __setattr__(self, name, value):
-        self.__dict__[name] = value
-        self.__dict__["_call"] = None
+
+class _Plan:
+    """run(): the C call.  Every address is read from its tensor at the call: a tensor's storage can be replaced in place
+    (`t.data = u`, `t.set_(u)`, `t.resize_(n)`), which no attribute of the plan shows."""
+
+    def _keep_params(self, params):
+        """The values a plan is built with stay its own; a struct that names no tensor is built once."""
+        self.params, self._prm = params, replace(params)
+        names_tensors = any(t is not None for t in (params.layer_K, params.allow, params.margin))
+        self._cp = None if names_tensors else self._prm._build_c()
+
+    def _params(self) -> CParams:
+        return self._prm.c() if self._cp is None else self._cp
 
     def run(self, stream=None):
-        call = self._call
-        if call is None:
-            call = self.__dict__["_call"] = self._marshal()
-        rc = call[0](*call[2], _stream(stream))
+        call, name, args = self._marshal()
+        rc = call(*args, _stream(stream))
         if rc != TA_OK:
-            raise TaError(rc, call[1])
+            raise TaError(rc, name)
         return self
 
 
 class EvictPlan(_Plan):
-    """Pre-allocated outputs and marshalled arguments of one ta_evict configuration.
+    """Pre-allocated outputs and validated sizes of one ta_evict configuration.
 
-    run() only performs the C call, so it can sit inside a timed loop.
+    run() only reads the tensors' addresses and performs the C call, so it can sit inside a timed loop.
     """
 
     def __init__(self, tok, tab_ids, tab_len, Q, Kin, Vin, K: int, params: Params,
@@ -541,12 +550,12 @@ class EvictPlan(_Plan):
         if paged is not None:
             Kin, Vin = paged.Kpool, paged.Vpool
         dev = Kin.device
-        self.params, self.K = params, int(K)
+        self._keep_params(params)
+        self.K = int(K)
         self.lse = lse                     # row log-sum-exps of the prefill attention kernel: ta_evict_lse
         self.scored = params.alpha != 0.0
         if paged is not None:
             self.lay = paged.layout(Q if self.scored else None)
-            self._pg = paged.c()
         else:
             self.lay = layout_of(Kin, Q if self.scored else None)
         lay = self.lay
@@ -577,18 +586,16 @@ class EvictPlan(_Plan):
         shape = (lay.layers, B, lay.hkv, self.K, lay.d)
         self.Kout = torch.zeros(shape, dtype=torch.bfloat16, device=dev)
         self.Vout = torch.zeros(shape, dtype=torch.bfloat16, device=dev)
-        self._cp = params.c()
 
     def _marshal(self):
         """(function, its name, arguments but the stream) of this configuration."""
-        head = (_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data, self.E, _ptr(self.anchor_B),
-                _ptr(self.Q), _ptr(self.Kin), _ptr(self.Vin))
-        sizes = (ctypes.byref(self.lay), ctypes.byref(self._cp), self.K)
-        outs = (_ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch), _ptr(self.A), _ptr(self.idx), _ptr(self.cnt),
-                _ptr(self.Kout), _ptr(self.Vout))
+        tok, seq_len, anchor_B, *inputs = _ptrs(self.tok, self.seq_len, self.anchor_B, self.Q, self.Kin, self.Vin)
+        head = (tok, seq_len, _host(self.ids), _host(self.lens), self.E, anchor_B, *inputs)
+        sizes = (ctypes.byref(self.lay), ctypes.byref(self._params()), self.K)
+        outs = (*_ptrs(self.anchor, self.spons, self.vouch, self.A, self.idx, self.cnt, self.Kout, self.Vout),)
         ws = (_ptr(self.ws), 0 if self.ws is None else self.ws.numel())
         if self.paged is not None:
-            return lib().ta_evict_paged, "ta_evict_paged", head + (ctypes.byref(self._pg), _ptr(self.lse)) + sizes + outs + ws
+            return lib().ta_evict_paged, "ta_evict_paged", head + (ctypes.byref(self.paged.c()), _ptr(self.lse)) + sizes + outs + ws
         if self.lse is not None:
             return lib().ta_evict_lse, "ta_evict_lse", head + (_ptr(self.lse),) + sizes + outs
         if self.static_scratch:
@@ -640,7 +647,8 @@ class LayerEvictPlan(_Plan):
         assert layers >= 1 and len(V_layers) == layers
         K0 = K_layers[0]
         dev = K0.device
-        self.params, self.K = params, int(K)
+        self._keep_params(params)
+        self.K = int(K)
         self.scored = params.alpha != 0.0
         self.paged, self.lse = paged, lse
         for t in list(K_layers) + list(V_layers):
@@ -652,8 +660,6 @@ class LayerEvictPlan(_Plan):
             # (a PagedKV whose own pools may be None and whose layer stride is not used)
             assert paged.layers == layers
             lay.batch, lay.hkv, lay.n, lay.d = paged.batch, paged.hkv, paged.n, paged.d
-            self._pg = paged.c()
-            self._pg.stride[0] = 0
         else:
             assert K0.dim() == 4 and K0.stride(3) == 1
             lay.batch, lay.hkv, lay.n, lay.d = K0.shape
@@ -700,20 +706,20 @@ class LayerEvictPlan(_Plan):
         self.ws = torch.empty(nbytes, dtype=torch.uint8, device=dev)      # score scratch + the address table
         self.Kout = [torch.zeros((B, lay.hkv, self.K, lay.d), dtype=torch.bfloat16, device=dev) for _ in range(layers)]
         self.Vout = [torch.zeros((B, lay.hkv, self.K, lay.d), dtype=torch.bfloat16, device=dev) for _ in range(layers)]
-        table = lambda ts: (ctypes.c_void_p * layers)(*[t.data_ptr() for t in ts])
-        self._tables = [table(self.Q_layers) if self.scored else None, table(self.K_layers), table(self.V_layers),
-                        table(self.Kout), table(self.Vout)]     # host arrays, kept alive with the plan
-        addr = lambda a: None if a is None else ctypes.cast(a, ctypes.c_void_p)
-        self._lp = CLayerPtrs(*[addr(a) for a in self._tables])
-        self._cp = params.c()
 
     def _marshal(self):
-        head = (_ptr(self.tok), _ptr(self.seq_len), self.ids.ctypes.data, self.lens.ctypes.data, self.E, _ptr(self.anchor_B),
-                ctypes.byref(self._lp))
-        tail = (ctypes.byref(self.lay), ctypes.byref(self._cp), self.K, _ptr(self.anchor), _ptr(self.spons), _ptr(self.vouch),
-                _ptr(self.A), _ptr(self.idx), _ptr(self.cnt), _ptr(self.ws), self.ws.numel())
+        tables = [None if ts is None else array("Q", _ptrs(*ts))
+                  for ts in (self.Q_layers, self.K_layers, self.V_layers, self.Kout, self.Vout)]
+        lp = CLayerPtrs(*[None if t is None else t.buffer_info()[0] for t in tables])
+        lp.tables = tables                                      # host arrays, kept alive with the struct that names them
+        tok, seq_len, anchor_B = _ptrs(self.tok, self.seq_len, self.anchor_B)
+        head = (tok, seq_len, _host(self.ids), _host(self.lens), self.E, anchor_B, ctypes.byref(lp))
+        tail = (ctypes.byref(self.lay), ctypes.byref(self._params()), self.K,
+                *_ptrs(self.anchor, self.spons, self.vouch, self.A, self.idx, self.cnt, self.ws), self.ws.numel())
         if self.paged is not None:
-            return lib().ta_evict_layers_paged, "ta_evict_layers_paged", head + (ctypes.byref(self._pg), _ptr(self.lse)) + tail
+            pg = self.paged.c()
+            pg.stride[0] = 0
+            return lib().ta_evict_layers_paged, "ta_evict_layers_paged", head + (ctypes.byref(pg), _ptr(self.lse)) + tail
         assert self.lse is None, "row log-sum-exps are taken by the paged form only"
         return lib().ta_evict_layers, "ta_evict_layers", head + tail
 
@@ -740,7 +746,6 @@ class DecodeState:
         max_pages * page_size >= K + 1); None: dense [layers][batch][hkv][K+1][d] tensors allocated here."""
         self.layers, self.batch, self.hq, self.hkv, self.K, self.cap, self.d = layers, batch, hq, hkv, K, cap, d
         self.pages = pages
-        self._cpages = None if pages is None else pages.c()
         i32, dev = torch.int32, device
         self.tok = torch.zeros((batch, cap), dtype=i32, device=dev)
         self.len = torch.zeros((batch,), dtype=i32, device=dev)
@@ -757,23 +762,17 @@ class DecodeState:
         self.A = torch.zeros((layers, batch, hkv, K + 1), dtype=torch.float32, device=dev)
         self.stepped = torch.zeros((batch,), dtype=i32, device=dev)
 
-    def __setattr__(self, name, value):
-        self.__dict__[name] = value
-        self.__dict__["_c"] = None
-
     def c(self) -> CDecodeState:
-        """The ABI's struct: the same one until an attribute is assigned."""
-        if self._c is None:
-            self.__dict__["_c"] = self._build_c()
-        return self._c
-
-    def _build_c(self) -> CDecodeState:
-        return CDecodeState(self.layers, self.batch, self.hq, self.hkv, self.d, self.K, self.cap,
-                            self.tok.data_ptr(), self.len.data_ptr(), self.anchor.data_ptr(),
-                            self.budget.data_ptr(), self.vouch.data_ptr(), self.spons.data_ptr(),
-                            self.Kc.data_ptr(), self.Vc.data_ptr(),
-                            self.pos.data_ptr(), self.A.data_ptr(), self.stepped.data_ptr(),
-                            None if self._cpages is None else ctypes.addressof(self._cpages))
+        """The ABI's struct, from the tensors' present addresses."""
+        pages = None if self.pages is None else self.pages.c()
+        c = CDecodeState(self.layers, self.batch, self.hq, self.hkv, self.d, self.K, self.cap,
+                         self.tok.data_ptr(), self.len.data_ptr(), self.anchor.data_ptr(),
+                         self.budget.data_ptr(), self.vouch.data_ptr(), self.spons.data_ptr(),
+                         self.Kc.data_ptr(), self.Vc.data_ptr(),
+                         self.pos.data_ptr(), self.A.data_ptr(), self.stepped.data_ptr(),
+                         None if pages is None else ctypes.addressof(pages))
+        c.paged = pages                                         # kept alive with the struct that names it
+        return c
 
 
 def ta_decode_init(state: DecodeState, tok, anchor, idx, cnt, Kout, Vout, params: Params,
