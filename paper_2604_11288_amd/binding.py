@@ -220,12 +220,12 @@ def _check(rc, where):
 
 
 def _table(tab_ids, tab_len):
-    """Host copies of the anchor table in the ABI's [E][TA_MAX_GRAM] / [E] int32 form (arrays that already have it as they are)."""
-    tab_len = np.ascontiguousarray(tab_len, dtype=np.int32)
+    """Host copies of the anchor table in the ABI's [E][TA_MAX_GRAM] / [E] int32 form: plans outlive the caller's arrays, which
+    may be filled again for another request."""
+    tab_len = np.array(tab_len, dtype=np.int32, order="C", ndmin=1)
     E = int(tab_len.shape[0])
-    if (E and type(tab_ids) is np.ndarray and tab_ids.dtype == np.int32 and tab_ids.shape == (E, TA_MAX_GRAM)
-            and tab_ids.flags.c_contiguous):
-        return tab_ids, tab_len, E
+    if E and type(tab_ids) is np.ndarray and tab_ids.dtype == np.int32 and tab_ids.shape == (E, TA_MAX_GRAM):
+        return np.array(tab_ids, order="C"), tab_len, E
     ids = np.full((max(E, 1), TA_MAX_GRAM), -1, np.int32)
     if E:
         src = np.asarray(tab_ids, dtype=np.int32).reshape(E, -1)

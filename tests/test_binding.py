@@ -132,3 +132,14 @@ def test_decode_state_passes_present_addresses(recorder, paged):
     old = _move(tensors)
     step()
     assert not recorder.addresses & {t.data_ptr() for t in old}
+
+
+@pytest.mark.parametrize("form", ("dense", "layers"))
+@pytest.mark.parametrize("as_list", (False, True))
+def test_plan_keeps_its_own_anchor_table(recorder, form, as_list):
+    """The caller's arrays are filled again for the next request: the plan built from them runs on with what it was given."""
+    ids, lens = TABLE[0].copy(), TABLE[1].copy()
+    plan, _ = _plan(form, table=(ids.tolist() if as_list else ids, lens))
+    ids[:], lens[:] = 9, 1
+    plan.run(STREAM)
+    assert [w.tolist() for w in recorder.words] == [TABLE[0].ravel().tolist(), TABLE[1].tolist()]
