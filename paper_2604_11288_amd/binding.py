@@ -94,20 +94,8 @@ class Params:
     allow: Optional[torch.Tensor] = None         # device uint8 [B][n]: allowlist of positions
     margin: Optional[torch.Tensor] = None        # device float [units][2] (out): margin of every unit's cut
 
-    def __setattr__(self, name, value):
-        self.__dict__[name] = value
-        self.__dict__["_c"] = None
-
     def c(self) -> CParams:
-        """The ABI's struct: the same one until a field is assigned (a struct that names tensors is built anew)."""
-        if self.__dict__.get("_c") is not None:
-            return self._c
-        c = self._build_c()
-        if self.layer_K is None and self.allow is None and self.margin is None:
-            self.__dict__["_c"] = c
-        return c
-
-    def _build_c(self) -> CParams:
+        """The ABI's struct, a new one for each caller."""
         for t, dt in ((self.layer_K, torch.int32), (self.allow, torch.uint8), (self.margin, torch.float32)):
             assert t is None or (t.dtype == dt and t.is_contiguous())
         return CParams(self.n_sink, self.n_recent, self.span_L, self.sponsor_B, self.rho,
@@ -523,7 +511,7 @@ class _Plan:
         """The values a plan is built with stay its own; a struct that names no tensor is built once."""
         self.params, self._prm = params, replace(params)
         names_tensors = any(t is not None for t in (params.layer_K, params.allow, params.margin))
-        self._cp = None if names_tensors else self._prm._build_c()
+        self._cp = None if names_tensors else self._prm.c()
 
     def _params(self) -> CParams:
         return self._prm.c() if self._cp is None else self._cp

@@ -1,7 +1,9 @@
 """The binding hands the library the tensors' present addresses.
 
 The calls are recorded in the library's place, so these run without a GPU: what is checked is which addresses reach the C ABI."""
+import copy
 import ctypes
+import pickle
 from types import SimpleNamespace
 
 import numpy as np
@@ -143,3 +145,24 @@ def test_plan_keeps_its_own_anchor_table(recorder, form, as_list):
     ids[:], lens[:] = 9, 1
     plan.run(STREAM)
     assert [w.tolist() for w in recorder.words] == [TABLE[0].ravel().tolist(), TABLE[1].tolist()]
+
+
+@pytest.mark.parametrize("fork", (copy.deepcopy, lambda x: pickle.loads(pickle.dumps(x))))
+def test_params_and_state_can_be_copied_after_use(recorder, fork):
+    """A generation is forked by copying its state: the copy has tensors of its own and the same values."""
+    prm, state = tb.Params(alpha=0.25), tb.DecodeState(LAYERS, B, HQ, HKV, K, N, "cpu")
+    tb.ta_decode_step(state, *[torch.zeros(8) for _ in range(4)], *TABLE, prm, stream=STREAM)
+    state.budget.fill_(3.0)
+    prm2, state2 = fork(prm), fork(state)
+    assert prm2 == prm and bytes(prm2.c()) == bytes(prm.c())
+    for name, t in vars(state).items():
+        if isinstance(t, torch.Tensor):
+            other = getattr(state2, name)
+            assert torch.equal(other, t) and other.data_ptr() != t.data_ptr()
+
+
+def test_params_struct_is_the_callers_own():
+    """What a caller changes in a returned struct stays in that struct."""
+    prm = tb.Params()
+    prm.c().alpha = 0.0
+    assert prm.c().alpha == prm.alpha == 1.0
