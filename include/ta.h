@@ -155,9 +155,12 @@ typedef struct ta_layout {
 
 /* Bytes of DEVICE scratch that ta_score / ta_evict need for this layout (0 when
  * no attention term is computed).  The workspace holds per-chunk softmax row
- * statistics; its contents are meaningless between calls.  A larger workspace is used where
- * it helps: layouts of few units are then cut into more chunks (up to 32 per unit, i.e. 32 *
- * units * 8 bytes * the rows of a unit rounded up to 128, 256 or 512). */
+ * statistics; its contents are meaningless between calls.
+ * A workspace of at least 32 * units * 8 bytes * the rows of a unit (rounded up to 128, 256
+ * or 512), or of 8 MiB where that is less, lets layouts of few units be cut into more chunks, which is
+ * faster.  The chunks group the sums of a row's normaliser, so the scores of a layout may differ
+ * in their last bits between workspaces on the two sides of that size; on either side they do not
+ * depend on it (nor on whether the room is the caller's or that of ta_evict_static). */
 size_t ta_workspace_bytes(const ta_layout *lay, const ta_params *prm);
 
 /*
@@ -443,7 +446,8 @@ typedef struct ta_layer_ptrs {
  * base + l * layer stride.  Every other argument and output as in ta_evict, except
  *   ws   DEVICE, at least ta_workspace_bytes(lay, prm) rounded up to a multiple of 256, plus
  *        TA_LAYER_WS_BYTES (needed when prm->alpha == 0 too): the table is validated on the
- *        host and then kept there for the kernels.
+ *        host and then kept at the workspace's end for the kernels.  The room in front of it
+ *        counts for the larger size that ta_workspace_bytes names.
  * Errors: as ta_evict; SHAPE also for lay->layers > TA_MAX_LAYER_PTRS; NULL for a missing
  * array or entry; ALIGN for an entry that is not 16-byte aligned; SHAPE for an output entry
  * equal to an input entry of the same layer.
@@ -581,7 +585,8 @@ int32_t ta_init(void);
 /*
  * ta_evict for callers that cannot allocate device memory or hand over a workspace: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments,
- * outputs, kernels and errors as ta_evict, minus `ws` / `ws_bytes`: the per-chunk softmax row
+ * outputs (those of a workspace of the larger size that ta_workspace_bytes names), kernels and
+ * errors as ta_evict, minus `ws` / `ws_bytes`: the per-chunk softmax row
  * statistics of the score step go to a static device buffer of TA_STATIC_SCRATCH_BYTES that
  * lives inside the library (one copy per GPU, held until the process ends).  The call
  * allocates and frees nothing and calls no allocating routine.

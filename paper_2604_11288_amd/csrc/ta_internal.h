@@ -98,8 +98,8 @@ struct LayerPtrs {
 hipError_t launch_layer_table(const LayerPtrs& host_table, LayerPtrs* dev_table, int32_t layers, hipStream_t st);
 
 // ---- score ------------------------------------------------------------------
-// Scratch bytes the score step needs, and its largest grid, for a validated layout.  launch_score uses what ws_bytes gives it
-// beyond that where more chunks are faster.
+// Scratch bytes the score step needs, and its largest grid, for a validated layout.  launch_score cuts
+// the units into more chunks where that is faster and ws_bytes has the room that include/ta.h states for it.
 size_t score_workspace_bytes(const ta_layout& lay);
 int64_t score_grid_blocks(const ta_layout& lay);
 // With `rider` set, the match + voucher expansion of all sequences runs as trailing workgroups

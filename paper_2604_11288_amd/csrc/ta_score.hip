@@ -830,6 +830,17 @@ ScorePlan base_plan(const ta_layout& lay)
 
 int64_t stats_bytes(const ScorePlan& p, int64_t nchunks) { return p.units * nchunks * p.rows_pad * 2 * (int64_t)sizeof(float); }
 
+// The room for statistics that a workspace of ws_bytes (at least the base plan's) offers: that of MAX_CHUNKS chunks per unit, at
+// most 8 MiB, or if the workspace has less the base plan's.  There is nothing between the two: the chunks group the sums of a
+// row's normaliser, and its last bits should not follow the exact size of the caller's buffer.
+int64_t stats_room(const ta_layout& lay, int64_t ws_bytes)
+{
+    const ScorePlan p = base_plan(lay);
+    const int64_t need = stats_bytes(p, p.nchunks), most = stats_bytes(p, MAX_CHUNKS);
+    const int64_t full = most < (int64_t(8) << 20) ? most : int64_t(8) << 20;
+    return full > need && ws_bytes >= full ? full : need;
+}
+
 // The plan that runs, given `room` bytes for the statistics (at least the base plan's): the chunk count whose fullest compute
 // unit is done first.  A workgroup costs its stages plus the prologue (Q fragments, first stages, statistics merge) and
 // epilogue, about SETUP stages' time; a compute unit that gets k of them costs k times that, and one workgroup of four
@@ -881,7 +892,7 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
                         int causal, float* A, float* ws, size_t ws_bytes, const float* lse, const MatchRider* rider,
                         const ta_paged_kv* pg, const LayerPtrs* lp, hipStream_t st, int32_t gathered)
 {
-    const ScorePlan p = make_plan(lay, lse ? INT64_MAX : (int64_t)ws_bytes);
+    const ScorePlan p = make_plan(lay, lse ? INT64_MAX : stats_room(lay, (int64_t)ws_bytes));
     ScoreArgs a;
     a.Ql = lp ? reinterpret_cast<const uint4* const*>(&lp->Q[0]) : nullptr;
     a.Kl = lp ? reinterpret_cast<const uint4* const*>(&lp->K[0]) : nullptr;

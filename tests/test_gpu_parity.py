@@ -282,6 +282,31 @@ def test_score_chunks_of_each_sequences_own_length(n, hq):
     _check_score(w, seq_len=[n, 1, 63, 64, 65, n - 1, n // 2, 0, n - n % 64])
 
 
+@pytest.mark.parametrize("layers,hkv,n,hq,window", [(1, 8, 4096, 32, 32), (2, 8, 3001, 32, 16), (24, 8, 4096, 64, 32), (1, 1, 20000, 4, 32)])
+def test_score_bits_follow_the_workspace_only_at_the_stated_size(layers, hkv, n, hq, window):
+    # more chunks group a normaliser's sums in another way: that happens at one size of the workspace (the last layout has
+    # none: it needs the larger number of chunks anyway), and the pass with the library's own scratch is on its far side
+    w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=layers, batch=1, n=n, hq=hq, hkv=hkv, window=window)
+    Q, K, V = wl.make_qkv(w, device=DEV)
+    prm = _prm(w)
+    need = ta.ta_workspace_bytes(ta.layout_of(K, Q), prm)
+    rows = hq // hkv * window
+    most = min(32 * layers * hkv * 8 * (128 if rows <= 128 else 256), 8 << 20)
+    score = lambda nbytes: ta.ta_score(Q, K, prm, ws=torch.empty(nbytes, dtype=torch.uint8, device=DEV)).cpu().numpy()
+    small, large = score(need), score(max(need, most))
+    for nbytes in (need + 16, need * 5 // 4, (need + most) // 2, most - 16):
+        if need <= nbytes < most:
+            assert np.array_equal(score(nbytes).view(np.uint32), small.view(np.uint32)), nbytes
+    assert np.array_equal(score(32 << 20).view(np.uint32), large.view(np.uint32))
+    # a normaliser sums n positive terms: two orders differ by at most 2 n roundings of its value, and so does a score, which
+    # is a sum of the rows' terms divided by their normalisers
+    assert np.max(np.abs(large - small)) <= 2 * n * 2.0 ** -24 * np.max(np.abs(small))
+    td = wl.make_tokens(w)
+    for static in (False, True):
+        plan = ta.EvictPlan(_dev(td.tok), td.tab_ids, td.tab_len, Q, K, V, 64, prm, static_scratch=static).run()
+        assert np.array_equal(plan.A.cpu().numpy().view(np.uint32), large.view(np.uint32)), static
+
+
 @pytest.mark.parametrize("window,layers,batch", [(16, 4, 97), (13, 5, 60), (32, 3, 90), (32, 4, 60), (64, 2, 70)])
 def test_score_more_workgroups_than_run_at_once(window, layers, batch):
     # the second sweep takes units and chunks in the opposite order; 64 rows and fewer have workgroups of their own.  Some
