@@ -6,7 +6,7 @@
 //   decode_seq_vouch_kernel  per sequence: append the token, test the anchor table at the new
 //                            position only, set its budget; voucher and sponsor flag of every
 //                            position from the current budgets
-//   decode_unit_kernel       one wavefront per unit: write the new k/v row into the
+//   decode_unit_kernel       one to eight wavefronts per unit: write the new k/v row into the
 //                            free slot, add the decode queries' softmax weights over
 //                            the cached rows to A (H2O-style cumulative attention,
 //                            Eq. 1), free the slot that ranks last under the
@@ -310,16 +310,17 @@ __device__ __forceinline__ s16x4 hi_half(const uint4& v)
     return c.s;
 }
 
-// One wavefront per unit, no workgroup barriers.  SMALL: at most SPL * 64 slots, so a
+// A unit is the work of one workgroup of WAVES wavefronts.  SMALL: at most WAVES * SPL * 64 slots, so a
 // lane's slots (position, voucher, flags, accumulated attention) stay in its registers from the
 // first round trip to the ranking and nothing loops over slots.
 // DT_RING: 16-row key tiles in flight per wavefront.
-// WAVES > 1 (one wavefront would stream a unit's keys one tile after the other and loop over its slots):
-// WAVES wavefronts share a unit.  Each keeps its
-// SPL * 64 slots in registers like the SMALL form and streams every WAVES-th key tile; the slot
-// table, the logits and three small exchanges go through LDS (three workgroup barriers).  Every logit, every
-// softmax statistic (each wavefront reduces all of them, in the single wavefront's order) and every slot's
-// key is computed by the same instructions as in the single-wavefront form: the two give the same bits.
+// WAVES == 1: no workgroup barriers.
+// WAVES > 1 (one wavefront would stream a unit's keys one tile after the other): each wavefront has SPL * 64 of
+// the slots in its registers and streams every WAVES-th key tile; the slot table, the logits and four small exchanges
+// (first free slot, softmax statistics, free count, worst key) go through LDS, with four workgroup barriers.  Every logit,
+// every softmax statistic (of a head by one wavefront, in the single wavefront's order; the wavefronts take every
+// WAVES-th head) and every slot's key is computed by the same instructions as in the single-wavefront form: all forms
+// give the same bits.
 template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES, int SPL>
 __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& pg)
 {

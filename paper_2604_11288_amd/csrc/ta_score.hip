@@ -8,14 +8,16 @@
 //
 // Column sums need every row's (max, normaliser) over ALL keys before any row
 // can be added into a column, so the keys are swept twice:
-//   sweep 1 (stats)  : per row, online (m, Z) over a chunk of keys -> workspace
+//   sweep 1 (stats)  : per row, (m, Z) over a chunk of keys -> workspace; m is a logit
+//                      the row has had, close enough to its largest (see reduce below),
+//                      and Z the sum of 2^(s - m)
 //   sweep 2 (colsum) : merge the chunk statistics of a row into one constant
 //                      c_r = m_r + log2 Z_r, recompute S, p = 2^(s - c_r),
 //                      sum p over the rows -> A
 // Both sweeps are one kernel template.  A workgroup owns one chunk of keys of
 // one unit and streams it through LDS in 64-key stages: a ring of four 16 KB
-// buffers filled by direct global->LDS loads issued three stages ahead (no
-// staging registers), 16-byte chunks XOR-swizzled by row so that the
+// buffers (three for units of at most 64 rows) filled by direct global->LDS loads
+// issued as many stages ahead but one (no staging registers), 16-byte chunks XOR-swizzled by row so that the
 // ds_read_b128 fragment loads are conflict free.  Blocks are numbered so that
 // all chunks of a unit run on one XCD (block b lands on XCD b mod 8): the
 // unit's Q rows and chunk statistics are then fetched into one L2 only.  The M rows are split
@@ -334,9 +336,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         const int32_t r = row_base + GROUP_ROWS * rg + 32 * t + c32;
         my_lim[t] = r >= a.rows ? -1 : (a.causal ? nb - W + (r - head_of(r) * W) : nb - 1);
     }
-    // ---- sweep 2: merge the chunk statistics of a row into its constant (before any direct
-    // load is issued: these are ordinary loads, and waiting for them later would also wait for
-    // every direct load issued in between).  Chunks are added in index order, four loads in flight.
+    // ---- sweep 2: merge the chunk statistics of a row into its constant.  These are ordinary loads behind the direct loads of
+    // Q and the first FIRST stages: waiting for them waits for those as well, which the first stage does in any case.  Each half
+    // of the chunks is added in index order, then the two halves.
     if constexpr (COLSUM) {
         constexpr int ROWS = GROUP_ROWS * RG, PARTS = THREADS / ROWS;
         static_assert(PARTS == 2, "two threads per row");
@@ -767,7 +769,8 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
     a.backwards = !a.lse && rounds;
     // Keys that will not be read again are loaded with the streaming hint, which leaves less to evict: those of the only or the
     // second sweep, and in the first all but the last LLC_BYTES, which the second will begin with - of the last units or, where all
-    // run at once, of the last stages of each.  (Two sweeps, 128 rows, us: 256 units of 16 384 keys 396 -> 379, ragged 2048 of
+    // run at once, of the last stages of each.  (Counted as if every sequence had n keys.  The last units of a ragged batch are
+    // its shortest: of 2048 units of 2048..16384 keys some 40 MB are kept, not 256.)  (Two sweeps, 128 rows, us: 256 units of 16 384 keys 396 -> 379, ragged 2048 of
     // 2048..16384 1815 -> 1739, ragged 1024 of 1500..3001 238 -> 228; one sweep: 256 units of 4096 keys 59 -> 52, of 16 384
     // 208 -> 195.  Streaming both sweeps of 256 units of 4096 keys: 5 % slower.)  Not below SMALL_BYTES, where the keys may
     // be in the caches (64 units of 4096 keys 31 -> 33), and not the first sweep of 256 rows, which is bound by arithmetic
@@ -805,7 +808,8 @@ int32_t padded_rows(int32_t rows)
 }
 
 struct ScorePlan {
-    int32_t rows, rows_pad, chunk_keys, nchunks;
+    int32_t rows, rows_pad;
+    int32_t chunk_keys, nchunks;       // chunks per unit, and what one has of a sequence of n keys (a shorter one is divided by as many)
     int64_t units;
 };
 
