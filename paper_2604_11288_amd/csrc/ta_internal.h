@@ -35,6 +35,9 @@ private:
     uint64_t done_ = 0;
 };
 
+// Compute units of the device that the process first asked for (MI355X: 256); what the launch rules count workgroups against.
+int compute_units();
+
 // Kernel attributes of the select and decode kernels (dynamic LDS above 64 KB) for the current
 // device; called by their launchers and by ta_init.
 hipError_t select_setup();

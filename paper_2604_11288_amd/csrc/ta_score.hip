@@ -42,6 +42,20 @@
 
 namespace ta {
 
+int compute_units()
+{
+    static std::atomic<int> cached{0};                     // callers on several threads may race to fill it
+    int cu = cached.load(std::memory_order_relaxed);
+    if (cu == 0) {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cu < 1)
+            cu = 256;                                      // MI355X
+        cached.store(cu, std::memory_order_relaxed);
+    }
+    return cu;
+}
+
 namespace {
 
 constexpr int STAGE_KEYS = 64;
@@ -706,20 +720,6 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
             }
         }
     }
-}
-
-int compute_units()
-{
-    static std::atomic<int> cached{0};                     // callers on several threads may race to fill it
-    int cu = cached.load(std::memory_order_relaxed);
-    if (cu == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cu < 1)
-            cu = 256;                                      // MI355X
-        cached.store(cu, std::memory_order_relaxed);
-    }
-    return cu;
 }
 
 template <int RG, int RT, bool COLSUM, bool STREAM, bool PASSES>

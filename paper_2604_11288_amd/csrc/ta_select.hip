@@ -520,13 +520,24 @@ constexpr int SR_BINS = 2048;
 constexpr int SR_CAND = 256;                                 // members of a bin that are ranked one against the other
 
 // Rows moved by the workgroup that selects them: one launch fewer, some 2 us, but a workgroup moves no more than one compute
-// unit can.  So budgets up to 256 (a layer's 8 units of 4096 positions, whole pass in us, launch of its own / here: 16 rows 23.1 /
-// 20.6, 128 rows 25.2 / 22.9, 256 rows 24.7 / 23.6, but 512 rows 25.0 / 27.5), and any where the units are about as many as
-// the compute units (256 units of 4096 positions, 1024 rows 146.2 / 144.4; 192 of 8192 194.8 / 192.7; 128 of 4096 82.3 / 88.2).
-// With more units than that the launch of its own spreads the rows better (512 of up to 3001 positions, 64 rows 133.4 / 136.0).
+// unit can, and each has one to itself.  Whole pass in us, launch of its own / here, 256 compute units:
+//   more units than compute units: never.  The last of them select and move in a second round (4096 positions, 64 rows: 256
+//     units 107.9 / 106.4, 264 132.0 / 133.1; 1024 rows: 256 141.6 / 139.0, 264 164.5 / 174.1; ragged 1500..3001, 64 rows: 256
+//     69.4 / 67.6, 288 89.4 / 91.4).
+//   at least three quarters of them: any budget.  1024 rows, 4096 positions: 128 units 80.6 / 87.1, 160 95.9 / 98.7, 176 110.1 /
+//     111.9, 192 114.9 / 113.6, 224 128.2 / 126.4; 8192 positions: 144 144.7 / 146.0, 176 174.3 / 173.9, 192 184.4 / 182.5;
+//     2048 positions, half of them kept: 176 82.2 / 83.1, 192 86.2 / 86.5, 240 97.8 / 95.1.  (Fewer rows break even
+//     earlier, ragged lengths later: 512 rows 160 83.2 / 83.8, 176 97.3 / 96.6; 1500..3001 positions, 1024 rows 192 89.3 / 91.1,
+//     224 94.5 / 94.5, 256 103.9 / 102.3.)
+//   fewer: up to 256 rows.  64 rows, 4096 positions: 64 units 40.5 / 38.9, 128 61.9 / 60.4; 256 rows: 8 units 23.9 / 23.9, 32 31.4 /
+//     32.2, 128 65.0 / 65.3, 160 80.9 / 79.8; 320 rows: 8 units 23.6 / 24.5, 32 31.6 / 34.2; 512 rows: 16 units 26.5 / 29.5.
 constexpr int SR_GATHER_MAX_K = 2048;                      // the list passes through the histogram's memory
 constexpr int SR_GATHER_FEW_K = 256;
-constexpr int SR_GATHER_MIN_UNITS = 192, SR_GATHER_MAX_UNITS = 256;
+bool gathers_here(int64_t units, int32_t K)
+{
+    const int64_t cus = compute_units();
+    return units <= cus && K <= (4 * units >= 3 * cus ? SR_GATHER_MAX_K : SR_GATHER_FEW_K);
+}
 
 struct SelectRegLds {
     uint32_t hist[32 * 65];                                  // bin b at (b % 32) * 65 + b / 32: 64 lanes read a row of it at once; then the list to gather
@@ -1671,7 +1682,7 @@ hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* s
             hipLaunchKernelGGL(kernel, dim3(blocks), dim3(SR_THREADS), 0, st, a, g);
         };
         const std::false_type plain{};
-        const bool fits = job && !capped && !(job->table && job->Kin_l) && units <= SR_GATHER_MAX_UNITS && K <= (units >= SR_GATHER_MIN_UNITS ? SR_GATHER_MAX_K : SR_GATHER_FEW_K);
+        const bool fits = job && !capped && !(job->table && job->Kin_l) && gathers_here(units, K);
         if (fits) {
             *gathered = true;
             if (job->table) run(plain, std::integral_constant<int, GATHER_PAGED>{}, *job);
