@@ -167,7 +167,7 @@ select_kernel(SelectArgs a)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    // Same block -> unit order as the score step: A is then read from the L2 that holds it.
+    // Same block -> unit order as the score step: A is read from the L2 that wrote it (unless the second sweep went backwards).
     const int32_t place = (int32_t)blockIdx.x;
     if (place >= a.units) return;
     const int32_t unit = __builtin_amdgcn_readfirstlane(unit_at(place, a.seq_len, a.batch, a.hkv, a.units));
@@ -588,7 +588,7 @@ select_reg_kernel(SelectArgs a, std::conditional_t<GATHER != GATHER_NONE, Compac
     __shared__ __align__(16) SelectRegLds L;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    // Same block -> unit order as the score step: A is then read from the L2 that holds it.
+    // Same block -> unit order as the score step: A is read from the L2 that wrote it (unless the second sweep went backwards).
     const int32_t place = (int32_t)blockIdx.x;
     if (place >= a.units) return;
     const int32_t unit = __builtin_amdgcn_readfirstlane(unit_at(place, a.seq_len, a.batch, a.hkv, a.units));
