@@ -48,17 +48,19 @@ SCORE_TRAFFIC = {
     "c4_long_context": {      # profiles/evict_pass_c4_long_context_K1024.txt
         "bytes_per_step": 69.40e9,
         "sources": {
-            "ta_score.hip": "d586b676b008b66c77dcd736a4dda21b8437eed7104d9782f522f756f6b1b06c",
-            "ta_score_common.h": "3e4b78495a5669b06b80090303e2ac50ab9622f4b9ead1de520e8aee81424db4",
-            "ta_match_device.h": "37bdb219a8d33ec055dec043135dc59baa6bb3078a260fc18fd0d5fdc3f6b979",
+            "ta_score.hip": "8c972c5ac6a32788f9a60e1e679db3445405c1cc76480813ec1397509f5bceda",
+            "ta_score_common.h": "63db8ddf5fa51de1c9c0bba8099d89dd4e23ca91ac5c5163b227273ce568d4e2",
+            "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
+            "ta_order.h": "1a77538c7a7256d587852a368d83bc1fc94c7e4666c07d0a6da1a535f7435ffa",
         },
     },
     "c2_full_model": {        # profiles/score_two_sweep_c2_full_model_K1024.txt
         "bytes_per_step": 559.4e6,
         "sources": {
-            "ta_score.hip": "d586b676b008b66c77dcd736a4dda21b8437eed7104d9782f522f756f6b1b06c",
-            "ta_score_common.h": "3e4b78495a5669b06b80090303e2ac50ab9622f4b9ead1de520e8aee81424db4",
-            "ta_match_device.h": "37bdb219a8d33ec055dec043135dc59baa6bb3078a260fc18fd0d5fdc3f6b979",
+            "ta_score.hip": "8c972c5ac6a32788f9a60e1e679db3445405c1cc76480813ec1397509f5bceda",
+            "ta_score_common.h": "63db8ddf5fa51de1c9c0bba8099d89dd4e23ca91ac5c5163b227273ce568d4e2",
+            "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
+            "ta_order.h": "1a77538c7a7256d587852a368d83bc1fc94c7e4666c07d0a6da1a535f7435ffa",
         },
     },
 }

@@ -751,6 +751,9 @@ constexpr int LOOP_SPL = 5;                                // slots per lane and
 // 23.0 / 19.4, 4096 units 63.7 / 55, 16 384 units 225 / 201; 129 slots, 4096 units 36.6 / 34.6; 65 slots, 4096 units 22.1 /
 // 24.5; 701 slots, 1024 units 48.1 / 38; 1501 slots, 2048 units 198 / 125).  More wavefronts with fewer slots per lane where
 // a budget leaves the choice (1025 slots, 256 units: four wavefronts 20.4, eight 19.3; 601 slots: 14.9, 15.3).
+// Paged slots follow the same lines (16 per page: 257 slots, 256 units 20.7 / 12.9, 4096 units 64.8 / 60.8; 193 slots, 16 384 units
+// 169.5 / 164.6; 513 slots 427.7 / 416.7); at 16 384 units of 257 slots they lose 1 % to 4 % (219.5 / 222.0, after prompts of up
+// to 16 384 positions 227 / 237).
 static_assert(TA_MAX_DECODE_K + 1 <= 8 * 4 * 64, "the widest form");
 constexpr int FEW_UNITS = 512;
 UnitForm unit_form(bool scored, int slots, int64_t units)
