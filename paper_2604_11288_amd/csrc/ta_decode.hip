@@ -312,7 +312,8 @@ __device__ __forceinline__ s16x4 hi_half(const uint4& v)
 
 // A unit is the work of one workgroup of WAVES wavefronts.  SMALL: at most WAVES * SPL * 64 slots, so a
 // lane's slots (position, voucher, flags, accumulated attention) stay in its registers from the
-// first round trip to the ranking and nothing loops over slots.
+// first round trip to the ranking and nothing loops over slots; without it (more slots than a lane holds, and no
+// attention term) one wavefront loops over them.
 // DT_RING: 16-row key tiles in flight per wavefront.
 // WAVES == 1: no workgroup barriers.
 // WAVES > 1 (one wavefront would stream a unit's keys one tile after the other): each wavefront has SPL * 64 of
@@ -325,7 +326,8 @@ template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES, i
 __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& pg)
 {
     extern __shared__ float s_dyn[];
-    static_assert(WAVES == 1 || (SCORED && SMALL), "several wavefronts: an attention term, slots in registers");
+    static_assert(WAVES == 1 || SCORED, "several wavefronts: an attention term");
+    static_assert(SMALL || !SCORED, "with an attention term a unit's slots are in registers");
 
     const int lane = threadIdx.x & 63;
     const int wave = WAVES > 1 ? (int)(threadIdx.x >> 6) : 0;
@@ -586,54 +588,31 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         // wavefronts: each takes every WAVES-th head (a head's reduction runs in one wavefront, in the
         // single wavefront's order) and the results are exchanged through LDS.
         const auto mine = [&](int h) { return h < G && (WAVES == 1 || h % WAVES == wave); };
-        if (SMALL) {
-            // a head's logits in registers, all requested at once (a loop over the slots, one LDS round trip per 64 of them and
-            // pass, took 4.2 of the 18.7 us of a unit of 1025 slots); lanes past the last slot add exp2(-inf) = 0
-            constexpr int NV = WAVES * SPL;
-            const auto one_head = [&](int h, float& m, float& inv) {
-                float lg[NV];
+        // a head's logits in registers, all requested at once (a loop over the slots, one LDS round trip per 64 of them and
+        // pass, took 4.2 of the 18.7 us of a unit of 1025 slots); lanes past the last slot add exp2(-inf) = 0
+        constexpr int NV = WAVES * SPL;
+        const auto one_head = [&](int h, float& m, float& inv) {
+            float lg[NV];
 #pragma unroll
-                for (int j = 0; j < NV; ++j) {
-                    const int s = lane + 64 * j;
-                    const float x = s_w[h * wstride + (s < slots ? s : slots - 1)];
-                    lg[j] = s < slots ? x : -INFINITY;
-                }
-                m = lg[0];
-#pragma unroll
-                for (int j = 1; j < NV; ++j) m = fmaxf(m, lg[j]);
-                m = wave_max_dpp(m);
-                float z = 0.0f;
-#pragma unroll
-                for (int j = 0; j < NV; ++j) z += __builtin_amdgcn_exp2f(lg[j] - m);
-                inv = __builtin_amdgcn_rcpf(wave_sum_dpp(z));
-            };
-#pragma unroll
-            for (int h = 0; h < GH; ++h) {
-                m_h[h] = -INFINITY;
-                inv_h[h] = 0.0f;
-                if (mine(h)) one_head(h, m_h[h], inv_h[h]);
+            for (int j = 0; j < NV; ++j) {
+                const int s = lane + 64 * j;
+                const float x = s_w[h * wstride + (s < slots ? s : slots - 1)];
+                lg[j] = s < slots ? x : -INFINITY;
             }
-        } else {
+            m = lg[0];
 #pragma unroll
-            for (int h = 0; h < GH; ++h) m_h[h] = -INFINITY;
-            for (int s = lane; s < slots; s += 64) {
+            for (int j = 1; j < NV; ++j) m = fmaxf(m, lg[j]);
+            m = wave_max_dpp(m);
+            float z = 0.0f;
 #pragma unroll
-                for (int h = 0; h < GH; ++h)
-                    if (mine(h)) m_h[h] = fmaxf(m_h[h], s_w[h * wstride + s]);
-            }
+            for (int j = 0; j < NV; ++j) z += __builtin_amdgcn_exp2f(lg[j] - m);
+            inv = __builtin_amdgcn_rcpf(wave_sum_dpp(z));
+        };
 #pragma unroll
-            for (int h = 0; h < GH; ++h)
-                if (mine(h)) m_h[h] = wave_max_dpp(m_h[h]);
-            float z_h[GH];
-#pragma unroll
-            for (int h = 0; h < GH; ++h) z_h[h] = 0.0f;
-            for (int s = lane; s < slots; s += 64) {
-#pragma unroll
-                for (int h = 0; h < GH; ++h)
-                    if (mine(h)) z_h[h] += __builtin_amdgcn_exp2f(s_w[h * wstride + s] - m_h[h]);
-            }
-#pragma unroll
-            for (int h = 0; h < GH; ++h) inv_h[h] = mine(h) ? __builtin_amdgcn_rcpf(wave_sum_dpp(z_h[h])) : 0.0f;
+        for (int h = 0; h < GH; ++h) {
+            m_h[h] = -INFINITY;
+            inv_h[h] = 0.0f;
+            if (mine(h)) one_head(h, m_h[h], inv_h[h]);
         }
         if (WAVES > 1) {
             static_assert(WAVES == 1 || GH <= 16, "the exchange area holds 16 heads");
@@ -692,7 +671,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     for (int j = 0; SMALL && j < SPL; ++j) rank_slot(sbase + lane + 64 * j, p0[j], v0[j], fl0[j], a0[j]);
     for (int s0 = lane; !SMALL && s0 < slots; s0 += SPL * 64) {    // more slots than a lane's registers hold
         int32_t p4[SPL];
-        float v4[SPL], a4[SPL];
+        float v4[SPL];
         uint8_t fl4[SPL];
 #pragma unroll
         for (int j = 0; j < SPL; ++j) {
@@ -701,15 +680,9 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
             const int32_t pc = p4[j] < 0 ? 0 : p4[j];
             v4[j] = vouch[pc];
             fl4[j] = spons[pc];
-            if (SCORED) {
-                const float av = A[s < slots ? s : slots - 1];
-                a4[j] = (!a.last_query && p4[j] >= 0 && s != f) ? av : 0.0f;
-            } else {
-                a4[j] = 0.0f;
-            }
         }
 #pragma unroll
-        for (int j = 0; j < SPL; ++j) rank_slot(s0 + 64 * j, p4[j], v4[j], fl4[j], a4[j]);
+        for (int j = 0; j < SPL; ++j) rank_slot(s0 + 64 * j, p4[j], v4[j], fl4[j], 0.0f);
     }
     nfree = wave_sum_dpp(nfree);
     worst = wave_min_dpp(worst);
@@ -738,8 +711,8 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     if (wave == 0 && lane == 0 && a.evicted) a.evicted[unit] = evict_pos;
 }
 
-// How a unit's slots are spread: over `waves` wavefronts with `spl` slots per lane in registers; spl 0: one wavefront that
-// loops over its slots.
+// How a unit's slots are spread: over `waves` wavefronts with `spl` slots per lane in registers; spl 0 (no attention term): one
+// wavefront that loops over its slots.
 struct UnitForm {
     int waves, spl;
 };
@@ -764,7 +737,7 @@ UnitForm unit_form(bool scored, int slots, int64_t units)
     if (slots <= 512) return {4, 2};
     if (slots <= 768) return {4, 3};
     if (slots <= 1536) return {8, 3};
-    return {8, 4};                                         // at most 2048 slots; {1, 0} where the LDS does not hold the logits as well
+    return {8, 4};                                         // at most 2048 slots
 }
 
 // Key tiles in flight: two per wavefront where wavefronts share a unit - enough with all that then share a compute unit, and the
@@ -790,8 +763,7 @@ UnitKernel unit_kernel(bool scored, UnitForm f)
         case 4 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 4, 2>;
         case 4 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 4, 3>;
         case 8 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 8, 3>;
-        case 8 * 8 + 4: return decode_unit_kernel<GH, PAGED, true, true, 8, 4>;
-        default: return decode_unit_kernel<GH, PAGED, true, false, 1, LOOP_SPL>;
+        default: return decode_unit_kernel<GH, PAGED, true, true, 8, 4>;
     }
 }
 
@@ -825,7 +797,7 @@ hipError_t unit_attributes()
 {
     // dynamic LDS above 64 KB (large budgets with an attention term) needs the attribute
     hipError_t e = hipSuccess;
-    for (const UnitForm f : {UnitForm{1, 2}, UnitForm{2, 2}, UnitForm{4, 2}, UnitForm{4, 3}, UnitForm{8, 3}, UnitForm{8, 4}, UnitForm{1, 0}})
+    for (const UnitForm f : {UnitForm{1, 2}, UnitForm{2, 2}, UnitForm{4, 2}, UnitForm{4, 3}, UnitForm{8, 3}, UnitForm{8, 4}})
         for (const UnitKernel k : {unit_kernel<GH, false>(true, f), unit_kernel<GH, true>(true, f)})
             if (e == hipSuccess)
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -918,15 +890,14 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
     const size_t page_list = st.pages ? (size_t)((slots - 1) / pg.page_size + 1) : 0;      // the pages of the unit's slots
     // per wavefront a key tile and the new key row; several wavefronts: 64 words more
     const auto scored_floats = [&](int waves) { return wstride + (1024 + 64) * (size_t)waves + (waves > 1 ? 64 : 0) + (size_t)G * wstride; };
-    UnitForm form = unit_form(prm.alpha != 0.0f, slots, units);
-    if (form.waves > 1 && (scored_floats(form.waves) + page_list) * sizeof(float) > 160 * 1024) form = {1, 0};
+    const UnitForm form = unit_form(prm.alpha != 0.0f, slots, units);
     size_t lds_floats = prm.alpha != 0.0f ? scored_floats(form.waves) : wstride;
     a.pg_off = (int32_t)lds_floats;
     a.units = (int32_t)units;
     a.decay = prm.budget_decay;
     lds_floats += page_list;
     const size_t lds = lds_floats * sizeof(float);
-    if (lds > 160 * 1024) return hipErrorInvalidValue;
+    if (lds > 160 * 1024) return hipErrorInvalidValue;      // (a unit's logits are at most 15 360: 113 KB in all)
     const hipError_t attr_err = decode_setup();
     if (attr_err != hipSuccess) return attr_err;
     // the units, then one workgroup per 256 positions for the budget decay
