@@ -228,7 +228,7 @@ def test_decode_large_budget_eight_heads_per_group():
 
 
 def test_decode_budget_of_a_thousand_rows_four_wavefronts_per_unit():
-    # 1001 slots: past the register-resident budget of one wavefront, within that of four
+    # 1001 slots: eight wavefronts per unit with three slots per lane (two per lane hold 512 slots in four)
     w = wl.scaled(wl.CONFIGS["c5_agentic_prefill"], layers=2, batch=2, n=1300, hq=8, hkv=2, ragged=(900, 1300))
     ev, _ = _run_decode(w, K=1000, steps=6, p_anchor=0.2, check_every=2)
     assert ev > 0
@@ -297,10 +297,10 @@ def test_decode_last_query_rule(rank):
     (64, True, False, 64, 36, 8),      # [pages][heads][64][d]
     (24, False, True, 64, 36, 8),      # a page size that is no power of two; rows compacted straight into the pages
     (128, True, True, 64, 36, 8),      # all slots of a unit in one page
-    (16, False, True, 400, 8, 8),      # more slots than one wavefront keeps in registers: four wavefronts per unit
+    (16, False, True, 400, 8, 8),      # 401 slots over 26 pages
     (16, False, False, 64, 10, 16),    # 8 query heads per KV head
     (16, False, True, 400, 6, 16),
-    (16, True, True, 1000, 4, 8),      # 1001 slots: four wavefronts per unit at any number of units
+    (16, True, True, 1000, 4, 8),      # 1001 slots: eight wavefronts per unit
     (32, True, True, 64, 10, 32),      # 16 query heads per KV head (512 query rows per unit in the prefill)
 ])
 def test_decode_over_a_paged_slot_pool(page_size, heads_first, in_place, K, steps, hq):
@@ -344,11 +344,13 @@ def test_compact_into_pages_touches_nothing_else():
 
 
 @pytest.mark.parametrize("paged", [None, (16, False)])
-@pytest.mark.parametrize("K,big,n", [(400, 96, 1024),      # four wavefronts per unit against one (768 units)
-                                     (1400, 136, 1600)])   # eight against one (1088 units)
+@pytest.mark.parametrize("K,big,n", [(400, 96, 1024),      # four wavefronts per unit on both sides (768 units)
+                                     (1400, 136, 1600),    # eight on both (1088 units)
+                                     (100, 96, 600),       # four against one
+                                     (200, 96, 700)])      # four against two
 def test_several_wavefronts_per_unit_give_the_single_wavefronts_bits(paged, K, big, n):
-    """Few units with more slots than one wavefront keeps in registers run several wavefronts per unit.  The
-    same sequence alone (8 units) and as every member of a large batch (one wavefront per unit) must leave
+    """The number of wavefronts per unit follows the slots and, at small budgets, the number of units.  The
+    same sequence alone (8 units) and as every member of a large batch must leave
     the same state, bit for bit, after the same steps."""
     steps = 6
     w1 = wl.scaled(wl.CONFIGS["c2_full_model"], layers=1, batch=1, n=n, planted=4)
@@ -387,6 +389,15 @@ def test_several_wavefronts_per_unit_give_the_single_wavefronts_bits(paged, K, b
     for x1, xb in zip(*states):
         assert _same_bits(x1, xb)
     assert (states[0][4] >= 0).any()                      # slots were evicted on the way
+
+
+@pytest.mark.parametrize("paged", [None, (1, False)])
+@pytest.mark.parametrize("K,hq", [(959, 16), (1919, 8)])
+def test_decode_as_many_logits_as_a_unit_may_have(K, hq, paged):
+    # heads x slots = 15 360, with eight wavefronts' key tiles (and a page list of one slot per page) in the LDS beside them
+    w = wl.scaled(wl.CONFIGS["c5_agentic_prefill"], layers=1, batch=2, n=K + 20, hq=hq, hkv=1, window=8, planted=2, ragged=(K - 2, K + 20))
+    ev, _ = _run_decode(w, K=K, steps=3, p_anchor=0.1, paged=paged)
+    assert ev > 0
 
 
 @pytest.mark.parametrize("paged", [None, (16, False)])

@@ -63,7 +63,7 @@ def test_captured_pass_replays_to_the_eager_result(form):
             assert torch.equal(got, ref), (form, replay)
 
 
-@pytest.mark.parametrize("K", [120, 400])                  # 400: more slots than a wavefront's registers hold - four wavefronts per unit
+@pytest.mark.parametrize("K", [120, 400])                  # 121 and 401 slots: four wavefronts per unit, half and nearly all of their registers' slots
 def test_captured_decode_step_replays_like_eager_steps(K):
     # one generation step captured once; before every replay the step's inputs are copied into the
     # captured buffers.  Two states from the same prefill, one stepped eagerly, one by replays.

@@ -196,16 +196,16 @@ def test_score_c1_shape():
 
 
 @pytest.mark.parametrize("n,hq,hkv,window,causal", [
-    (1000, 8, 2, 32, True),       # ragged last stage (n not a multiple of 64), 2 chunks
+    (1000, 8, 2, 32, True),       # ragged last stage (n not a multiple of 64), 8 chunks of two stages
     (1000, 8, 2, 32, False),      # no mask
     (700, 6, 2, 5, True),         # 15 rows: padded row tile, rows of one tile span several heads
     (1500, 8, 2, 64, True),       # 256 rows: two row tiles per wavefront
     (600, 16, 2, 64, True),       # 512 rows: two passes of 256 rows over each chunk
-    (2500, 10, 2, 64, True),      # 320 rows: the second pass has 64 live rows; two chunks
+    (2500, 10, 2, 64, True),      # 320 rows: the second pass has 64 live rows; 20 chunks
     (64, 4, 1, 64, True),         # window as long as the context
     (33, 4, 4, 1, True),          # one query row per head
-    (8192, 4, 1, 32, True),       # 128 rows, 4 chunks of 2048 keys
-    (8300, 4, 1, 32, True),       # ragged last chunk and last stage
+    (8192, 4, 1, 32, True),       # 128 rows, 32 chunks of 256 keys
+    (8300, 4, 1, 32, True),       # 26 chunks of 320 keys, ragged last chunk and last stage
     (4096, 4, 1, 32, False),      # no mask at the headline context length
 ])
 def test_score_shapes(n, hq, hkv, window, causal):
@@ -227,7 +227,7 @@ def test_score_chunks_past_the_sequence_end():
 
 
 def test_score_long_context_chunking():
-    # 40000 keys: chunks of 2048 keys, 20 chunks whose statistics are merged
+    # 40000 keys: 32 chunks of 1280 keys whose statistics are merged
     w = wl.scaled(wl.CONFIGS["c4_long_context"], layers=1, batch=1, n=40000, hq=4, hkv=1, window=64)
     _check_score(w)
 
@@ -336,7 +336,7 @@ def _select_case(n, K, ns, nr, alpha, A, td, b=0, seq_len=None, beta=0.5, gamma=
     (4096, 256, 4, 4, 8, "zeros"),       # A == 0 everywhere: recency decides
     (5000, 300, 0, 0, 8, "uniform"),     # no mandatory class
     (1000, 2000, 4, 4, 4, "uniform"),    # K >= n: keep everything
-    (40000, 1024, 4, 128, 60, "uniform"),  # keys do not fit LDS: recomputed per pass
+    (40000, 1024, 4, 128, 60, "uniform"),  # rows longer than a workgroup's registers hold: the streaming form
     (33000, 512, 4, 64, 32, "ties"),
 ])
 def test_select_bit_exact_given_same_scores(n, K, ns, nr, planted, mode):

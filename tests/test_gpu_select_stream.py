@@ -1,11 +1,12 @@
 """The streaming form of step 4 (one read of every input, candidate list in LDS) against the oracle.
 
-ta_select picks that form for rows longer than its LDS key cache and for launches of many units;
+ta_select picks that form for rows longer than a workgroup's registers hold and for launches of many units;
 these cases reach it at sizes the oracle finishes in seconds, on inputs chosen to drive its
 branches: repeated cuts of the list (utilities that grow towards the start of the sequence, so
 every segment of the walk beats the threshold), thousands of exact ties (position passes), pool
 overflow, no mandatory class, ragged lengths below and above the budget, per-layer budgets, and
-budgets whose list does not fit (those fall back to the cached kernel and must agree as well).
+budgets whose list does not fit (those fall back to the kernel that recomputes its keys and must agree as well).
+The register form, which takes the shorter rows of fewer units, is tested at its limits further down.
 """
 import numpy as np
 import pytest
@@ -83,7 +84,7 @@ def _check(layers, batch, hkv, n, K, ns, nr, mode, planted=8, ragged=None, beta=
     (3000, 700, 4, 64, "early", 8),      # every segment of the walk beats the threshold: a cut per segment
 ])
 def test_streaming_select_many_units(n, K, ns, nr, mode, planted):
-    # 16 x 16 x 8 = 2048 units: enough for ta_select to take the streaming form on short rows
+    # 16 x 16 x 8 = 2048 units: ta_select takes the streaming form on short rows from 1024 on
     checked = _check(16, 16, 8, n, K, ns, nr, mode, planted=planted, sample=300)
     assert checked >= 300
 
@@ -108,7 +109,7 @@ def test_streaming_select_per_layer_budgets():
     (70000, 1024, "early"),              # long rows, dozens of cuts of the list
     (131072, 1024, "uniform"),           # the long-context row length
     (50000, 4000, "ties"),               # list of more than 4000 entries
-    (40000, 7000, "uniform"),            # the list would not fit: cached-kernel fallback, same answer
+    (40000, 7000, "uniform"),            # the list would not fit: keys recomputed in every pass, same answer
 ])
 def test_streaming_select_long_rows(n, K, mode):
     _check(1, 2, 3, n, K, 4, 128, mode, planted=40)
