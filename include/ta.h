@@ -576,9 +576,11 @@ int32_t ta_decode_step(const ta_decode_state *st, const int32_t *new_tok, const 
 
 /*
  * ta_decode_step with the same results, as one launch instead of two where that is faster.
- *   sync int32 [batch][TA_DECODE_SYNC_WORDS] (DEVICE), or NULL: ta_decode_step.  Words of the state's own in which
- *   the workgroups of a launch count what has been read.  All zero before a state's first step; every step leaves them
- *   zero again.  Calls that may overlap must not share them, as they must not share the state.
+ *   sync int32 [batch][TA_DECODE_SYNC_WORDS] (DEVICE, on an 8-byte boundary, else: ta_decode_step), or NULL:
+ *   ta_decode_step.  Words of the state's own in which the workgroups of a launch count what has been read.  All
+ *   zero before a state's first step (with others a sequence may stay as it is); every step leaves them zero again.
+ *   Calls that may overlap must not share them, as they must not share the state.  Steps of different states may
+ *   overlap: no workgroup waits for another.
  * Errors: as ta_decode_step.
  */
 #define TA_DECODE_SYNC_WORDS 288

@@ -291,16 +291,20 @@ struct UnitArgs {
     float decay;
 };
 
-// A step as one launch (FUSED below): what its sequence part works with, and the words through which the units of a sequence tell
-// the workgroups that append and decay that they have read what those overwrite.
+// A step as one launch (FUSED below): what its sequence part works with, and the words in which the workgroups of a sequence count
+// themselves once they have read the length, which the last of them moves on.
 constexpr int NEAR_SPAN = 7;                               // positions before its own whose flags a slot's one 8-byte load brings
-constexpr int SYNC_LINES = 8;                              // lines of 32 words on which a sequence's units count, then one for the workgroups that are done
+constexpr int SYNC_LINES = 8;                              // lines of 32 words on which a sequence's units count, then one for the lines that are complete and the trailing workgroups
 constexpr int SYNC_WORDS = (SYNC_LINES + 1) * 32;          // of a sequence: one line took 1 to 5 us per step, the units' additions following one another
+constexpr int MAX_TILES = 32;
+constexpr int TILE_PER = 4;                                // positions of a thread in flight
 static_assert(SYNC_WORDS == TA_DECODE_SYNC_WORDS, "as the header states it");
 struct StepArgs {
     const int32_t* new_tok;
     int32_t* sync;                                         // [batch][SYNC_WORDS], zero between steps
     int32_t per_seq;                                       // units of a sequence
+    int32_t tiles, tile_shift;                             // tiles of 1 << tile_shift positions
+    int32_t parts;                                         // what the last line counts up to
     int32_t L;                                             // at most NEAR_SPAN
     unsigned long long span;                               // the bytes of a slot's eight flags that its L predecessors are
     float pw[NEAR_SPAN + 1];
@@ -339,62 +343,113 @@ __device__ __forceinline__ bool is_anchor(const AnchorTest& t, int32_t p)
 // units of a sequence that count on a line
 __device__ __forceinline__ int32_t units_on(int32_t per_seq, int32_t line) { return (per_seq - line + SYNC_LINES - 1) / SYNC_LINES; }
 
-// Trailing workgroups of the one-launch form: the append, and the budget decay of 4 positions per thread.  They overwrite what the
-// units read, so they request their own inputs, wait until every unit of the sequence has counted itself in, and write then.
-// Units have lower block numbers and wait for nobody, so the wait ends; should something else be using the words, it ends all the
-// same after some seconds, with nothing written.  The last one of a sequence appends (the others read the length) and sets the words
-// back to zero.  No fence is needed: what a unit has read is in its registers when it counts.
-template <int THREADS>
-__device__ __forceinline__ void append_and_decay(const ta_decode_state& st, const StepArgs& f, int r, float decay, int32_t* s_x)
+// The last line's first two words, as one: below, how many lines are complete and how many tiles of positions have read the length; above, a bit
+// per tile, set once its vouchers are in memory.
+__device__ __forceinline__ unsigned long long* total_of(const StepArgs& f, int b)
 {
-    const int tiles = (st.cap + 4 * THREADS - 1) / (4 * THREADS);
-    const int b = r / tiles, tile = r - b * tiles;
-    const int tid = (int)threadIdx.x, lane = tid & 63;
-    const size_t row = (size_t)b * st.cap;
-    const int32_t p_new = st.len[b];
+    return reinterpret_cast<unsigned long long*>(f.sync + (size_t)b * SYNC_WORDS + 32 * SYNC_LINES);
+}
+__device__ __forceinline__ uint32_t vouched(unsigned long long total) { return (uint32_t)(total >> 32); }
+__device__ __forceinline__ bool completes(const StepArgs& f, unsigned long long total) { return (int32_t)(uint32_t)total == f.parts - 1; }
+
+// Append of a sequence in the one-launch form, by the first wavefront of whichever of its workgroups counts in last.  The length is all that it
+// overwrites and others read (the new position's token, flag and budget are nothing to them, the flag that they test themselves).  Sets the
+// words back to zero.  p_new: the length before the step; t0: the token; an: is it an anchor there.
+__device__ __forceinline__ void append(const ta_decode_state& st, const StepArgs& f, int b, int32_t p_new, int32_t t0, bool an, float decay)
+{
+    const int lane = (int)threadIdx.x;
+    if (lane < SYNC_LINES) __hip_atomic_store(&f.sync[(size_t)b * SYNC_WORDS + 32 * lane], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane != 0) return;
+    __hip_atomic_store(total_of(f, b), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const bool live = p_new >= 0 && p_new < st.cap;        // else: at capacity, left alone
+    if (live) {
+        const size_t o = (size_t)b * st.cap + p_new;
+        st.tok[o] = t0;
+        st.anchor[o] = an ? 1 : 0;
+        st.budget[o] = __fmul_rn(decay, an ? f.B : 0.0f);
+        st.len[b] = p_new + 1;
+    }
+    st.stepped[b] = live ? (p_new + 1) | (an ? (1 << 30) : 0) : 0;
+}
+
+// Trailing workgroups of the one-launch form: the vouchers of a tile of positions, then the decay of its budgets.  Units may need those
+// budgets, and may run before or after, but nobody waits for anybody, whatever else the chip runs and wherever workgroups are placed (steps
+// of other states may overlap: one that waited could hold the place of the one it waits for).  A budget is overwritten only once all vouchers
+// that are computed from it are in memory, which their tile's bit says: a unit that needs a voucher adds the budgets up, then looks at the
+// bit of the position's tile, and where it is set takes the voucher that is there (vouchers_of_slots).  The last NEAR_SPAN budgets of a tile
+// belong to vouchers of the next one too: of the two workgroups the one that sets its bit second overwrites them.
+// A chain of five round trips (inputs, vouchers stored, bit set, budgets stored, counted with the bit), some 5 us beside the units' key stream.
+template <int THREADS>
+__device__ __forceinline__ void vouch_and_decay(const ta_decode_state& st, const StepArgs& f, int r, float decay, int32_t* s_x)
+{
+    constexpr int PER = TILE_PER, CHUNK = PER * THREADS;
+    float* s_B = reinterpret_cast<float*>(s_x) + 4;        // budgets of NEAR_SPAN positions and those of a chunk
+    const int b = r / f.tiles, tile = r - b * f.tiles;
+    const int tid = (int)threadIdx.x;
+    const size_t row = (size_t)b * st.cap;
+    const int32_t p_new = st.len[b], t0 = f.new_tok[b];
+    const bool live = p_new >= 0 && p_new < st.cap;        // else: at capacity, left alone
+    const int32_t first = tile << f.tile_shift, end = tile == f.tiles - 1 ? st.cap : first + (1 << f.tile_shift);
+    const uint8_t* anchor = st.anchor + row;
     float* B = st.budget + row;
-    float v[4];
+    const int32_t exist = live ? (end < p_new + 1 ? end : p_new + 1) : first;      // with the appended position
+    int32_t q = first;
+    do {                                                   // one round unless rows are long (the first does not wait for the length)
+        unsigned long long near[PER];
+        float own[PER + 1];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int p = tile * (4 * THREADS) + j * THREADS + tid;
-        v[j] = B[p < st.cap ? p : 0];
-    }
-    int32_t* words = f.sync + (size_t)b * SYNC_WORDS;
-    bool an = false;
-    if (tid < 64) {
-        if (live) an = is_anchor(request_anchor(st, f, b, p_new), p_new);
-        const int32_t want = lane < SYNC_LINES ? units_on(f.per_seq, lane) : 0;
-        bool all = false;
-        for (int32_t spins = 0; !all && spins < (1 << 22); ++spins) {
-            const int32_t have = lane < SYNC_LINES ? __hip_atomic_load(&words[32 * lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-            all = __ballot(have < want) == 0ull;
-            if (!all) __builtin_amdgcn_s_sleep(1);
+        for (int j = 0; j < PER; ++j) {
+            const int32_t p = q + j * THREADS + tid < st.cap ? q + j * THREADS + tid : st.cap - 1;
+            __builtin_memcpy(&near[j], anchor + (p > NEAR_SPAN ? p - NEAR_SPAN : 0), 8);       // (any address; a row has more than NEAR_SPAN)
+            own[j] = B[p];
         }
-        if (lane == 0) s_x[0] = all ? 1 : 0;
-    }
-    asm volatile("" ::"v"(p_new));                        // read in front of the barrier, behind which the workgroup counts
+        own[PER] = B[tid < NEAR_SPAN && q >= NEAR_SPAN ? q - NEAR_SPAN + tid : 0];
+        if (q != first) __syncthreads();                   // the chunk before has been read
+#pragma unroll
+        for (int j = 0; j < PER; ++j) s_B[NEAR_SPAN + j * THREADS + tid] = own[j];
+        if (tid < NEAR_SPAN) s_B[tid] = own[PER];
+        __syncthreads();                                   // the budgets are in LDS
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int32_t p = q + j * THREADS + tid;
+            if (p >= exist) continue;
+            if (p < NEAR_SPAN) near[j] <<= 8 * (NEAR_SPAN - p);
+            float v = 0.0f;
+            if ((near[j] & f.span) != 0ull) {
+#pragma unroll 1
+                for (int k = 1; k <= f.L; ++k)             // increasing distance, as in the fixed-order sum
+                    if (((near[j] >> (8 * (NEAR_SPAN - k))) & 0xFFull) != 0ull) v = __fadd_rn(v, __fmul_rn(s_B[NEAR_SPAN + j * THREADS + tid - k], f.pw[k]));
+            }
+            __hip_atomic_store(&st.vouch[row + p], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        q += CHUNK;
+    } while (q < exist);
+    asm volatile("s_waitcnt vmcnt(0)" ::"v"(p_new) : "memory");                    // this wavefront's vouchers are where every workgroup reads them
     __syncthreads();
-    if (s_x[0] == 0) return;
+    unsigned long long total = 0ull;
+    if (tid == 0) {
+        total = __hip_atomic_fetch_add(total_of(f, b), (1ull << (32 + tile)) + 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_x[0] = (int32_t)vouched(total);
+        s_x[1] = completes(f, total) ? 1 : 0;
+    }
+    __syncthreads();                                       // which tiles' vouchers are done
+    const uint32_t done = (uint32_t)s_x[0];
+    const int32_t from = tile > 0 && (done >> (tile - 1) & 1u) ? first - NEAR_SPAN : first;
+    int32_t to = tile == f.tiles - 1 || (done >> (tile + 1) & 1u) ? end : end - NEAR_SPAN;
+    to = live ? (to < p_new ? to : p_new) : from;          // (the new position's budget comes with the append)
+    const bool kept = end - first <= CHUNK;                // one round: the budgets are in LDS still
+    for (q = from + tid; q < to; q += CHUNK) {
+        float v[PER];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int p = tile * (4 * THREADS) + j * THREADS + tid;
-        if (live && p < p_new) B[p] = __fmul_rn(decay, v[j]);
-    }
-    if (tid >= 64) return;
-    int32_t done = 0;
-    if (lane == 0) done = __hip_atomic_fetch_add(&words[32 * SYNC_LINES], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (__builtin_amdgcn_readfirstlane(done) != tiles - 1) return;
-    if (lane <= SYNC_LINES) __hip_atomic_store(&words[32 * lane], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (lane == 0) {
-        if (live) {
-            st.tok[row + p_new] = f.new_tok[b];
-            st.anchor[row + p_new] = an ? 1 : 0;
-            B[p_new] = __fmul_rn(decay, an ? f.B : 0.0f);
-            st.len[b] = p_new + 1;
+        for (int j = 0; j < PER; ++j) {
+            const int32_t p = q + j * THREADS < to ? q + j * THREADS : q;
+            v[j] = kept ? s_B[NEAR_SPAN + p - first] : B[p];
         }
-        st.stepped[b] = live ? (p_new + 1) | (an ? (1 << 30) : 0) : 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (q + j * THREADS < to) B[q + j * THREADS] = __fmul_rn(decay, v[j]);
     }
+    if (tid < 64 && s_x[1] != 0) append(st, f, b, p_new, t0, live && is_anchor(request_anchor(st, f, b, p_new), p_new), decay);
 }
 
 __device__ __forceinline__ uint32_t ordered_bits(float u)
@@ -446,7 +501,7 @@ __device__ __forceinline__ void flags_of_slots(const UnitArgs& a, const StepArgs
 
 // Behind the barrier that follows: is the new position an anchor, and the slots' vouchers if they decide.
 template <int WAVES, int SPL>
-__device__ __forceinline__ uint8_t vouchers_of_slots(const StepArgs& fs, const float* budget, const int32_t (&p0)[SPL],
+__device__ __forceinline__ uint8_t vouchers_of_slots(const ta_decode_state& st, const StepArgs& fs, int b, const int32_t (&p0)[SPL],
                                                      const unsigned long long (&near)[SPL], float (&v0)[SPL], const int32_t* s_x)
 {
     const uint8_t an_new = (uint8_t)s_x[16];
@@ -454,6 +509,7 @@ __device__ __forceinline__ uint8_t vouchers_of_slots(const StepArgs& fs, const f
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) some |= s_x[8 + w];
     if (some == 0) {                                       // uniform in the workgroup: vouchers decide
+        const float* budget = st.budget + (size_t)b * st.cap;
 #pragma unroll
         for (int j = 0; j < SPL; ++j)
 #pragma unroll 1
@@ -462,8 +518,15 @@ __device__ __forceinline__ uint8_t vouchers_of_slots(const StepArgs& fs, const f
                     v0[j] = __fadd_rn(v0[j], __fmul_rn(budget[p0[j] - k], fs.pw[k]));
             }
 #pragma unroll
-        for (int j = 0; j < SPL; ++j) asm volatile("" : "+v"(v0[j]));
-        __syncthreads();                                   // every wavefront's budgets are in registers
+        for (int j = 0; j < SPL; ++j) asm volatile("" : "+v"(v0[j])::"memory");    // the budgets have been read
+        const uint32_t done = vouched(__hip_atomic_load(total_of(fs, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+#pragma unroll
+        for (int j = 0; j < SPL; ++j)                      // (without a sponsor, free slots among them: zero whatever the tile does)
+            if ((near[j] & fs.span) != 0ull && (done >> (p0[j] >> fs.tile_shift) & 1u))
+                v0[j] = __hip_atomic_load(&st.vouch[(size_t)b * st.cap + p0[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int j = 0; j < SPL; ++j) asm volatile("" : "+v"(v0[j])::"memory");
+        __syncthreads();                                   // every wavefront's vouchers are in registers
     }
     return an_new;
 }
@@ -482,7 +545,8 @@ __device__ __forceinline__ uint8_t vouchers_of_slots(const StepArgs& fs, const f
 // give the same bits.
 // FUSED: the step is this one launch.  A unit tests the table at the new position itself and finds its slots' sponsors by one 8-byte
 // load of flags each.  Vouchers it needs only where no plain slot is left to evict: any plain slot ranks below every
-// sponsored one, and its own voucher is zero.  It counts itself in once it has read all that the trailing workgroups overwrite.
+// sponsored one, and its own voucher is zero.  It counts itself in once it has read what the append overwrites, and the last workgroup
+// of a sequence to do so appends.
 template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES, int SPL, bool FUSED = false>
 __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& pg, const StepArgs* fs = nullptr)
 {
@@ -495,7 +559,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     const int wave = WAVES > 1 ? (int)(threadIdx.x >> 6) : 0;
     const int sub = lane & 15, grp = lane >> 4;            // 16 lanes per key row, 4 rows per instruction
     if ((int)blockIdx.x >= a.units) {                      // trailing workgroups: budget decay
-        if constexpr (FUSED) append_and_decay<64 * WAVES>(st, *fs, (int)blockIdx.x - a.units, a.decay, reinterpret_cast<int32_t*>(s_dyn));
+        if constexpr (FUSED) vouch_and_decay<64 * WAVES>(st, *fs, (int)blockIdx.x - a.units, a.decay, reinterpret_cast<int32_t*>(s_dyn));
         else if (wave == 0) decay_rider(st, (int)blockIdx.x - a.units, a.decay);
         return;
     }
@@ -625,14 +689,30 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     }
     const int32_t len_new = FUSED ? (stepped < 0 || stepped >= st.cap ? 0 : stepped + 1) : stepped & 0x3FFFFFFF;
     uint8_t an_new = FUSED ? 0 : (uint8_t)((stepped >> 30) & 1);
+    // A unit counts itself in on its line, and a line's last unit counts the line; the sums before its own additions come back while it goes on.
+    bool counted = false;
+    int32_t before = -1, t_new = 0;
+    unsigned long long total = ~0ull;
+    const int32_t line = FUSED ? (l * st.hkv + g) & (SYNC_LINES - 1) : 0;
     const auto count_in = [&]() {
-        if (!FUSED || wave != 0 || lane != 0) return;
-        const int32_t line = (l * st.hkv + g) & (SYNC_LINES - 1);
-        __hip_atomic_fetch_add(&fs->sync[(size_t)b * SYNC_WORDS + 32 * line], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!FUSED || wave != 0 || counted) return;
+        counted = true;
+        t_new = fs->new_tok[b];
+        if (lane == 0) before = __hip_atomic_fetch_add(&fs->sync[(size_t)b * SYNC_WORDS + 32 * line], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
+    const auto count_line = [&]() {
+        if (!FUSED || wave != 0 || lane != 0 || before != units_on(fs->per_seq, line) - 1) return;
+        before = -1;
+        total = __hip_atomic_fetch_add(total_of(*fs, b), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    const auto is_last = [&]() { return wave == 0 && (int32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)total) == fs->parts - 1; };
     if (len_new == 0 || f >= slots) {                      // a sequence at capacity, or no room: nothing to do
         if (wave == 0 && lane == 0 && a.evicted) a.evicted[unit] = -1;
-        count_in();
+        if constexpr (FUSED) {
+            count_in();
+            count_line();
+            if (is_last()) append(st, *fs, b, stepped, t_new, len_new != 0 && is_anchor(request_anchor(st, *fs, b, stepped), stepped), a.decay);
+        }
         return;                                            // (every wavefront of the unit: the same test)
     }
     const int32_t p_new = len_new - 1;
@@ -671,13 +751,28 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     } else if (lane < 32 && wave == 0) Vc[row_at(f) + lane - 16] = nrow;
     __builtin_amdgcn_wave_barrier();                       // the slot table is in LDS for every lane
 
+    // A unit that will not need vouchers has read all that anybody overwrites and counts itself in early: what its sequence's last one then
+    // does hides behind the key stream (256 units x 1025 slots 17.1 -> 16.5 us).  That the first wavefront has a plain slot is enough to know.
+    const auto count_in_early = [&]() {
+        if (wave != 0) return;
+        bool plain = false;
+#pragma unroll
+        for (int j = 0; FUSED && j < SPL; ++j) {
+            const int32_t p = p0[j];
+            const unsigned long long n = p < NEAR_SPAN ? near[j] << (8 * (NEAR_SPAN - (p < 0 ? 0 : p))) : near[j];
+            plain = plain || (p >= a.n_sink && p < len_new - a.n_recent && (n & fs->span) == 0ull);
+        }
+        if (__ballot(plain) != 0ull) count_in();
+    };
+
     float m_h[GH], inv_h[GH];
     if constexpr (!SCORED && FUSED) {
         AnchorTest test = {};
         if (wave == WAVES - 1) test = request_anchor(st, *fs, b, p_new);
+        count_in_early();
         flags_of_slots<WAVES, SPL>(a, *fs, wave, p_new, len_new, test, p0, near, fl0, v0, s_x);
         __syncthreads();                                   // every wavefront has read its flags
-        an_new = vouchers_of_slots<WAVES, SPL>(*fs, st.budget + srow, p0, near, v0, s_x);
+        an_new = vouchers_of_slots<WAVES, SPL>(st, *fs, b, p0, near, v0, s_x);
         count_in();
     }
     if (SCORED) {
@@ -745,6 +840,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
             for (int j = 0; j < DT_RING; ++j) one_tile(j, tiles[j], true);
             if (WAVES > 1) new_key();
             if (FUSED && wave == WAVES - 1) test = request_anchor(st, *fs, b, p_new);
+            if constexpr (FUSED) count_in_early();
             for (tb = DT_RING; tb + 2 * DT_RING <= ntiles; tb += DT_RING) {
 #pragma unroll
                 for (int j = 0; j < DT_RING; ++j) one_tile(tb + j, tiles[j], true);
@@ -752,6 +848,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         } else if (WAVES > 1) {
             new_key();
             if (FUSED && wave == WAVES - 1) test = request_anchor(st, *fs, b, p_new);
+            if constexpr (FUSED) count_in_early();
         }
         for (; tb < ntiles; tb += DT_RING) {
 #pragma unroll
@@ -761,11 +858,14 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         if (WAVES == 1) new_key();
         __builtin_amdgcn_wave_barrier();                   // behind the tile's own logit for the slot
         if (has_free && i16 < G && kq == 0) s_w[i16 * wstride + f] = new_logit;
-        if constexpr (FUSED) flags_of_slots<WAVES, SPL>(a, *fs, wave, p_new, len_new, test, p0, near, fl0, v0, s_x);
+        if constexpr (FUSED) {
+            count_line();
+            flags_of_slots<WAVES, SPL>(a, *fs, wave, p_new, len_new, test, p0, near, fl0, v0, s_x);
+        }
         if (WAVES > 1) __syncthreads();                    // the logits of every wavefront's tiles are in LDS
         else __builtin_amdgcn_wave_barrier();
         if constexpr (FUSED) {
-            an_new = vouchers_of_slots<WAVES, SPL>(*fs, st.budget + srow, p0, near, v0, s_x);
+            an_new = vouchers_of_slots<WAVES, SPL>(st, *fs, b, p0, near, v0, s_x);
             count_in();
         }
         // softmax statistics of all heads at once: one pass for the maxima, one for the sums.  Several
@@ -809,6 +909,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
                     s_stat[16 + h] = inv;
                 }
             }
+            if constexpr (FUSED) count_line();
             __syncthreads();                               // every head's statistics
 #pragma unroll
             for (int h = 0; h < GH; ++h) {
@@ -884,6 +985,10 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     nfree = __ballot(nfree > 0) != 0ull ? 1 : 0;           // is a slot of this wavefront's still free?
     worst = wave_min_dpp(worst);
     if (WAVES > 1) {
+        if constexpr (FUSED && !SCORED) count_line();
+        if constexpr (FUSED) {
+            if (is_last()) append(st, *fs, b, p_new, t_new, an_new != 0, a.decay);
+        }
         // without an attention term no barrier lies between the last exchange and this one: other words
         int32_t* s_e = s_x + (SCORED ? 8 : 32);
         if (lane == 0) {
@@ -935,18 +1040,19 @@ constexpr int LOOP_SPL = 5;                                // slots per lane and
 // to 16 384 positions 227 / 237).
 //
 // A step as one launch wants several wavefronts per unit, and is ahead of two while there are not so many units that their counting
-// shows.  us per step, one launch / two: 256 units x 257 slots 9.0 / 10.9, x 1025 16.2 / 17.9 (paged 18.3 / 19.7), x 501 with 16 heads per
-// group 12.3 / 14.5; 1024 x 257 17.4 / 18.9, x 1025 47.9 / 50.2; 4096 x 129 32.3 / 33.8, x 257 54.9 / 56.1; 6144 x 131 46.5 / 47.7, x 257 80.1 /
-// 79.6; 8192 x 257 105.8 / 104.4, x 513 192.8 / 195.6; 16 384 x 257 209.4 / 203.1.  So where it can be had, two wavefronts share a unit
-// that one would hold up to 2048 units (1024 units x 65 slots 9.5 / 12.0, x 101 10.1 / 12.0, paged 11.2 / 13.6; 2048 x 31 10.8 / 11.9, x 65 12.9 / 14.5,
-// x 101 with 8 heads per group 16.8 / 18.7; 3072 x 65 18.2 / 17.8, x 111 21.9 / 23.0; 4096 x 65 22.0 / 21.1).
+// shows, nor rows so long that a tile of positions takes its workgroup several rounds.  us per step, one launch / two: 256 units x 257 slots
+// 9.0 / 10.9, x 1025 16.5 / 17.9 (paged 18.4 / 19.5), x 501 with 8 heads per group 11.4 / 12.8; 1024 x 257 17.1 / 18.4, x 1025 48.5 / 49.4; 3072 x 129 26.4 /
+// 27.1, x 257 42.6 / 43.2; 4096 x 129 32.7 / 33.1, x 257 55.3 / 55.4, x 513 98.3 / 99.9.  So where it can be had, two wavefronts share a unit that one
+// would hold up to 1536 units (1024 units x 65 slots 9.6 / 11.8; 1536 x 65 12.0 / 12.9, x 101 13.7 / 15.0, paged 15.4 / 16.8; 2048 x 31 12.2 / 11.6, x 65
+// 14.7 / 14.4, x 101 with 8 heads per group 17.5 / 18.7).  Rows of positions: 256 units x 257 slots, 32 768 positions 9.6 / 11.7, 65 536 12.3 / 11.8,
+// 131 072 18.6 / 11.8; 1024 x 257, 32 768 18.5 / 19.1, 65 536 21.6 / 19.3; 16 sequences of 16 units x 101 slots, 32 768 9.3 / 11.9, 65 536 12.7 / 12.5.
 //
 // Without an attention term a unit only reads its slot table and flags, so that one launch takes as many wavefronts as hold all slots, while
 // the chip starts them at once (us per step as the calls are issued, at least 8.3; one launch / two, there with a wavefront per
 // unit: 16 units x 1501 slots 8.3 / 14.6; 256 x 1025 8.6 / 12.3, paged 9.2 / 12.9; 1024 x 2001 11.2 / 19.7; 1536 x 1501 11.6 / 16.7; 3072 x 501 10.1 /
 // 12.0; 4096 x 201 paged 10.2 / 12.8; with 16 384 wavefronts: 2048 x 1025 13.1 / 13.9, paged 15.9 / 14.5; 4096 x 257 11.3 / 11.5, paged 12.6 / 11.3).
 static_assert(TA_MAX_DECODE_K + 1 <= 8 * 4 * 64, "the widest form");
-constexpr int FEW_UNITS = 512, FEW_UNITS_ONE_LAUNCH = 2048, ONE_LAUNCH_UNITS = 4096, ONE_LAUNCH_PLAIN_WAVES = 12288;
+constexpr int FEW_UNITS = 512, FEW_UNITS_ONE_LAUNCH = 1536, ONE_LAUNCH_UNITS = 4096, ONE_LAUNCH_POSITIONS = 40960, ONE_LAUNCH_PLAIN_WAVES = 12288;
 // one: a step of one launch can be had, and is taken if several wavefronts share a unit
 UnitForm unit_form(bool scored, int slots, int64_t units, bool one)
 {
@@ -963,10 +1069,12 @@ UnitForm unit_form(bool scored, int slots, int64_t units, bool one)
     return {8, 4};                                         // at most 2048 slots
 }
 
-// Can a step be one launch: given words to count in, a span whose flags one load holds, and not too many units.
+// Can a step be one launch: given words to count in (two of them are one number of eight bytes), a span whose flags one load holds, not too
+// many units and rows that are not too long.
 bool one_launch(const ta_params& prm, const ta_decode_state& st, int64_t units, const int32_t* sync)
 {
-    return sync && units <= ONE_LAUNCH_UNITS && prm.span_L <= NEAR_SPAN && st.cap > NEAR_SPAN;
+    return sync && ((uintptr_t)sync & 7) == 0 && units <= ONE_LAUNCH_UNITS && prm.span_L <= NEAR_SPAN && st.cap > NEAR_SPAN &&
+           st.cap <= ONE_LAUNCH_POSITIONS;
 }
 
 // Key tiles in flight: two per wavefront where wavefronts share a unit - enough with all that then share a compute unit, and the
@@ -980,7 +1088,7 @@ decode_unit_kernel(ta_decode_state st, UnitArgs a, SlotPages pg)
     decode_unit<GH, PAGED, SCORED, SMALL, (WAVES > 1 ? 2 : PAGED ? 4 : 3), WAVES, SPL>(st, a, pg);
 }
 
-// Paged slots: at most 128 registers (one to six of them in scratch), so that two workgroups of eight wavefronts share a compute unit as
+// Paged slots: at most 128 registers (none to eight of them in scratch), so that two workgroups of eight wavefronts share a compute unit as
 // those of the two-launch form do: with 131 to 135 they did not, and where units are more than compute units the step fell behind two
 // launches (us per step, 135 / 128 registers / two launches: 320 units x 1135 slots 29.3 / 25.7 / 28.0, 512 x 1025 33.7 / 30.0 / 31.5, 1024 x 1025
 // 63.2 / 55.0 / 55.3, 256 x 1025 17.9 / 17.8 / 20.0).
@@ -1153,18 +1261,23 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
     a.by_batch = divider((uint32_t)st.batch);
     a.decay = prm.budget_decay;
     lds_floats += page_list;
+    if (one && lds_floats < 4 + NEAR_SPAN + (size_t)TILE_PER * 64 * form.waves) lds_floats = 4 + NEAR_SPAN + (size_t)TILE_PER * 64 * form.waves;
     const size_t lds = lds_floats * sizeof(float);
     if (lds > 160 * 1024) return hipErrorInvalidValue;      // (a unit's logits are at most 15 360: 113 KB in all)
     const hipError_t attr_err = decode_setup();
     if (attr_err != hipSuccess) return attr_err;
     if (one) {
-        const unsigned tiles = (unsigned)((st.cap + 256 * form.waves - 1) / (256 * form.waves));     // 4 positions per thread
-        const uint64_t grid = (uint64_t)units + (uint64_t)tiles * (uint64_t)st.batch;
-        if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
+        const int32_t per_seq = (int32_t)(units / (unsigned)st.batch);
         StepArgs sa;
+        sa.tile_shift = 0;                                 // TILE_PER positions per thread, more where that would be too many tiles
+        while ((1 << sa.tile_shift) < TILE_PER * 64 * form.waves || ((st.cap - 1) >> sa.tile_shift) >= MAX_TILES) ++sa.tile_shift;
+        sa.tiles = ((st.cap - 1) >> sa.tile_shift) + 1;
+        sa.parts = (per_seq < SYNC_LINES ? per_seq : SYNC_LINES) + sa.tiles;
+        const uint64_t grid = (uint64_t)units + (uint64_t)sa.tiles * (uint64_t)st.batch;
+        if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
         sa.new_tok = new_tok;
         sa.sync = sync;
-        sa.per_seq = (int32_t)(units / (unsigned)st.batch);
+        sa.per_seq = per_seq;
         sa.L = prm.span_L;
         sa.span = prm.span_L > 0 ? ((1ull << (8 * prm.span_L)) - 1ull) << (8 * (NEAR_SPAN - prm.span_L)) : 0ull;
         for (int k = 0; k <= NEAR_SPAN; ++k) sa.pw[k] = tab.pw[k];

@@ -13,11 +13,16 @@ import pytest
 from paper_2604_11288_amd import build
 
 
-def _passable(text):
-    """Lines of the barriers that a path reaches with an LDS write outstanding."""
+def _lines(text):
+    """A kernel's instructions and labels, and where each label stands."""
     lines = [re.sub(r"\s+", " ", line.split(";")[0]).strip() for line in text.split("\n")]
     lines = [line for line in lines if line and (not line.startswith(".") or line.startswith(".LBB"))]
-    label = {line[:-1]: i for i, line in enumerate(lines) if line.endswith(":")}
+    return lines, {line[:-1]: i for i, line in enumerate(lines) if line.endswith(":")}
+
+
+def _passable(text):
+    """Lines of the barriers that a path reaches with an LDS write outstanding."""
+    lines, label = _lines(text)
     seen, todo, found = {}, [(0, False)], set()
     while todo:
         i, pending = todo.pop()
@@ -41,18 +46,63 @@ def _passable(text):
     return sorted(found)
 
 
+def _polls(text):
+    """Lines by which a workgroup may wait for another one: a sleep, or a read past the caches that workgroups do not share from
+    which a path leads back to it."""
+    lines, label = _lines(text)
+    found = [i for i, line in enumerate(lines) if line.startswith("s_sleep")]
+    for read in (i for i, line in enumerate(lines) if re.match(r"(global|flat|buffer)_load.*\bsc1\b", line)):
+        seen, todo = set(), [read + 1]
+        while todo:
+            i = todo.pop()
+            while i < len(lines) and i not in seen:
+                seen.add(i)
+                op, _, rest = lines[i].partition(" ")
+                if op == "s_endpgm":
+                    break
+                if op == "s_branch":
+                    i = label[rest]
+                    continue
+                if op.startswith("s_cbranch"):
+                    todo.append(label[rest])
+                i += 1
+        if read in seen:
+            found.append(read)
+    return found
+
+
 def test_the_check_finds_a_missing_wait():
     body = "k:\n.LBB0_1:\n%ss_barrier\nds_write_b32 v0, v1\ns_cbranch_scc0 .LBB0_1\ns_endpgm\n"
     assert _passable(body % "") and not _passable(body % "s_waitcnt lgkmcnt(0)\n")
 
 
-@pytest.mark.skipif(shutil.which(build.HIPCC) is None and not os.path.exists(build.HIPCC), reason="no hipcc")
-def test_score_kernels_wait_for_lds_writes(tmp_path):
-    out = tmp_path / "score.s"
+def test_the_check_finds_a_wait_for_another_workgroup():
+    body = "k:\n.LBB0_1:\nglobal_load_dword v0, v1, s[0:1]%s\ns_cbranch_vccz .LBB0_%d\ns_nop 0\n.LBB0_2:\ns_endpgm\n"
+    assert _polls(body % (" sc1", 1)) and not _polls(body % (" sc1", 2)) and not _polls(body % ("", 1))
+
+
+def _kernels(source, out):
+    """(name, emitted text) of a source's kernels."""
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
-    subprocess.run([build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(build.CSRC, "ta_score.hip"), "-o", str(out)],
+    subprocess.run([build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", str(out)],
                    check=True, stderr=subprocess.DEVNULL)
     text = out.read_text()
-    kernels = [(m.group(1), text[m.start():text.index(".Lfunc_end", m.start())]) for m in re.finditer(r"^(_Z\S+):\s*; @", text, re.M)]
+    return [(m.group(1), text[m.start():text.index(".Lfunc_end", m.start())]) for m in re.finditer(r"^(_Z\S+):\s*; @", text, re.M)]
+
+
+needs_hipcc = pytest.mark.skipif(shutil.which(build.HIPCC) is None and not os.path.exists(build.HIPCC), reason="no hipcc")
+
+
+@needs_hipcc
+def test_score_kernels_wait_for_lds_writes(tmp_path):
+    kernels = _kernels("ta_score.hip", tmp_path / "score.s")
     assert len(kernels) > 20
     assert not [name for name, body in kernels if _passable(body)]
+
+
+@needs_hipcc
+def test_no_workgroup_of_a_generation_step_waits_for_another(tmp_path):
+    """Steps of different states may overlap on one GPU: a workgroup that waited could hold the place of the one it waits for."""
+    kernels = _kernels("ta_decode.hip", tmp_path / "decode.s")
+    assert len(kernels) > 50
+    assert not [name for name, body in kernels if _polls(body)]

@@ -12,6 +12,7 @@ import pytest
 import torch
 
 import paper_2604_11288_amd as ta
+from paper_2604_11288_amd import binding as tb
 from paper_2604_11288_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -48,6 +49,8 @@ def _state(layers, batch, hq, hkv, K, n, cap, prm, page_size, vocabulary, lens, 
     ((2, 3, 8, 2, 64, 300), dict(span_L=0), 400, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=1), 100, 0),
     ((2, 3, 8, 2, 64, 300), dict(span_L=7), 100, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=8), 100, 0),
     ((2, 3, 8, 2, 64, 300), {}, 17, 0), ((2, 3, 8, 2, 300, 900), dict(rho=1.5), 20, 16),                                       # nearly all sponsored: vouchers decide
+    ((8, 3, 8, 4, 900, 5000), dict(budget_decay=0.0), 17, 0), ((32, 3, 8, 8, 100, 3000), dict(budget_decay=0.5), 17, 0),       # and their tiles are overwritten meanwhile
+    ((8, 5, 8, 4, 300, 2044), dict(budget_decay=0.5), 17, 64),
     ((2, 1, 8, 2, 8, 100), {}, 400, 0), ((2, 1, 8, 2, 40, 100), dict(n_sink=0, n_recent=0), 40, 0), ((2, 1, 8, 2, 1, 9), dict(n_sink=0, n_recent=1), 40, 0),
     ((3, 2, 8, 2, 64, 300), dict(gamma=2.0, budget_decay=1.25), 60, 0), ((3, 2, 8, 2, 64, 300), dict(last_query=1), 60, 0),
 ])
@@ -82,11 +85,72 @@ def test_one_launch_equals_two(shape, kw, vocabulary, page_size):
     ((2, 2, 8, 2, 255, 700), {}, 400, 0), ((2, 2, 8, 2, 256, 700), {}, 400, 16), ((1, 2, 4, 1, 511, 1500), {}, 400, 0), ((1, 1, 4, 1, 767, 1500), {}, 400, 0),
     ((1, 2, 4, 1, 1535, 2500), {}, 400, 64), ((1, 1, 4, 1, 2047, 2500), {}, 400, 0),                        # every spread of the slots, at its limit
     ((2, 3, 8, 2, 64, 300), dict(span_L=0), 400, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=7), 100, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=8), 100, 0),
-    ((2, 3, 8, 2, 64, 300), {}, 17, 0), ((2, 3, 8, 2, 300, 900), dict(rho=1.5), 20, 16),                     # vouchers decide
+    ((2, 3, 8, 2, 64, 300), {}, 17, 0), ((2, 3, 8, 2, 300, 900), dict(rho=1.5), 20, 16), ((32, 3, 8, 8, 100, 3000), dict(budget_decay=0.0), 17, 0),  # vouchers decide
     ((2, 1, 8, 2, 1, 9), dict(n_sink=0, n_recent=1), 40, 0), ((40, 13, 8, 8, 8, 60), dict(beta=-1.0), 40, 0),
 ])
 def test_one_launch_equals_two_without_attention(shape, kw, vocabulary, page_size):
     test_one_launch_equals_two(shape, {**dict(alpha=0.0), **kw}, vocabulary, page_size)
+
+
+def test_steps_of_two_states_overlap():
+    """Two states on two streams, each with more workgroups of positions than an XCD can hold: nothing of one waits for the other, and
+    both end as they do one after the other."""
+    layers, batch, hq, hkv, K, n, cap, steps = 4, 32, 8, 2, 300, 700, 40000, 12
+    prm = ta.Params()
+    states = []
+    for seed in (3, 4):
+        lens = [n - 7 * b - seed for b in range(batch)]
+        (st, ids, tab_len), (alone, _, _) = (_state(layers, batch, hq, hkv, K, n, cap, prm, 0, 400, lens, seed) for _ in range(2))
+        alone.sync = None                                         # two launches
+        states.append((st, alone))
+    g = torch.Generator(device=DEV).manual_seed(6)
+    inputs = [[(torch.randint(0, 400, (batch,), generator=g, device=DEV, dtype=torch.int32),
+                *(torch.randn((layers, batch, h, 128), generator=g, device=DEV).to(torch.bfloat16) for h in (hq, hkv, hkv)))
+               for _ in states] for _ in range(steps)]
+    for step in inputs:
+        for (_, alone), x in zip(states, step):
+            ta.ta_decode_step(alone, *x, ids, tab_len, prm)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in states]
+    for step in inputs:
+        for (st, _), x, stream in zip(states, step, streams):
+            ta.ta_decode_step(st, *x, ids, tab_len, prm, stream=stream)
+    torch.cuda.synchronize()
+    for st, alone in states:
+        for name in STATE:
+            assert torch.equal(getattr(st, name), getattr(alone, name)), name
+        assert not st.sync.any()
+
+
+@pytest.mark.parametrize("n", (8, 505, 1018, 1023, 1024, 2041, 3066, 32760, 40900))
+def test_budgets_decay_once_in_every_tile(n):
+    """Tiles of 1024 and 2048 positions, lengths that end at and step over their edges."""
+    prm = ta.Params(n_sink=0, n_recent=1, budget_decay=0.75)
+    lens = [n, max(1, n - 5), max(1, n // 2)]
+    st, ids, tab_len = _state(1, 3, 4, 1, 5, n, n + 9, prm, 0, 40, lens, 7)
+    g = torch.Generator(device=DEV).manual_seed(8)
+    want = st.budget.clone()
+    for t in range(8):
+        tok = torch.randint(0, 40, (3,), generator=g, device=DEV, dtype=torch.int32)
+        ta.ta_decode_step(st, tok, *(torch.randn((1, 3, h, 128), generator=g, device=DEV).to(torch.bfloat16) for h in (4, 1, 1)), ids, tab_len, prm)
+        for b in range(3):
+            want[b, lens[b] + t] = prm.sponsor_B if st.anchor[b, lens[b] + t] else 0.0
+        want *= 0.75
+    assert torch.equal(st.budget, want) and st.len.tolist() == [x + 8 for x in lens]
+
+
+def test_words_off_an_eight_byte_boundary():
+    """Two of the words are one number of eight bytes: elsewhere the step is two launches and leaves them alone."""
+    prm = ta.Params()
+    (st, ids, tab_len), (two, _, _) = (_state(1, 2, 4, 1, 64, 200, 240, prm, 0, 100, [200, 150], 4) for _ in range(2))
+    st.sync, two.sync = torch.zeros(2 * tb.TA_DECODE_SYNC_WORDS + 1, dtype=torch.int32, device=DEV)[1:], None
+    g = torch.Generator(device=DEV).manual_seed(9)
+    for _ in range(3):
+        x = [torch.randint(0, 100, (2,), generator=g, device=DEV, dtype=torch.int32)]
+        x += [torch.randn((1, 2, h, 128), generator=g, device=DEV).to(torch.bfloat16) for h in (4, 1, 1)]
+        for s in (st, two):
+            ta.ta_decode_step(s, *x, ids, tab_len, prm)
+    assert all(torch.equal(getattr(st, name), getattr(two, name)) for name in STATE) and not st.sync.any()
 
 
 def test_copies_count_in_words_of_their_own():
