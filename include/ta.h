@@ -487,8 +487,7 @@ int32_t ta_evict_layers_paged(const int32_t *tok, const int32_t *seq_len,
  *                 vouch  float [batch][cap]   scratch of a step: voucher of each position from the
  *                 spons  uint8 [batch][cap]   current budgets (Eq. 2), and its flags (bit 0: sponsored,
  *                                             bit 1: an anchor itself, except at the position just
- *                                             appended); rewritten by every ta_decode_step, not used by
- *                                             a ta_decode_step_sync that is one launch
+ *                                             appended); rewritten by every step
  *                 stepped int32 [batch]       scratch of a step: 0 if the sequence was at capacity and
  *                                             left alone, else its new length in bits 0-29 and, in
  *                                             bit 30, whether the appended token is an anchor

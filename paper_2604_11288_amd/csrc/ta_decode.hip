@@ -372,7 +372,7 @@ __device__ __forceinline__ void append(const ta_decode_state& st, const StepArgs
     st.stepped[b] = live ? (p_new + 1) | (an ? (1 << 30) : 0) : 0;
 }
 
-// Trailing workgroups of the one-launch form: the vouchers of a tile of positions, then the decay of its budgets.  Units may need those
+// Trailing workgroups of the one-launch form: vouchers and flags of a tile of positions, then the decay of its budgets.  Units may need those
 // budgets, and may run before or after, but nobody waits for anybody, whatever else the chip runs and wherever workgroups are placed (steps
 // of other states may overlap: one that waited could hold the place of the one it waits for).  A budget is overwritten only once all vouchers
 // that are computed from it are in memory, which their tile's bit says: a unit that needs a voucher adds the budgets up, then looks at the
@@ -421,6 +421,7 @@ __device__ __forceinline__ void vouch_and_decay(const ta_decode_state& st, const
                     if (((near[j] >> (8 * (NEAR_SPAN - k))) & 0xFFull) != 0ull) v = __fadd_rn(v, __fmul_rn(s_B[NEAR_SPAN + j * THREADS + tid - k], f.pw[k]));
             }
             __hip_atomic_store(&st.vouch[row + p], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            st.spons[row + p] = ((near[j] & f.span) != 0ull ? 1 : 0) | (p < p_new && (near[j] >> 56) != 0ull ? 2 : 0);     // as decode_seq_vouch_kernel
         }
         q += CHUNK;
     } while (q < exist);

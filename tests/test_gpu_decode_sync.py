@@ -17,7 +17,7 @@ from paper_2604_11288_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-STATE = ("tok", "len", "anchor", "budget", "pos", "A", "Kc", "Vc", "stepped")
+STATE = ("tok", "len", "anchor", "budget", "vouch", "spons", "pos", "A", "Kc", "Vc", "stepped")
 
 
 def _state(layers, batch, hq, hkv, K, n, cap, prm, page_size, vocabulary, lens, seed):
