@@ -1,12 +1,15 @@
-"""The score kernels wait for what a wavefront has written to LDS before it reaches a barrier, in the code that the compiler emits.
+"""The kernels wait for what a wavefront has written to LDS before it reaches a barrier, in the code that the compiler emits.
 
 A barrier does not wait for a wavefront's own LDS writes; the wait is an instruction in front of it, which the compiler places and once
-left out where the barrier is reached over a loop's back edge.  The test compiles the score kernels to assembly and follows every path.
+left out where the barrier is reached over a loop's back edge.  The test compiles every source to assembly and follows every path.
 """
+import functools
 import os
 import re
 import shutil
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -81,28 +84,42 @@ def test_the_check_finds_a_wait_for_another_workgroup():
     assert _polls(body % (" sc1", 1)) and not _polls(body % (" sc1", 2)) and not _polls(body % ("", 1))
 
 
-def _kernels(source, out):
-    """(name, emitted text) of a source's kernels."""
+@functools.lru_cache(maxsize=None)
+def _emitted():
+    """The text that the compiler emits for every source, by source."""
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
-    subprocess.run([build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", str(out)],
-                   check=True, stderr=subprocess.DEVNULL)
-    text = out.read_text()
+    with tempfile.TemporaryDirectory() as tmp:
+        def emit(source):
+            out = os.path.join(tmp, source + ".s")
+            subprocess.run([build.HIPCC, *flags, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", out],
+                           check=True, stderr=subprocess.DEVNULL)
+            with open(out) as f:
+                return f.read()
+        with ThreadPoolExecutor(max_workers=len(build.SOURCES)) as pool:
+            return dict(zip(build.SOURCES, pool.map(emit, build.SOURCES)))
+
+
+def _kernels(source):
+    """(name, emitted text) of a source's kernels."""
+    text = _emitted()[source]
     return [(m.group(1), text[m.start():text.index(".Lfunc_end", m.start())]) for m in re.finditer(r"^(_Z\S+):\s*; @", text, re.M)]
 
 
 needs_hipcc = pytest.mark.skipif(shutil.which(build.HIPCC) is None and not os.path.exists(build.HIPCC), reason="no hipcc")
+AT_LEAST = {"ta_api.hip": 0, "ta_score.hip": 20, "ta_select.hip": 30, "ta_decode.hip": 50}       # kernels of a source; of the others one
 
 
 @needs_hipcc
-def test_score_kernels_wait_for_lds_writes(tmp_path):
-    kernels = _kernels("ta_score.hip", tmp_path / "score.s")
-    assert len(kernels) > 20
+@pytest.mark.parametrize("source", build.SOURCES)
+def test_kernels_wait_for_lds_writes(source):
+    kernels = _kernels(source)
+    assert len(kernels) >= AT_LEAST.get(source, 1)
     assert not [name for name, body in kernels if _passable(body)]
 
 
 @needs_hipcc
-def test_no_workgroup_of_a_generation_step_waits_for_another(tmp_path):
+def test_no_workgroup_of_a_generation_step_waits_for_another():
     """Steps of different states may overlap on one GPU: a workgroup that waited could hold the place of the one it waits for."""
-    kernels = _kernels("ta_decode.hip", tmp_path / "decode.s")
+    kernels = _kernels("ta_decode.hip")
     assert len(kernels) > 50
     assert not [name for name, body in kernels if _polls(body)]

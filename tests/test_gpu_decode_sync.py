@@ -17,6 +17,7 @@ from paper_2604_11288_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+MARK = 32 * 8 + 1                  # the word with a bit per tile of positions; its highest belongs to none where rows are short: a step of one launch clears it
 STATE = ("tok", "len", "anchor", "budget", "vouch", "spons", "pos", "A", "Kc", "Vc", "stepped")
 
 
@@ -44,10 +45,10 @@ def _state(layers, batch, hq, hkv, K, n, cap, prm, page_size, vocabulary, lens, 
 @pytest.mark.parametrize("shape,kw,vocabulary,page_size", [
     ((2, 1, 8, 2, 300, 900), {}, 400, 0), ((2, 2, 8, 2, 300, 900), {}, 400, 16), ((1, 1, 4, 1, 600, 1500), {}, 400, 0),
     ((1, 2, 4, 1, 1024, 1500), {}, 400, 0), ((1, 1, 4, 1, 1600, 2500), {}, 400, 64), ((16, 9, 8, 4, 150, 400), {}, 400, 0),
-    ((32, 5, 16, 4, 111, 300), {}, 400, 0), ((32, 16, 8, 4, 40, 100), {}, 400, 16),   # every spread of the slots
+    ((32, 5, 16, 4, 111, 300), {}, 400, 0), ((32, 12, 8, 4, 40, 100), {}, 400, 16), ((32, 16, 8, 4, 40, 100), dict(launches=2), 400, 16),   # every spread of the slots
     ((1, 1, 7, 1, 200, 500), {}, 400, 0), ((1, 1, 12, 1, 200, 500), {}, 400, 0), ((1, 1, 16, 1, 200, 500), {}, 400, 16),       # heads of a group
     ((2, 3, 8, 2, 64, 300), dict(span_L=0), 400, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=1), 100, 0),
-    ((2, 3, 8, 2, 64, 300), dict(span_L=7), 100, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=8), 100, 0),
+    ((2, 3, 8, 2, 64, 300), dict(span_L=7), 100, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=8, launches=2), 100, 0),
     ((2, 3, 8, 2, 64, 300), {}, 17, 0), ((2, 3, 8, 2, 300, 900), dict(rho=1.5), 20, 16),                                       # nearly all sponsored: vouchers decide
     ((8, 3, 8, 4, 900, 5000), dict(budget_decay=0.0), 17, 0), ((32, 3, 8, 8, 100, 3000), dict(budget_decay=0.5), 17, 0),       # and their tiles are overwritten meanwhile
     ((8, 5, 8, 4, 300, 2044), dict(budget_decay=0.5), 17, 64),
@@ -57,6 +58,8 @@ def _state(layers, batch, hq, hkv, K, n, cap, prm, page_size, vocabulary, lens, 
 def test_one_launch_equals_two(shape, kw, vocabulary, page_size):
     layers, batch, hq, hkv, K, n = shape
     steps = 24
+    kw = dict(kw)
+    launches = kw.pop("launches", 1)
     prm = ta.Params(**{**dict(n_sink=4, n_recent=4), **kw})
     lens = [n] + [max(1, n // 3 - b) for b in range(batch - 1)]
     cap = n + 11                                                  # the first sequence reaches its capacity on the way
@@ -68,6 +71,7 @@ def test_one_launch_equals_two(shape, kw, vocabulary, page_size):
         tok = torch.randint(0, vocabulary, (batch,), generator=g, device=DEV, dtype=torch.int32)
         q, k, v = (torch.randn((layers, batch, h, 128), generator=g, device=DEV).to(torch.bfloat16) for h in (hq, hkv, hkv))
         turns.sync = words if t % 3 else None
+        one.sync[:, MARK] = -1 << 31
         got = []
         for st in (one, two, turns):
             evicted = torch.full((layers, batch, hkv), -7, dtype=torch.int32, device=DEV)
@@ -78,15 +82,17 @@ def test_one_launch_equals_two(shape, kw, vocabulary, page_size):
             for name in STATE:
                 a, b = getattr(st, name), getattr(two, name)
                 assert torch.equal(a.view(torch.int16) if a.dtype == torch.bfloat16 else a, b.view(torch.int16) if b.dtype == torch.bfloat16 else b), (t, name)
+        assert one.sync[:, MARK].any().item() == (launches == 2)
+        one.sync[:, MARK] = 0
         assert not one.sync.any() and not words.any()
 
 
 @pytest.mark.parametrize("shape,kw,vocabulary,page_size", [
     ((2, 2, 8, 2, 255, 700), {}, 400, 0), ((2, 2, 8, 2, 256, 700), {}, 400, 16), ((1, 2, 4, 1, 511, 1500), {}, 400, 0), ((1, 1, 4, 1, 767, 1500), {}, 400, 0),
     ((1, 2, 4, 1, 1535, 2500), {}, 400, 64), ((1, 1, 4, 1, 2047, 2500), {}, 400, 0),                        # every spread of the slots, at its limit
-    ((2, 3, 8, 2, 64, 300), dict(span_L=0), 400, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=7), 100, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=8), 100, 0),
+    ((2, 3, 8, 2, 64, 300), dict(span_L=0), 400, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=7), 100, 0), ((2, 3, 8, 2, 64, 300), dict(span_L=8, launches=2), 100, 0),
     ((2, 3, 8, 2, 64, 300), {}, 17, 0), ((2, 3, 8, 2, 300, 900), dict(rho=1.5), 20, 16), ((32, 3, 8, 8, 100, 3000), dict(budget_decay=0.0), 17, 0),  # vouchers decide
-    ((2, 1, 8, 2, 1, 9), dict(n_sink=0, n_recent=1), 40, 0), ((40, 13, 8, 8, 8, 60), dict(beta=-1.0), 40, 0),
+    ((2, 1, 8, 2, 1, 9), dict(n_sink=0, n_recent=1), 40, 0), ((40, 13, 8, 8, 8, 60), dict(beta=-1.0, launches=2), 40, 0),
 ])
 def test_one_launch_equals_two_without_attention(shape, kw, vocabulary, page_size):
     test_one_launch_equals_two(shape, {**dict(alpha=0.0), **kw}, vocabulary, page_size)
@@ -156,6 +162,15 @@ def test_words_off_an_eight_byte_boundary():
 def test_copies_count_in_words_of_their_own():
     prm = ta.Params()
     st, ids, tab_len = _state(1, 1, 4, 1, 64, 200, 240, prm, 0, 100, [200], 4)
-    for fork in (copy.copy, copy.deepcopy):
-        other = fork(st)
+    g = torch.Generator(device=DEV).manual_seed(10)
+    deep, shallow = copy.deepcopy(st), copy.copy(st)              # the shallow one goes on with the same tensors
+    for other in (deep, shallow):
         assert other.sync.data_ptr() != st.sync.data_ptr() and not other.sync.any()
+    for t in range(6):
+        x = [torch.randint(0, 100, (1,), generator=g, device=DEV, dtype=torch.int32)]
+        x += [torch.randn((1, 1, h, 128), generator=g, device=DEV).to(torch.bfloat16) for h in (4, 1, 1)]
+        for s in (deep, (st, shallow)[t % 2]):
+            s.sync[:, MARK] = -1 << 31
+            ta.ta_decode_step(s, *x, ids, tab_len, prm)
+            assert not s.sync.any()                               # one launch
+        assert all(torch.equal(getattr(st, name), getattr(deep, name)) for name in STATE)
