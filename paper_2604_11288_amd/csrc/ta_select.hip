@@ -582,7 +582,8 @@ static_assert(sizeof(SelectRegLds::hist) >= sizeof(uint32_t) * SR_GATHER_MAX_K, 
 // list holds (a table that hits nearly everywhere): false, and the caller takes the whole row.  (Not with the margin output, which
 // wants the best of the evicted ones, nor with the fixed partition, which ranks both classes.)
 // ASK: the vouchers may be anything.  A position whose voucher is not zero joins the list as a flagged one does, and if one of the last
-// K - c2 has a voucher below zero, or none (NaN), the whole row is taken.
+// K - c2 has a voucher below zero, or none (NaN), the whole row is taken.  The flags are counted first: where they alone fill the list no
+// voucher is looked at.
 // What it measured: where launch_select chooses.
 constexpr int SR_LIST = 4 * SR_THREADS;
 constexpr int SR_SEG = 32 * SR_THREADS;                    // a thread's flags of a segment are the bits of one word
@@ -686,39 +687,7 @@ __device__ __forceinline__ bool select_reg(const SelectArgs& a, const std::condi
         const int32_t tail = plain_end > 0 ? plain_end : 0;  // every position from it on is in the list
         if (nb - tail > SR_LIST) return false;               // uniform
         const auto first = [&](int s) { return SR_SEG * s + 32 * tid; };
-        uint32_t in[SEGS] = {};                              // bit i: position first(s) + i is in the list
-        if constexpr (ASK) {
-            uint32_t* bits = list->entry;
-#pragma unroll
-            for (int s = 0; s < SEGS; ++s) bits[s * SR_THREADS + tid] = 0u;
-            if (tid == 0) list->below_zero = 0u;
-            __syncthreads();
-            const int32_t quads = (tail + 3) >> 2;
-            for (int32_t q0 = 0; q0 < quads; q0 += 8 * SR_THREADS) {
-                float4 v[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int32_t q = q0 + j * SR_THREADS + tid;
-                    v[j] = load_quad_f(vouch, quad_start(4 * (q < quads ? q : quads - 1), n));
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int32_t q = q0 + j * SR_THREADS + tid;
-                    if (q >= quads) continue;
-                    const float4 x = move_down(v[j], 4 * q - quad_start(4 * q, n));
-                    const uint32_t set = (x.x != 0.0f ? 1u : 0u) | (x.y != 0.0f ? 2u : 0u) | (x.z != 0.0f ? 4u : 0u) | (x.w != 0.0f ? 8u : 0u);
-                    if (set) atomicOr(&bits[q >> 3], set << (4 * (q & 7)));
-                }
-            }
-            bool below = false;
-            for (int32_t p = tail + tid; p < nb; p += SR_THREADS) below = below || !(vouch[p] >= 0.0f);
-            if (below) list->below_zero = 1u;
-            __syncthreads();
-            if (list->below_zero != 0u) return false;        // uniform in the workgroup
-#pragma unroll
-            for (int s = 0; s < SEGS; ++s) in[s] = bits[s * SR_THREADS + tid];
-        }
-        uint32_t sp[SEGS] = {}, an[SEGS] = {}, upto[SEGS];
+        uint32_t in[SEGS], sp[SEGS] = {}, an[SEGS] = {}, upto[SEGS];         // bit i: position first(s) + i; in: is in the list
         u32x4_any f[SEGS][4];
         if (SEGS > 1 || first(0) < tail) {                   // (a short row's wavefronts that have none of it do not work on it)
 #pragma unroll
@@ -728,6 +697,19 @@ __device__ __forceinline__ bool select_reg(const SelectArgs& a, const std::condi
                 f[s][2] = load_flags16(anchor, first(s), n);
                 f[s][3] = load_flags16(anchor, first(s) + 16, n);
             }
+        }
+        constexpr int ASK_QUADS = 8;                         // of vouchers, per thread in flight, behind the flags
+        const int32_t quads = (tail + 3) >> 2;
+        float4 v[ASK ? ASK_QUADS : 1];
+        const auto load_vouchers = [&](int32_t q0) {
+#pragma unroll
+            for (int j = 0; ASK && j < ASK_QUADS; ++j) {
+                const int32_t q = q0 + j * SR_THREADS + tid;
+                v[j] = load_quad_f(vouch, quad_start(4 * (q < quads ? q : quads > 0 ? quads - 1 : 0), n));
+            }
+        };
+        load_vouchers(0);
+        if (SEGS > 1 || first(0) < tail) {
 #pragma unroll
             for (int s = 0; s < SEGS; ++s) {
                 const int32_t p0 = first(s);
@@ -736,14 +718,52 @@ __device__ __forceinline__ bool select_reg(const SelectArgs& a, const std::condi
                 an[s] = flags16(f[s][2], p0, n) | flags16(f[s][3], p0 + 16, n) << 16;
             }
         }
+        const auto in_front = [&](int s) {                   // the positions of the word before the tail
+            const int32_t left = tail - first(s);
+            return left >= 32 ? 0xFFFFFFFFu : left > 0 ? (1u << left) - 1u : 0u;
+        };
 #pragma unroll
         for (int s = 0; s < SEGS; ++s) {
             const int32_t p0 = first(s);
-            in[s] |= sp[s] | an[s];
+            in[s] = sp[s] | an[s];
             if (p0 < ns) in[s] |= ns - p0 < 32 ? (1u << (ns - p0)) - 1u : 0xFFFFFFFFu;
-            if (p0 + 32 > tail) in[s] &= p0 < tail ? (1u << (tail - p0)) - 1u : 0u;
-            upto[s] = wave_scan_dpp((uint32_t)__popc(in[s]));
+            in[s] &= in_front(s);
         }
+        if constexpr (ASK) {
+            uint32_t* bits = list->entry;
+            uint32_t flagged = 0u;
+#pragma unroll
+            for (int s = 0; s < SEGS; ++s) {
+                bits[s * SR_THREADS + tid] = 0u;
+                flagged += (uint32_t)__popc(in[s]);
+            }
+            flagged = wave_sum_dpp(flagged);
+            if (lane == 0) list->totals[wave] = flagged;
+            if (tid == 0) list->below_zero = 0u;
+            __syncthreads();
+            if (__builtin_amdgcn_readlane((int)row_sum_dpp(list->totals[lane & (SR_WAVES - 1)]), 0) + nb - tail > SR_LIST) return false;     // uniform
+            for (int32_t q0 = 0; q0 < quads;) {
+#pragma unroll
+                for (int j = 0; j < ASK_QUADS; ++j) {
+                    const int32_t q = q0 + j * SR_THREADS + tid;
+                    if (q >= quads) continue;
+                    const float4 x = move_down(v[j], 4 * q - quad_start(4 * q, n));
+                    const uint32_t set = (x.x != 0.0f ? 1u : 0u) | (x.y != 0.0f ? 2u : 0u) | (x.z != 0.0f ? 4u : 0u) | (x.w != 0.0f ? 8u : 0u);
+                    if (set) atomicOr(&bits[q >> 3], set << (4 * (q & 7)));
+                }
+                q0 += ASK_QUADS * SR_THREADS;
+                if (q0 < quads) load_vouchers(q0);           // uniform
+            }
+            bool below = false;
+            for (int32_t p = tail + tid; p < nb; p += SR_THREADS) below = below || !(vouch[p] >= 0.0f);
+            if (below) list->below_zero = 1u;
+            __syncthreads();
+            if (list->below_zero != 0u) return false;        // uniform in the workgroup
+#pragma unroll
+            for (int s = 0; s < SEGS; ++s) in[s] |= bits[s * SR_THREADS + tid] & in_front(s);
+        }
+#pragma unroll
+        for (int s = 0; s < SEGS; ++s) upto[s] = wave_scan_dpp((uint32_t)__popc(in[s]));
         if (lane == 63) {
 #pragma unroll
             for (int s = 0; s < SEGS; ++s) list->totals[s * SR_WAVES + wave] = upto[s];
@@ -1984,6 +2004,9 @@ hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* s
         // 16 384 12.2 / 7.1, 4 x 32 768 18.9 / 8.6; with vouchers asked: 4096 5.5 / 8.6, 8192 8.8 / 9.3, 9000 10.4 / 8.4, 16 384 12.2 / 8.9,
         // 4 x 32 768 18.9 / 10.8.  Rows beyond the registers (above), the walk / list: 4 x 131 072 71.6 / 14.3; with vouchers asked 40 000
         // 31.3 / 15.3, 4 x 131 072 71.6 / 21.7.  Whole pass, one sequence of 131 072 positions in 32 layers, budget 256: 89.5 / 32.2.
+        // A row with more flagged positions than the list holds is taken as a whole after all, and pays for finding that out: of 8192 positions
+        // 0.4 us, 16 384 1.0, 32 768 2.0; with vouchers asked 9000 and 16 384 1.5, 32 768 3.1 (3.4 and 5.0 with the vouchers read in front of
+        // the count; 4 x 131 072, whole call, 87.0 -> 78.8).
         if (list && n > (own_vouchers ? 4 : 8) * SR_THREADS) {
             const auto sparse = own_vouchers ? (n <= 8 * SR_THREADS    ? select_sparse_kernel<2, false>
                                                 : n <= 16 * SR_THREADS ? select_sparse_kernel<4, false>

@@ -88,3 +88,20 @@ def test_selection_with_any_vouchers(n, K, layers, hkv, vouchers):
                 ora.select(None, a[b, :nb], s[b, :nb], v[b, :nb], K, prm.n_sink, prm.n_recent, alpha=0.0, beta=prm.beta, gamma=prm.gamma))
         assert (cnt[:, b] == len(want)).all()
         assert (idx[:, b, :, :len(want)] == want).all(), (b, nb)
+
+
+@pytest.mark.parametrize("n,K,flagged,vouchers", [
+    (8193, 300, 0.9, 0.003), (16387, 64, 0.5, 0.003), (32768, 512, 0.2, 0.9), (131072, 64, 0.05, 0.003),     # the flags alone fill the list
+    (32768, 512, 0.12, 0.0), (32768, 512, 0.11, 0.01), (32768, 512, 0.1, 0.1), (131071, 512, 0.03, 0.0),     # about as many; vouchers as well
+])
+def test_selection_with_many_flags_and_any_vouchers(n, K, flagged, vouchers):
+    rng = np.random.default_rng(n + K)
+    lens = np.array([n, n - 1, n // 2 + 1], np.int32)
+    a, s = rng.random((3, n)) < flagged / 8, rng.random((3, n)) < flagged
+    v = np.where(rng.random((3, n)) < vouchers, rng.random((3, n)) * 2, 0.0).astype(np.float32)
+    prm = ta.Params(alpha=0.0)
+    dev = [torch.from_numpy(x).to(DEV) for x in (a.astype(np.uint8), s.astype(np.uint8), v)]
+    idx, cnt = (x.cpu().numpy().reshape(3, -1) for x in ta.ta_select(None, *dev, K, prm, 1, 1, seq_len=torch.from_numpy(lens).to(DEV)))
+    for b, nb in enumerate(lens):
+        want = ora.select(None, a[b, :nb], s[b, :nb], v[b, :nb], K, prm.n_sink, prm.n_recent, alpha=0.0, beta=prm.beta, gamma=prm.gamma)
+        assert cnt[b, 0] == len(want) and np.array_equal(idx[b], want), (b, nb)
