@@ -1346,16 +1346,22 @@ constexpr int SS_MAX_LDS = 144 * 1024;                     // dynamic LDS of a w
 //   up to 8192 positions of one length, up to 1280 units: the registers.  1024 x 1000, 64 13.0 / 13.4, x 2000, 128 13.9 / 18.1, x 8192, 64
 //     22.5 / 25.4; 1280 x 1500, 64 15.6 / 16.4, x 8192, 256 26.9 / 27.3; 1536 x 1000, 64 17.4 / 15.2, x 4000, 256 21.2 / 21.1; 2048 x 2048, 256 23.8 /
 //     22.8; ragged from a quarter, 1024 x 4096, 256 16.5 / 15.0, x 8192 22.0 / 19.0.
-//   budgets from 384 on: up to 2048 units of one length, 1024 of any.  2048 x 1000, 400 24.4 / 24.8, x 4096, 384 29.3 / 38.2, x 8192, 1024 43.6 / 59.2;
+//   budgets from 384 on: up to 2048 units of one length, 1024 of any (two workgroups to a compute unit: twice what runs at once).  2048 x 1000, 400 24.4 / 24.8, x 4096, 384 29.3 / 38.2, x 8192, 1024 43.6 / 59.2;
 //     16 384 x 1000, 400 165 / 130, x 4000, 1024 218 / 268; ragged 1024 x 1000, 384 10.9 / 12.7, x 8192, 384 23.2 / 24.5, x 8192, 1024 23.8 / 28.4;
 //     3072 x 4096, 512 50.4 / 46.2.
+//   budgets from 640 on and rows of more than 2048 positions: up to 2048 units, ragged or not.  With the fills of the outputs, ragged from an
+//     eighth: 1056 x 4096, 640 21.1 / 27.9, x 4096, 2048 20.1 / 34.2; 1536 x 8192, 640 36.5 / 37.4; 2048 x 3000, 1024 31.4 / 31.2, x 4096, 640
+//     33.8 / 38.6, x 8192, 768 47.2 / 51.7; from a half: 1056 x 8192, 1024 33.6 / 47.0; 1536 x 8192, 640 39.3 / 40.7; 2048 x 4096, 1024 38.9 / 55.3; not
+//     1536 x 2048, 768 28.1 / 25.1; 2048 x 2000, 512 35.2 / 34.4; 3072 x 4096, 640 56.3 / 57.4 and from an eighth 50.8 / 49.6.
+//   (Ragged: lengths are given.  What they are the host does not know.)
 // Long rows: sixteen wavefronts per unit up to 512 units (512 of 65 537: 97 us against 118 with four; 1024 of 40 001: 129 against 92,
 // both before the walk lost its branches).
 constexpr int64_t SS_MIN_UNITS = 1024;
 bool registers_for_many(int64_t units, int32_t n, int32_t K, bool ragged)
 {
     if (n > 8 * SR_THREADS) return false;
-    return K >= 384 ? units <= (ragged ? 1024 : 2048) : units <= 1280 && !ragged;
+    if (K < 384) return units <= 1280 && !ragged;
+    return units <= (!ragged || (K >= 640 && n > 2 * SR_THREADS) ? 2048 : 1024);
 }
 constexpr int64_t SS_BIG_MAX_UNITS = 512;
 

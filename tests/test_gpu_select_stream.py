@@ -131,6 +131,12 @@ def test_streaming_select_rows_at_odd_addresses(n, layers):
     _check(layers, 4, 4, n, 120, 4, 8, "uniform", ragged=(100, n), sample=150)     # 1024 units
 
 
+@pytest.mark.parametrize("layers,n,K,low", [(32, 2049, 640, 100), (33, 2049, 640, 2049), (33, 4097, 900, 500), (34, 8192, 639, 8000), (64, 2303, 700, 600), (65, 2303, 700, 600)])
+def test_many_units_with_lengths_on_both_sides_of_the_line(layers, n, K, low):
+    """Larger budgets: registers up to 2048 units, the walk beyond; below 640 the walk from 1025 units on."""
+    _check(layers, 4, 8, n, K, 4, 8, "ties" if n == 4097 else "uniform", ragged=(low, n), sample=60)
+
+
 @pytest.mark.parametrize("spread", [1e-30, 1.0, 1e30])
 def test_register_select_with_outliers_and_crowded_bins(spread):
     # nearly all keys in one bin of the first level (a few values far away), then exact ties among thousands
