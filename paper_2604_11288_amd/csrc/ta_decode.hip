@@ -343,11 +343,24 @@ __device__ __forceinline__ bool is_anchor(const AnchorTest& t, int32_t p)
 // units of a sequence that count on a line
 __device__ __forceinline__ int32_t units_on(int32_t per_seq, int32_t line) { return (per_seq - line + SYNC_LINES - 1) / SYNC_LINES; }
 
+// An index that the compiler takes to differ from lane to lane.  Where it sees one address, it adds up what the lanes of a wavefront add itself and
+// waits right there for the sum that comes back, and for all that was requested before.
+__device__ __forceinline__ uint32_t lane_index(uint32_t i)
+{
+    asm volatile("" : "+v"(i));
+    return i;
+}
+
 // The last line's first two words, as one: below, how many lines are complete and how many tiles of positions have read the length; above, a bit
 // per tile, set once its vouchers are in memory.
 __device__ __forceinline__ unsigned long long* total_of(const StepArgs& f, int b)
 {
     return reinterpret_cast<unsigned long long*>(f.sync + (size_t)b * SYNC_WORDS + 32 * SYNC_LINES);
+}
+__device__ __forceinline__ unsigned long long add_to_total(const StepArgs& f, int b, unsigned long long v)
+{
+    const uint32_t at = lane_index((uint32_t)(b * (SYNC_WORDS / 2) + 16 * SYNC_LINES));
+    return __hip_atomic_fetch_add(reinterpret_cast<unsigned long long*>(f.sync) + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ uint32_t vouched(unsigned long long total) { return (uint32_t)(total >> 32); }
 __device__ __forceinline__ bool completes(const StepArgs& f, unsigned long long total) { return (int32_t)(uint32_t)total == f.parts - 1; }
@@ -429,7 +442,7 @@ __device__ __forceinline__ void vouch_and_decay(const ta_decode_state& st, const
     __syncthreads();
     unsigned long long total = 0ull;
     if (tid == 0) {
-        total = __hip_atomic_fetch_add(total_of(f, b), (1ull << (32 + tile)) + 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        total = add_to_total(f, b, (1ull << (32 + tile)) + 1ull);
         s_x[0] = (int32_t)vouched(total);
         s_x[1] = completes(f, total) ? 1 : 0;
     }
@@ -699,12 +712,12 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         if (!FUSED || wave != 0 || counted) return;
         counted = true;
         t_new = fs->new_tok[b];
-        if (lane == 0) before = __hip_atomic_fetch_add(&fs->sync[(size_t)b * SYNC_WORDS + 32 * line], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane == 0) before = __hip_atomic_fetch_add(&fs->sync[lane_index((uint32_t)(b * SYNC_WORDS + 32 * line))], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     const auto count_line = [&]() {
         if (!FUSED || wave != 0 || lane != 0 || before != units_on(fs->per_seq, line) - 1) return;
         before = -1;
-        total = __hip_atomic_fetch_add(total_of(*fs, b), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        total = add_to_total(*fs, b, 1ull);
     };
     const auto is_last = [&]() { return wave == 0 && (int32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)total) == fs->parts - 1; };
     if (len_new == 0 || f >= slots) {                      // a sequence at capacity, or no room: nothing to do
