@@ -305,6 +305,7 @@ struct StepArgs {
     int32_t per_seq;                                       // units of a sequence
     int32_t tiles, tile_shift;                             // tiles of 1 << tile_shift positions
     int32_t parts;                                         // what the last line counts up to
+    int32_t lead;                                          // workgroups of positions, where they come in front of the units
     int32_t L;                                             // at most NEAR_SPAN
     unsigned long long span;                               // the bytes of a slot's eight flags that its L predecessors are
     float pw[NEAR_SPAN + 1];
@@ -385,7 +386,7 @@ __device__ __forceinline__ void append(const ta_decode_state& st, const StepArgs
     st.stepped[b] = live ? (p_new + 1) | (an ? (1 << 30) : 0) : 0;
 }
 
-// Trailing workgroups of the one-launch form: vouchers and flags of a tile of positions, then the decay of its budgets.  Units may need those
+// Workgroups of positions of the one-launch form: vouchers and flags of a tile of positions, then the decay of its budgets.  Units may need those
 // budgets, and may run before or after, but nobody waits for anybody, whatever else the chip runs and wherever workgroups are placed (steps
 // of other states may overlap: one that waited could hold the place of the one it waits for).  A budget is overwritten only once all vouchers
 // that are computed from it are in memory, which their tile's bit says: a unit that needs a voucher adds the budgets up, then looks at the
@@ -572,12 +573,17 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     const int lane = threadIdx.x & 63;
     const int wave = WAVES > 1 ? (int)(threadIdx.x >> 6) : 0;
     const int sub = lane & 15, grp = lane >> 4;            // 16 lanes per key row, 4 rows per instruction
-    if ((int)blockIdx.x >= a.units) {                      // trailing workgroups: budget decay
-        if constexpr (FUSED) vouch_and_decay<64 * WAVES>(st, *fs, (int)blockIdx.x - a.units, a.decay, reinterpret_cast<int32_t*>(s_dyn));
-        else if (wave == 0) decay_rider(st, (int)blockIdx.x - a.units, a.decay);
+    // Workgroups of positions: behind the units, whose keys they leave the memory to; without an attention term in front of them, as their chain of
+    // round trips is then what takes longest (us per step, behind / in front: 512 units x 1025 slots 9.1 / 7.5, 1024 x 1025 12.1 / 10.0, 3072 x 501
+    // 12.1 / 10.8, 4096 x 201 10.7 / 9.0; with an attention term 1024 x 257 15.9 / 16.4).
+    constexpr bool LEAD = FUSED && !SCORED;
+    int unit = (int)blockIdx.x;
+    if (LEAD ? unit < fs->lead : unit >= a.units) {
+        if constexpr (FUSED) vouch_and_decay<64 * WAVES>(st, *fs, LEAD ? unit : unit - a.units, a.decay, reinterpret_cast<int32_t*>(s_dyn));
+        else if (wave == 0) decay_rider(st, unit - a.units, a.decay);
         return;
     }
-    const int unit = blockIdx.x;
+    if (LEAD) unit -= fs->lead;
     const int slots = st.K + 1;
     const int G = a.group;
     const int pair = (int)divide((uint32_t)unit, a.by_hkv), l = (int)divide((uint32_t)pair, a.by_batch);
@@ -1289,6 +1295,7 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
         sa.parts = (per_seq < SYNC_LINES ? per_seq : SYNC_LINES) + sa.tiles;
         const uint64_t grid = (uint64_t)units + (uint64_t)sa.tiles * (uint64_t)st.batch;
         if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
+        sa.lead = (int32_t)(grid - units);
         sa.new_tok = new_tok;
         sa.sync = sync;
         sa.per_seq = per_seq;
