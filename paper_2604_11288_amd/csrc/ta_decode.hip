@@ -19,6 +19,7 @@
 // head columns), fed with whole key rows that are turned into operand fragments
 // through a small LDS tile.
 #include <math.h>
+#include <type_traits>
 
 #include "ta_internal.h"
 #include "ta_order.h"
@@ -308,6 +309,7 @@ struct StepArgs {
     int32_t lead;                                          // workgroups of positions, where they come in front of the units
     int32_t L;                                             // at most NEAR_SPAN
     unsigned long long span;                               // the bytes of a slot's eight flags that its L predecessors are
+    uint32_t span_bits;                                    // and their bits
     float pw[NEAR_SPAN + 1];
     int4 rid[TA_MAX_TABLE];                                // n-grams reversed
     int32_t len[TA_MAX_TABLE];                             // 0 past the table's end
@@ -490,34 +492,46 @@ __device__ __forceinline__ s16x4 hi_half(const uint4& v)
     return c.s;
 }
 
+// A bit per byte of eight flags.
+__host__ __device__ __forceinline__ uint32_t flag_bits(unsigned long long flags)
+{
+    const auto four = [](uint32_t x) {                     // 0x80 in every byte that is not zero, then their four bits together
+        const uint32_t high = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;
+        return ((high >> 7) * 0x01020408u) >> 24 & 15u;
+    };
+    return four((uint32_t)flags) | four((uint32_t)(flags >> 32)) << 4;
+}
+
+// What is asked of a slot's eight flags, as the bytes that they are loaded as or a bit each: is one of its L predecessors an anchor, is the
+// one k positions before, is the slot's own position.
+__device__ __forceinline__ bool sponsored(unsigned long long near, const StepArgs& f) { return (near & f.span) != 0ull; }
+__device__ __forceinline__ bool sponsored(uint32_t near, const StepArgs& f) { return (near & f.span_bits) != 0u; }
+__device__ __forceinline__ bool flag_before(unsigned long long near, int k) { return ((near >> (8 * (NEAR_SPAN - k))) & 0xFFull) != 0ull; }
+__device__ __forceinline__ bool flag_before(uint32_t near, int k) { return ((near >> (NEAR_SPAN - k)) & 1u) != 0u; }
+
 // One-launch form: the flags of a lane's slots; s_x[8 + wave] tells the other wavefronts whether one of them is plain - ranks below all
-// sponsored ones - and the last wavefront's s_x[16] whether the new position is an anchor.
-template <int WAVES, int SPL>
-__device__ __forceinline__ void flags_of_slots(const UnitArgs& a, const StepArgs& fs, int wave, int32_t p_new, int32_t len_new, const AnchorTest& test,
-                                               const int32_t (&p0)[SPL], unsigned long long (&near)[SPL], uint8_t (&fl0)[SPL], float (&v0)[SPL], int32_t* s_x)
+// sponsored ones.
+template <int SPL, typename Near>
+__device__ __forceinline__ void flags_of_slots(const UnitArgs& a, const StepArgs& fs, int wave, int32_t len_new,
+                                               const int32_t (&p0)[SPL], const Near (&near)[SPL], uint8_t (&fl0)[SPL], float (&v0)[SPL], int32_t* s_x)
 {
     const int lane = (int)threadIdx.x & 63;
     bool plain = false;
 #pragma unroll
     for (int j = 0; j < SPL; ++j) {
         const int32_t p = p0[j];
-        if (p < NEAR_SPAN) near[j] <<= 8 * (NEAR_SPAN - (p < 0 ? 0 : p));
-        fl0[j] = (uint8_t)(((near[j] & fs.span) != 0ull ? 1 : 0) | ((near[j] >> 56) != 0ull ? 2 : 0));
+        fl0[j] = (uint8_t)((sponsored(near[j], fs) ? 1 : 0) | (flag_before(near[j], 0) ? 2 : 0));
         v0[j] = 0.0f;
         plain = plain || (p >= a.n_sink && p < len_new - a.n_recent && !(fl0[j] & 1));
     }
     const bool some = __ballot(plain) != 0ull;
     if (lane == 0) s_x[8 + wave] = some ? 1 : 0;
-    if (wave == WAVES - 1) {
-        const bool an = is_anchor(test, p_new);
-        if (lane == 0) s_x[16] = an ? 1 : 0;
-    }
 }
 
 // Behind the barrier that follows: is the new position an anchor, and the slots' vouchers if they decide.
-template <int WAVES, int SPL>
+template <int WAVES, int SPL, typename Near>
 __device__ __forceinline__ uint8_t vouchers_of_slots(const ta_decode_state& st, const StepArgs& fs, int b, const int32_t (&p0)[SPL],
-                                                     const unsigned long long (&near)[SPL], float (&v0)[SPL], const int32_t* s_x)
+                                                     const Near (&near)[SPL], float (&v0)[SPL], const int32_t* s_x)
 {
     const uint8_t an_new = (uint8_t)s_x[16];
     int some = 0;
@@ -529,7 +543,7 @@ __device__ __forceinline__ uint8_t vouchers_of_slots(const ta_decode_state& st, 
         for (int j = 0; j < SPL; ++j)
 #pragma unroll 1
             for (int k = 1; k <= fs.L; ++k) {              // increasing distance, as in the fixed-order sum
-                if (p0[j] >= k && ((near[j] >> (8 * (NEAR_SPAN - k))) & 0xFFull) != 0ull)
+                if (p0[j] >= k && flag_before(near[j], k))
                     v0[j] = __fadd_rn(v0[j], __fmul_rn(budget[p0[j] - k], fs.pw[k]));
             }
 #pragma unroll
@@ -537,7 +551,7 @@ __device__ __forceinline__ uint8_t vouchers_of_slots(const ta_decode_state& st, 
         const uint32_t done = vouched(__hip_atomic_load(total_of(fs, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 #pragma unroll
         for (int j = 0; j < SPL; ++j)                      // (without a sponsor, free slots among them: zero whatever the tile does)
-            if ((near[j] & fs.span) != 0ull && (done >> (p0[j] >> fs.tile_shift) & 1u))
+            if (sponsored(near[j], fs) && (done >> (p0[j] >> fs.tile_shift) & 1u))
                 v0[j] = __hip_atomic_load(&st.vouch[(size_t)b * st.cap + p0[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int j = 0; j < SPL; ++j) asm volatile("" : "+v"(v0[j])::"memory");
@@ -711,27 +725,25 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     uint8_t an_new = FUSED ? 0 : (uint8_t)((stepped >> 30) & 1);
     // A unit counts itself in on its line, and a line's last unit counts the line; the sums before its own additions come back while it goes on.
     bool counted = false;
-    int32_t before = -1, t_new = 0;
-    unsigned long long total = ~0ull;
+    int32_t before = -1, sum = -1;
     const int32_t line = FUSED ? (l * st.hkv + g) & (SYNC_LINES - 1) : 0;
     const auto count_in = [&]() {
         if (!FUSED || wave != 0 || counted) return;
         counted = true;
-        t_new = fs->new_tok[b];
         if (lane == 0) before = __hip_atomic_fetch_add(&fs->sync[lane_index((uint32_t)(b * SYNC_WORDS + 32 * line))], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     const auto count_line = [&]() {
         if (!FUSED || wave != 0 || lane != 0 || before != units_on(fs->per_seq, line) - 1) return;
         before = -1;
-        total = add_to_total(*fs, b, 1ull);
+        sum = (int32_t)(uint32_t)add_to_total(*fs, b, 1ull);
     };
-    const auto is_last = [&]() { return wave == 0 && (int32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)total) == fs->parts - 1; };
+    const auto is_last = [&]() { return wave == 0 && __builtin_amdgcn_readfirstlane(sum) == fs->parts - 1; };
     if (len_new == 0 || f >= slots) {                      // a sequence at capacity, or no room: nothing to do
         if (wave == 0 && lane == 0 && a.evicted) a.evicted[unit] = -1;
         if constexpr (FUSED) {
             count_in();
             count_line();
-            if (is_last()) append(st, *fs, b, stepped, t_new, len_new != 0 && is_anchor(request_anchor(st, *fs, b, stepped), stepped), a.decay);
+            if (is_last()) append(st, *fs, b, stepped, fs->new_tok[b], len_new != 0 && is_anchor(request_anchor(st, *fs, b, stepped), stepped), a.decay);
         }
         return;                                            // (every wavefront of the unit: the same test)
     }
@@ -745,7 +757,11 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     const float* vouch = st.vouch + srow;
     float v0[SPL], a0[SPL];
     uint8_t fl0[SPL];
-    unsigned long long near[FUSED ? SPL : 1];              // flags of the positions p - NEAR_SPAN .. p of a slot, a byte each
+    unsigned long long bytes[FUSED ? SPL : 1];             // flags of the positions p - NEAR_SPAN .. p of a slot, a byte each
+    // the same, zeroes in front of the sequence; behind the key stream a bit each, which takes half the registers (paged slots, four
+    // wavefronts of three slots per lane: three registers in scratch cost 1536 units x 513 slots 41.5 -> 47.4 us)
+    using Near = std::conditional_t<SCORED, uint32_t, unsigned long long>;
+    Near near[FUSED ? SPL : 1];
 #pragma unroll
     for (int j = 0; SMALL && j < SPL; ++j) {
         const int s = sbase + lane + 64 * j;
@@ -753,7 +769,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         if (s >= slots) p0[j] = -2;
         const int32_t pc = p0[j] < 0 ? 0 : p0[j];
         if constexpr (FUSED) {
-            __builtin_memcpy(&near[j], st.anchor + srow + (pc > NEAR_SPAN ? pc - NEAR_SPAN : 0), 8);     // (any address)
+            __builtin_memcpy(&bytes[j], st.anchor + srow + (pc > NEAR_SPAN ? pc - NEAR_SPAN : 0), 8);     // (any address)
         } else {
             v0[j] = vouch[pc];
             fl0[j] = spons[pc];
@@ -771,28 +787,44 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     } else if (lane < 32 && wave == 0) Vc[row_at(f) + lane - 16] = nrow;
     __builtin_amdgcn_wave_barrier();                       // the slot table is in LDS for every lane
 
-    // A unit that will not need vouchers has read all that anybody overwrites and counts itself in early: what its sequence's last one then
-    // does hides behind the key stream (256 units x 1025 slots 17.1 -> 16.5 us).  That the first wavefront has a plain slot is enough to know.
-    const auto count_in_early = [&]() {
-        if (wave != 0) return;
+    // The flags have arrived.  A unit that will not need vouchers has read all that anybody overwrites and counts itself in early: what its
+    // sequence's last one then does hides behind the key stream (256 units x 1025 slots 17.1 -> 16.5 us).  That the first wavefront has a plain
+    // slot is enough to know.
+    const auto take_flags = [&]() {
+        AnchorTest test = {};
+        if constexpr (FUSED && !SCORED) {
+            if (wave == WAVES - 1) test = request_anchor(st, *fs, b, p_new);
+        }
         bool plain = false;
 #pragma unroll
         for (int j = 0; FUSED && j < SPL; ++j) {
             const int32_t p = p0[j];
-            const unsigned long long n = p < NEAR_SPAN ? near[j] << (8 * (NEAR_SPAN - (p < 0 ? 0 : p))) : near[j];
-            plain = plain || (p >= a.n_sink && p < len_new - a.n_recent && (n & fs->span) == 0ull);
+            const unsigned long long eight = p < NEAR_SPAN ? bytes[j] << (8 * (NEAR_SPAN - (p < 0 ? 0 : p))) : bytes[j];
+            if constexpr (SCORED) near[j] = flag_bits(eight);
+            else near[j] = eight;
+            plain = plain || (p >= a.n_sink && p < len_new - a.n_recent && !sponsored(near[j], *fs));
         }
-        if (__ballot(plain) != 0ull) count_in();
+        if (wave == 0 && __ballot(plain) != 0ull) count_in();
+        // The table, for the unit.  s_x[16]: is the new position an anchor; s_x[17]: its token.  (Looked up here: the inputs kept in registers
+        // through the key stream took nine of them.)
+        if constexpr (FUSED) {
+            if (wave == WAVES - 1) {
+                if constexpr (SCORED) test = request_anchor(st, *fs, b, p_new);
+                const bool an = is_anchor(test, p_new);
+                if (lane == 0) {
+                    s_x[16] = an ? 1 : 0;
+                    s_x[17] = test.t0;
+                }
+            }
+        }
     };
 
     float m_h[GH], inv_h[GH];
     if constexpr (!SCORED && FUSED) {
-        AnchorTest test = {};
-        if (wave == WAVES - 1) test = request_anchor(st, *fs, b, p_new);
-        count_in_early();
-        flags_of_slots<WAVES, SPL>(a, *fs, wave, p_new, len_new, test, p0, near, fl0, v0, s_x);
+        take_flags();
+        flags_of_slots(a, *fs, wave, len_new, p0, near, fl0, v0, s_x);
         __syncthreads();                                   // every wavefront has read its flags
-        an_new = vouchers_of_slots<WAVES, SPL>(st, *fs, b, p0, near, v0, s_x);
+        an_new = vouchers_of_slots<WAVES>(st, *fs, b, p0, near, v0, s_x);
         count_in();
     }
     if (SCORED) {
@@ -853,22 +885,19 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         // Passes of DT_RING tiles.  While every tile of a pass has a successor DT_RING further on, the
         // pass is straight-line code (first pass apart from the loop: other loads are still in flight
         // around it); the last one or two passes test every tile.
-        AnchorTest test = {};
         int tb = 0;
         if (2 * DT_RING <= ntiles) {
 #pragma unroll
             for (int j = 0; j < DT_RING; ++j) one_tile(j, tiles[j], true);
             if (WAVES > 1) new_key();
-            if (FUSED && wave == WAVES - 1) test = request_anchor(st, *fs, b, p_new);
-            if constexpr (FUSED) count_in_early();
+            if constexpr (FUSED) take_flags();
             for (tb = DT_RING; tb + 2 * DT_RING <= ntiles; tb += DT_RING) {
 #pragma unroll
                 for (int j = 0; j < DT_RING; ++j) one_tile(tb + j, tiles[j], true);
             }
         } else if (WAVES > 1) {
             new_key();
-            if (FUSED && wave == WAVES - 1) test = request_anchor(st, *fs, b, p_new);
-            if constexpr (FUSED) count_in_early();
+            if constexpr (FUSED) take_flags();
         }
         for (; tb < ntiles; tb += DT_RING) {
 #pragma unroll
@@ -880,12 +909,12 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         if (has_free && i16 < G && kq == 0) s_w[i16 * wstride + f] = new_logit;
         if constexpr (FUSED) {
             count_line();
-            flags_of_slots<WAVES, SPL>(a, *fs, wave, p_new, len_new, test, p0, near, fl0, v0, s_x);
+            flags_of_slots(a, *fs, wave, len_new, p0, near, fl0, v0, s_x);
         }
         if (WAVES > 1) __syncthreads();                    // the logits of every wavefront's tiles are in LDS
         else __builtin_amdgcn_wave_barrier();
         if constexpr (FUSED) {
-            an_new = vouchers_of_slots<WAVES, SPL>(st, *fs, b, p0, near, v0, s_x);
+            an_new = vouchers_of_slots<WAVES>(st, *fs, b, p0, near, v0, s_x);
             count_in();
         }
         // softmax statistics of all heads at once: one pass for the maxima, one for the sums.  Several
@@ -1007,7 +1036,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     if (WAVES > 1) {
         if constexpr (FUSED && !SCORED) count_line();
         if constexpr (FUSED) {
-            if (is_last()) append(st, *fs, b, p_new, t_new, an_new != 0, a.decay);
+            if (is_last()) append(st, *fs, b, p_new, s_x[17], an_new != 0, a.decay);
         }
         // without an attention term no barrier lies between the last exchange and this one: other words
         int32_t* s_e = s_x + (SCORED ? 8 : 32);
@@ -1301,6 +1330,7 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
         sa.per_seq = per_seq;
         sa.L = prm.span_L;
         sa.span = prm.span_L > 0 ? ((1ull << (8 * prm.span_L)) - 1ull) << (8 * (NEAR_SPAN - prm.span_L)) : 0ull;
+        sa.span_bits = flag_bits(sa.span);
         for (int k = 0; k <= NEAR_SPAN; ++k) sa.pw[k] = tab.pw[k];
         for (int e = 0; e < TA_MAX_TABLE; ++e) {
             sa.rid[e] = make_int4(tab.rid[e][0], tab.rid[e][1], tab.rid[e][2], tab.rid[e][3]);
