@@ -295,9 +295,10 @@ struct UnitArgs {
 // A step as one launch (FUSED below): what its sequence part works with, and the words in which the workgroups of a sequence count
 // themselves once they have read the length, which the last of them moves on.
 constexpr int NEAR_SPAN = 7;                               // positions before its own whose flags a slot's one 8-byte load brings
-constexpr int SYNC_LINES = 8;                              // lines of 32 words on which a sequence's units count, then one for the lines that are complete and the trailing workgroups
+constexpr int SYNC_LINES = 8;                              // lines of 32 words on which a sequence's units count, then one for the lines that are complete and the tiles of positions
 constexpr int SYNC_WORDS = (SYNC_LINES + 1) * 32;          // of a sequence: one line took 1 to 5 us per step, the units' additions following one another
-constexpr int MAX_TILES = 32;
+constexpr int COUNT_BITS = 8, MAX_TILES = 64 - COUNT_BITS;   // of the last line's number: a count of up to SYNC_LINES + MAX_TILES, and a bit per tile
+static_assert(SYNC_LINES + MAX_TILES < (1 << COUNT_BITS), "the count");
 constexpr int TILE_PER = 4;                                // positions of a thread in flight
 static_assert(SYNC_WORDS == TA_DECODE_SYNC_WORDS, "as the header states it");
 struct StepArgs {
@@ -306,7 +307,7 @@ struct StepArgs {
     int32_t per_seq;                                       // units of a sequence
     int32_t tiles, tile_shift;                             // tiles of 1 << tile_shift positions
     int32_t parts;                                         // what the last line counts up to
-    int32_t lead;                                          // workgroups of positions, where they come in front of the units
+    int32_t lead;                                          // workgroups of positions in front of the units: all or none
     int32_t L;                                             // at most NEAR_SPAN
     unsigned long long span;                               // the bytes of a slot's eight flags that its L predecessors are
     uint32_t span_bits;                                    // and their bits
@@ -365,8 +366,8 @@ __device__ __forceinline__ unsigned long long add_to_total(const StepArgs& f, in
     const uint32_t at = lane_index((uint32_t)(b * (SYNC_WORDS / 2) + 16 * SYNC_LINES));
     return __hip_atomic_fetch_add(reinterpret_cast<unsigned long long*>(f.sync) + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint32_t vouched(unsigned long long total) { return (uint32_t)(total >> 32); }
-__device__ __forceinline__ bool completes(const StepArgs& f, unsigned long long total) { return (int32_t)(uint32_t)total == f.parts - 1; }
+__device__ __forceinline__ unsigned long long vouched(unsigned long long total) { return total >> COUNT_BITS; }
+__device__ __forceinline__ bool completes(const StepArgs& f, unsigned long long total) { return (int32_t)((uint32_t)total & ((1u << COUNT_BITS) - 1u)) == f.parts - 1; }
 
 // Append of a sequence in the one-launch form, by the first wavefront of whichever of its workgroups counts in last.  The length is all that it
 // overwrites and others read (the new position's token, flag and budget are nothing to them, the flag that they test themselves).  Sets the
@@ -445,14 +446,15 @@ __device__ __forceinline__ void vouch_and_decay(const ta_decode_state& st, const
     __syncthreads();
     unsigned long long total = 0ull;
     if (tid == 0) {
-        total = add_to_total(f, b, (1ull << (32 + tile)) + 1ull);
-        s_x[0] = (int32_t)vouched(total);
-        s_x[1] = completes(f, total) ? 1 : 0;
+        total = add_to_total(f, b, (1ull << (COUNT_BITS + tile)) + 1ull);
+        s_x[0] = (int32_t)(uint32_t)total;
+        s_x[1] = (int32_t)(uint32_t)(total >> 32);
     }
     __syncthreads();                                       // which tiles' vouchers are done
-    const uint32_t done = (uint32_t)s_x[0];
-    const int32_t from = tile > 0 && (done >> (tile - 1) & 1u) ? first - NEAR_SPAN : first;
-    int32_t to = tile == f.tiles - 1 || (done >> (tile + 1) & 1u) ? end : end - NEAR_SPAN;
+    total = (unsigned long long)(uint32_t)s_x[1] << 32 | (uint32_t)s_x[0];
+    const unsigned long long done = vouched(total);
+    const int32_t from = tile > 0 && (done >> (tile - 1) & 1ull) ? first - NEAR_SPAN : first;
+    int32_t to = tile == f.tiles - 1 || (done >> (tile + 1) & 1ull) ? end : end - NEAR_SPAN;
     to = live ? (to < p_new ? to : p_new) : from;          // (the new position's budget comes with the append)
     const bool kept = end - first <= CHUNK;                // one round: the budgets are in LDS still
     for (q = from + tid; q < to; q += CHUNK) {
@@ -466,7 +468,7 @@ __device__ __forceinline__ void vouch_and_decay(const ta_decode_state& st, const
         for (int j = 0; j < PER; ++j)
             if (q + j * THREADS < to) B[q + j * THREADS] = __fmul_rn(decay, v[j]);
     }
-    if (tid < 64 && s_x[1] != 0) append(st, f, b, p_new, t0, live && is_anchor(request_anchor(st, f, b, p_new), p_new), decay);
+    if (tid < 64 && completes(f, total)) append(st, f, b, p_new, t0, live && is_anchor(request_anchor(st, f, b, p_new), p_new), decay);
 }
 
 __device__ __forceinline__ uint32_t ordered_bits(float u)
@@ -548,10 +550,10 @@ __device__ __forceinline__ uint8_t vouchers_of_slots(const ta_decode_state& st, 
             }
 #pragma unroll
         for (int j = 0; j < SPL; ++j) asm volatile("" : "+v"(v0[j])::"memory");    // the budgets have been read
-        const uint32_t done = vouched(__hip_atomic_load(total_of(fs, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const unsigned long long done = vouched(__hip_atomic_load(total_of(fs, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 #pragma unroll
         for (int j = 0; j < SPL; ++j)                      // (without a sponsor, free slots among them: zero whatever the tile does)
-            if (sponsored(near[j], fs) && (done >> (p0[j] >> fs.tile_shift) & 1u))
+            if (sponsored(near[j], fs) && (done >> (p0[j] >> fs.tile_shift) & 1ull))
                 v0[j] = __hip_atomic_load(&st.vouch[(size_t)b * st.cap + p0[j]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int j = 0; j < SPL; ++j) asm volatile("" : "+v"(v0[j])::"memory");
@@ -587,17 +589,13 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     const int lane = threadIdx.x & 63;
     const int wave = WAVES > 1 ? (int)(threadIdx.x >> 6) : 0;
     const int sub = lane & 15, grp = lane >> 4;            // 16 lanes per key row, 4 rows per instruction
-    // Workgroups of positions: behind the units, whose keys they leave the memory to; without an attention term in front of them, as their chain of
-    // round trips is then what takes longest (us per step, behind / in front: 512 units x 1025 slots 9.1 / 7.5, 1024 x 1025 12.1 / 10.0, 3072 x 501
-    // 12.1 / 10.8, 4096 x 201 10.7 / 9.0; with an attention term 1024 x 257 15.9 / 16.4).
-    constexpr bool LEAD = FUSED && !SCORED;
     int unit = (int)blockIdx.x;
-    if (LEAD ? unit < fs->lead : unit >= a.units) {
-        if constexpr (FUSED) vouch_and_decay<64 * WAVES>(st, *fs, LEAD ? unit : unit - a.units, a.decay, reinterpret_cast<int32_t*>(s_dyn));
+    if constexpr (FUSED) unit -= fs->lead;
+    if (unit < 0 || unit >= a.units) {                     // in front of the units or behind them: workgroups of positions
+        if constexpr (FUSED) vouch_and_decay<64 * WAVES>(st, *fs, unit < 0 ? unit + fs->lead : unit - a.units, a.decay, reinterpret_cast<int32_t*>(s_dyn));
         else if (wave == 0) decay_rider(st, unit - a.units, a.decay);
         return;
     }
-    if (LEAD) unit -= fs->lead;
     const int slots = st.K + 1;
     const int G = a.group;
     const int pair = (int)divide((uint32_t)unit, a.by_hkv), l = (int)divide((uint32_t)pair, a.by_batch);
@@ -725,7 +723,8 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     uint8_t an_new = FUSED ? 0 : (uint8_t)((stepped >> 30) & 1);
     // A unit counts itself in on its line, and a line's last unit counts the line; the sums before its own additions come back while it goes on.
     bool counted = false;
-    int32_t before = -1, sum = -1;
+    int32_t before = -1;
+    uint32_t sum = ~0u;                                    // (no count there can be)
     const int32_t line = FUSED ? (l * st.hkv + g) & (SYNC_LINES - 1) : 0;
     const auto count_in = [&]() {
         if (!FUSED || wave != 0 || counted) return;
@@ -735,9 +734,9 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     const auto count_line = [&]() {
         if (!FUSED || wave != 0 || lane != 0 || before != units_on(fs->per_seq, line) - 1) return;
         before = -1;
-        sum = (int32_t)(uint32_t)add_to_total(*fs, b, 1ull);
+        sum = (uint32_t)add_to_total(*fs, b, 1ull);
     };
-    const auto is_last = [&]() { return wave == 0 && __builtin_amdgcn_readfirstlane(sum) == fs->parts - 1; };
+    const auto is_last = [&]() { return wave == 0 && completes(*fs, (uint32_t)__builtin_amdgcn_readfirstlane((int)sum)); };
     if (len_new == 0 || f >= slots) {                      // a sequence at capacity, or no room: nothing to do
         if (wave == 0 && lane == 0 && a.evicted) a.evicted[unit] = -1;
         if constexpr (FUSED) {
@@ -1089,19 +1088,20 @@ constexpr int LOOP_SPL = 5;                                // slots per lane and
 // to 16 384 positions 227 / 237).
 //
 // A step as one launch wants several wavefronts per unit, and is ahead of two while there are not so many units that their counting
-// shows, nor rows so long that a tile of positions takes its workgroup several rounds.  us per step, one launch / two: 256 units x 257 slots
-// 9.0 / 10.9, x 1025 16.5 / 17.9 (paged 18.4 / 19.5), x 501 with 8 heads per group 11.4 / 12.8; 1024 x 257 17.1 / 18.4, x 1025 48.5 / 49.4; 3072 x 129 26.4 /
-// 27.1, x 257 42.6 / 43.2; 4096 x 129 32.7 / 33.1, x 257 55.3 / 55.4, x 513 98.3 / 99.9.  So where it can be had, two wavefronts share a unit that one
-// would hold up to 1536 units (1024 units x 65 slots 9.6 / 11.8; 1536 x 65 12.0 / 12.9, x 101 13.7 / 15.0, paged 15.4 / 16.8; 2048 x 31 12.2 / 11.6, x 65
-// 14.7 / 14.4, x 101 with 8 heads per group 17.5 / 18.7).  Rows of positions: 256 units x 257 slots, 32 768 positions 9.6 / 11.7, 65 536 12.3 / 11.8,
-// 131 072 18.6 / 11.8; 1024 x 257, 32 768 18.5 / 19.1, 65 536 21.6 / 19.3; 16 sequences of 16 units x 101 slots, 32 768 9.3 / 11.9, 65 536 12.7 / 12.5.
+// shows.  us per step (replayed from a graph), one launch / two: 256 units x 257 slots 8.6 / 10.3, x 1025 15.2 / 17.0 (paged 16.3 / 18.0), x 501 with
+// 8 heads per group 10.7 / 12.6; 1024 x 257 15.8 / 16.8, x 1025 46.9 / 48.7 (paged 51.4 / 53.0); 1536 x 513 paged 41.8 / 43.3; 3072 x 129 25.1 / 25.5, x 257
+// 41.7 / 42.7; 4096 x 129 31.3 / 31.7, x 257 54.2 / 55.0, x 513 96.3 / 98.1.  So where it can be had, two wavefronts share a unit that one would hold up
+// to 1792 units; 2048 of them fill the chip, and the workgroups of positions begin behind them (1024 units x 65 slots 8.6 / 10.2; 1536 x 65
+// 10.6 / 11.6, x 101 12.5 / 13.8, paged 13.7 / 15.2; 1792 x 31 9.4 / 9.9, x 65 11.0 / 12.1, paged 12.2 / 13.6; 2048 x 31 11.7 / 10.2, x 65 13.3 / 13.1, x 101
+// 14.7 / 15.3).
 //
 // Without an attention term a unit only reads its slot table and flags, so that one launch takes as many wavefronts as hold all slots, while
-// the chip starts them at once (us per step as the calls are issued, at least 8.3; one launch / two, there with a wavefront per
-// unit: 16 units x 1501 slots 8.3 / 14.6; 256 x 1025 8.6 / 12.3, paged 9.2 / 12.9; 1024 x 2001 11.2 / 19.7; 1536 x 1501 11.6 / 16.7; 3072 x 501 10.1 /
-// 12.0; 4096 x 201 paged 10.2 / 12.8; with 16 384 wavefronts: 2048 x 1025 13.1 / 13.9, paged 15.9 / 14.5; 4096 x 257 11.3 / 11.5, paged 12.6 / 11.3).
+// the chip starts them at once (us per step, one launch / two, there with a wavefront per unit: 16 units x 1501 slots 7.5 / 14.6; 256 x 1025
+// 6.9 / 12.2, paged 7.3 / 12.8; 1024 x 2001 12.1 / 19.2; 1536 x 1501 13.7 / 16.6; 2048 x 501 8.8 / 10.4; 3072 x 501 10.5 / 11.1; 4096 x 201 8.9 / 9.0, paged
+// 9.8 / 9.4, and as the calls are issued 9.9 / 11.9; 256 x 257 up to 57 344 positions 7.5 / 6.9, as issued 9.1 / 12.5; with 16 384 wavefronts, before
+// anything was counted: 2048 x 1025 13.1 / 13.9, paged 15.9 / 14.5; 4096 x 257 11.3 / 11.5, paged 12.6 / 11.3).
 static_assert(TA_MAX_DECODE_K + 1 <= 8 * 4 * 64, "the widest form");
-constexpr int FEW_UNITS = 512, FEW_UNITS_ONE_LAUNCH = 1536, ONE_LAUNCH_UNITS = 4096, ONE_LAUNCH_POSITIONS = 40960, ONE_LAUNCH_PLAIN_WAVES = 12288;
+constexpr int FEW_UNITS = 512, FEW_UNITS_ONE_LAUNCH = 1792, ONE_LAUNCH_UNITS = 4096, ONE_LAUNCH_PLAIN_WAVES = 12288;
 // one: a step of one launch can be had, and is taken if several wavefronts share a unit
 UnitForm unit_form(bool scored, int slots, int64_t units, bool one)
 {
@@ -1118,13 +1118,29 @@ UnitForm unit_form(bool scored, int slots, int64_t units, bool one)
     return {8, 4};                                         // at most 2048 slots
 }
 
-// Can a step be one launch: given words to count in (two of them are one number of eight bytes), a span whose flags one load holds, not too
-// many units and rows that are not too long.
+// Can a step be one launch: given words to count in (two of them are one number of eight bytes), a span whose flags one load holds, and not
+// too many units.
 bool one_launch(const ta_params& prm, const ta_decode_state& st, int64_t units, const int32_t* sync)
 {
-    return sync && ((uintptr_t)sync & 7) == 0 && units <= ONE_LAUNCH_UNITS && prm.span_L <= NEAR_SPAN && st.cap > NEAR_SPAN &&
-           st.cap <= ONE_LAUNCH_POSITIONS;
+    return sync && ((uintptr_t)sync & 7) == 0 && units <= ONE_LAUNCH_UNITS && prm.span_L <= NEAR_SPAN && st.cap > NEAR_SPAN;
 }
+// And in this form: rows not so long that a tile of positions takes its workgroup more rounds than the units hide.  Two launches spread them better
+// where sequences are few and units short.  us per step, one launch / two, sequences as long as the rows: 256 units x 257 slots of one sequence, 57 344
+// positions in one round 8.7 / 10.5, 65 536 in two 11.9 / 10.7; x 1025, 131 072 in two 16.8 / 20.5; 1024 x 257 of four, 65 536 in two 19.4 / 22.7, 200 000 in
+// four 23.9 / 29.2; 1024 x 65, 40 960 in two 11.2 / 11.4, in four 17.4 / 11.4; without an attention term 1024 x 501, 65 536 in two 11.0 / 11.5, 131 072 in four
+// 17.5 / 13.7.
+int rounds_of(const ta_decode_state& st, UnitForm f) { return (int)((st.cap - 1) / ((int64_t)MAX_TILES * TILE_PER * 64 * f.waves)) + 1; }
+bool rows_fit(bool scored, const ta_decode_state& st, UnitForm f)
+{
+    if (f.waves >= 8) return rounds_of(st, f) <= 2;
+    if (st.batch < 4) return rounds_of(st, f) <= 1;
+    return rounds_of(st, f) <= (scored ? 2 : 1) * (f.waves >= 4 ? 2 : 1);
+}
+// The workgroups of positions: behind the units, whose keys they leave the memory to (us per step, in front / behind: 256 units x 1025 slots 15.7 /
+// 15.1, 1024 x 257 16.5 / 16.0); in front of them where their chain of round trips is what takes longest, which is without an
+// attention term (512 x 1025 7.5 / 9.1, 1024 x 1025 10.0 / 12.1, 3072 x 501 10.8 / 12.1, 4096 x 201 9.0 / 10.7) or with several rounds (1024 x 257, rows
+// of 40 960 positions in two 18.8 / 21.0; 256 x 1025, 131 072 in two 17.0 / 19.2).
+bool positions_first(bool scored, const ta_decode_state& st, UnitForm f) { return !scored || rounds_of(st, f) > 1; }
 
 // Key tiles in flight: two per wavefront where wavefronts share a unit - enough with all that then share a compute unit, and the
 // registers let more of them do so (six, us per step: 1025 slots, 256 units 21.0 -> 19.8, 1024 units 56.6 -> 52.7; 1501
@@ -1137,10 +1153,10 @@ decode_unit_kernel(ta_decode_state st, UnitArgs a, SlotPages pg)
     decode_unit<GH, PAGED, SCORED, SMALL, (WAVES > 1 ? 2 : PAGED ? 4 : 3), WAVES, SPL>(st, a, pg);
 }
 
-// Paged slots: at most 128 registers (none to eight of them in scratch), so that two workgroups of eight wavefronts share a compute unit as
+// Paged slots: at most 128 registers (none of them in scratch), so that two workgroups of eight wavefronts share a compute unit as
 // those of the two-launch form do: with 131 to 135 they did not, and where units are more than compute units the step fell behind two
 // launches (us per step, 135 / 128 registers / two launches: 320 units x 1135 slots 29.3 / 25.7 / 28.0, 512 x 1025 33.7 / 30.0 / 31.5, 1024 x 1025
-// 63.2 / 55.0 / 55.3, 256 x 1025 17.9 / 17.8 / 20.0).
+// 63.2 / 55.0 / 55.3, 256 x 1025 17.9 / 17.8 / 20.0; from a graph, with none in scratch, 25.1, 28.0, 51.4, 16.3 / 27.0, 29.5, 53.0, 18.0).
 template <int GH, bool PAGED, bool SCORED, int WAVES, int SPL>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(PAGED && SCORED ? 4 : 2)))
 decode_step_kernel(ta_decode_state st, UnitArgs a, SlotPages pg, StepArgs f)
@@ -1300,8 +1316,9 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
     const auto scored_floats = [&](int waves) { return wstride + (1024 + 64) * (size_t)waves + (waves > 1 ? 64 : 0) + (size_t)G * wstride; };
     const bool scored = prm.alpha != 0.0f;
     const bool can = one_launch(prm, st, units, sync);
-    const UnitForm form = unit_form(scored, slots, units, can);
-    const bool one = can && form.waves > 1;
+    const UnitForm shared = unit_form(scored, slots, units, can);
+    const bool one = can && shared.waves > 1 && rows_fit(scored, st, shared);
+    const UnitForm form = one ? shared : unit_form(scored, slots, units, false);
     size_t lds_floats = scored ? scored_floats(form.waves) : wstride + (form.waves > 1 ? 64 : 0);
     a.pg_off = (int32_t)lds_floats;
     a.units = (int32_t)units;
@@ -1324,7 +1341,7 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
         sa.parts = (per_seq < SYNC_LINES ? per_seq : SYNC_LINES) + sa.tiles;
         const uint64_t grid = (uint64_t)units + (uint64_t)sa.tiles * (uint64_t)st.batch;
         if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
-        sa.lead = (int32_t)(grid - units);
+        sa.lead = positions_first(scored, st, form) ? (int32_t)(grid - units) : 0;
         sa.new_tok = new_tok;
         sa.sync = sync;
         sa.per_seq = per_seq;

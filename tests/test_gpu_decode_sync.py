@@ -17,7 +17,7 @@ from paper_2604_11288_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-MARK = 32 * 8 + 1                  # the word with a bit per tile of positions; its highest belongs to none where rows are short: a step of one launch clears it
+MARK = 32 * 8 + 1                  # the word with a bit per tile of positions; its highest belongs to none where there are fewer than 56: a step of one launch clears it
 STATE = ("tok", "len", "anchor", "budget", "vouch", "spons", "pos", "A", "Kc", "Vc", "stepped")
 
 
@@ -128,18 +128,24 @@ def test_steps_of_two_states_overlap():
         assert not st.sync.any()
 
 
-@pytest.mark.parametrize("n", (8, 505, 1018, 1023, 1024, 2041, 3066, 32760, 40900))
-def test_budgets_decay_once_in_every_tile(n):
-    """Tiles of 1024 and 2048 positions, lengths that end at and step over their edges."""
+@pytest.mark.parametrize("n,K", [(n, 5) for n in (8, 505, 1018, 1023, 1024, 2041, 3066, 32760, 40900, 57335, 57336)] +
+                         [(500, 6), (28663, 6), (28664, 6), (65528, 900), (114680, 900), (229367, 900), (229368, 900),
+                          (57336, 7), (100000, 7), (229367, 7), (229368, 7), (40000, 8), (57335, 8), (57336, 8)])
+def test_budgets_decay_once_in_every_tile(n, K):
+    """Tiles of 512 to 4096 positions, lengths that end at and step over their edges, the longest rows of one launch and one position more."""
     prm = ta.Params(n_sink=0, n_recent=1, budget_decay=0.75)
-    lens = [n, max(1, n - 5), max(1, n // 2)]
-    st, ids, tab_len = _state(1, 3, 4, 1, 5, n, n + 9, prm, 0, 40, lens, 7)
+    layers, B, waves, rounds = {5: (1, 3, 4, 1), 6: (171, 3, 2, 1), 7: (1, 4, 4, 4), 8: (129, 4, 2, 2), 900: (1, 3, 8, 2)}[K]
+    lens = [n, max(1, n - 5), max(1, n // 2), max(1, n - 1000)][:B]
+    st, ids, tab_len = _state(layers, B, 4, 1, K, n, n + 9, prm, 0, 40, lens, 7)
     g = torch.Generator(device=DEV).manual_seed(8)
     want = st.budget.clone()
+    tiles = -(-(n + 9) // (256 * waves * rounds))                 # at most 56, else two launches
     for t in range(8):
-        tok = torch.randint(0, 40, (3,), generator=g, device=DEV, dtype=torch.int32)
-        ta.ta_decode_step(st, tok, *(torch.randn((1, 3, h, 128), generator=g, device=DEV).to(torch.bfloat16) for h in (4, 1, 1)), ids, tab_len, prm)
-        for b in range(3):
+        tok = torch.randint(0, 40, (B,), generator=g, device=DEV, dtype=torch.int32)
+        st.sync[:, MARK] = -1 << 31 if tiles != 56 else 0
+        ta.ta_decode_step(st, tok, *(torch.randn((layers, B, h, 128), generator=g, device=DEV).to(torch.bfloat16) for h in (4, 1, 1)), ids, tab_len, prm)
+        assert tiles == 56 or st.sync[:, MARK].any().item() == (tiles > 56)
+        for b in range(B):
             want[b, lens[b] + t] = prm.sponsor_B if st.anchor[b, lens[b] + t] else 0.0
         want *= 0.75
     assert torch.equal(st.budget, want) and st.len.tolist() == [x + 8 for x in lens]
