@@ -1879,7 +1879,7 @@ __device__ __forceinline__ void select_stream(const SelectArgs& a, const int32_t
 }
 
 // WPE: wavefronts per SIMD.  Short candidate lists (budgets up to about 1300): six, which the many short units of a ragged
-// batch need to hide their round trips (two registers go to scratch for it); long lists keep the registers.
+// batch need to hide their round trips (up to six registers of the instance with the margin output go to scratch for it); long lists keep the registers.
 template <int PER_THREAD, int WPE, bool MARGIN, bool OPTS>
 __global__ void __launch_bounds__(SS_THREADS) __attribute__((amdgpu_waves_per_eu(WPE)))
 select_stream_kernel(SelectArgs a, int32_t cap)
@@ -2012,7 +2012,7 @@ hipError_t launch_select(const float* A, const uint8_t* anchor, const uint8_t* s
         // 31.3 / 15.3, 4 x 131 072 71.6 / 21.7.  Whole pass, one sequence of 131 072 positions in 32 layers, budget 256: 89.5 / 32.2.
         // A row with more flagged positions than the list holds is taken as a whole after all, and pays for finding that out: of 8192 positions
         // 0.4 us, 16 384 1.0, 32 768 2.0; with vouchers asked 9000 and 16 384 1.5, 32 768 3.1 (3.4 and 5.0 with the vouchers read in front of
-        // the count; 4 x 131 072, whole call, 87.0 -> 78.8).
+        // the count; 4 x 131 072, whole call, 87.0 -> 78.8).  (Of more than 16 384 positions four to eight registers are then in scratch.)
         if (list && n > (own_vouchers ? 4 : 8) * SR_THREADS) {
             const auto sparse = own_vouchers ? (n <= 8 * SR_THREADS    ? select_sparse_kernel<2, false>
                                                 : n <= 16 * SR_THREADS ? select_sparse_kernel<4, false>
