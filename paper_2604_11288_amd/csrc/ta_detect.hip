@@ -44,14 +44,21 @@ struct DetectArgs {
     int32_t rank;
 };
 
+// Direct global->LDS load, 16 bytes per lane, lane i lands at lds_base + 16 i (inline assembly so that the compiler does not wait
+// for all of them before every LDS read).  STREAM: with the non-temporal hint.
+template <bool STREAM = false>
 __device__ __forceinline__ void dma16(const void* base, uint32_t off, uint32_t lds_base)
 {
-    // direct global->LDS load, 16 bytes per lane, lane i lands at lds_base + 16 i (inline assembly
-    // so that the compiler does not wait for all of them before every LDS read)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(lds_base), "v"(off), "s"(base)
-                 : "memory", "m0");
+    if constexpr (STREAM)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(lds_base), "v"(off), "s"(base)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(lds_base), "v"(off), "s"(base)
+                     : "memory", "m0");
 }
 
 constexpr int vm_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
@@ -91,11 +98,18 @@ __device__ __forceinline__ float add_squares(uint4 v, float acc)
 
 enum { MODE_MLP = 0, MODE_COSINE = 1 };
 
+// The first of `steps` steps over the features: another one from workgroup to neighbouring workgroup of an XCD (workgroup b runs
+// on XCD b mod 8), the others follow in order and wrap round.  Rows lie a power of two apart more often than not, so
+// workgroups that start together at feature 0 all read the same offset within their rows and crowd a few memory channels (us, all
+// at feature 0 / rotated: 131 072 positions, d_model 4096, 128 units 231 / 180 = 6.0 TB/s; 65 536, d_model 2048, 65 / 49; 64 units,
+// 131 072, d_model 4096, 207 / 188; 128 256 rows and 16 concepts, 32 positions per workgroup, 211 / 147 = 7.15 TB/s).
+__device__ __forceinline__ int first_step(int steps) { return (int)((blockIdx.x >> 3) % (uint32_t)steps); }
+
 // ---- shared form: the wavefronts of a workgroup share every slice ---------------------------------------
 // TW: wavefront rows over the positions (64 TW positions per workgroup); HT: 32-unit hidden tiles
 // per wavefront; MH: wavefront columns over the hidden units (m = 32 HT MH); MODE: which epilogue; DT_RING: slice
-// buffers, loads run DT_RING - 1 slices ahead
-template <int TW, int HT, int MH, int MODE, int DT_RING>
+// buffers, loads run DT_RING - 1 slices ahead; STREAM: see launch_hint
+template <int TW, int HT, int MH, int MODE, int DT_RING, bool STREAM>
 __global__ void __launch_bounds__(64 * TW * MH, 2)
 detect_kernel(DetectArgs a)
 {
@@ -152,13 +166,16 @@ detect_kernel(DetectArgs a)
     const uint32_t half_back = ((lane & 7) ^ (lane >> 3)) >= 4 ? 64u : 0u;   // half a slice: the second half repeats the first
     const char* hbase = reinterpret_cast<const char*>(a.h) + tile0 * a.h_row_bytes;
     const char* wbase = reinterpret_cast<const char*>(a.W1);
-    const auto issue = [&](int s) {
-        const uint32_t dst = lds0 + (uint32_t)(s % DT_RING) * BUF_BYTES;
+    const int first = first_step(nstages);
+    const auto slice_of = [&](int i) { return first + i >= nstages ? first + i - nstages : first + i; };
+    const auto issue = [&](int i) {
+        const uint32_t dst = lds0 + (uint32_t)(i % DT_RING) * BUF_BYTES;
+        const int s = slice_of(i);
         const char* hs = hbase + (size_t)s * (DT_KS * 2);
         const char* ws = wbase + (size_t)s * (DT_KS * 2);
         const uint32_t back = s * DT_KS + 32 >= a.dm ? half_back : 0u;
 #pragma unroll
-        for (int j = 0; j < LH; ++j) dma16(hs, off_h[j] - back, __builtin_amdgcn_readfirstlane(dst + ins_h[j] * 1024));
+        for (int j = 0; j < LH; ++j) dma16<STREAM>(hs, off_h[j] - back, __builtin_amdgcn_readfirstlane(dst + ins_h[j] * 1024));
 #pragma unroll
         for (int j = 0; j < LW; ++j)
             dma16(ws, off_w[j] - back, __builtin_amdgcn_readfirstlane(dst + H_BYTES + ins_w[j] * 1024));
@@ -211,7 +228,7 @@ detect_kernel(DetectArgs a)
         const uint4* buf = s_buf + (size_t)(s % DT_RING) * (BUF_BYTES / 16);
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) {
-            if (ks == 2 && s * DT_KS + 32 >= a.dm) break;   // uniform
+            if (ks == 2 && slice_of(s) * DT_KS + 32 >= a.dm) break;   // uniform
             uint4 hraw[2], wraw[HT];
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) hraw[tt] = buf[slot_h[tt][ks]];
@@ -359,7 +376,7 @@ struct SplitShape {
     static constexpr int LDS_BYTES = UNITS * 16 + (M + THREADS + WV * M + WV * POS) * 4;
 };
 
-template <int PT, int NT, int WV, int R, int MODE>
+template <int PT, int NT, int WV, int R, int MODE, bool STREAM>
 __global__ void __launch_bounds__(64 * WV)
 detect_split_kernel(DetectArgs a)
 {
@@ -398,14 +415,17 @@ detect_split_kernel(DetectArgs a)
     const char* wbase = reinterpret_cast<const char*>(a.W1);
     uint4* ring = s_buf + wave * (R * S::STEP_UNITS);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)ring;
-    const auto half = [&](int i) { return 64 * (wave + WV * i) + 32 >= a.dm; };
+    const int first = mine > 0 ? first_step(mine) : 0;
+    const auto step_of = [&](int i) { return wave + WV * (first + i >= mine ? first + i - mine : first + i); };
+    const auto half = [&](int i) { return 64 * step_of(i) + 32 >= a.dm; };
     const auto issue = [&](int i) {
         const uint32_t dst = lds0 + (uint32_t)(i % R) * (S::STEP_UNITS * 16);
-        const size_t at = (size_t)(wave + WV * i) * 128;
+        const size_t at = (size_t)step_of(i) * 128;
         const uint32_t back = half(i) ? half_back : 0u;
 #pragma unroll
-        for (int j = 0; j < LPS; ++j)
-            dma16((j < 2 * PT ? hbase : wbase) + at, off[j] - back, __builtin_amdgcn_readfirstlane(dst + j * 1024));
+        for (int j = 0; j < 2 * PT; ++j) dma16<STREAM>(hbase + at, off[j] - back, __builtin_amdgcn_readfirstlane(dst + j * 1024));
+#pragma unroll
+        for (int j = 2 * PT; j < LPS; ++j) dma16(wbase + at, off[j] - back, __builtin_amdgcn_readfirstlane(dst + j * 1024));
     };
     // this lane's fragments inside a 2 KB tile of 16 rows
     const int slot0 = r16 * 8 + (grp ^ (r16 & 7)), slot1 = r16 * 8 + ((4 + grp) ^ (r16 & 7));
@@ -554,7 +574,7 @@ detect_split_kernel(DetectArgs a)
     }
 }
 
-template <int TW, int HT, int MH, int MODE, int RING>
+template <int TW, int HT, int MH, int MODE, int RING, bool STREAM>
 hipError_t launch_one(const DetectArgs& a, hipStream_t st)
 {
     constexpr int M = 32 * HT * MH;
@@ -562,74 +582,86 @@ hipError_t launch_one(const DetectArgs& a, hipStream_t st)
     const size_t lds = (size_t)RING * (DT_TOKENS + M) * 128 + (size_t)M * 4 + (size_t)(MH + 1) * DT_TOKENS * 4;
     static DeviceOnce setup;                               // dynamic LDS above 64 KB needs the attribute (per instantiation)
     const hipError_t attr_err = setup.run([&](int) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_kernel<TW, HT, MH, MODE, RING>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_kernel<TW, HT, MH, MODE, RING, STREAM>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned blocks = (unsigned)((a.total + DT_TOKENS - 1) / DT_TOKENS);
-    hipLaunchKernelGGL((detect_kernel<TW, HT, MH, MODE, RING>), dim3(blocks), dim3(64 * TW * MH), lds, st, a);
+    hipLaunchKernelGGL((detect_kernel<TW, HT, MH, MODE, RING, STREAM>), dim3(blocks), dim3(64 * TW * MH), lds, st, a);
     return hipGetLastError();
 }
 
-template <int PT, int NT, int WV, int R, int MODE>
+template <int PT, int NT, int WV, int R, int MODE, bool STREAM>
 hipError_t launch_split(const DetectArgs& a, hipStream_t st)
 {
     using S = SplitShape<PT, NT, WV, R>;
     static DeviceOnce setup;
     const hipError_t attr_err = setup.run([&](int) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE, STREAM>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES);
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned blocks = (unsigned)((a.total + S::POS - 1) / S::POS);
-    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
+    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE, STREAM>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
     return hipGetLastError();
 }
 
 // Which form runs.  A workgroup of the split form streams all of W1 (1 MB at d_model 4096, 128 units) for its 16, 32 or
 // 64 positions, and the sum of these streams is what bounds it (about 12 TB/s over all L2s); a workgroup of the
 // shared form does so for 128 or 256 positions but needs many positions to fill the chip.  So: the smallest tile
-// that gives every compute unit at most one workgroup (16 positions up to 4096, 32 up to 8192), then 64 positions, and
-// the shared form where W1's traffic counts.  Measured at d_model 4096, in us, split / shared form (and before either,
-// 256 positions per workgroup and 64-byte slices):
-//   128 units:  4096 positions 19 (95);  8192: 28 / 47 (108);  16384: 38 / 49 (113);  32768: 72 / 70 (128);
-//               65536: 136 / 133 (153);  524288: 1018 / 863 (856)
-//   256 units:  4096: 31 (110);  8192: 42 / 64 (110);  16384: 75 / 65 (115);  32768: 147 / 82 (120);
-//               65536: 285 / 145 (153);  524288: 2220 / 1161 (1213)
-//   64 units:   4096: 13 (62);  16384: 31 (73);  262144: 420 (432)
-//   32 units:   4096: 11 (56);  16384: 29 (68);  262144: 380 (423)
-//   16 concepts (cosine): 8000 rows 13 (55);  128256 rows 174 = 6.0 TB/s (212)
-template <int MODE>
+// that gives every compute unit at most one workgroup (16 positions up to 4096, 32 up to 8192, 64 up to 16384), then
+// the shared form where W1's traffic counts.  Measured at d_model 4096, in us, split / shared form (ring of three buffers, of two):
+//   128 units:  8192: 25 / 47;  16384: 34.5 / 61;  20000: 63 / 52, 64;  28672: 66 / 52, 64;  32768: 67 / 54, 66;  40000: 98 / 102, 82;
+//               131072: 254 / 205, 180;  d_model 2048, 20000: 38 / -, 35;  28672: 39.7 / 29.2, 34.8
+//   256 units:  8192: 42 / 64;  16384: 75 / 65;  32768: 147 / 82;  131072: - / 320 (128 positions), 265 (256)
+//   64 units, 64 positions with four wavefronts / 32:  16384: 26.4 / 35;  65536: 95 / 124;  131072: 187 / 245
+//   32 units:   65536: 83;  262144: 315 = 6.8 TB/s
+//   up to 16 concepts (cosine), 32 positions with four wavefronts / 16 with eight:  8000 rows 13.4 / 15.2;  32000: 39.4 / 41.3;
+//               128256: 146 / 164;  d_model 2048, 100000: 59 / -;  d_model 1024, 160000: 47
+template <int MODE, bool STREAM>
 hipError_t launch_width(const DetectArgs& a, hipStream_t st)
 {
     const int64_t P = a.total;
-    // Rows of few steps: fewer wavefronts, so that each has several steps of its own to keep in flight (d_model 1024: 93388 rows
-    // and 16 concepts 28 us with four wavefronts, 37 with eight; 131072 positions, 32 units 52 / 56, 64 units 58 with two
-    // wavefronts, 68 with four; d_model 2048: 70 / 76, 100 / 108, 108 / 124).
+    const int64_t cus = compute_units();
+    // Rows of few steps: fewer wavefronts, so that each has several steps of its own to keep in flight (d_model 1024, 131072
+    // positions: 32 units 52 us with four wavefronts, 56 with eight, 64 units 58 with two, 68 with four; d_model 2048: 100 / 108, 108 / 124).
     const bool narrow = a.dm <= 2048;
-    if (MODE == MODE_COSINE && a.wrows <= 16) return narrow ? launch_split<2, 1, 4, 2, MODE>(a, st) : launch_split<1, 1, 8, 2, MODE>(a, st);
+    if (MODE == MODE_COSINE && a.wrows <= 16) return launch_split<2, 1, 4, 2, MODE, STREAM>(a, st);
     switch (a.m) {
         case 32:
-            if (P <= 4096) return launch_split<1, 2, 8, 2, MODE>(a, st);
-            if (P <= 8192) return launch_split<2, 2, 4, 2, MODE>(a, st);
-            if (narrow && P > 24576) return launch_split<2, 2, 4, 2, MODE>(a, st);
-            return launch_split<4, 2, 8, 1, MODE>(a, st);
+            if (P <= 4096) return launch_split<1, 2, 8, 2, MODE, STREAM>(a, st);
+            if (P <= 8192) return launch_split<2, 2, 4, 2, MODE, STREAM>(a, st);
+            if (narrow && P > 24576) return launch_split<2, 2, 4, 2, MODE, STREAM>(a, st);
+            return launch_split<4, 2, 8, 1, MODE, STREAM>(a, st);
         case 64:
-            if (P <= 4096) return launch_split<1, 4, 4, 3, MODE>(a, st);
-            if (P <= 8192) return launch_split<2, 4, 4, 2, MODE>(a, st);
-            if (narrow && P > 24576) return launch_split<4, 4, 2, 2, MODE>(a, st);
-            return launch_split<4, 4, 4, 2, MODE>(a, st);
+            if (P <= 4096) return launch_split<1, 4, 4, 3, MODE, STREAM>(a, st);
+            if (P <= 8192) return launch_split<2, 4, 4, 2, MODE, STREAM>(a, st);
+            if (narrow && P > 24576) return launch_split<4, 4, 2, 2, MODE, STREAM>(a, st);
+            return launch_split<4, 4, 4, 2, MODE, STREAM>(a, st);
         case 128:
-            if (P <= 4096) return launch_split<1, 8, 4, 2, MODE>(a, st);
-            if (P <= 8192) return launch_split<2, 8, 4, 1, MODE>(a, st);
-            if (P <= 24576) return launch_split<4, 8, 4, 1, MODE>(a, st);
-            return launch_one<2, 2, 2, MODE, 2>(a, st);
+            if (P <= 4096) return launch_split<1, 8, 4, 2, MODE, STREAM>(a, st);
+            if (P <= 8192) return launch_split<2, 8, 4, 1, MODE, STREAM>(a, st);
+            if (P <= 64 * cus) return launch_split<4, 8, 4, 1, MODE, STREAM>(a, st);
+            // 128 positions per workgroup; three buffers (one workgroup per compute unit) while that is one round of workgroups
+            if (P <= 128 * cus) return launch_one<2, 2, 2, MODE, 3, STREAM>(a, st);
+            return launch_one<2, 2, 2, MODE, 2, STREAM>(a, st);
         default:
-            if (P <= 4096) return launch_split<1, 16, 4, 1, MODE>(a, st);
-            if (P <= 8192) return launch_split<2, 16, 4, 1, MODE>(a, st);
-            if (P <= 32768) return launch_one<2, 2, 4, MODE, 3>(a, st);
-            return launch_one<4, 2, 4, MODE, 2>(a, st);
+            if (P <= 4096) return launch_split<1, 16, 4, 1, MODE, STREAM>(a, st);
+            if (P <= 8192) return launch_split<2, 16, 4, 1, MODE, STREAM>(a, st);
+            if (P <= 32768) return launch_one<2, 2, 4, MODE, 3, STREAM>(a, st);
+            return launch_one<4, 2, 4, MODE, 2, STREAM>(a, st);
     }
+}
+
+// The rows of h (or x) are read once.  Where they are many the streaming hint leaves the rest of a workgroup's operands in the
+// caches (us, without / with it, eight sets of inputs in turn: 128 256 rows of 4096 and 16 concepts 173 / 166; 131 072 positions of 4096
+// and 64 units 216 / 204; 8192 of 4096 and 128 units, 64 MiB, 27.5 / 26.8); fewer may lie in the caches from whoever wrote them, and the hint gives
+// up what stays there (4096 of 4096 and 128 units 17.3 / 19.1).
+template <int MODE>
+hipError_t launch_hint(const DetectArgs& a, hipStream_t st)
+{
+    constexpr int64_t STREAM_BYTES = int64_t(64) << 20;
+    return a.total * a.dm * 2 >= STREAM_BYTES ? launch_width<MODE, true>(a, st) : launch_width<MODE, false>(a, st);
 }
 
 }  // namespace
@@ -657,7 +689,7 @@ hipError_t launch_detect(const void* h, int64_t h_row_stride, const void* W1, co
     a.scale = scale;
     a.rank = rank;
     a.wrows = m;
-    return launch_width<MODE_MLP>(a, st);
+    return launch_hint<MODE_MLP>(a, st);
 }
 
 hipError_t launch_cosine(const void* x, int64_t x_row_stride, const void* C, int32_t E, int64_t rows, int32_t dm,
@@ -681,7 +713,7 @@ hipError_t launch_cosine(const void* x, int64_t x_row_stride, const void* C, int
     a.B = 0.0f;
     a.scale = 0.0f;
     a.rank = 0;
-    return launch_width<MODE_COSINE>(a, st);
+    return launch_hint<MODE_COSINE>(a, st);
 }
 
 }  // namespace ta

@@ -117,6 +117,21 @@ def test_detect_forms_at_their_limits(m, n):
     _check_decisions(got[:, rows], ref, anchor.cpu().numpy()[:, rows], anchor_B.cpu().numpy()[:, rows], 0.3, True, 15.0, 2.0)
 
 
+@pytest.mark.parametrize("m", [32, 64, 128, 256])
+@pytest.mark.parametrize("n, dm", [(17000, 2080), (33600, 1056)])
+def test_detect_streamed_rows(n, dm, m):
+    # 64 MiB of hidden states and more (streaming loads), steps that start elsewhere in every workgroup, the last one half a step
+    assert n * dm * 2 >= 64 << 20
+    h, W1, W2 = wl.make_detector_inputs(1, n, dm, m, seed=wl.BASE_SEED + n + m, p_anchor=0.1, device=DEV)
+    conf, anchor, anchor_B = ta.ta_detect_anchors(h, W1, W2, ta.Params(), 0.3, True, 2.0)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(0, 70), np.arange(130 * 64 - 35, 130 * 64 + 35), np.arange(n - 70, n)]))
+    ref = _conf_ref(h[:, _dev(rows)], W1, W2)
+    got = conf.cpu().numpy()
+    assert _close(got[:, rows], ref).all(), np.abs(got[:, rows] - ref).max()
+    _check_decisions(got[:, rows], ref, anchor.cpu().numpy()[:, rows], anchor_B.cpu().numpy()[:, rows], 0.3, True, 15.0, 2.0)
+
+
 def test_detect_rejects_unsupported_shapes():
     prm = ta.Params(n_sink=4, n_recent=4)
     h, W1, W2 = wl.make_detector_inputs(1, 64, 64, 32, device=DEV)
