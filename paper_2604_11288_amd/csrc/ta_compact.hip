@@ -2,79 +2,70 @@
 // along the sequence dimension, Sec. 3.2 "Token selection"; Alg. 1, eviction
 // step).  Pure data movement, bound by HBM.
 //
-// A 256-byte row (d = 128 bf16) is moved by 16 lanes with one 16-byte load and
-// one 16-byte store each, so a wavefront moves 4 rows per instruction.  A
-// workgroup takes ROWS_PER_BLOCK consecutive output rows of one unit and issues
-// all of its loads (K and V) before the first store to keep many requests in
-// flight per lane.
+// A 256-byte row (d = 128 bf16) is moved by 16 lanes with one 16-byte load and one 16-byte store each, two rows in flight
+// per lane.  A workgroup takes 32 consecutive output rows of one unit and one of the two tensors: the first half of the launch
+// moves the keys, the second the values.  The memory's changes between reading and writing bound it, and these cost
+// least where few places are open at a time.  (us, 64 rows of both tensors per workgroup / this: 256 units x 1024 rows 46.6 / 44.2,
+// 1024 x 512 95 / 90, in one run of rows 96.5 / 83.3 = 6.4 TB/s read and written, 1024 x 777 141.5 / 132, 4096 x 100 80.8 / 73.4; one
+// tensor, 64 rows of 256 threads 45.5, 92.7, 88.8, 136.5, 76.5; 16 rows of 128 threads 43.9, 89.4, 85, 132.9, 69.7, but 2048 x 20 11.0 for 9.3.)
 #include "ta_gather.h"
 
 namespace ta {
 
 namespace {
 
-constexpr int COMPACT_THREADS = 256;
-constexpr int ROWS_PER_ITER = COMPACT_THREADS / 16;     // 16 rows per pass over the block
-constexpr int COMPACT_ITERS = 4;
+constexpr int COMPACT_THREADS = 256, COMPACT_ITERS = 2;
+constexpr int ROWS_PER_ITER = COMPACT_THREADS / 16;      // 16 rows per pass over the block
 constexpr int ROWS_PER_BLOCK = ROWS_PER_ITER * COMPACT_ITERS;
 
 template <bool PAGED, bool LAYERED, bool DST_PAGED = false>
 __global__ void __launch_bounds__(COMPACT_THREADS)
 compact_kernel(CompactArgs a)
 {
-    const int32_t unit = (int32_t)(blockIdx.x / (uint32_t)a.blocks_per_unit);
-    const int32_t blk = (int32_t)(blockIdx.x % (uint32_t)a.blocks_per_unit);
-    const int32_t h = unit % a.hkv;
-    const int32_t b = (unit / a.hkv) % a.batch;
-    const int32_t l = unit / (a.hkv * a.batch);
+    const int32_t unit = (int32_t)divide(blockIdx.x, a.by_blocks);
+    const int32_t blk = (int32_t)blockIdx.x - unit * a.blocks_per_unit;
+    const bool values = blockIdx.y != 0;
+    const int32_t pair = (int32_t)divide((uint32_t)unit, a.by_hkv), h = unit - pair * a.hkv;
+    const int32_t l = (int32_t)divide((uint32_t)pair, a.by_batch), b = pair - l * a.batch;
     const int32_t sel = a.idx_shared ? b : unit;
+    const int lane16 = threadIdx.x & 15;
+    const int32_t row0 = blk * ROWS_PER_BLOCK + (int32_t)(threadIdx.x >> 4);
+    const int32_t* idx = a.idx + (size_t)sel * (size_t)a.K;
+    int32_t p[COMPACT_ITERS];
+#pragma unroll
+    for (int j = 0; j < COMPACT_ITERS; ++j) {              // requested together with the count
+        const int32_t r = row0 + j * ROWS_PER_ITER;
+        p[j] = idx[r < a.K ? r : a.K - 1];
+    }
     int32_t cnt = a.cnt[sel];
     cnt = cnt > a.K ? a.K : cnt;
-    const int32_t* idx = a.idx + (size_t)sel * (size_t)a.K;
-    const int64_t out_base = (int64_t)(LAYERED ? unit - l * a.hkv * a.batch : unit) * a.K * 16;
-
-    const int lane16 = threadIdx.x & 15;
-    const int rsub = threadIdx.x >> 4;
     if (blk * ROWS_PER_BLOCK >= cnt) return;              // whole block past the retained rows
-    // named registers (not an indexed array) so the loads stay in VGPRs
-    const int32_t row0 = blk * ROWS_PER_BLOCK + rsub;
     const RowSource<PAGED, LAYERED> rows(a, l, b, h, lane16);
-    auto src = [&](int32_t r) -> int64_t {
-        r = r < cnt ? r : cnt - 1;                          // tail lanes re-read the last row, store nothing
-        int32_t p = idx[r];
-        p = p < 0 ? 0 : (p >= a.n ? a.n - 1 : p);
-        return rows(p);
-    };
-    static_assert(COMPACT_ITERS == 4, "loads below are written out four times");
-    const int64_t o0 = src(row0), o1 = src(row0 + ROWS_PER_ITER);
-    const int64_t o2 = src(row0 + 2 * ROWS_PER_ITER), o3 = src(row0 + 3 * ROWS_PER_ITER);
+    const u32x4* in = reinterpret_cast<const u32x4*>(LAYERED ? global_ptr(values ? a.Vin_l[l] : a.Kin_l[l]) : (values ? a.Vin : a.Kin));
+    u32x4* out = reinterpret_cast<u32x4*>(LAYERED ? global_ptr(values ? a.Vout_l[l] : a.Kout_l[l]) : (values ? a.Vout : a.Kout));
+    u32x4 v[COMPACT_ITERS];
+#pragma unroll
+    for (int j = 0; j < COMPACT_ITERS; ++j) {
+        const int32_t r = row0 + j * ROWS_PER_ITER;        // (past the last row: an index within the tensor, not stored)
+        const int32_t q = r < cnt ? p[j] : p[0];
+        v[j] = __builtin_nontemporal_load(&in[rows(q < 0 ? 0 : (q >= a.n ? a.n - 1 : q))]);
+    }
     // The compacted rows are not read again by this pass: streaming stores keep them from
     // lingering in the caches as dirty lines that the next kernel's reads would have to evict.
-    const u32x4* Kin = reinterpret_cast<const u32x4*>(LAYERED ? global_ptr(a.Kin_l[l]) : a.Kin);
-    const u32x4* Vin = reinterpret_cast<const u32x4*>(LAYERED ? global_ptr(a.Vin_l[l]) : a.Vin);
-    u32x4* Kout = reinterpret_cast<u32x4*>(LAYERED ? global_ptr(a.Kout_l[l]) : a.Kout);
-    u32x4* Vout = reinterpret_cast<u32x4*>(LAYERED ? global_ptr(a.Vout_l[l]) : a.Vout);
-    const u32x4 k0 = __builtin_nontemporal_load(&Kin[o0]), k1 = __builtin_nontemporal_load(&Kin[o1]);
-    const u32x4 k2 = __builtin_nontemporal_load(&Kin[o2]), k3 = __builtin_nontemporal_load(&Kin[o3]);
-    const u32x4 v0 = __builtin_nontemporal_load(&Vin[o0]), v1 = __builtin_nontemporal_load(&Vin[o1]);
-    const u32x4 v2 = __builtin_nontemporal_load(&Vin[o2]), v3 = __builtin_nontemporal_load(&Vin[o3]);
-    auto put = [&](int32_t r, const u32x4& kk, const u32x4& vv) {
-        if (r < cnt) {
-            int64_t off = out_base + (int64_t)r * 16 + lane16;
-            if (DST_PAGED) {
-                const int32_t slot = r / a.d_page_size;
-                int32_t page = a.d_table[(size_t)b * a.d_max_pages + slot];
-                page = page < 0 ? 0 : (page >= a.d_num_pages ? a.d_num_pages - 1 : page);
-                off = l * a.d_layer + (int64_t)page * a.d_page + (int64_t)(r - slot * a.d_page_size) * a.d_pos + h * a.d_head + lane16;
-            }
-            __builtin_nontemporal_store(kk, &Kout[off]);
-            __builtin_nontemporal_store(vv, &Vout[off]);
+    const int64_t out_base = (int64_t)(LAYERED ? unit - l * a.hkv * a.batch : unit) * a.K * 16 + lane16;
+#pragma unroll
+    for (int j = 0; j < COMPACT_ITERS; ++j) {
+        const int32_t r = row0 + j * ROWS_PER_ITER;
+        if (r >= cnt) continue;
+        int64_t off = out_base + (int64_t)r * 16;
+        if (DST_PAGED) {
+            const int32_t slot = r / a.d_page_size;
+            int32_t page = a.d_table[(size_t)b * a.d_max_pages + slot];
+            page = page < 0 ? 0 : (page >= a.d_num_pages ? a.d_num_pages - 1 : page);
+            off = l * a.d_layer + (int64_t)page * a.d_page + (int64_t)(r - slot * a.d_page_size) * a.d_pos + h * a.d_head + lane16;
         }
-    };
-    put(row0, k0, v0);
-    put(row0 + ROWS_PER_ITER, k1, v1);
-    put(row0 + 2 * ROWS_PER_ITER, k2, v2);
-    put(row0 + 3 * ROWS_PER_ITER, k3, v3);
+        __builtin_nontemporal_store(v[j], &out[off]);
+    }
 }
 
 // Writes a table of per-layer addresses, handed over by value, to device memory: the kernels of the
@@ -172,6 +163,9 @@ CompactArgs make_compact_args(const void* Kin, const void* Vin, const int32_t* i
     a.K = K;
     a.idx_shared = idx_shared;
     a.blocks_per_unit = (K + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
+    a.by_blocks = divider((uint32_t)a.blocks_per_unit);
+    a.by_hkv = divider((uint32_t)lay.hkv);
+    a.by_batch = divider((uint32_t)lay.batch);
     return a;
 }
 
@@ -183,7 +177,7 @@ hipError_t launch_compact(const void* Kin, const void* Vin, const int32_t* idx, 
     const CompactArgs a = make_compact_args(Kin, Vin, idx, cnt, lay, K, idx_shared, Kout, Vout, pg, lp, dst_pg);
     int64_t units = (int64_t)lay.layers * lay.batch * lay.hkv;
     int64_t blocks = units * a.blocks_per_unit;
-    const dim3 grid((unsigned)blocks), block(COMPACT_THREADS);
+    const dim3 grid((unsigned)blocks, 2), block(COMPACT_THREADS);
     if (dst_pg && pg) hipLaunchKernelGGL((compact_kernel<true, false, true>), grid, block, 0, st, a);
     else if (dst_pg) hipLaunchKernelGGL((compact_kernel<false, false, true>), grid, block, 0, st, a);
     else if (pg && lp) hipLaunchKernelGGL((compact_kernel<true, true>), grid, block, 0, st, a);

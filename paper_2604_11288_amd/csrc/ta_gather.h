@@ -1,6 +1,7 @@
 // Step 5's arguments, and the gather of one unit's rows by a workgroup that has just selected them.
 #pragma once
 #include "ta_internal.h"
+#include "ta_order.h"
 
 namespace ta {
 
@@ -17,6 +18,7 @@ struct CompactArgs {
     int32_t batch, hkv, n, K;
     int32_t idx_shared;
     int32_t blocks_per_unit;
+    Divider by_blocks, by_hkv, by_batch;
     // paged input: rows are addressed through the block table (s_batch unused, s_page per page)
     const int32_t* table;
     int64_t s_page;
