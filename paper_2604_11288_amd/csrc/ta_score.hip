@@ -204,7 +204,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 
     __shared__ float s_c[COLSUM ? GROUP_ROWS * RG : 1];            // per-row constant m + log2 Z
     __shared__ int32_t s_lim[COLSUM ? GROUP_ROWS * RG : 1];        // per-row last visible key
-    __shared__ float s_part[COLSUM ? 2 : 1][RG][STAGE_KEYS];
+    // Partial column sums of the row groups, by stage: two halves, one of which is written out while the other fills.
+    constexpr int FLUSH = RG == 1 ? 4 : 8;                 // stages of a half
+    __shared__ float s_part[COLSUM ? 2 * FLUSH : 1][RG][STAGE_KEYS];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -593,66 +595,32 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                 const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(colsum), __float_as_uint(colsum), false, false);
                 colsum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
             }
-            if (hf == 0) s_part[s & 1][rg][32 * kt + c32] = colsum;
+            if (hf == 0) s_part[s % (2 * FLUSH)][rg][32 * kt + c32] = colsum;
         }
     };
-    // column sums of stage s: add the row groups' partial sums (complete after the next barrier)
-    const auto flush = [&](int s) {
+    // Column sums of the stages before `to` that have not been written yet: the row groups' partial sums added up (complete after
+    // the barrier that follows their reduction), FLUSH stages at a time, a stage per wavefront.  (With a store in every stage, by the
+    // first wavefront, that one has more to do than the others, and the wait for its loads waits for the stores among them: one sweep,
+    // us, 192 units of 8192 keys, 256 rows 127.6 / 121.9, 512 of 1500..3001 57.2 / 54.8, 2048 of 2048..16 384 871 / 862, 256 of 16 384
+    // 194.8 / 193.  Most of what the stores cost is the memory's: without any 180, whatever the size of the bursts.)
+    int flushed = 0;
+    const auto flush = [&](int to) {
         if constexpr (COLSUM) {
-            if (tid < STAGE_KEYS) {
-                const int32_t key = key_lo + stage_pos(s) * STAGE_KEYS + tid;
+            for (int s = flushed + wave; s < to; s += WAVES) {
+                const int32_t key = key_lo + stage_pos(s) * STAGE_KEYS + lane;
                 if (key < key_hi) {
-                    float v = s_part[s & 1][0][tid];
+                    float v = s_part[s % (2 * FLUSH)][0][lane];
 #pragma unroll
-                    for (int w = 1; w < RG; ++w) v += s_part[s & 1][w][tid];
+                    for (int w = 1; w < RG; ++w) v += s_part[s % (2 * FLUSH)][w][lane];
                     float* dst = &a.A[(size_t)unit * n + key];
                     *dst = row_base > 0 ? *dst + v : v;    // the same thread wrote it in the pass before
                 }
             }
+            flushed = to;
         }
     };
     using fast_tag = std::integral_constant<bool, false>;
     using masked_tag = std::integral_constant<bool, true>;
-
-    int flushed = 0, reduced = 0;                          // stages whose column sums are written / in LDS
-    const auto flush_pending = [&]() {
-        for (; flushed < reduced; ++flushed) flush(flushed);
-    };
-    // The same in two halves for the pipelined loop: the LDS reads of the partial sums are issued
-    // right behind the barrier and their sum is stored after the stage's MFMAs and reduction.  Done
-    // in one piece at the top of the stage, the wavefront that flushes waits for its reads behind
-    // the fragment reads of every other wavefront (all issued at the barrier), falls behind by that
-    // wait in every stage, and the whole workgroup waits for it at the next barrier.
-    float fl_v[RG];
-    int32_t fl_key = -1;
-    const auto flush_begin = [&]() {
-        fl_key = -1;
-        if constexpr (COLSUM) {
-            if (flushed < reduced) {
-                if (tid < STAGE_KEYS) {
-                    const int32_t key = key_lo + stage_pos(flushed) * STAGE_KEYS + tid;
-                    if (key < key_hi) {
-                        fl_key = key;
-#pragma unroll
-                        for (int w = 0; w < RG; ++w) fl_v[w] = s_part[flushed & 1][w][tid];
-                    }
-                }
-                ++flushed;
-            }
-            flush_pending();                               // (the pipelined loop never has a second stage pending)
-        }
-    };
-    const auto flush_end = [&]() {
-        if constexpr (COLSUM) {
-            if (fl_key >= 0) {
-                float v = fl_v[0];
-#pragma unroll
-                for (int w = 1; w < RG; ++w) v += fl_v[w];
-                float* dst = &a.A[(size_t)unit * n + fl_key];
-                *dst = row_base > 0 ? *dst + v : v;
-            }
-        }
-    };
 
     // (A) fully visible stages: MFMAs of stage s and the reduction of stage s-1 in one block.
     // Two accumulator sets alternate (loop unrolled by two) so that no registers are copied.
@@ -663,52 +631,37 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         int s = 1;
         for (; s + 1 < nfast; s += 2) {
             stage_sync(s);
-            flush_begin();                                 // reductions before this barrier are complete
             mma(s, acc_odd);
             reduce(s - 1, acc_even, fast_tag{});
-            flush_end();
-            reduced = s;
+            if (s % FLUSH == 1 && s > 1) flush(s - 1);     // these were reduced in front of this stage's barrier
             stage_sync(s + 1);
-            flush_begin();
             mma(s + 1, acc_even);
             reduce(s, acc_odd, fast_tag{});
-            flush_end();
-            reduced = s + 1;
         }
-        const bool odd_left = s < nfast;                   // one more stage, into the odd set
-        if (odd_left) {
+        if (s < nfast) {                                   // one more stage, into the odd set
             stage_sync(s);
-            flush_pending();
             mma(s, acc_odd);
             reduce(s - 1, acc_even, fast_tag{});
-            reduced = s;
+            reduce(s, acc_odd, fast_tag{});
+        } else {
+            reduce(s - 1, acc_even, fast_tag{});
         }
-        if constexpr (COLSUM) {
-            // the drain below writes the partial-sum buffer that the last flush above read
-            __syncthreads();
-            flush_pending();
-        }
-        if (odd_left) reduce(nfast - 1, acc_odd, fast_tag{});
-        else reduce(nfast - 1, acc_even, fast_tag{});
-        reduced = nfast;
-        if constexpr (COLSUM) {
-            // both partial-sum buffers are pending here; empty them before loop (B) reuses one
-            __syncthreads();
-            flush_pending();
-        }
+        // at most FLUSH + 2 stages are pending: the next ones go elsewhere
+        if constexpr (COLSUM) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if constexpr (COLSUM) __syncthreads();
+        flush(nfast);
     }
     // (B) the few stages near the causal diagonal or past the sequence end: masked, not pipelined
     for (int s = nfast; s < nstages; ++s) {
         stage_sync(s);
-        flush_pending();
+        if (s - flushed >= FLUSH) flush(s);
         f32x16 acc_cur[ROW_TILES];
         mma(s, acc_cur);
         reduce(s, acc_cur, masked_tag{});
-        reduced = s + 1;
     }
     if constexpr (COLSUM) {
         __syncthreads();
-        flush_pending();
+        flush(nstages);
         if (row_base == 0) zero_share();
     }
 
