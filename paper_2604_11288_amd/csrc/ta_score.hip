@@ -134,11 +134,11 @@ struct RiderArgs {
 // RG row groups of RT 32-row MFMA tiles each per workgroup; 2 * RG wavefronts.
 // row_base: first of the 64 * RG rows this call works on (units with more rows than the widest workgroup's 256 take several
 // calls; more row groups would leave too few registers per lane)
-template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM>
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool TURNS>
 __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], int32_t row_base);
 
 // one tile per wavefront: four wavefronts per SIMD (at most 128 registers each)
-template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool PASSES>
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool PASSES, bool TURNS>
 __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_kernel(ScoreArgs a)
 {
@@ -146,16 +146,16 @@ score_kernel(ScoreArgs a)
     // a workgroup holds 64 * RG rows at a time; a unit with more rows is done in passes over its chunk
     // (the keys of the later passes come from the L2; their column sums are added to the first pass's)
     if constexpr (!PASSES) {
-        score_body<RG, RT, COLSUM, PAGED, STREAM>(a, s_k, 0);
+        score_body<RG, RT, COLSUM, PAGED, STREAM, TURNS>(a, s_k, 0);
     } else {
         for (int32_t row_base = 0; row_base < a.rows_pad; row_base += 64 * RG) {
             if (row_base > 0) __syncthreads();             // the previous pass is done with the LDS
-            score_body<RG, RT, COLSUM, PAGED, STREAM>(a, s_k, row_base);
+            score_body<RG, RT, COLSUM, PAGED, STREAM, TURNS>(a, s_k, row_base);
         }
     }
 }
 
-template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool PASSES>
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool PASSES, bool TURNS>
 __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_match_kernel(ScoreArgs a, RiderArgs r)
 {
@@ -169,16 +169,16 @@ score_match_kernel(ScoreArgs a, RiderArgs r)
         return;
     }
     if constexpr (!PASSES) {
-        score_body<RG, RT, COLSUM, PAGED, STREAM>(a, s_k, 0);
+        score_body<RG, RT, COLSUM, PAGED, STREAM, TURNS>(a, s_k, 0);
     } else {
         for (int32_t row_base = 0; row_base < a.rows_pad; row_base += 64 * RG) {
             if (row_base > 0) __syncthreads();
-            score_body<RG, RT, COLSUM, PAGED, STREAM>(a, s_k, row_base);
+            score_body<RG, RT, COLSUM, PAGED, STREAM, TURNS>(a, s_k, row_base);
         }
     }
 }
 
-template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM>
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool TURNS>
 __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], const int32_t row_base)
 {
     constexpr int ROW_TILES = RT;
@@ -205,7 +205,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     __shared__ float s_c[COLSUM ? GROUP_ROWS * RG : 1];            // per-row constant m + log2 Z
     __shared__ int32_t s_lim[COLSUM ? GROUP_ROWS * RG : 1];        // per-row last visible key
     // Partial column sums of the row groups, by stage: two halves, one of which is written out while the other fills.
-    constexpr int FLUSH = RG == 1 ? 4 : 8;                 // stages of a half
+    constexpr int TURN = RING % 2 ? 2 * RING : RING;       // stages of a turn of the main loop: ring buffers and accumulators have their numbers
+    constexpr int FLUSH = TURN;                            // stages of a half
     __shared__ float s_part[COLSUM ? 2 * FLUSH : 1][RG][STAGE_KEYS];
 
     const int tid = threadIdx.x;
@@ -489,6 +490,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     // Iteration s issues the MFMAs of stage s while the vector ALUs reduce the
     // accumulators of stage s-1 (softmax statistics or column sums), so the matrix pipe
     // and the VALU of a wavefront overlap instead of alternating.
+    int ahead = -1;                                        // the stage that the main loop has left off at, its own request made
     const auto stage_sync = [&](int s) {
         if (s > 0) {
             // stage s has landed once at most the loads of the later stages issued so far
@@ -502,19 +504,23 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
             if constexpr (COLSUM) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __syncthreads();                               // every wavefront: stage s landed, stage s-1 consumed
         }
-        if (s + RING - 1 < nstages) stage_issue(s + RING - 1);   // overwrites the buffer of stage s-1
+        if (s != ahead && s + RING - 1 < nstages) stage_issue(s + RING - 1);   // overwrites the buffer of stage s-1
     };
-    const auto mma = [&](int s, f32x16 (&acc)[ROW_TILES]) {
-        const uint4* buf = &s_k[s % RING][0];
-        bf16x8 kf[8];
+    // eight steps of 16 features, in two halves: the fragments of a half, and its products
+    const auto fragments = [&](int ring, int half, bf16x8 (&kf)[8]) {
+        const uint4* buf = &s_k[ring][0];
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) kf[ks] = as_frag(buf[kslot[ks]]);
+        for (int ks = 4 * half; ks < 4 * half + 4; ++ks) kf[ks] = as_frag(buf[kslot[ks]]);
+    };
+    const auto products = [&](int half, const bf16x8 (&kf)[8], f32x16 (&acc)[ROW_TILES]) {
+        if (half == 0) {
 #pragma unroll
-        for (int t = 0; t < ROW_TILES; ++t)
+            for (int t = 0; t < ROW_TILES; ++t)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
+                for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
+        }
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
+        for (int ks = 4 * half; ks < 4 * half + 4; ++ks)
 #pragma unroll
             for (int t = 0; t < ROW_TILES; ++t) {
                 if constexpr (!COLSUM)   // keys x rows: acc[t][i] = key tile + 8*(i/4) + 4*hf + i%4, this lane's row
@@ -522,6 +528,13 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                 else                     // rows x keys: acc[t][i] = row 64*rg + 32*t + 8*(i/4) + 4*hf + i%4, key tile + c32
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[t][ks], kf[ks], acc[t], 0, 0, 0);
             }
+    };
+    const auto mma = [&](int s, f32x16 (&acc)[ROW_TILES]) {
+        bf16x8 kf[8];
+        fragments(s % RING, 0, kf);
+        fragments(s % RING, 1, kf);
+        products(0, kf, acc);
+        products(1, kf, acc);
     };
     // online update of a row tile's statistics from its accumulators (the exact running maximum)
     const auto online = [&](f32x16& acc, int t, auto masked_tag) {
@@ -537,34 +550,53 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         z_run[t] = z_run[t] * fast_exp2(m_run[t] - mref) + sum;
         m_run[t] = mnew;
     };
-    // reduction of the accumulators of stage s; MASKED: some key of the stage is hidden from some row
-    const auto reduce = [&](int s, f32x16 (&acc)[ROW_TILES], auto masked_tag) {
-        constexpr bool MASKED = decltype(masked_tag)::value;
-        const int32_t tile_key0 = key_lo + stage_pos(s) * STAGE_KEYS + 32 * kt;
-        float colsum = 0.0f;
-        if constexpr (!COLSUM && !MASKED) {
-            // The reference of a row's exponents does not have to be the maximum: any logit the row has had keeps Z at 1 or
-            // more, and fp32 holds sums far above it.  So a stage only sums against the reference it finds (no maximum,
-            // no rescaling); one whose sum passes 2^64 - the first of the chunk, whose reference is -inf, and any
-            // with a logit 64 octaves above the reference - is reduced again with the maximum.
-            float sum[ROW_TILES];
+    // Reduction of the accumulators of a fully visible stage, a row tile after the other, then what is left of it.
+    // Statistics: the reference of a row's exponents does not have to be the maximum: any logit the row has had keeps Z at 1 or
+    // more, and fp32 holds sums far above it.  So a stage only sums against the reference it finds (no maximum,
+    // no rescaling); one whose sum passes 2^64 - the first of the chunk, whose reference is -inf, and any
+    // with a logit 64 octaves above the reference - is reduced again with the maximum.
+    float sums[COLSUM ? 1 : ROW_TILES];                    // of the stage: a key's over the rows so far; a row's over the keys, by tile
+    const auto reduce_tile = [&](int t, const f32x16 (&acc)[ROW_TILES]) {
+        if constexpr (COLSUM) {
+            if (t == 0) sums[0] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sums[0] += fast_exp2(fmaf(acc[t][i], sc, -cst[t][i]));
+        } else {
+            sums[t] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sums[t] += fast_exp2(fmaf(acc[t][i], sc, -m_run[t]));
+        }
+    };
+    const auto write_colsum = [&](float colsum, int slot) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(colsum), __float_as_uint(colsum), false, false);
+        colsum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        if (hf == 0) s_part[slot][rg][32 * kt + c32] = colsum;
+    };
+    const auto reduce_rest = [&](int slot, f32x16 (&acc)[ROW_TILES]) {
+        if constexpr (COLSUM) {
+            write_colsum(sums[0], slot);
+        } else {
             bool small = true;
 #pragma unroll
-            for (int t = 0; t < ROW_TILES; ++t) {
-                sum[t] = 0.0f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) sum[t] += fast_exp2(fmaf(acc[t][i], sc, -m_run[t]));
-                small = small && sum[t] < 1.8446744e19f;
-            }
+            for (int t = 0; t < ROW_TILES; ++t) small = small && sums[t] < 1.8446744e19f;
             if (__ballot(!small) == 0ull) {                // uniform
 #pragma unroll
-                for (int t = 0; t < ROW_TILES; ++t) z_run[t] += sum[t];
+                for (int t = 0; t < ROW_TILES; ++t) z_run[t] += sums[t];
             } else {
 #pragma unroll
-                for (int t = 0; t < ROW_TILES; ++t) online(acc[t], t, masked_tag);
+                for (int t = 0; t < ROW_TILES; ++t) online(acc[t], t, std::integral_constant<bool, false>{});
             }
-            return;
         }
+    };
+    const auto reduce = [&](int s, f32x16 (&acc)[ROW_TILES]) {
+#pragma unroll
+        for (int t = 0; t < ROW_TILES; ++t) reduce_tile(t, acc);
+        reduce_rest(s % (2 * FLUSH), acc);
+    };
+    // of a stage some key of which is hidden from some row
+    const auto reduce_masked = [&](int s, f32x16 (&acc)[ROW_TILES]) {
+        const int32_t tile_key0 = key_lo + stage_pos(s) * STAGE_KEYS + 32 * kt;
+        float colsum = 0.0f;
 #pragma unroll
         for (int t = 0; t < ROW_TILES; ++t) {
             if constexpr (!COLSUM) {
@@ -574,29 +606,18 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                     const int32_t key = tile_key0 + 8 * (i >> 2) + 4 * hf + (i & 3);
                     acc[t][i] = key <= lim ? acc[t][i] : -INFINITY;
                 }
-                online(acc[t], t, masked_tag);
+                online(acc[t], t, std::integral_constant<bool, true>{});
             } else {
-                if constexpr (!MASKED) {
+                const int32_t key = tile_key0 + c32;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) colsum += fast_exp2(fmaf(acc[t][i], sc, -cst[t][i]));
-                } else {
-                    const int32_t key = tile_key0 + c32;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int row = GROUP_ROWS * rg + 32 * t + 8 * (i >> 2) + 4 * hf + (i & 3);
-                        const float p = fast_exp2(fmaf(acc[t][i], sc, -cst[t][i]));
-                        colsum += key <= s_lim[row] ? p : 0.0f;
-                    }
+                for (int i = 0; i < 16; ++i) {
+                    const int row = GROUP_ROWS * rg + 32 * t + 8 * (i >> 2) + 4 * hf + (i & 3);
+                    const float p = fast_exp2(fmaf(acc[t][i], sc, -cst[t][i]));
+                    colsum += key <= s_lim[row] ? p : 0.0f;
                 }
             }
         }
-        if constexpr (COLSUM) {
-            {
-                const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(colsum), __float_as_uint(colsum), false, false);
-                colsum = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-            }
-            if (hf == 0) s_part[s % (2 * FLUSH)][rg][32 * kt + c32] = colsum;
-        }
+        if constexpr (COLSUM) write_colsum(colsum, s % (2 * FLUSH));
     };
     // Column sums of the stages before `to` that have not been written yet: the row groups' partial sums added up (complete after
     // the barrier that follows their reduction), FLUSH stages at a time, a stage per wavefront.  (With a store in every stage, by the
@@ -606,7 +627,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     int flushed = 0;
     const auto flush = [&](int to) {
         if constexpr (COLSUM) {
-            for (int s = flushed + wave; s < to; s += WAVES) {
+            for (int s = flushed + __builtin_amdgcn_readfirstlane(wave); s < to; s += WAVES) {
                 const int32_t key = key_lo + stage_pos(s) * STAGE_KEYS + lane;
                 if (key < key_hi) {
                     float v = s_part[s % (2 * FLUSH)][0][lane];
@@ -619,32 +640,80 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
             flushed = to;
         }
     };
-    using fast_tag = std::integral_constant<bool, false>;
-    using masked_tag = std::integral_constant<bool, true>;
-
+    // The main loop: whole turns of TURN stages, as long as every stage that they request is a fully visible one too.  The barrier stands
+    // in the middle of a stage: in front of it the stage's first products and half of the reduction of the one before, with the last reads
+    // of its buffer, which is free behind it; behind it the first fragments of the next stage are read, under the stage's
+    // other products.  So neither the matrix pipe nor the vector unit waits for LDS behind a barrier, which the two wavefronts of a
+    // SIMD reach together.  What a stage needs is known or steps on by itself - the buffer's number, the wait, the address (one step on,
+    // at the end of the rotation back by all) - and costs some 20 scalar instructions, not 60 and ten branches.  (One sweep / two, us, all stages
+    // as in (A) / this: 256 units of 16 384 keys, 256 rows 325 / 280, 633 / 570; 192 of 8192, 256 rows 129 / 114, 253 / 238; 256 of 4096,
+    // 512 rows 171 / 149, 336 / 303; 128 rows, 256 units of 16 384 198 / 187, 383 / 365, 2048 of 2048..16 384 873 / 857, 1690 / 1600.)
+    const auto turns = [&](int& s, f32x16 (&acc_even)[ROW_TILES], f32x16 (&acc_odd)[ROW_TILES]) {
+        if (s + TURN + RING - 1 >= nfast) return;
+        bf16x8 kf[8];
+        stage_sync(s);                                     // requests s + RING - 1
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        fragments(1 % RING, 0, kf);
+        int p = stage_pos(s + RING);                       // place of the stage to request
+        const char* from = PAGED ? nullptr : reinterpret_cast<const char*>(kbase + (int64_t)(key_lo + p * STAGE_KEYS) * a.k_sp);
+        const int64_t step = (COLSUM ? -1 : 1) * (int64_t)STAGE_KEYS * a.k_sp * 16, back = step - step * nfast;
+        const auto run = [&](int end, auto stream_tag) {
+            for (; s + TURN + RING - 1 < end; s += TURN) {
+                const int half = s % (2 * TURN) == 1 ? 0 : TURN;
+#pragma unroll
+                for (int j = 0; j < TURN; ++j) {           // stage s + j: buffer (1 + j) % RING
+                    f32x16 (&acc)[ROW_TILES] = (1 + j) & 1 ? acc_odd : acc_even;
+                    f32x16 (&before)[ROW_TILES] = j & 1 ? acc_odd : acc_even;
+                    fragments((1 + j) % RING, 1, kf);
+                    products(0, kf, acc);
+                    reduce_tile(0, before);
+                    wait_but(RING - 2);                    // the next stage is in
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // this one has been read, and the partial sums are in LDS
+                    __syncthreads();
+                    const uint4* src = PAGED ? stage_base(key_lo + p * STAGE_KEYS) : reinterpret_cast<const uint4*>(from);
+                    const uint32_t dst = lds_wave + (uint32_t)((1 + j) % RING) * (STAGE_UNITS * 16u);
+#pragma unroll
+                    for (int i = 0; i < LPS; ++i) load_to_lds_16<decltype(stream_tag)::value>(src, lane_off[i], dst + WAVES * i * 1024u);
+                    const bool wrap = COLSUM ? p == 0 : p == nfast - 1;
+                    from += wrap ? back : step;
+                    p = wrap ? (COLSUM ? nfast - 1 : 0) : (COLSUM ? p - 1 : p + 1);
+                    fragments((2 + j) % RING, 0, kf);
+                    products(1, kf, acc);
+#pragma unroll
+                    for (int t = 1; t < ROW_TILES; ++t) reduce_tile(t, before);
+                    reduce_rest(half + j, before);
+                    if (j == 1 && s > TURN) flush(s - 1);
+                }
+            }
+        };
+        if constexpr (STREAM && !COLSUM) run(keep_from < nfast ? keep_from : nfast, std::integral_constant<bool, true>{});
+        run(nfast, std::integral_constant<bool, STREAM && COLSUM>{});
+        ahead = s;
+    };
     // (A) fully visible stages: MFMAs of stage s and the reduction of stage s-1 in one block.
-    // Two accumulator sets alternate (loop unrolled by two) so that no registers are copied.
+    // Two accumulator sets alternate (loops unrolled by two or by a turn) so that no registers are copied.
     if (nfast > 0) {
         f32x16 acc_even[ROW_TILES], acc_odd[ROW_TILES];
         stage_sync(0);
         mma(0, acc_even);
         int s = 1;
+        if constexpr (TURNS) turns(s, acc_even, acc_odd);
         for (; s + 1 < nfast; s += 2) {
             stage_sync(s);
             mma(s, acc_odd);
-            reduce(s - 1, acc_even, fast_tag{});
-            if (s % FLUSH == 1 && s > 1) flush(s - 1);     // these were reduced in front of this stage's barrier
+            reduce(s - 1, acc_even);
+            if (s - flushed > FLUSH) flush(s - 1);         // these were reduced in front of this stage's barrier
             stage_sync(s + 1);
             mma(s + 1, acc_even);
-            reduce(s, acc_odd, fast_tag{});
+            reduce(s, acc_odd);
         }
         if (s < nfast) {                                   // one more stage, into the odd set
             stage_sync(s);
             mma(s, acc_odd);
-            reduce(s - 1, acc_even, fast_tag{});
-            reduce(s, acc_odd, fast_tag{});
+            reduce(s - 1, acc_even);
+            reduce(s, acc_odd);
         } else {
-            reduce(s - 1, acc_even, fast_tag{});
+            reduce(s - 1, acc_even);
         }
         // at most FLUSH + 2 stages are pending: the next ones go elsewhere
         if constexpr (COLSUM) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -657,7 +726,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         if (s - flushed >= FLUSH) flush(s);
         f32x16 acc_cur[ROW_TILES];
         mma(s, acc_cur);
-        reduce(s, acc_cur, masked_tag{});
+        reduce_masked(s, acc_cur);
     }
     if constexpr (COLSUM) {
         __syncthreads();
@@ -704,7 +773,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     }
 }
 
-template <int RG, int RT, bool COLSUM, bool STREAM, bool PASSES>
+template <int RG, int RT, bool COLSUM, bool STREAM, bool PASSES, bool TURNS>
 hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
 {
     if (rider && RG == 1) {
@@ -722,20 +791,20 @@ hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* r
             r.tab = *rider->tab;
             r.score_blocks = blocks;
             const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
-            if (a.table) hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, true, STREAM, PASSES>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
-            else hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, false, STREAM, PASSES>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            if (a.table) hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, true, STREAM, PASSES, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            else hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, false, STREAM, PASSES, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
             return hipGetLastError();
         }
     }
     if (a.table) {
-        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true, STREAM, PASSES>), dim3(blocks), dim3(128 * RG), 0, st, a);
+        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true, STREAM, PASSES, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
     } else {
-        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false, STREAM, PASSES>), dim3(blocks), dim3(128 * RG), 0, st, a);
+        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false, STREAM, PASSES, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
     }
     return hipGetLastError();
 }
 
-template <int RG, int RT, bool PASSES = false>
+template <int RG, int RT, bool PASSES, bool TURNS>
 hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_t gathered, hipStream_t st)
 {
     // One launch per sweep over all units.  (Splitting the units into cache-sized groups
@@ -764,8 +833,8 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
     const int64_t bytes = units * a.n * 256;
     const bool stream = !PASSES && bytes > SMALL_BYTES && !(gathered >= a.n / 8 && bytes <= 2 * LLC_BYTES);
     const auto column_sums = [&](const MatchRider* with) {
-        if (stream) return launch_sweep<RG, RT, true, !PASSES, PASSES>(a, blocks, with, st);
-        return launch_sweep<RG, RT, true, false, PASSES>(a, blocks, with, st);
+        if (stream) return launch_sweep<RG, RT, true, !PASSES, PASSES, TURNS>(a, blocks, with, st);
+        return launch_sweep<RG, RT, true, false, PASSES, TURNS>(a, blocks, with, st);
     };
     if (a.lse) return column_sums(rider);                  // the row normalisers are given: column sums alone
     a.keep_place = 0x7FFFFFFF;
@@ -773,8 +842,8 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
     if (rounds) a.keep_place = (int32_t)(units - units * LLC_BYTES / bytes);
     else a.keep_stage = (int32_t)(1024 - 1024 * LLC_BYTES / bytes);
     constexpr bool FIRST = RG < 4;
-    const hipError_t e = FIRST && bytes > LLC_BYTES ? launch_sweep<RG, RT, false, FIRST, PASSES>(a, blocks, rider, st)
-                                                    : launch_sweep<RG, RT, false, false, PASSES>(a, blocks, rider, st);
+    const hipError_t e = FIRST && bytes > LLC_BYTES ? launch_sweep<RG, RT, false, FIRST, PASSES, TURNS>(a, blocks, rider, st)
+                                                    : launch_sweep<RG, RT, false, false, PASSES, TURNS>(a, blocks, rider, st);
     if (e != hipSuccess) return e;
     return column_sums(nullptr);
 }
@@ -929,16 +998,24 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
     a.nchunks = p.nchunks;
     a.causal = causal;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)lay.d));
+    // The kernels with the main loop of whole turns: from a turn of stages on, for up to 128 rows from chunks of 48.  Two workgroups or more share a
+    // compute unit there and cover each other's waits, the longer code has to be fetched, and it pays for itself later.  (Whole pass, us, without /
+    // with: 8 units of 4096 keys, chunks of 2 stages, 18.37 / 18.5, 512 paged ones of 1500..3001, of up to 47, 139.2 / 139.8, 256 of 4096,
+    // of 32, 144.4 / 144.3; one sweep over 256 of 16 384, of 128, 193 / 188; narrow workgroups 256 of 4096 47.5 / 47.5.)
+    const int32_t stages = p.chunk_keys / STAGE_KEYS;
     switch (a.rows_pad) {
         // two 32-row tiles per wavefront (one tile per wavefront with twice the wavefronts - four
         // per SIMD instead of two - was measured: same time at 128 rows, 5 % slower at 256)
         case 128:
-            if (p.rows <= 64 && (!rider || p.units * lay.n >= (a.table ? NARROW_KEYS_PAGED : NARROW_KEYS))) return launch_rg<1, 2>(a, p.units, rider, gathered, st);
-            return launch_rg<2, 2>(a, p.units, rider, gathered, st);
-        case 256: return launch_rg<4, 2>(a, p.units, rider, gathered, st);
+            if (p.rows <= 64 && (!rider || p.units * lay.n >= (a.table ? NARROW_KEYS_PAGED : NARROW_KEYS))) return launch_rg<1, 2, false, false>(a, p.units, rider, gathered, st);
+            if (stages >= 48) return launch_rg<2, 2, false, true>(a, p.units, rider, gathered, st);
+            return launch_rg<2, 2, false, false>(a, p.units, rider, gathered, st);
+        case 256:
+            if (stages >= 12) return launch_rg<4, 2, false, true>(a, p.units, rider, gathered, st);
+            return launch_rg<4, 2, false, false>(a, p.units, rider, gathered, st);
         // 512 rows: two passes of 256 (eight row groups at once leave 128 registers per lane: spills, 3x slower), in kernels of
         // their own: the pass loop costs the column sums' main loop the registers that keep its two pipes busy (1.5 %)
-        default: return launch_rg<4, 2, true>(a, p.units, rider, gathered, st);
+        default: return launch_rg<4, 2, true, true>(a, p.units, rider, gathered, st);
     }
 }
 

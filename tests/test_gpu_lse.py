@@ -122,3 +122,28 @@ def test_whole_pass_with_given_lse():
     with pytest.raises(ta.TaError):            # nothing to fuse without an attention term
         ta.ta_evict_lse(_dev(td.tok), td.tab_ids, td.tab_len, Q, K, V, _dev(lse), Kb,
                         ta.Params(n_sink=4, n_recent=4, alpha=0.0), seq_len=seq)
+
+
+@pytest.mark.parametrize("W", [32, 64])
+@pytest.mark.parametrize("G", [4])
+def test_score_long_chunks_at_every_remainder(W, G):
+    """Chunks of many stages: lengths whose fully visible stages end at every place of a turn of the main loop (four stages), at its start-up and
+    in a partial stage, with both sweeps and with the second alone, against float64."""
+    chunks, most = 18, 57 if W == 32 else 19                         # (with 14 units); 64-key stages in a chunk of the longest sequence
+    lens = [64 * chunks * k - cut for k, cut in zip(range(most, most - 12, -1), (0, 1, 63, 64, 65, 200, 0, 640, 2048, 5, 64, 1000))] + [64 * chunks * 2, 700]
+    n, B = max(lens), len(lens)
+    g = torch.Generator(device=DEV).manual_seed(W)
+    K = torch.randn((1, B, 1, n, 128), generator=g, device=DEV).to(torch.bfloat16)
+    Q = torch.randn((1, B, G, W, 128), generator=g, device=DEV).to(torch.bfloat16)
+    seq_len = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    ref, lse = torch.zeros((B, n), dtype=torch.float64, device=DEV), torch.empty((1, B, G, W), device=DEV)
+    for b, m in enumerate(lens):
+        s = (Q[0, b].reshape(-1, 128).double() @ K[0, b, 0, :m].double().T) * 128 ** -0.5
+        hidden = torch.arange(m, device=DEV)[None, :] > m - W + torch.arange(W, device=DEV).repeat(G)[:, None]
+        s.masked_fill_(hidden, -np.inf)
+        lse[0, b] = s.logsumexp(1).view(G, W)
+        ref[b, :m] = s.softmax(1).sum(0)
+    A = torch.full((1, B, 1, n), -1.0, device=DEV)
+    for got in (ta.ta_score(Q, K, ta.Params(), seq_len=seq_len, A=A.clone()), ta.ta_score_lse(Q, K, lse, ta.Params(), seq_len=seq_len, A=A.clone())):
+        torch.cuda.synchronize()
+        assert ((got[0, :, 0].double() - ref).abs() <= 1e-3 * ref.abs() + 1e-7).all()    # the bar of every score
