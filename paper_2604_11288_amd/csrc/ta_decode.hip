@@ -290,6 +290,7 @@ struct UnitArgs {
     int32_t group;                                         // query heads per KV head
     Divider by_hkv, by_batch;
     float decay;
+    int32_t keep;                                          // workgroups before this one load keys without the streaming hint
 };
 
 // A step as one launch (FUSED below): what its sequence part works with, and the words in which the workgroups of a sequence count
@@ -578,7 +579,7 @@ __device__ __forceinline__ uint8_t vouchers_of_slots(const ta_decode_state& st, 
 // load of flags each.  Vouchers it needs only where no plain slot is left to evict: any plain slot ranks below every
 // sponsored one, and its own voucher is zero.  It counts itself in once it has read what the append overwrites, and the last workgroup
 // of a sequence to do so appends.
-template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES, int SPL, bool FUSED = false>
+template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES, int SPL, bool KEEP, bool FUSED = false>
 __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& pg, const StepArgs* fs = nullptr)
 {
     extern __shared__ float s_dyn[];
@@ -645,8 +646,18 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     const int ntiles = (((slots + 15) >> 4) - wave + WAVES - 1) / WAVES;
     const auto tile_of = [&](int tile) { return wave + WAVES * tile; };
     uint4 qf[4], tiles[DT_RING][4];                        // DT_RING tiles in flight
-    // Key rows are read once per step: the non-temporal hint keeps them from displacing the slot tables,
-    // the accumulated attention and the per-sequence arrays in the caches (231 -> 210 us on 16 384 units).
+    // Key rows are read once per step.  Those that the last-level cache can hold until the next step (KEEP: the rule beside kept_units) are loaded
+    // as they are; the others have the non-temporal hint, which keeps them from displacing those, the slot tables, the accumulated attention and the
+    // per-sequence arrays (231 -> 210 us on 16 384 units).
+    const auto load_key = [&](const uint4* from) -> uint4 {
+        if constexpr (KEEP) {
+            return *from;
+        } else {
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+            const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(from));
+            return make_uint4(v.x, v.y, v.z, v.w);
+        }
+    };
     const auto load_tile = [&](int tile, uint4 (&dst)[4]) {
         if (!PAGED) {                                      // dense unit: one uniform base, a 32-bit byte offset per lane
             const char* base = reinterpret_cast<const char*>(Kc);
@@ -654,11 +665,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
             for (int t = 0; t < 4; ++t) {
                 int row = tile_of(tile) * 16 + 4 * t + grp;
                 row = row < slots ? row : slots - 1;       // past the last slot: a valid row, masked at the store
-                {
-                    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-                    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (uint32_t)(row * 256 + sub * 16)));
-                    dst[t] = make_uint4(v.x, v.y, v.z, v.w);
-                }
+                dst[t] = load_key(reinterpret_cast<const uint4*>(base + (uint32_t)(row * 256 + sub * 16)));
             }
             return;
         }
@@ -666,9 +673,7 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         for (int t = 0; t < 4; ++t) {
             int row = tile_of(tile) * 16 + 4 * t + grp;
             row = row < slots ? row : slots - 1;
-            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-            const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(&Kc[row_at(row) + sub]));
-            dst[t] = make_uint4(v.x, v.y, v.z, v.w);
+            dst[t] = load_key(&Kc[row_at(row) + sub]);
         }
     };
     if (SCORED) {
@@ -1142,54 +1147,79 @@ bool rows_fit(bool scored, const ta_decode_state& st, UnitForm f)
 // of 40 960 positions in two 18.8 / 21.0; 256 x 1025, 131 072 in two 17.0 / 19.2).
 bool positions_first(bool scored, const ta_decode_state& st, UnitForm f) { return !scored || rounds_of(st, f) > 1; }
 
+// Units whose keys the last-level cache (256 MB) is to hold until the next step, which reads them again: all where they fit, else 192 MB of them - the
+// rest has the streaming hint and passes by.  (us per step, hint everywhere / this: 256 units x 1025 slots 16.6 / 15.9, paged 17.9 / 17.1; 8192 x 101 47.2 / 42.0,
+// paged 54.1 / 45.8; 4096 x 257, 257 MB, 55.3 / 48.6; 6144 x 257 80.2 / 73.5, paged 89.1 / 80.8; 16 384 x 257 201.6 / 197.0, paged 226.4 / 219.7; 2048 x 1025 94.1 / 89.8.  Of more
+// than fit, 256 MB kept instead of 192: 16 384 x 257 206, 15 360 x 129 102.6 / 97.7; all of them: 218, 115.7.)
+constexpr int64_t CACHED_BYTES = int64_t(272) << 20, KEPT_BYTES = int64_t(192) << 20;
+int32_t kept_units(int64_t units, int slots)
+{
+    const int64_t of_unit = (int64_t)slots * 256;
+    return (int32_t)(units * of_unit <= CACHED_BYTES ? units : KEPT_BYTES / of_unit);
+}
+
 // Key tiles in flight: two per wavefront where wavefronts share a unit - enough with all that then share a compute unit, and the
 // registers let more of them do so (six, us per step: 1025 slots, 256 units 21.0 -> 19.8, 1024 units 56.6 -> 52.7; 1501
 // slots, 1024 units 94.4 -> 75.4).  One wavefront per unit: three at four wavefronts per SIMD; paged slots need
 // more registers for their addresses: four at three wavefronts per SIMD instead of spilling.
-template <int GH, bool PAGED, bool SCORED, bool SMALL, int WAVES, int SPL>
+// How a launch's key loads go: all with the streaming hint, none, or none in the workgroups before UnitArgs::keep.  (A load whose hint is decided at run
+// time loses it; the third has the unit's code twice, which costs a step of one launch 0.5 us and one over pages 1.5, so the others have kernels of their own.)
+enum { STREAM_KEYS, KEEP_KEYS, KEEP_SOME };
+
+template <int GH, bool PAGED, bool SCORED, bool SMALL, int WAVES, int SPL, int KEYS>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu((WAVES > 1 ? 2 : PAGED ? 3 : 4))))
 decode_unit_kernel(ta_decode_state st, UnitArgs a, SlotPages pg)
 {
-    decode_unit<GH, PAGED, SCORED, SMALL, (WAVES > 1 ? 2 : PAGED ? 4 : 3), WAVES, SPL>(st, a, pg);
+    constexpr int RING = WAVES > 1 ? 2 : PAGED ? 4 : 3;
+    if (KEYS == KEEP_KEYS || (KEYS == KEEP_SOME && (int32_t)blockIdx.x < a.keep)) decode_unit<GH, PAGED, SCORED, SMALL, RING, WAVES, SPL, true>(st, a, pg);
+    else decode_unit<GH, PAGED, SCORED, SMALL, RING, WAVES, SPL, false>(st, a, pg);
 }
 
 // Paged slots: at most 128 registers (none of them in scratch), so that two workgroups of eight wavefronts share a compute unit as
 // those of the two-launch form do: with 131 to 135 they did not, and where units are more than compute units the step fell behind two
 // launches (us per step, 135 / 128 registers / two launches: 320 units x 1135 slots 29.3 / 25.7 / 28.0, 512 x 1025 33.7 / 30.0 / 31.5, 1024 x 1025
 // 63.2 / 55.0 / 55.3, 256 x 1025 17.9 / 17.8 / 20.0; from a graph, with none in scratch, 25.1, 28.0, 51.4, 16.3 / 27.0, 29.5, 53.0, 18.0).
-template <int GH, bool PAGED, bool SCORED, int WAVES, int SPL>
+template <int GH, bool PAGED, bool SCORED, int WAVES, int SPL, int KEYS>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(PAGED && SCORED ? 4 : 2)))
 decode_step_kernel(ta_decode_state st, UnitArgs a, SlotPages pg, StepArgs f)
 {
-    decode_unit<GH, PAGED, SCORED, true, 2, WAVES, SPL, true>(st, a, pg, &f);
+    if (KEYS == KEEP_KEYS || (KEYS == KEEP_SOME && (int32_t)blockIdx.x < a.keep)) decode_unit<GH, PAGED, SCORED, true, 2, WAVES, SPL, true, true>(st, a, pg, &f);
+    else decode_unit<GH, PAGED, SCORED, true, 2, WAVES, SPL, false, true>(st, a, pg, &f);
 }
 
 using UnitKernel = void (*)(ta_decode_state, UnitArgs, SlotPages);
 using StepKernel = void (*)(ta_decode_state, UnitArgs, SlotPages, StepArgs);
 
-template <int GH, bool PAGED, bool SCORED>
-StepKernel step_kernel(UnitForm f)
+template <int GH, bool PAGED, bool SCORED, int KEYS>
+StepKernel step_kernel_of(UnitForm f)
 {
     switch (f.waves * 8 + f.spl) {
-        case 2 * 8 + 2: return decode_step_kernel<GH, PAGED, SCORED, 2, 2>;
-        case 4 * 8 + 2: return decode_step_kernel<GH, PAGED, SCORED, 4, 2>;
-        case 4 * 8 + 3: return decode_step_kernel<GH, PAGED, SCORED, 4, 3>;
-        case 8 * 8 + 3: return decode_step_kernel<GH, PAGED, SCORED, 8, 3>;
-        default: return decode_step_kernel<GH, PAGED, SCORED, 8, 4>;
+        case 2 * 8 + 2: return decode_step_kernel<GH, PAGED, SCORED, 2, 2, KEYS>;
+        case 4 * 8 + 2: return decode_step_kernel<GH, PAGED, SCORED, 4, 2, KEYS>;
+        case 4 * 8 + 3: return decode_step_kernel<GH, PAGED, SCORED, 4, 3, KEYS>;
+        case 8 * 8 + 3: return decode_step_kernel<GH, PAGED, SCORED, 8, 3, KEYS>;
+        default: return decode_step_kernel<GH, PAGED, SCORED, 8, 4, KEYS>;
     }
+}
+
+template <int GH, bool PAGED, bool SCORED>
+StepKernel step_kernel(UnitForm f, bool all_kept)
+{
+    if constexpr (!SCORED) return step_kernel_of<GH, PAGED, false, STREAM_KEYS>(f);      // (no keys)
+    else return all_kept ? step_kernel_of<GH, PAGED, true, KEEP_KEYS>(f) : step_kernel_of<GH, PAGED, true, (PAGED ? STREAM_KEYS : KEEP_SOME)>(f);
 }
 
 template <int GH, bool PAGED>
 UnitKernel unit_kernel(bool scored, UnitForm f)
 {
-    if (!scored) return f.spl ? decode_unit_kernel<GH, PAGED, false, true, 1, LOOP_SPL> : decode_unit_kernel<GH, PAGED, false, false, 1, LOOP_SPL>;
+    if (!scored) return f.spl ? decode_unit_kernel<GH, PAGED, false, true, 1, LOOP_SPL, STREAM_KEYS> : decode_unit_kernel<GH, PAGED, false, false, 1, LOOP_SPL, STREAM_KEYS>;
     switch (f.waves * 8 + f.spl) {
-        case 1 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 1, 2>;
-        case 2 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 2, 2>;
-        case 4 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 4, 2>;
-        case 4 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 4, 3>;
-        case 8 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 8, 3>;
-        default: return decode_unit_kernel<GH, PAGED, true, true, 8, 4>;
+        case 1 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 1, 2, KEEP_SOME>;
+        case 2 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 2, 2, KEEP_SOME>;
+        case 4 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 4, 2, KEEP_SOME>;
+        case 4 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 4, 3, KEEP_SOME>;
+        case 8 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 8, 3, KEEP_SOME>;
+        default: return decode_unit_kernel<GH, PAGED, true, true, 8, 4, KEEP_SOME>;
     }
 }
 
@@ -1228,7 +1258,8 @@ hipError_t unit_attributes()
             if (e == hipSuccess)
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     for (const UnitForm f : {UnitForm{2, 2}, UnitForm{4, 2}, UnitForm{4, 3}, UnitForm{8, 3}, UnitForm{8, 4}})
-        for (const StepKernel k : {step_kernel<GH, false, true>(f), step_kernel<GH, true, true>(f)})
+        for (const StepKernel k : {step_kernel<GH, false, true>(f, false), step_kernel<GH, true, true>(f, false), step_kernel<GH, false, true>(f, true),
+                                   step_kernel<GH, true, true>(f, true)})
             if (e == hipSuccess)
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     return e;
@@ -1240,8 +1271,9 @@ void launch_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& 
 {
     if (one) {
         // (how many heads a group has is nothing to a unit without an attention term)
-        const StepKernel kernel = a.alpha != 0.0f ? (st.pages ? step_kernel<GH, true, true>(f) : step_kernel<GH, false, true>(f))
-                                                  : (st.pages ? step_kernel<4, true, false>(f) : step_kernel<4, false, false>(f));
+        const bool all = a.keep >= one->lead + a.units;
+        const StepKernel kernel = a.alpha != 0.0f ? (st.pages ? step_kernel<GH, true, true>(f, all) : step_kernel<GH, false, true>(f, all))
+                                                  : (st.pages ? step_kernel<4, true, false>(f, all) : step_kernel<4, false, false>(f, all));
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * f.waves), lds, s, st, a, pg, *one);
         return;
     }
@@ -1326,6 +1358,7 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
     a.by_hkv = divider((uint32_t)st.hkv);
     a.by_batch = divider((uint32_t)st.batch);
     a.decay = prm.budget_decay;
+    a.keep = kept_units(units, slots);
     lds_floats += page_list;
     if (one && lds_floats < 4 + NEAR_SPAN + (size_t)TILE_PER * 64 * form.waves) lds_floats = 4 + NEAR_SPAN + (size_t)TILE_PER * 64 * form.waves;
     const size_t lds = lds_floats * sizeof(float);
@@ -1342,6 +1375,7 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
         const uint64_t grid = (uint64_t)units + (uint64_t)sa.tiles * (uint64_t)st.batch;
         if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
         sa.lead = positions_first(scored, st, form) ? (int32_t)(grid - units) : 0;
+        a.keep += sa.lead;
         sa.new_tok = new_tok;
         sa.sync = sync;
         sa.per_seq = per_seq;

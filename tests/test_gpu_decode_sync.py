@@ -151,6 +151,39 @@ def test_budgets_decay_once_in_every_tile(n, K):
     assert torch.equal(st.budget, want) and st.len.tolist() == [x + 8 for x in lens]
 
 
+@pytest.mark.parametrize("layers,K,page_size", [(16, 279, 0), (16, 279, 16), (20, 220, 0), (20, 220, 16)])
+def test_more_keys_than_the_cache_keeps(layers, K, page_size):
+    """One launch and two over keys of more than 272 MB, part of which has the streaming hint: each layer's units end as they do in a state of that
+    layer alone, bit for bit."""
+    batch, hq, hkv, n = 32, 16, 8, 400
+    prm = ta.Params()
+    lens = [n - 3 * b for b in range(batch)]
+    big, ids, tab_len = _state(layers, batch, hq, hkv, K, n, n + 8, prm, page_size, 400, lens, 11)
+    assert layers * batch * hkv * (K + 1) * 256 > 272 << 20
+    of_layer = ("pos", "A", "Kc", "Vc")
+    alone = {}
+    for l in (0, 10, 11, layers - 1):                             # the first, those around the last that the cache is to hold, the last
+        pages = None
+        if page_size:
+            p = big.pages
+            pages = ta.PagedKV(p.Kpool[l:l + 1].clone(), p.Vpool[l:l + 1].clone(), p.table, p.page_size, p.num_pages, p.strides, 1, batch, hkv, K + 1)
+        alone[l] = ta.DecodeState(1, batch, hq, hkv, K, n + 8, DEV, pages=pages)
+        for name in STATE:
+            if not (page_size and name in ("Kc", "Vc")):
+                getattr(alone[l], name).copy_(getattr(big, name)[l:l + 1] if name in of_layer else getattr(big, name))
+    g = torch.Generator(device=DEV).manual_seed(12)
+    for _ in range(3):
+        tok = torch.randint(0, 400, (batch,), generator=g, device=DEV, dtype=torch.int32)
+        q, k, v = (torch.randn((layers, batch, h, 128), generator=g, device=DEV).to(torch.bfloat16) for h in (hq, hkv, hkv))
+        ta.ta_decode_step(big, tok, q, k, v, ids, tab_len, prm)
+        for l, st in alone.items():
+            ta.ta_decode_step(st, tok, q[l:l + 1].contiguous(), k[l:l + 1].contiguous(), v[l:l + 1].contiguous(), ids, tab_len, prm)
+    for l, st in alone.items():
+        for name in of_layer:
+            a, b = getattr(big, name)[l:l + 1], getattr(st, name)
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)) if a.dtype == torch.bfloat16 else torch.equal(a, b), (l, name)
+
+
 def test_words_off_an_eight_byte_boundary():
     """Two of the words are one number of eight bytes: elsewhere the step is two launches and leaves them alone."""
     prm = ta.Params()
