@@ -109,16 +109,6 @@ __device__ __forceinline__ float other_half(float v)
     return __uint_as_float((threadIdx.x & 32u) ? sw[0] : sw[1]);
 }
 
-// x mod n for numbers below 2^22: the quotient of the floats is off by one at most.  (The compiler's own is some thirty dependent
-// instructions.)
-__device__ __forceinline__ uint32_t remainder_of(uint32_t x, uint32_t n)
-{
-    const uint32_t q = (uint32_t)((float)x * __builtin_amdgcn_rcpf((float)n));
-    int32_t r = (int32_t)(x - q * n);
-    r = r < 0 ? r + (int32_t)n : r;
-    return (uint32_t)(r >= (int32_t)n ? r - (int32_t)n : r);
-}
-
 // s_waitcnt vmcnt(n) with the other counters left alone (gfx9 encoding)
 constexpr int vmcnt_imm(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
 
@@ -214,7 +204,6 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     const int c32 = lane & 31, hf = lane >> 5;
     const int rg = wave % RG, kt = wave / RG;              // row group, key tile of the stage
 
-    const int32_t seq_in_xcd = (int32_t)(blockIdx.x >> 3);
     int32_t chunk;
     int32_t place = place_of(blockIdx.x, a.nchunks, a.by_chunks, chunk);
     if (place >= a.units) return;
@@ -267,21 +256,14 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         return;
     }
 
-    // Stages whose keys are all visible to every row, [0, nfast), are visited in rotated
-    // order, starting at a stage that differs from block to block.  Chunks start at
-    // multiples of a large power of two, so blocks that advance in step would otherwise
-    // all read the same offset within their chunk at the same time and crowd a few
-    // memory channels.
+    // Stages whose keys are all visible to every row: [0, nfast).  The column-sum sweep visits them in the reverse order of the
+    // statistics sweep: what that sweep read last is the likeliest to still sit in the last-level cache.
+    // (Starting at a stage that differs from block to block, as an earlier form did, is no faster and costs its arithmetic.  Whole pass, us, with
+    // that / without: 8 units of 4096 keys 21.7 / 20.5, 256 of 16 384 with 64 rows 376 / 365, 2048 of 4096 794 / 785; full_model_4k 144.2 / 143.4,
+    // pooled_layers_8k 267.5 / 266.1, long_context_128k 4565 / 4540.)
     int nfast = min_lim >= key_lo + STAGE_KEYS - 1 ? (min_lim - key_lo + 1) / STAGE_KEYS : 0;
     nfast = nfast > nstages ? nstages : nfast;
-    const int rot = nfast > 1 ? (int)remainder_of((uint32_t)seq_in_xcd + 5u * (blockIdx.x & 7u), (uint32_t)nfast) : 0;
-    // The column-sum sweep visits them in the reverse order of the statistics sweep: what
-    // that sweep read last is the likeliest to still sit in the last-level cache.
-    const auto stage_pos = [&](int s) {
-        if (s >= nfast) return s;
-        const int p = (COLSUM ? nfast - 1 - s : s) + rot;
-        return p >= nfast ? p - nfast : p;
-    };
+    const auto stage_pos = [&](int s) { return COLSUM && s < nfast ? nfast - 1 - s : s; };
 
     // ---- K staging: direct global->LDS loads, 1 KB (4 key rows) per wavefront instruction.
     // Lane i of a load lands at (buffer + block*1 KB + 16*i): LDS slot row*16 + c' receives the
@@ -644,8 +626,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     // in the middle of a stage: in front of it the stage's first products and half of the reduction of the one before, with the last reads
     // of its buffer, which is free behind it; behind it the first fragments of the next stage are read, under the stage's
     // other products.  So neither the matrix pipe nor the vector unit waits for LDS behind a barrier, which the two wavefronts of a
-    // SIMD reach together.  What a stage needs is known or steps on by itself - the buffer's number, the wait, the address (one step on,
-    // at the end of the rotation back by all) - and costs some 20 scalar instructions, not 60 and ten branches.  (One sweep / two, us, all stages
+    // SIMD reach together.  What a stage needs is known or steps on by itself - the buffer's number, the wait, the address -
+    // and costs some 20 scalar instructions, not 60 and ten branches.  (One sweep / two, us, all stages
     // as in (A) / this: 256 units of 16 384 keys, 256 rows 325 / 280, 633 / 570; 192 of 8192, 256 rows 129 / 114, 253 / 238; 256 of 4096,
     // 512 rows 171 / 149, 336 / 303; 128 rows, 256 units of 16 384 198 / 187, 383 / 365, 2048 of 2048..16 384 873 / 857, 1690 / 1600.)
     const auto turns = [&](int& s, f32x16 (&acc_even)[ROW_TILES], f32x16 (&acc_odd)[ROW_TILES]) {
@@ -656,7 +638,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         fragments(1 % RING, 0, kf);
         int p = stage_pos(s + RING);                       // place of the stage to request
         const char* from = PAGED ? nullptr : reinterpret_cast<const char*>(kbase + (int64_t)(key_lo + p * STAGE_KEYS) * a.k_sp);
-        const int64_t step = (COLSUM ? -1 : 1) * (int64_t)STAGE_KEYS * a.k_sp * 16, back = step - step * nfast;
+        const int64_t step = (COLSUM ? -1 : 1) * (int64_t)STAGE_KEYS * a.k_sp * 16;
         const auto run = [&](int end, auto stream_tag) {
             for (; s + TURN + RING - 1 < end; s += TURN) {
                 const int half = s % (2 * TURN) == 1 ? 0 : TURN;
@@ -674,9 +656,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                     const uint32_t dst = lds_wave + (uint32_t)((1 + j) % RING) * (STAGE_UNITS * 16u);
 #pragma unroll
                     for (int i = 0; i < LPS; ++i) load_to_lds_16<decltype(stream_tag)::value>(src, lane_off[i], dst + WAVES * i * 1024u);
-                    const bool wrap = COLSUM ? p == 0 : p == nfast - 1;
-                    from += wrap ? back : step;
-                    p = wrap ? (COLSUM ? nfast - 1 : 0) : (COLSUM ? p - 1 : p + 1);
+                    from += step;
+                    p += COLSUM ? -1 : 1;
                     fragments((2 + j) % RING, 0, kf);
                     products(1, kf, acc);
 #pragma unroll
