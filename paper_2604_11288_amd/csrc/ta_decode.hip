@@ -57,9 +57,20 @@ __device__ __forceinline__ int32_t clamp_page(const SlotPages& pg, int32_t page)
     return page < 0 ? 0 : (page >= pg.num_pages ? pg.num_pages - 1 : page);
 }
 
+// Units whose keys the last-level cache (256 MB) is to hold until the next step, which reads them again: all where they fit, else 192 MB of them - the
+// rest has the streaming hint and passes by.  (us per step, hint everywhere / this: 256 units x 1025 slots 16.6 / 15.9, paged 17.9 / 17.1; 8192 x 101 47.2 / 42.0,
+// paged 54.1 / 45.8; 4096 x 257, 257 MB, 55.3 / 48.6; 6144 x 257 80.2 / 73.5, paged 89.1 / 80.8; 16 384 x 257 201.6 / 197.0, paged 226.4 / 219.7; 2048 x 1025 94.1 / 89.8.  Of more
+// than fit, 256 MB kept instead of 192: 16 384 x 257 206, 15 360 x 129 102.6 / 97.7; all of them: 218, 115.7.)
+constexpr int64_t CACHED_BYTES = int64_t(272) << 20, KEPT_BYTES = int64_t(192) << 20;
+int32_t kept_units(int64_t units, int slots)
+{
+    const int64_t of_unit = (int64_t)slots * 256;
+    return (int32_t)(units * of_unit <= CACHED_BYTES ? units : KEPT_BYTES / of_unit);
+}
+
 // ---- state initialisation -----------------------------------------------------
-constexpr int INIT_ITERS = 4;
-constexpr int INIT_ROWS = DU_THREADS / 16 * INIT_ITERS;    // cache slots per workgroup
+constexpr int INIT_ITERS = 2;
+constexpr int INIT_ROWS = DU_THREADS / 16 * INIT_ITERS;    // rows of one of the two tensors per workgroup
 
 struct InitArgs {
     const int32_t* tok;
@@ -72,7 +83,8 @@ struct InitArgs {
     const uint4* Kout;
     const uint4* Vout;
     int64_t rows;                                          // units * slots
-    int64_t row_blocks;                                    // workgroups of slots; those behind them fill the per-sequence arrays
+    int64_t slot_blocks, row_blocks;                       // workgroups of the slot tables; of the keys, and as many of the values
+    Divider by_slots, by_hkv, by_batch;
     int32_t n;
     float B;
 };
@@ -101,74 +113,89 @@ __device__ __forceinline__ void init_sequence(const ta_decode_state& st, const I
     }
 }
 
-// INIT_ROWS consecutive slots of the flat [units][slots] order per workgroup, 16 lanes per row, all loads of a lane (four
-// rows of K and V) before its first store, like the compaction: bound by HBM.  (One workgroup per unit with one row in flight per
-// lane: 65 us for 256 units of 1025 slots, 843 us for 16 384 of 257.)
-template <bool PAGED>
+// The unit of a row of the flat [units][slots] order.
+__device__ __forceinline__ int32_t init_unit(const InitArgs& a, int64_t row, int32_t slots)
+{
+    return a.rows <= 0x7FFFFFFF ? (int32_t)divide((uint32_t)row, a.by_slots) : (int32_t)(row / slots);
+}
+
+// Position and accumulated attention of a slot per thread.
+__device__ __forceinline__ void init_slots(const ta_decode_state& st, const InitArgs& a, int64_t row)
+{
+    if (row >= a.rows) return;
+    const int32_t slots = st.K + 1;
+    const int32_t unit = init_unit(a, row, slots), s = (int32_t)(row - (int64_t)unit * slots);
+    int32_t p = a.idx[(size_t)unit * st.K + (s < st.K ? s : st.K - 1)];
+    const bool kept = s < st.K && s < a.cnt[unit];
+    p = p < 0 ? 0 : (p >= a.n ? a.n - 1 : p);
+    st.pos[row] = kept ? p : -1;
+    st.A[row] = kept && a.A ? a.A[(size_t)unit * a.n + p] : 0.0f;
+}
+
+// The slot tables, the keys, the values, then the per-sequence arrays.  Rows move as in the compaction: INIT_ROWS consecutive slots of the
+// flat [units][slots] order and one tensor per workgroup, 16 lanes per row, all loads of a lane before its first store, bound by HBM; the slot tables, two
+// dependent loads each, have threads of their own.  Keys that the cache can hold until the first step are stored without the streaming hint
+// (KEEP).  (With the first step, us, both tensors by 64 rows behind their slots' tables / this: 256 units of 1025 slots 69 / 61.3, over pages 71.5 / 62.8; 2048
+// of 65 46 / 41; 4096 of 257 253.6 / 238; 16 384 of 257 970 / 922, over pages 1034 / 993; the slot tables behind the rows 933, keys without the hint where they do not fit 1001.)
+template <bool PAGED, bool KEEP>
 __global__ void __launch_bounds__(DU_THREADS)
 decode_init_kernel(ta_decode_state st, InitArgs a, SlotPages pg)
 {
-    if ((int64_t)blockIdx.x >= a.row_blocks) {
-        init_sequence(st, a, (int32_t)((int64_t)blockIdx.x - a.row_blocks));
+    int64_t block = (int64_t)blockIdx.x;
+    if (block < a.slot_blocks) {
+        init_slots(st, a, block * DU_THREADS + threadIdx.x);
         return;
     }
+    block -= a.slot_blocks;
+    if (block >= 2 * a.row_blocks) {
+        init_sequence(st, a, (int32_t)(block - 2 * a.row_blocks));
+        return;
+    }
+    const bool values = block >= a.row_blocks;
+    if (values) block -= a.row_blocks;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     const int32_t slots = st.K + 1;
-    const int64_t row0 = (int64_t)blockIdx.x * INIT_ROWS;
-    const int64_t unit0 = row0 / slots;                    // uniform
-    const int32_t slot0 = (int32_t)(row0 - unit0 * slots);
+    const int64_t row0 = block * INIT_ROWS;
+    const int32_t unit0 = init_unit(a, row0, slots);       // uniform
+    const int32_t slot0 = (int32_t)(row0 - (int64_t)unit0 * slots);
     const int lane16 = threadIdx.x & 15, rsub = threadIdx.x >> 4;
-    int64_t from[INIT_ITERS], to[INIT_ITERS];
-    bool live[INIT_ITERS], kept[INIT_ITERS];
+    const u32x4* in = reinterpret_cast<const u32x4*>(values ? a.Vout : a.Kout);
+    u32x4* out = reinterpret_cast<u32x4*>(values ? st.Vc : st.Kc);
+    int64_t to[INIT_ITERS];
+    bool live[INIT_ITERS];
+    int32_t slot[INIT_ITERS], count[INIT_ITERS];
+    u32x4 v[INIT_ITERS];
 #pragma unroll
     for (int i = 0; i < INIT_ITERS; ++i) {
         const int32_t off = 16 * i + rsub;
-        const int32_t du = (slot0 + off) / slots;
+        const int32_t du = (int32_t)divide((uint32_t)(slot0 + off), a.by_slots);
         live[i] = row0 + off < a.rows;
-        const int32_t unit = (int32_t)(live[i] ? unit0 + du : unit0);
+        const int32_t unit = live[i] ? unit0 + du : unit0;
         const int32_t s = live[i] ? slot0 + off - du * slots : slot0;
-        int32_t c = a.cnt[unit];
-        c = c < 0 ? 0 : (c > st.K ? st.K : c);
-        kept[i] = s < c;
         const int32_t sr = s < st.K ? s : st.K - 1;        // a readable row; the spare slot is zeroed
-        from[i] = ((int64_t)unit * st.K + sr) * 16 + lane16;
+        v[i] = __builtin_nontemporal_load(&in[((int64_t)unit * st.K + sr) * 16 + lane16]);
+        slot[i] = s;
+        count[i] = a.cnt[unit];
         if (PAGED) {
-            const int g = unit % st.hkv;
-            const int b = (unit / st.hkv) % st.batch;
-            const int l = unit / (st.hkv * st.batch);
+            const int32_t pair = (int32_t)divide((uint32_t)unit, a.by_hkv), g = unit - pair * st.hkv;
+            const int32_t l = (int32_t)divide((uint32_t)pair, a.by_batch), b = pair - l * st.batch;
             const int32_t j = page_index(pg, s);
             const int32_t page = clamp_page(pg, pg.table[(size_t)b * pg.max_pages + j]);
             to[i] = l * pg.s_layer + g * pg.s_head + (int64_t)page * pg.s_page + (int64_t)(s - j * pg.page_size) * pg.s_slot + lane16;
         } else {
             to[i] = ((int64_t)unit * slots + s) * 16 + lane16;
         }
-        if (lane16 == 0 && live[i]) {
-            int32_t p = -1;
-            float at = 0.0f;
-            if (kept[i]) {
-                p = a.idx[(size_t)unit * st.K + s];
-                p = p < 0 ? 0 : (p >= a.n ? a.n - 1 : p);
-                if (a.A) at = a.A[(size_t)unit * a.n + p];
-            }
-            st.pos[(size_t)unit * slots + s] = p;
-            st.A[(size_t)unit * slots + s] = at;
-        }
     }
-    if (!a.Kout) return;                                   // paged state whose rows are in place already
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    const u32x4 *Kin = reinterpret_cast<const u32x4*>(a.Kout), *Vin = reinterpret_cast<const u32x4*>(a.Vout);
-    u32x4 *Kc = reinterpret_cast<u32x4*>(st.Kc), *Vc = reinterpret_cast<u32x4*>(st.Vc);
-    u32x4 kv[INIT_ITERS], vv[INIT_ITERS];
 #pragma unroll
     for (int i = 0; i < INIT_ITERS; ++i) {
-        kv[i] = __builtin_nontemporal_load(&Kin[from[i]]);
-        vv[i] = __builtin_nontemporal_load(&Vin[from[i]]);
-    }
-#pragma unroll
-    for (int i = 0; i < INIT_ITERS; ++i) {
-        if (live[i]) {
-            __builtin_nontemporal_store(kept[i] ? kv[i] : zero, &Kc[to[i]]);
-            __builtin_nontemporal_store(kept[i] ? vv[i] : zero, &Vc[to[i]]);
+        if (!live[i]) continue;
+        const u32x4 row = slot[i] < st.K && slot[i] < count[i] ? v[i] : zero;
+        if (KEEP && !values) {
+            out[to[i]] = row;
+            asm volatile("");                              // (else the compiler makes one store of the two, without the hint)
+        } else {
+            __builtin_nontemporal_store(row, &out[to[i]]);
         }
     }
 }
@@ -1147,17 +1174,6 @@ bool rows_fit(bool scored, const ta_decode_state& st, UnitForm f)
 // of 40 960 positions in two 18.8 / 21.0; 256 x 1025, 131 072 in two 17.0 / 19.2).
 bool positions_first(bool scored, const ta_decode_state& st, UnitForm f) { return !scored || rounds_of(st, f) > 1; }
 
-// Units whose keys the last-level cache (256 MB) is to hold until the next step, which reads them again: all where they fit, else 192 MB of them - the
-// rest has the streaming hint and passes by.  (us per step, hint everywhere / this: 256 units x 1025 slots 16.6 / 15.9, paged 17.9 / 17.1; 8192 x 101 47.2 / 42.0,
-// paged 54.1 / 45.8; 4096 x 257, 257 MB, 55.3 / 48.6; 6144 x 257 80.2 / 73.5, paged 89.1 / 80.8; 16 384 x 257 201.6 / 197.0, paged 226.4 / 219.7; 2048 x 1025 94.1 / 89.8.  Of more
-// than fit, 256 MB kept instead of 192: 16 384 x 257 206, 15 360 x 129 102.6 / 97.7; all of them: 218, 115.7.)
-constexpr int64_t CACHED_BYTES = int64_t(272) << 20, KEPT_BYTES = int64_t(192) << 20;
-int32_t kept_units(int64_t units, int slots)
-{
-    const int64_t of_unit = (int64_t)slots * 256;
-    return (int32_t)(units * of_unit <= CACHED_BYTES ? units : KEPT_BYTES / of_unit);
-}
-
 // Key tiles in flight: two per wavefront where wavefronts share a unit - enough with all that then share a compute unit, and the
 // registers let more of them do so (six, us per step: 1025 slots, 256 units 21.0 -> 19.8, 1024 units 56.6 -> 52.7; 1501
 // slots, 1024 units 94.4 -> 75.4).  One wavefront per unit: three at four wavefronts per SIMD; paged slots need
@@ -1310,14 +1326,21 @@ hipError_t launch_decode_init(const ta_decode_state& st, const int32_t* tok, con
     a.Kout = (const uint4*)Kout;
     a.Vout = (const uint4*)Vout;
     a.rows = (int64_t)st.layers * st.batch * st.hkv * (st.K + 1);
-    a.row_blocks = (a.rows + INIT_ROWS - 1) / INIT_ROWS;
+    a.slot_blocks = (a.rows + DU_THREADS - 1) / DU_THREADS;
+    a.row_blocks = Kout ? (a.rows + INIT_ROWS - 1) / INIT_ROWS : 0;      // (paged state whose rows are in place already: none)
+    a.by_slots = divider((uint32_t)(st.K + 1));
+    a.by_hkv = divider((uint32_t)st.hkv);
+    a.by_batch = divider((uint32_t)st.batch);
     a.n = n;
     a.B = B;
-    const int64_t grid = a.row_blocks + (int64_t)((st.cap + DU_THREADS - 1) / DU_THREADS) * st.batch;
+    const int64_t grid = a.slot_blocks + 2 * a.row_blocks + (int64_t)((st.cap + DU_THREADS - 1) / DU_THREADS) * st.batch;
     if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
     const SlotPages pg = slot_pages(st);
-    if (st.pages) hipLaunchKernelGGL(decode_init_kernel<true>, dim3((unsigned)grid), dim3(DU_THREADS), 0, s, st, a, pg);
-    else hipLaunchKernelGGL(decode_init_kernel<false>, dim3((unsigned)grid), dim3(DU_THREADS), 0, s, st, a, pg);
+    const int64_t units = (int64_t)st.layers * st.batch * st.hkv;
+    const bool keep = A && kept_units(units, st.K + 1) == units;         // (without scores no step reads the keys)
+    const auto kernel = st.pages ? (keep ? decode_init_kernel<true, true> : decode_init_kernel<true, false>)
+                                 : (keep ? decode_init_kernel<false, true> : decode_init_kernel<false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(DU_THREADS), 0, s, st, a, pg);
     return hipGetLastError();
 }
 
