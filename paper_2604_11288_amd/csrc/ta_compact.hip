@@ -22,8 +22,10 @@ template <bool PAGED, bool LAYERED, bool DST_PAGED = false>
 __global__ void __launch_bounds__(COMPACT_THREADS)
 compact_kernel(CompactArgs a)
 {
-    const int32_t unit = (int32_t)divide(blockIdx.x, a.by_blocks);
-    const int32_t blk = (int32_t)blockIdx.x - unit * a.blocks_per_unit;
+    const uint32_t block = blockIdx.z * GRID_LINE + blockIdx.x;
+    if (block >= a.blocks) return;
+    const int32_t unit = (int32_t)divide(block, a.by_blocks);
+    const int32_t blk = (int32_t)block - unit * a.blocks_per_unit;
     const bool values = blockIdx.y != 0;
     const int32_t pair = (int32_t)divide((uint32_t)unit, a.by_hkv), h = unit - pair * a.hkv;
     const int32_t l = (int32_t)divide((uint32_t)pair, a.by_batch), b = pair - l * a.batch;
@@ -163,6 +165,7 @@ CompactArgs make_compact_args(const void* Kin, const void* Vin, const int32_t* i
     a.K = K;
     a.idx_shared = idx_shared;
     a.blocks_per_unit = (K + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
+    a.blocks = (uint32_t)((int64_t)lay.layers * lay.batch * lay.hkv * a.blocks_per_unit);
     a.by_blocks = divider((uint32_t)a.blocks_per_unit);
     a.by_hkv = divider((uint32_t)lay.hkv);
     a.by_batch = divider((uint32_t)lay.batch);
@@ -175,9 +178,10 @@ hipError_t launch_compact(const void* Kin, const void* Vin, const int32_t* idx, 
                           const ta_paged_kv* dst_pg)
 {
     const CompactArgs a = make_compact_args(Kin, Vin, idx, cnt, lay, K, idx_shared, Kout, Vout, pg, lp, dst_pg);
-    int64_t units = (int64_t)lay.layers * lay.batch * lay.hkv;
-    int64_t blocks = units * a.blocks_per_unit;
-    const dim3 grid((unsigned)blocks, 2), block(COMPACT_THREADS);
+    const int64_t blocks = (int64_t)lay.layers * lay.batch * lay.hkv * a.blocks_per_unit;
+    if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;              // (Divider)
+    const GridLines lines(blocks);
+    const dim3 grid(lines.x, 2, lines.lines), block(COMPACT_THREADS);
     if (dst_pg && pg) hipLaunchKernelGGL((compact_kernel<true, false, true>), grid, block, 0, st, a);
     else if (dst_pg) hipLaunchKernelGGL((compact_kernel<false, false, true>), grid, block, 0, st, a);
     else if (pg && lp) hipLaunchKernelGGL((compact_kernel<true, true>), grid, block, 0, st, a);

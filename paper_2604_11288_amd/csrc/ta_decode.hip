@@ -84,6 +84,7 @@ struct InitArgs {
     const uint4* Vout;
     int64_t rows;                                          // units * slots
     int64_t slot_blocks, row_blocks;                       // workgroups of the slot tables; of the keys, and as many of the values
+    int64_t seq_blocks;                                    // of the per-sequence arrays
     Divider by_slots, by_hkv, by_batch;
     int32_t n;
     float B;
@@ -141,14 +142,14 @@ template <bool PAGED, bool KEEP>
 __global__ void __launch_bounds__(DU_THREADS)
 decode_init_kernel(ta_decode_state st, InitArgs a, SlotPages pg)
 {
-    int64_t block = (int64_t)blockIdx.x;
+    int64_t block = (int64_t)blockIdx.y * GRID_LINE + blockIdx.x;
     if (block < a.slot_blocks) {
         init_slots(st, a, block * DU_THREADS + threadIdx.x);
         return;
     }
     block -= a.slot_blocks;
     if (block >= 2 * a.row_blocks) {
-        init_sequence(st, a, (int32_t)(block - 2 * a.row_blocks));
+        if (block < 2 * a.row_blocks + a.seq_blocks) init_sequence(st, a, (int32_t)(block - 2 * a.row_blocks));
         return;
     }
     const bool values = block >= a.row_blocks;
@@ -1333,14 +1334,14 @@ hipError_t launch_decode_init(const ta_decode_state& st, const int32_t* tok, con
     a.by_batch = divider((uint32_t)st.batch);
     a.n = n;
     a.B = B;
-    const int64_t grid = a.slot_blocks + 2 * a.row_blocks + (int64_t)((st.cap + DU_THREADS - 1) / DU_THREADS) * st.batch;
-    if (grid > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    a.seq_blocks = (int64_t)((st.cap + DU_THREADS - 1) / DU_THREADS) * st.batch;
+    const GridLines grid(a.slot_blocks + 2 * a.row_blocks + a.seq_blocks);
     const SlotPages pg = slot_pages(st);
     const int64_t units = (int64_t)st.layers * st.batch * st.hkv;
     const bool keep = A && kept_units(units, st.K + 1) == units;         // (without scores no step reads the keys)
     const auto kernel = st.pages ? (keep ? decode_init_kernel<true, true> : decode_init_kernel<true, false>)
                                  : (keep ? decode_init_kernel<false, true> : decode_init_kernel<false, false>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(DU_THREADS), 0, s, st, a, pg);
+    hipLaunchKernelGGL(kernel, dim3(grid.x, grid.lines), dim3(DU_THREADS), 0, s, st, a, pg);
     return hipGetLastError();
 }
 

@@ -18,6 +18,7 @@ struct CompactArgs {
     int32_t batch, hkv, n, K;
     int32_t idx_shared;
     int32_t blocks_per_unit;
+    uint32_t blocks;                           // of either tensor
     Divider by_blocks, by_hkv, by_batch;
     // paged input: rows are addressed through the block table (s_batch unused, s_page per page)
     const int32_t* table;

@@ -20,6 +20,15 @@ inline Divider divider(uint32_t d)
 
 __device__ __forceinline__ uint32_t divide(uint32_t x, const Divider& by) { return (uint32_t)(((uint64_t)x * by.mul) >> by.shift); }
 
+// A launch's dimension holds fewer than 2^32 threads, 2^24 workgroups of 256: a longer row of workgroups goes in lines of GRID_LINE, the last
+// of them padded.
+constexpr uint32_t GRID_LINE = 1u << 23;
+struct GridLines {
+    uint32_t x, lines;
+    explicit GridLines(int64_t blocks)
+        : x(blocks < (int64_t)GRID_LINE ? (uint32_t)blocks : GRID_LINE), lines((uint32_t)((blocks + GRID_LINE - 1) / GRID_LINE)) {}
+};
+
 // The unit that comes `at`-th: as numbered when all sequences are equally long, else all units of the longest sequence
 // first, then those of the next (equal lengths in batch order).  The longest units then start first and the shortest fill the
 // gaps at the end, and a compute unit's second workgroup is shorter than its first.  Every wavefront works the order out for

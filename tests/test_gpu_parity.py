@@ -428,6 +428,16 @@ def test_compact_bit_exact_strided_and_shared():
         assert np.array_equal(wl.bf16_bits(Vo[l, b, h][:c]), ora.compact(wl.bf16_bits(V[l, b, h]), sidx[b][:c]))
 
 
+def test_compact_more_workgroups_than_one_line():
+    # 2^23 workgroups of a tensor and a few more: a second line of the launch, all but empty
+    layers, hkv = (1 << 20) + 1, 8
+    K = torch.randint(-30000, 30000, (layers, 1, hkv, 1, 128), dtype=torch.int16, device=DEV).view(torch.bfloat16)
+    V = K.flip(0)
+    idx, cnt = torch.zeros((layers, 1, hkv, 1), dtype=torch.int32, device=DEV), torch.ones((layers, 1, hkv), dtype=torch.int32, device=DEV)
+    Ko, Vo = ta.ta_compact(K, V, idx, cnt, 1)
+    assert torch.equal(Ko.view(torch.int16), K.view(torch.int16)) and torch.equal(Vo.view(torch.int16), V.view(torch.int16))
+
+
 # --------------------------------------------------------------------------
 # the fused pass
 # --------------------------------------------------------------------------
