@@ -48,19 +48,19 @@ SCORE_TRAFFIC = {
     "c4_long_context": {      # profiles/evict_pass_c4_long_context_K1024.txt
         "bytes_per_step": 69.40e9,
         "sources": {
-            "ta_score.hip": "8291d47415297e013db848fe0dc35ad28a28eb5c2b7b6df2eed76b93ec9ffe74",
+            "ta_score.hip": "6f13e8aa8b86104124f84be1fc44b18b1fdaeac96c91aae69f3069c7a924b3bb",
             "ta_score_common.h": "63db8ddf5fa51de1c9c0bba8099d89dd4e23ca91ac5c5163b227273ce568d4e2",
             "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
-            "ta_order.h": "1a77538c7a7256d587852a368d83bc1fc94c7e4666c07d0a6da1a535f7435ffa",
+            "ta_order.h": "27e88482dbbf44b482f6d8f51f84bef8be18f49efa01d8c75eb2464c1f23b8d4",
         },
     },
     "c2_full_model": {        # profiles/score_two_sweep_c2_full_model_K1024.txt
         "bytes_per_step": 559.4e6,
         "sources": {
-            "ta_score.hip": "8291d47415297e013db848fe0dc35ad28a28eb5c2b7b6df2eed76b93ec9ffe74",
+            "ta_score.hip": "6f13e8aa8b86104124f84be1fc44b18b1fdaeac96c91aae69f3069c7a924b3bb",
             "ta_score_common.h": "63db8ddf5fa51de1c9c0bba8099d89dd4e23ca91ac5c5163b227273ce568d4e2",
             "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
-            "ta_order.h": "1a77538c7a7256d587852a368d83bc1fc94c7e4666c07d0a6da1a535f7435ffa",
+            "ta_order.h": "27e88482dbbf44b482f6d8f51f84bef8be18f49efa01d8c75eb2464c1f23b8d4",
         },
     },
 }
