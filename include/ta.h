@@ -201,6 +201,7 @@ int32_t ta_match_anchors(const int32_t *tok, const int32_t *seq_len, int32_t B, 
  *                    confidence; scale = 1 gives vouchers conf * rho^k); 0 elsewhere
  * Positions >= seq_len[b] get 0 in all three outputs.  The outputs feed
  * ta_expand_vouchers (then ta_select) in place of the table match.
+ * Equal rows of a call get equal outputs, to the last bit.
  *
  *   h        DEVICE bf16 [B][n][d_model], rows h_row_stride elements apart (>= d_model,
  *            multiple of 8), sequences n * h_row_stride apart; 16-byte aligned
@@ -224,7 +225,9 @@ int32_t ta_detect_anchors(const void *h, int64_t h_row_stride, const void *W1, c
  *   anchor[b][p] = 1 iff sim > tau  (strict; the paper gives no value for tau)
  * Positions >= seq_len[b] get 0 in both outputs.  Input embeddings depend on the
  * token ID only: run this over the embedding table once (B = 1, n = vocabulary
- * size) and use ta_lookup_anchors per sequence, or run it per position.
+ * size) and use ta_lookup_anchors per sequence, or run it per position.  Equal rows of a
+ * call get equal similarities, to the last bit; for E <= 16 the two ways agree to the last
+ * bit, for more concepts the order of summation follows the number of rows.
  *
  *   x        DEVICE bf16 [B][n][d_model], rows x_row_stride elements apart (>= d_model,
  *            multiple of 8), sequences n * x_row_stride apart; 16-byte aligned

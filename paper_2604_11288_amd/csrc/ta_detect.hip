@@ -98,18 +98,78 @@ __device__ __forceinline__ float add_squares(uint4 v, float acc)
 
 enum { MODE_MLP = 0, MODE_COSINE = 1 };
 
-// The first of `steps` steps over the features: another one from workgroup to neighbouring workgroup of an XCD (workgroup b runs
-// on XCD b mod 8), the others follow in order and wrap round.  Rows lie a power of two apart more often than not, so
-// workgroups that start together at feature 0 all read the same offset within their rows and crowd a few memory channels (us, all
-// at feature 0 / rotated: 131 072 positions, d_model 4096, 128 units 231 / 180 = 6.0 TB/s; 65 536, d_model 2048, 65 / 49; 64 units,
-// 131 072, d_model 4096, 207 / 188; 128 256 rows and 16 concepts, 32 positions per workgroup, 211 / 147 = 7.15 TB/s).
-__device__ __forceinline__ int first_step(int steps) { return (int)((blockIdx.x >> 3) % (uint32_t)steps); }
+// The order in which a wavefront visits its `steps` steps over the features.  Rows lie a power of two apart more often than not, so workgroups that
+// all begin at feature 0 read the same offset within their rows at the same time and crowd a few memory channels.  So the steps are dealt out, `chunk`
+// at a time, to 2^log parts, and neighbouring workgroups begin with different ones.  The sums of a part start from zero, and the parts' sums are added
+// up as a balanced tree (close_part).  A workgroup visits part (start ^ i) as the i-th: whatever its start, the same pairs of the tree meet, with at most
+// their operands exchanged, so a row's result does not depend, to the last bit, on where the row stands in the call.  (A start that wraps
+// round, each workgroup's another, spreads the reads further but adds up in as many orders.)
+// us, all at feature 0 / parts / wrapping starts: 128 256 rows of 4096, 16 concepts, four parts of four steps 187 / 150 = 7.0 TB/s / 148; 131 072
+// positions of 4096, 128 units, four parts of 1 KB 240 / 203 / 191, 32 768 62 / 54 / 50; 64 units, four parts 208 / 200 / 188; 65 536 of 4096, 32 units, eight
+// parts 95 / 87 / 85; 131 072 of 2048, 32 units 100 / 88 / 88.  Which chunk is best differs by form: with 4 KB, or 2 KB where W1 counts, between
+// the starts these crowd the channels of the L2 in turn (64 units, 2 KB 235; 128 units, two parts 4 KB apart 400).
+struct Visit {
+    int steps, log, chunk, start, part, at, left;          // at: this step; left: steps of its part, with this one
+    // (workgroup b runs on XCD b mod 8: neighbours of an XCD start at different parts)
+    __device__ __forceinline__ Visit(int n, int l, int c) : steps(n), log(l), chunk(c), start((int)(blockIdx.x >> 3) & ((1 << l) - 1)), part(0) { open(); }
+    __device__ __forceinline__ void open()
+    {
+        const int turn = chunk << log, turns = steps / turn;
+        at = (start ^ part) * chunk;
+        const int rest = steps - turns * turn - at;
+        left = turns * chunk + (rest < 0 ? 0 : (rest > chunk ? chunk : rest));
+    }
+    __device__ __forceinline__ void step()
+    {
+        ++at;
+        --left;
+        if (at % chunk == 0) at += (chunk << log) - chunk;
+    }
+    __device__ __forceinline__ bool last() const { return part + 1 == 1 << log; }
+    __device__ __forceinline__ void to_full()              // on to a part that has steps left, if there is one
+    {
+        while (left == 0 && !last()) {
+            ++part;
+            open();
+        }
+    }
+};
+
+// The end of a part: level l of the tree holds the sums of 2^(l + 1) parts, and behind the last part the accumulators get its top.
+template <int LOG, int N, typename T>
+__device__ __forceinline__ void close_part(const Visit& v, T (&acc)[N], T (&tree)[LOG ? LOG : 1][N])
+{
+    if constexpr (LOG > 0) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            tree[0][j] += acc[j];
+            acc[j] = T{};
+        }
+#pragma unroll
+        for (int l = 1; l < LOG; ++l) {
+            if (((v.part + 1) & ((1 << l) - 1)) && !v.last()) break;   // uniform
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                tree[l][j] += tree[l - 1][j];
+                tree[l - 1][j] = T{};
+            }
+        }
+        if (v.last())
+#pragma unroll
+            for (int j = 0; j < N; ++j) acc[j] = tree[LOG - 1][j];
+    }
+}
+
+// Rows of less than 4 KB are read in order: their parts would be too short to pay for the additions (20 000 positions of 1024, 128 units, four
+// parts / one 18.5 / 17.3 us).
+template <int LOG>
+__device__ __forceinline__ int parts_log(int dm) { return dm >= 2048 ? LOG : 0; }
 
 // ---- shared form: the wavefronts of a workgroup share every slice ---------------------------------------
 // TW: wavefront rows over the positions (64 TW positions per workgroup); HT: 32-unit hidden tiles
 // per wavefront; MH: wavefront columns over the hidden units (m = 32 HT MH); MODE: which epilogue; DT_RING: slice
-// buffers, loads run DT_RING - 1 slices ahead; STREAM: see launch_hint
-template <int TW, int HT, int MH, int MODE, int DT_RING, bool STREAM>
+// buffers, loads run DT_RING - 1 slices ahead; STREAM: see launch_hint; LOG, CHUNK: see Visit
+template <int TW, int HT, int MH, int MODE, int DT_RING, bool STREAM, int LOG, int CHUNK>
 __global__ void __launch_bounds__(64 * TW * MH, 2)
 detect_kernel(DetectArgs a)
 {
@@ -166,11 +226,13 @@ detect_kernel(DetectArgs a)
     const uint32_t half_back = ((lane & 7) ^ (lane >> 3)) >= 4 ? 64u : 0u;   // half a slice: the second half repeats the first
     const char* hbase = reinterpret_cast<const char*>(a.h) + tile0 * a.h_row_bytes;
     const char* wbase = reinterpret_cast<const char*>(a.W1);
-    const int first = first_step(nstages);
-    const auto slice_of = [&](int i) { return first + i >= nstages ? first + i - nstages : first + i; };
+    Visit ahead(nstages, parts_log<LOG>(a.dm), CHUNK), now = ahead;      // the slice to request, the slice to work on
+    ahead.to_full();
     const auto issue = [&](int i) {
         const uint32_t dst = lds0 + (uint32_t)(i % DT_RING) * BUF_BYTES;
-        const int s = slice_of(i);
+        const int s = ahead.at;
+        ahead.step();
+        ahead.to_full();
         const char* hs = hbase + (size_t)s * (DT_KS * 2);
         const char* ws = wbase + (size_t)s * (DT_KS * 2);
         const uint32_t back = s * DT_KS + 32 >= a.dm ? half_back : 0u;
@@ -219,38 +281,53 @@ detect_kernel(DetectArgs a)
     float xx[2] = {0.0f, 0.0f}, cc[HT];                    // cosine mode: squared norms, this lane's half of each row
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht) cc[ht] = 0.0f;
+    f32x16 acc_tree[2][LOG ? LOG : 1][HT] = {};
+    float xx_tree[LOG ? LOG : 1][2] = {}, cc_tree[LOG ? LOG : 1][HT] = {};
 
-    for (int s = 0; s < nstages; ++s) {
-        const int later = nstages - 1 - s;
-        wait_but(later < DT_RING - 2 ? later : DT_RING - 2);
-        __syncthreads();                                   // slice s landed everywhere, slice s-1 consumed
-        if (s + DT_RING - 1 < nstages) issue(s + DT_RING - 1);
-        const uint4* buf = s_buf + (size_t)(s % DT_RING) * (BUF_BYTES / 16);
+    int s = 0;
+    for (;;) {
+        for (; now.left > 0; now.step(), ++s) {
+            const int later = nstages - 1 - s;
+            wait_but(later < DT_RING - 2 ? later : DT_RING - 2);
+            __syncthreads();                                   // slice s landed everywhere, slice s-1 consumed
+            if (s + DT_RING - 1 < nstages) issue(s + DT_RING - 1);
+            const uint4* buf = s_buf + (size_t)(s % DT_RING) * (BUF_BYTES / 16);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            if (ks == 2 && slice_of(s) * DT_KS + 32 >= a.dm) break;   // uniform
-            uint4 hraw[2], wraw[HT];
+            for (int ks = 0; ks < 4; ++ks) {
+                if (ks == 2 && now.at * DT_KS + 32 >= a.dm) break;   // uniform
+                uint4 hraw[2], wraw[HT];
 #pragma unroll
-            for (int tt = 0; tt < 2; ++tt) hraw[tt] = buf[slot_h[tt][ks]];
+                for (int tt = 0; tt < 2; ++tt) hraw[tt] = buf[slot_h[tt][ks]];
 #pragma unroll
-            for (int ht = 0; ht < HT; ++ht) wraw[ht] = buf[slot_w[ht][ks]];
-            if constexpr (MODE == MODE_COSINE) {
+                for (int ht = 0; ht < HT; ++ht) wraw[ht] = buf[slot_w[ht][ks]];
+                if constexpr (MODE == MODE_COSINE) {
 #pragma unroll
-                for (int tt = 0; tt < 2; ++tt) xx[tt] = add_squares(hraw[tt], xx[tt]);
+                    for (int tt = 0; tt < 2; ++tt) xx[tt] = add_squares(hraw[tt], xx[tt]);
 #pragma unroll
-                for (int ht = 0; ht < HT; ++ht) cc[ht] = add_squares(wraw[ht], cc[ht]);
+                    for (int ht = 0; ht < HT; ++ht) cc[ht] = add_squares(wraw[ht], cc[ht]);
+                }
+                bf16x8 hfrag[2], wfrag[HT];
+#pragma unroll
+                for (int tt = 0; tt < 2; ++tt) hfrag[tt] = as_frag(hraw[tt]);
+#pragma unroll
+                for (int ht = 0; ht < HT; ++ht) wfrag[ht] = as_frag(wraw[ht]);
+#pragma unroll
+                for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt)   // rows: hidden units of the tile, columns: positions
+                        acc[tt][ht] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfrag[ht], hfrag[tt], acc[tt][ht], 0, 0, 0);
             }
-            bf16x8 hfrag[2], wfrag[HT];
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt) hfrag[tt] = as_frag(hraw[tt]);
-#pragma unroll
-            for (int ht = 0; ht < HT; ++ht) wfrag[ht] = as_frag(wraw[ht]);
-#pragma unroll
-            for (int ht = 0; ht < HT; ++ht)
-#pragma unroll
-                for (int tt = 0; tt < 2; ++tt)   // rows: hidden units of the tile, columns: positions
-                    acc[tt][ht] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfrag[ht], hfrag[tt], acc[tt][ht], 0, 0, 0);
         }
+        if constexpr (LOG == 0) break;
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) close_part<LOG>(now, acc[tt], acc_tree[tt]);
+        if constexpr (MODE == MODE_COSINE) {
+            close_part<LOG>(now, xx, xx_tree);
+            close_part<LOG>(now, cc, cc_tree);
+        }
+        if (now.last()) break;
+        ++now.part;
+        now.open();
     }
 
     if constexpr (MODE == MODE_MLP) {
@@ -363,7 +440,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // units, and loading the operand fragments straight into registers, where neighbouring lanes lie in different rows,
 // 40 us), and the partial sums of the WV wavefronts meet once, in LDS, after the last step.
 // PT: 16-position tiles of a workgroup; NT: 16-unit tiles of the hidden layer (concepts); WV wavefronts, each of which
-// contracts every WV-th step of 64 features; R: steps in flight per wavefront
+// contracts every WV-th step of 64 features; R: steps in flight per wavefront; LOG, CHUNK: see Visit
 template <int PT, int NT, int WV, int R>
 struct SplitShape {
     static constexpr int POS = 16 * PT, M = 16 * NT, THREADS = 64 * WV;
@@ -376,7 +453,7 @@ struct SplitShape {
     static constexpr int LDS_BYTES = UNITS * 16 + (M + THREADS + WV * M + WV * POS) * 4;
 };
 
-template <int PT, int NT, int WV, int R, int MODE, bool STREAM>
+template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG, int CHUNK>
 __global__ void __launch_bounds__(64 * WV)
 detect_split_kernel(DetectArgs a)
 {
@@ -415,13 +492,15 @@ detect_split_kernel(DetectArgs a)
     const char* wbase = reinterpret_cast<const char*>(a.W1);
     uint4* ring = s_buf + wave * (R * S::STEP_UNITS);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)ring;
-    const int first = mine > 0 ? first_step(mine) : 0;
-    const auto step_of = [&](int i) { return wave + WV * (first + i >= mine ? first + i - mine : first + i); };
-    const auto half = [&](int i) { return 64 * step_of(i) + 32 >= a.dm; };
+    Visit ahead(mine, parts_log<LOG>(a.dm), CHUNK), now = ahead;         // the step to request, the step to work on
+    ahead.to_full();
+    const auto half = [&](const Visit& v) { return 64 * (wave + WV * v.at) + 32 >= a.dm; };
     const auto issue = [&](int i) {
         const uint32_t dst = lds0 + (uint32_t)(i % R) * (S::STEP_UNITS * 16);
-        const size_t at = (size_t)step_of(i) * 128;
-        const uint32_t back = half(i) ? half_back : 0u;
+        const size_t at = (size_t)(wave + WV * ahead.at) * 128;
+        const uint32_t back = half(ahead) ? half_back : 0u;
+        ahead.step();
+        ahead.to_full();
 #pragma unroll
         for (int j = 0; j < 2 * PT; ++j) dma16<STREAM>(hbase + at, off[j] - back, __builtin_amdgcn_readfirstlane(dst + j * 1024));
 #pragma unroll
@@ -440,6 +519,8 @@ detect_split_kernel(DetectArgs a)
     for (int p = 0; p < PT; ++p) xx[p] = 0.0f;
 #pragma unroll
     for (int j = 0; j < NT; ++j) cc[j] = 0.0f;
+    f32x4 acc_tree[PT][LOG ? LOG : 1][NT] = {};
+    float xx_tree[LOG ? LOG : 1][PT] = {}, cc_tree[LOG ? LOG : 1][NT] = {};
 
 #pragma unroll
     for (int i = 0; i < R; ++i)
@@ -453,7 +534,7 @@ detect_split_kernel(DetectArgs a)
             f[1][j] = buf[j * 128 + slot1];
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the fragments are in registers: the buffer is free
-        const bool whole = !half(i);
+        const bool whole = !half(now);
         if (more) issue(i + R);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -474,14 +555,25 @@ detect_split_kernel(DetectArgs a)
         }
     };
     int i = 0;
-    for (; i + R < mine; ++i) {
-        __builtin_amdgcn_s_waitcnt(vm_imm((R - 1) * LPS)); // step i is in; R - 1 later ones are on their way
-        asm volatile("" ::: "memory");
-        step(i, true);
+    for (;;) {
+        for (; now.left > 0; now.step(), ++i) {
+            const bool more = i + R < mine;
+            if (more) __builtin_amdgcn_s_waitcnt(vm_imm((R - 1) * LPS));   // step i is in; R - 1 later ones are on their way
+            else __builtin_amdgcn_s_waitcnt(vm_imm(0));
+            asm volatile("" ::: "memory");
+            step(i, more);
+        }
+        if constexpr (LOG == 0) break;
+#pragma unroll
+        for (int p = 0; p < PT; ++p) close_part<LOG>(now, acc[p], acc_tree[p]);
+        if constexpr (MODE == MODE_COSINE) {
+            close_part<LOG>(now, xx, xx_tree);
+            close_part<LOG>(now, cc, cc_tree);
+        }
+        if (now.last()) break;
+        ++now.part;
+        now.open();
     }
-    __builtin_amdgcn_s_waitcnt(vm_imm(0));
-    asm volatile("" ::: "memory");
-    for (; i < mine; ++i) step(i, false);
 
     __syncthreads();                                       // every wavefront is done with its ring
     if constexpr (MODE == MODE_MLP)
@@ -574,7 +666,7 @@ detect_split_kernel(DetectArgs a)
     }
 }
 
-template <int TW, int HT, int MH, int MODE, int RING, bool STREAM>
+template <int TW, int HT, int MH, int MODE, int RING, bool STREAM, int LOG = 0, int CHUNK = 1>
 hipError_t launch_one(const DetectArgs& a, hipStream_t st)
 {
     constexpr int M = 32 * HT * MH;
@@ -582,27 +674,27 @@ hipError_t launch_one(const DetectArgs& a, hipStream_t st)
     const size_t lds = (size_t)RING * (DT_TOKENS + M) * 128 + (size_t)M * 4 + (size_t)(MH + 1) * DT_TOKENS * 4;
     static DeviceOnce setup;                               // dynamic LDS above 64 KB needs the attribute (per instantiation)
     const hipError_t attr_err = setup.run([&](int) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_kernel<TW, HT, MH, MODE, RING, STREAM>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_kernel<TW, HT, MH, MODE, RING, STREAM, LOG, CHUNK>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned blocks = (unsigned)((a.total + DT_TOKENS - 1) / DT_TOKENS);
-    hipLaunchKernelGGL((detect_kernel<TW, HT, MH, MODE, RING, STREAM>), dim3(blocks), dim3(64 * TW * MH), lds, st, a);
+    hipLaunchKernelGGL((detect_kernel<TW, HT, MH, MODE, RING, STREAM, LOG, CHUNK>), dim3(blocks), dim3(64 * TW * MH), lds, st, a);
     return hipGetLastError();
 }
 
-template <int PT, int NT, int WV, int R, int MODE, bool STREAM>
+template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG = 0, int CHUNK = 1>
 hipError_t launch_split(const DetectArgs& a, hipStream_t st)
 {
     using S = SplitShape<PT, NT, WV, R>;
     static DeviceOnce setup;
     const hipError_t attr_err = setup.run([&](int) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE, STREAM>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, CHUNK>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES);
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned blocks = (unsigned)((a.total + S::POS - 1) / S::POS);
-    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE, STREAM>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
+    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, CHUNK>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
     return hipGetLastError();
 }
 
@@ -610,14 +702,15 @@ hipError_t launch_split(const DetectArgs& a, hipStream_t st)
 // 64 positions, and the sum of these streams is what bounds it (about 12 TB/s over all L2s); a workgroup of the
 // shared form does so for 128 or 256 positions but needs many positions to fill the chip.  So: the smallest tile
 // that gives every compute unit at most one workgroup (16 positions up to 4096, 32 up to 8192, 64 up to 16384), then
-// the shared form where W1's traffic counts.  Measured at d_model 4096, in us, split / shared form (ring of three buffers, of two):
-//   128 units:  8192: 25 / 47;  16384: 34.5 / 61;  20000: 63 / 52, 64;  28672: 66 / 52, 64;  32768: 67 / 54, 66;  40000: 98 / 102, 82;
-//               131072: 254 / 205, 180;  d_model 2048, 20000: 38 / -, 35;  28672: 39.7 / 29.2, 34.8
-//   256 units:  8192: 42 / 64;  16384: 75 / 65;  32768: 147 / 82;  131072: - / 320 (128 positions), 265 (256)
-//   64 units, 64 positions with four wavefronts / 32:  16384: 26.4 / 35;  65536: 95 / 124;  131072: 187 / 245
-//   32 units:   65536: 83;  262144: 315 = 6.8 TB/s
-//   up to 16 concepts (cosine), 32 positions with four wavefronts / 16 with eight:  8000 rows 13.4 / 15.2;  32000: 39.4 / 41.3;
-//               128256: 146 / 164;  d_model 2048, 100000: 59 / -;  d_model 1024, 160000: 47
+// the shared form where W1's traffic counts.  Measured at d_model 4096 where no other is given, launches of a graph over inputs in turn, in us, split /
+// shared form with three buffers / with two:
+//   128 units:  16384: 37 / - / 61;  24000: 64.6 / 52.0 / 65.8;  32768: 70.4 / 54.3 / 69.3;  40000: 98 / 102 / 85;  131072: 254 / 205 / 203;
+//               d_model 2048, 16500: 36.0 / 28.9 / 35.2;  24000: 38.5 / 29.9 / 36.3;  32768: 41.8 / 33.6 / 38.4;
+//               d_model 1024, 16500: 21.3 / 17.5 / 19.6;  24000: 25.0 / 19.3 / 21.4;  32768: 25.9 / 18.0 / 21.3
+//   256 units:  8192: 42 / 64 / -;  16384: 75 / 66 / -;  32768: 147 / 82 / -;  131072: - / 320 (128 positions) / 284 (256)
+//   64 units, 64 positions with four wavefronts / 32:  16384: 29.8 / 36.8;  65536: 108 / 133;  131072: 210 / 256
+//   32 units, 64 positions with eight wavefronts / 32 with four:  16384: 25.9 / 28.5;  65536: 91.8 / 93.4;  262144: 340 = 6.3 TB/s / 346
+//   up to 16 concepts (cosine), 32 positions with four wavefronts:  8000 rows 15.1;  32000: 45.2;  128256: 159;  d_model 2048, 100000: 65
 template <int MODE, bool STREAM>
 hipError_t launch_width(const DetectArgs& a, hipStream_t st)
 {
@@ -626,25 +719,25 @@ hipError_t launch_width(const DetectArgs& a, hipStream_t st)
     // Rows of few steps: fewer wavefronts, so that each has several steps of its own to keep in flight (d_model 1024, 131072
     // positions: 32 units 52 us with four wavefronts, 56 with eight, 64 units 58 with two, 68 with four; d_model 2048: 100 / 108, 108 / 124).
     const bool narrow = a.dm <= 2048;
-    if (MODE == MODE_COSINE && a.wrows <= 16) return launch_split<2, 1, 4, 2, MODE, STREAM>(a, st);
+    if (MODE == MODE_COSINE && a.wrows <= 16) return launch_split<2, 1, 4, 2, MODE, STREAM, 2, 4>(a, st);
     switch (a.m) {
         case 32:
             if (P <= 4096) return launch_split<1, 2, 8, 2, MODE, STREAM>(a, st);
-            if (P <= 8192) return launch_split<2, 2, 4, 2, MODE, STREAM>(a, st);
-            if (narrow && P > 24576) return launch_split<2, 2, 4, 2, MODE, STREAM>(a, st);
-            return launch_split<4, 2, 8, 1, MODE, STREAM>(a, st);
+            if (P <= 8192) return launch_split<2, 2, 4, 2, MODE, STREAM, 2, 2>(a, st);
+            if (narrow && P > 24576) return launch_split<2, 2, 4, 2, MODE, STREAM, 2, 2>(a, st);
+            return launch_split<4, 2, 8, 1, MODE, STREAM, 3, 1>(a, st);
         case 64:
             if (P <= 4096) return launch_split<1, 4, 4, 3, MODE, STREAM>(a, st);
             if (P <= 8192) return launch_split<2, 4, 4, 2, MODE, STREAM>(a, st);
-            if (narrow && P > 24576) return launch_split<4, 4, 2, 2, MODE, STREAM>(a, st);
-            return launch_split<4, 4, 4, 2, MODE, STREAM>(a, st);
+            if (narrow && P > 24576) return launch_split<4, 4, 2, 2, MODE, STREAM, 2, 4>(a, st);
+            return launch_split<4, 4, 4, 2, MODE, STREAM, 2, 1>(a, st);
         case 128:
             if (P <= 4096) return launch_split<1, 8, 4, 2, MODE, STREAM>(a, st);
             if (P <= 8192) return launch_split<2, 8, 4, 1, MODE, STREAM>(a, st);
             if (P <= 64 * cus) return launch_split<4, 8, 4, 1, MODE, STREAM>(a, st);
             // 128 positions per workgroup; three buffers (one workgroup per compute unit) while that is one round of workgroups
-            if (P <= 128 * cus) return launch_one<2, 2, 2, MODE, 3, STREAM>(a, st);
-            return launch_one<2, 2, 2, MODE, 2, STREAM>(a, st);
+            if (P <= 128 * cus) return launch_one<2, 2, 2, MODE, 3, STREAM, 2, 8>(a, st);
+            return launch_one<2, 2, 2, MODE, 2, STREAM, 2, 8>(a, st);
         default:
             if (P <= 4096) return launch_split<1, 16, 4, 1, MODE, STREAM>(a, st);
             if (P <= 8192) return launch_split<2, 16, 4, 1, MODE, STREAM>(a, st);

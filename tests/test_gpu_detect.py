@@ -132,6 +132,20 @@ def test_detect_streamed_rows(n, dm, m):
     _check_decisions(got[:, rows], ref, anchor.cpu().numpy()[:, rows], anchor_B.cpu().numpy()[:, rows], 0.3, True, 15.0, 2.0)
 
 
+@pytest.mark.parametrize("dm", [96, 1056, 2080, 4096, 4704])
+@pytest.mark.parametrize("m", [32, 64, 128, 256])
+def test_equal_rows_get_equal_results(m, dm):
+    # every form, by the number of positions: a row's sums do not depend on where it stands in the call
+    base, W1, W2 = wl.make_detector_inputs(1, 61, dm, m, seed=wl.BASE_SEED + m, p_anchor=0.1, device=DEV)
+    ref = _conf_ref(base, W1, W2)
+    for n in (300, 4097, 8193, 16500, 25000, 40000):
+        at = torch.arange(n, device=DEV) % 61
+        conf, anchor, anchor_B = ta.ta_detect_anchors(base[:, at].contiguous(), W1, W2, ta.Params(), 0.3, True, 2.0)
+        assert _close(conf[:, :61].cpu().numpy(), ref).all(), n
+        for t in (conf, anchor, anchor_B):
+            assert torch.equal(t[0], t[0, :61][at]), (n, t.dtype)
+
+
 def test_detect_rejects_unsupported_shapes():
     prm = ta.Params(n_sink=4, n_recent=4)
     h, W1, W2 = wl.make_detector_inputs(1, 64, 64, 32, device=DEV)
