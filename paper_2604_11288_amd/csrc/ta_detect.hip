@@ -109,15 +109,20 @@ enum { MODE_MLP = 0, MODE_COSINE = 1 };
 // parts 95 / 87 / 85; 131 072 of 2048, 32 units 100 / 88 / 88.  Which chunk is best differs by form: with 4 KB, or 2 KB where W1 counts, between
 // the starts these crowd the channels of the L2 in turn (64 units, 2 KB 235; 128 units, two parts 4 KB apart 400).
 struct Visit {
-    int steps, log, chunk, start, part, at, left;          // at: this step; left: steps of its part, with this one
-    // (workgroup b runs on XCD b mod 8: neighbours of an XCD start at different parts)
-    __device__ __forceinline__ Visit(int n, int l, int c) : steps(n), log(l), chunk(c), start((int)(blockIdx.x >> 3) & ((1 << l) - 1)), part(0) { open(); }
+    int steps, log, chunk, parts, base, start, part, at, left;   // at: this step; left: steps of its part, with this one
+    // The parts [base, base + parts).  (Workgroup b runs on XCD b mod 8: neighbours of an XCD start at different parts.)
+    __device__ __forceinline__ Visit(int n, int l, int c, int of = 1, int share = 0)
+        : steps(n), log(l), chunk(c), parts((1 << l) / of), base(share * parts), start((int)(blockIdx.x >> 3) & (parts - 1)), part(0) { open(); }
+    __device__ __forceinline__ int steps_in(int first, int count) const    // of that many parts that follow each other
+    {
+        const int turn = chunk << log, turns = steps / turn, most = count * chunk, rest = steps - turns * turn - first * chunk;
+        return turns * most + (rest < 0 ? 0 : (rest > most ? most : rest));
+    }
+    __device__ __forceinline__ int total() const { return steps_in(base, parts); }
     __device__ __forceinline__ void open()
     {
-        const int turn = chunk << log, turns = steps / turn;
-        at = (start ^ part) * chunk;
-        const int rest = steps - turns * turn - at;
-        left = turns * chunk + (rest < 0 ? 0 : (rest > chunk ? chunk : rest));
+        at = (base + (start ^ part)) * chunk;
+        left = steps_in(base + (start ^ part), 1);
     }
     __device__ __forceinline__ void step()
     {
@@ -125,7 +130,7 @@ struct Visit {
         --left;
         if (at % chunk == 0) at += (chunk << log) - chunk;
     }
-    __device__ __forceinline__ bool last() const { return part + 1 == 1 << log; }
+    __device__ __forceinline__ bool last() const { return part + 1 == parts; }
     __device__ __forceinline__ void to_full()              // on to a part that has steps left, if there is one
     {
         while (left == 0 && !last()) {
@@ -440,8 +445,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // units, and loading the operand fragments straight into registers, where neighbouring lanes lie in different rows,
 // 40 us), and the partial sums of the WV wavefronts meet once, in LDS, after the last step.
 // PT: 16-position tiles of a workgroup; NT: 16-unit tiles of the hidden layer (concepts); WV wavefronts, each of which
-// contracts every WV-th step of 64 features; R: steps in flight per wavefront; LOG, CHUNK: see Visit
-template <int PT, int NT, int WV, int R>
+// contracts every SHARES-th step of 64 features; R: steps in flight per wavefront; PW: wavefronts that have such a share of the steps together, each
+// half of its parts (2: twice as many requests in flight where the workgroups are few; the sums are those of 1, bit for bit); LOG, CHUNK: see Visit
+template <int PT, int NT, int WV, int R, int PW>
 struct SplitShape {
     static constexpr int POS = 16 * PT, M = 16 * NT, THREADS = 64 * WV;
     static constexpr int STEP_UNITS = (PT + NT) * 128;     // 16-byte units of a step
@@ -450,28 +456,35 @@ struct SplitShape {
     // tiles exchanged per round: as many as the ring's memory holds
     static constexpr int CH = RING_UNITS >= NT * TILE_UNITS ? NT : (RING_UNITS >= NT / 2 * TILE_UNITS ? (NT + 1) / 2 : (NT + 3) / 4);
     static constexpr int UNITS = RING_UNITS > CH * TILE_UNITS ? RING_UNITS : CH * TILE_UNITS;
-    static constexpr int LDS_BYTES = UNITS * 16 + (M + THREADS + WV * M + WV * POS) * 4;
+    static constexpr int NORMS = PW == 2 ? 4 * WV : WV;    // sums of squares per row: the wavefronts', or those of each one's four groups of lanes
+    static constexpr int LDS_BYTES = UNITS * 16 + (M + THREADS + NORMS * M + NORMS * POS) * 4;
 };
 
-template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG, int CHUNK>
+template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG, int CHUNK, int PW>
 __global__ void __launch_bounds__(64 * WV)
 detect_split_kernel(DetectArgs a)
 {
-    using S = SplitShape<PT, NT, WV, R>;
+    using S = SplitShape<PT, NT, WV, R, PW>;
     constexpr int POS = S::POS, M = S::M, THREADS = S::THREADS, LPS = 2 * (PT + NT);
     static_assert((R - 1) * LPS <= 63, "vmcnt range");
     extern __shared__ uint4 s_buf[];                       // step rings, then the partial sums
     float* s_w = reinterpret_cast<float*>(s_buf + S::UNITS);   // output weights, or reciprocal norms of the concepts
     float* s_part = s_w + M;
     float* s_cc = s_part + THREADS;                        // cosine mode: squared norms per wavefront
-    float* s_xx = s_cc + WV * M;
+    float* s_xx = s_cc + S::NORMS * M;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, grp = lane >> 4;
     const int64_t tile0 = (int64_t)blockIdx.x * POS;
     const int nsteps = (a.dm + 63) >> 6;                   // (the last one may be half a step)
-    const int mine = nsteps > wave ? (nsteps - wave + WV - 1) / WV : 0;
+    constexpr int SHARES = WV / PW;                        // wavefront w: every SHARES-th step from step w % SHARES on, parts by w / SHARES
+    constexpr int LOGW = PW == 2 ? LOG - 1 : LOG;
+    const int share = wave % SHARES;
+    Visit ahead(nsteps > share ? (nsteps - share + SHARES - 1) / SHARES : 0, PW == 2 ? LOG : parts_log<LOG>(a.dm), CHUNK, PW, wave / SHARES);
+    const int mine = ahead.total();
+    Visit now = ahead;                                     // the step to work on; ahead: the step to request
+    ahead.to_full();
 
     // A load instruction brings 8 rows x 128 bytes (one line), eight neighbouring lanes per row, chunks XOR-swizzled by row
     uint32_t off[LPS];
@@ -492,12 +505,10 @@ detect_split_kernel(DetectArgs a)
     const char* wbase = reinterpret_cast<const char*>(a.W1);
     uint4* ring = s_buf + wave * (R * S::STEP_UNITS);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint4*)ring;
-    Visit ahead(mine, parts_log<LOG>(a.dm), CHUNK), now = ahead;         // the step to request, the step to work on
-    ahead.to_full();
-    const auto half = [&](const Visit& v) { return 64 * (wave + WV * v.at) + 32 >= a.dm; };
+    const auto half = [&](const Visit& v) { return 64 * (share + SHARES * v.at) + 32 >= a.dm; };
     const auto issue = [&](int i) {
         const uint32_t dst = lds0 + (uint32_t)(i % R) * (S::STEP_UNITS * 16);
-        const size_t at = (size_t)(wave + WV * ahead.at) * 128;
+        const size_t at = (size_t)(share + SHARES * ahead.at) * 128;
         const uint32_t back = half(ahead) ? half_back : 0u;
         ahead.step();
         ahead.to_full();
@@ -519,8 +530,8 @@ detect_split_kernel(DetectArgs a)
     for (int p = 0; p < PT; ++p) xx[p] = 0.0f;
 #pragma unroll
     for (int j = 0; j < NT; ++j) cc[j] = 0.0f;
-    f32x4 acc_tree[PT][LOG ? LOG : 1][NT] = {};
-    float xx_tree[LOG ? LOG : 1][PT] = {}, cc_tree[LOG ? LOG : 1][NT] = {};
+    f32x4 acc_tree[PT][LOGW ? LOGW : 1][NT] = {};
+    float xx_tree[LOGW ? LOGW : 1][PT] = {}, cc_tree[LOGW ? LOGW : 1][NT] = {};
 
 #pragma unroll
     for (int i = 0; i < R; ++i)
@@ -563,12 +574,12 @@ detect_split_kernel(DetectArgs a)
             asm volatile("" ::: "memory");
             step(i, more);
         }
-        if constexpr (LOG == 0) break;
+        if constexpr (LOGW == 0) break;
 #pragma unroll
-        for (int p = 0; p < PT; ++p) close_part<LOG>(now, acc[p], acc_tree[p]);
+        for (int p = 0; p < PT; ++p) close_part<LOGW>(now, acc[p], acc_tree[p]);
         if constexpr (MODE == MODE_COSINE) {
-            close_part<LOG>(now, xx, xx_tree);
-            close_part<LOG>(now, cc, cc_tree);
+            close_part<LOGW>(now, xx, xx_tree);
+            close_part<LOGW>(now, cc, cc_tree);
         }
         if (now.last()) break;
         ++now.part;
@@ -580,26 +591,42 @@ detect_split_kernel(DetectArgs a)
         for (int j = tid; j < M; j += THREADS) s_w[j] = bf16_bits_to_float(a.W2[j]);
     // ---- the wavefronts' partial sums meet in LDS, CH tiles at a time; a thread owns one position and every
     // (THREADS / POS)-th quad of hidden units of each round
+    const auto of_share = [](auto sum, int w) {            // the top of a share's tree is over its wavefronts
+        if constexpr (PW == 2) return sum(w) + sum(w + SHARES);
+        else return sum(w);
+    };
+    const auto squares_of_share = [&](auto sum, int w) {   // (the groups of lanes are added up behind the tree, as the shuffles do)
+        if constexpr (PW == 2) {
+            const auto of = [&](int g) { return sum(g * WV + w) + sum(g * WV + w + SHARES); };
+            return (of(0) + of(1)) + (of(2) + of(3));
+        } else {
+            return sum(w);
+        }
+    };
     if constexpr (MODE == MODE_COSINE) {
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             float c = cc[j];
-            c += __shfl_xor(c, 16);
-            c += __shfl_xor(c, 32);
-            if (grp == 0) s_cc[wave * M + 16 * j + r16] = c;
+            if constexpr (PW == 1) {
+                c += __shfl_xor(c, 16);
+                c += __shfl_xor(c, 32);
+            }
+            if (PW == 2 || grp == 0) s_cc[(PW == 2 ? grp * WV + wave : wave) * M + 16 * j + r16] = c;
         }
 #pragma unroll
         for (int p = 0; p < PT; ++p) {
             float x = xx[p];
-            x += __shfl_xor(x, 16);
-            x += __shfl_xor(x, 32);
-            if (grp == 0) s_xx[wave * POS + 16 * p + r16] = x;
+            if constexpr (PW == 1) {
+                x += __shfl_xor(x, 16);
+                x += __shfl_xor(x, 32);
+            }
+            if (PW == 2 || grp == 0) s_xx[(PW == 2 ? grp * WV + wave : wave) * POS + 16 * p + r16] = x;
         }
         __syncthreads();
         for (int j = tid; j < M; j += THREADS) {
             float c = 0.0f;
 #pragma unroll
-            for (int w = 0; w < WV; ++w) c += s_cc[w * M + j];
+            for (int w = 0; w < SHARES; ++w) c += squares_of_share([&](int v) { return s_cc[v * M + j]; }, w);
             s_w[j] = c > 0.0f ? 1.0f / sqrtf(c) : 0.0f;
         }
     }
@@ -620,14 +647,12 @@ detect_split_kernel(DetectArgs a)
             }
         __syncthreads();
         for (int q = q0; q < 4 * CH; q += THREADS / POS) {
-            float4 z = s_red[q * POS + pos];
+            const auto sum = [&](int w) { return *reinterpret_cast<const f32x4*>(&s_red[(w * CH * 4 + q) * POS + pos]); };
+            f32x4 z = of_share(sum, 0);
 #pragma unroll
-            for (int w = 1; w < WV; ++w) {
-                const float4 v = s_red[(w * CH * 4 + q) * POS + pos];
-                z.x += v.x; z.y += v.y; z.z += v.z; z.w += v.w;
-            }
+            for (int w = 1; w < SHARES; ++w) z += of_share(sum, w);
             const float4 wt = *reinterpret_cast<const float4*>(&s_w[16 * j0 + 4 * q]);
-            const float zs[4] = {z.x, z.y, z.z, z.w}, ws[4] = {wt.x, wt.y, wt.z, wt.w};
+            const float zs[4] = {z[0], z[1], z[2], z[3]}, ws[4] = {wt.x, wt.y, wt.z, wt.w};
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 if constexpr (MODE == MODE_MLP)
@@ -659,7 +684,7 @@ detect_split_kernel(DetectArgs a)
     } else {
         float x2 = 0.0f;
 #pragma unroll
-        for (int w = 0; w < WV; ++w) x2 += s_xx[w * POS + tid];
+        for (int w = 0; w < SHARES; ++w) x2 += squares_of_share([&](int v) { return s_xx[v * POS + tid]; }, w);
         const float sim = past ? 0.0f : (x2 > 0.0f ? out / sqrtf(x2) : 0.0f);
         a.conf[t] = sim;
         a.anchor[t] = sim > a.thr ? 1 : 0;
@@ -683,18 +708,18 @@ hipError_t launch_one(const DetectArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG = 0, int CHUNK = 1>
+template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG = 0, int CHUNK = 1, int PW = 1>
 hipError_t launch_split(const DetectArgs& a, hipStream_t st)
 {
-    using S = SplitShape<PT, NT, WV, R>;
+    using S = SplitShape<PT, NT, WV, R, PW>;
     static DeviceOnce setup;
     const hipError_t attr_err = setup.run([&](int) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, CHUNK>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, CHUNK, PW>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES);
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned blocks = (unsigned)((a.total + S::POS - 1) / S::POS);
-    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, CHUNK>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
+    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, CHUNK, PW>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
     return hipGetLastError();
 }
 
@@ -710,7 +735,8 @@ hipError_t launch_split(const DetectArgs& a, hipStream_t st)
 //   256 units:  8192: 42 / 64 / -;  16384: 75 / 66 / -;  32768: 147 / 82 / -;  131072: - / 320 (128 positions) / 284 (256)
 //   64 units, 64 positions with four wavefronts / 32:  16384: 29.8 / 36.8;  65536: 108 / 133;  131072: 210 / 256
 //   32 units, 64 positions with eight wavefronts / 32 with four:  16384: 25.9 / 28.5;  65536: 91.8 / 93.4;  262144: 340 = 6.3 TB/s / 346
-//   up to 16 concepts (cosine), 32 positions with four wavefronts:  8000 rows 15.1;  32000: 45.2;  128256: 159;  d_model 2048, 100000: 65
+//   up to 16 concepts (cosine), 32 positions with four wavefronts / 16 with eight (two per share of the features):  512 rows 10.5 / 6.9;  4096:
+//               10.8 / 8.8;  6000: 14.0 / 15.3;  8000: 15.1 / 16.5;  32000: 45.2 / 47.6;  128256: 159 / 171;  d_model 2048, 4096: 7.8 / 6.7;  100000: 65 / 86
 template <int MODE, bool STREAM>
 hipError_t launch_width(const DetectArgs& a, hipStream_t st)
 {
@@ -719,7 +745,11 @@ hipError_t launch_width(const DetectArgs& a, hipStream_t st)
     // Rows of few steps: fewer wavefronts, so that each has several steps of its own to keep in flight (d_model 1024, 131072
     // positions: 32 units 52 us with four wavefronts, 56 with eight, 64 units 58 with two, 68 with four; d_model 2048: 100 / 108, 108 / 124).
     const bool narrow = a.dm <= 2048;
-    if (MODE == MODE_COSINE && a.wrows <= 16) return launch_split<2, 1, 4, 2, MODE, STREAM, 2, 4>(a, st);
+    if (MODE == MODE_COSINE && a.wrows <= 16) {            // (both forms of a d_model add up alike: a table's rows and a prompt's get the same results)
+        if (a.dm < 2048) return launch_split<2, 1, 4, 2, MODE, STREAM>(a, st);
+        if (P <= 4096) return launch_split<1, 1, 8, 2, MODE, STREAM, 2, 4, 2>(a, st);
+        return launch_split<2, 1, 4, 2, MODE, STREAM, 2, 4>(a, st);
+    }
     switch (a.m) {
         case 32:
             if (P <= 4096) return launch_split<1, 2, 8, 2, MODE, STREAM>(a, st);

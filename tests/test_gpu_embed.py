@@ -55,14 +55,14 @@ def test_largest_cosine_forms_at_their_limits(E, V):
     _check(sim, anchor, x, C, 0.6)
 
 
-@pytest.mark.parametrize("dm", [96, 1056, 2080, 4096, 4704])
+@pytest.mark.parametrize("dm", [96, 1056, 2048, 2080, 4096, 4704])
 @pytest.mark.parametrize("E", [5, 16, 60, 128, 200])
 def test_equal_rows_get_equal_results(E, dm):
     # every form, by the number of rows: a row's sums do not depend on where it stands in the call, and for up to 16 concepts (one
     # order of summation) nor on how many rows that has
     base, C = wl.make_embedding_inputs(61, dm, E, seed=wl.BASE_SEED + E, p_near=0.5, device=DEV)
     first = None
-    for V in (300, 4097, 8193, 16500, 25000, 40000):
+    for V in (61, 300, 4096, 4097, 8193, 16500, 25000, 40000):
         at = torch.arange(V, device=DEV) % 61
         sim, anchor = ta.ta_embed_anchors(base[at][None], C, 0.6)
         _check(sim[:, :61], anchor[:, :61], base, C, 0.6)
