@@ -124,12 +124,12 @@ def test_whole_pass_with_given_lse():
                         ta.Params(n_sink=4, n_recent=4, alpha=0.0), seq_len=seq)
 
 
-@pytest.mark.parametrize("W", [32, 64])
-@pytest.mark.parametrize("G", [4])
-def test_score_long_chunks_at_every_remainder(W, G):
-    """Chunks of many stages: lengths whose fully visible stages end at every place of a turn of the main loop (four stages), at its start-up and
+@pytest.mark.parametrize("G, W, most, page_size", [(4, 32, 57, 0), (4, 64, 19, 0), (8, 64, 19, 0), (1, 512, 19, 0), (4, 32, 70, 64), (4, 64, 19, 128), (8, 64, 19, 64)])
+def test_score_long_chunks_at_every_remainder(G, W, most, page_size):
+    """Chunks of many stages, 128, 256 and 512 rows (two passes over a chunk; with other rows' limits in each where the window has as many), dense and over pages (of which 64 of a chunk are at hand, longer ones
+    read the table): lengths whose fully visible stages end at every place of a turn of the main loop (four stages), at its start-up and
     in a partial stage, with both sweeps and with the second alone, against float64."""
-    chunks, most = 18, 57 if W == 32 else 19                         # (with 14 units); 64-key stages in a chunk of the longest sequence
+    chunks = 18                                                      # (with 14 units); most: 64-key stages in a chunk of the longest sequence
     lens = [64 * chunks * k - cut for k, cut in zip(range(most, most - 12, -1), (0, 1, 63, 64, 65, 200, 0, 640, 2048, 5, 64, 1000))] + [64 * chunks * 2, 700]
     n, B = max(lens), len(lens)
     g = torch.Generator(device=DEV).manual_seed(W)
@@ -144,6 +144,19 @@ def test_score_long_chunks_at_every_remainder(W, G):
         lse[0, b] = s.logsumexp(1).view(G, W)
         ref[b, :m] = s.softmax(1).sum(0)
     A = torch.full((1, B, 1, n), -1.0, device=DEV)
-    for got in (ta.ta_score(Q, K, ta.Params(), seq_len=seq_len, A=A.clone()), ta.ta_score_lse(Q, K, lse, ta.Params(), seq_len=seq_len, A=A.clone())):
+    if page_size:
+        slots = (n + page_size - 1) // page_size
+        table = torch.randperm(B * slots + 3, generator=torch.Generator().manual_seed(W))[:B * slots].view(B, slots).to(torch.int32).to(DEV)
+        pool = torch.zeros((1, B * slots + 3, page_size, 1, 128), dtype=torch.bfloat16, device=DEV)
+        for b in range(B):
+            rows = torch.zeros((slots * page_size, 128), dtype=torch.bfloat16, device=DEV)
+            rows[:n] = K[0, b, 0]
+            pool[0, table[b].long(), :, 0] = rows.view(slots, page_size, 128)
+        paged = ta.PagedKV(pool, pool, table, page_size, B * slots + 3, pool.stride()[:4], 1, B, 1, n)
+        both = (ta.ta_score_paged(Q, paged, ta.Params(), seq_len=seq_len, A=A.clone()),
+                ta.ta_score_paged(Q, paged, ta.Params(), seq_len=seq_len, lse=lse, A=A.clone()))
+    else:
+        both = ta.ta_score(Q, K, ta.Params(), seq_len=seq_len, A=A.clone()), ta.ta_score_lse(Q, K, lse, ta.Params(), seq_len=seq_len, A=A.clone())
+    for got in both:
         torch.cuda.synchronize()
         assert ((got[0, :, 0].double() - ref).abs() <= 1e-3 * ref.abs() + 1e-7).all()    # the bar of every score
