@@ -602,10 +602,11 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         if constexpr (COLSUM) write_colsum(colsum, s % (2 * FLUSH));
     };
     // Column sums of the stages before `to` that have not been written yet: the row groups' partial sums added up (complete after
-    // the barrier that follows their reduction), FLUSH stages at a time, a stage per wavefront.  (With a store in every stage, by the
-    // first wavefront, that one has more to do than the others, and the wait for its loads waits for the stores among them: one sweep,
-    // us, 192 units of 8192 keys, 256 rows 127.6 / 121.9, 512 of 1500..3001 57.2 / 54.8, 2048 of 2048..16 384 871 / 862, 256 of 16 384
-    // 194.8 / 193.  Most of what the stores cost is the memory's: without any 180, whatever the size of the bursts.)
+    // the barrier that follows their reduction), FLUSH stages at a time - a turn's, four, six in the narrow workgroups - and a stage per
+    // wavefront.  With a store in every stage, by the first wavefront, that one has more to do than the others, and the wait for its loads waits for the
+    // stores among them.  (Measured with bursts of eight stages, before the main loop went by turns: one sweep, us, a store in every stage /
+    // bursts, 192 units of 8192 keys, 256 rows 127.6 / 121.9, 512 of 1500..3001 57.2 / 54.8, 2048 of 2048..16 384 871 / 862, 256 of 16 384
+    // 194.8 / 193; without any stores 180, whatever the size of the bursts: most of what they cost is the memory's.)
     int flushed = 0;
     const auto flush = [&](int to) {
         if constexpr (COLSUM) {
@@ -616,7 +617,7 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 #pragma unroll
                     for (int w = 1; w < RG; ++w) v += s_part[s % (2 * FLUSH)][w][lane];
                     float* dst = &a.A[(size_t)unit * n + key];
-                    *dst = row_base > 0 ? *dst + v : v;    // the same thread wrote it in the pass before
+                    *dst = row_base > 0 ? *dst + v : v;    // (this workgroup's, from the pass before: a barrier lies between them)
                 }
             }
             flushed = to;
@@ -979,10 +980,12 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
     a.nchunks = p.nchunks;
     a.causal = causal;
     a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)lay.d));
-    // The kernels with the main loop of whole turns: from a turn of stages on, for up to 128 rows from chunks of 48.  Two workgroups or more share a
-    // compute unit there and cover each other's waits, the longer code has to be fetched, and it pays for itself later.  (Whole pass, us, without /
-    // with: 8 units of 4096 keys, chunks of 2 stages, 18.37 / 18.5, 512 paged ones of 1500..3001, of up to 47, 139.2 / 139.8, 256 of 4096,
-    // of 32, 144.4 / 144.3; one sweep over 256 of 16 384, of 128, 193 / 188; narrow workgroups 256 of 4096 47.5 / 47.5.)
+    // The kernels with the main loop of whole turns: with more than 128 rows from chunks of 12 stages on, for up to 128 rows from chunks of 48.  Two
+    // workgroups or more share a compute unit there and cover each other's waits, the longer code has to be fetched, and it pays for itself later.  (Whole
+    // pass, us, without / with: 8 units of 4096 keys, chunks of 2 stages, 18.37 / 18.5, 512 paged ones of 1500..3001, of up to 47, 139.2 / 139.8, 256 of 4096,
+    // of 32, 144.4 / 144.3; one sweep over 256 of 16 384, of 128, 193 / 188; narrow workgroups 256 of 4096 47.5 / 47.5.  512 rows, two sweeps: 8 units of
+    // 4096 keys, chunks of 2, 30.5 / 33.3, of 9000, of 5, 42.9 / 48.2, 256 of 700, of 11, 79.0 / 79.8, of 1000, of 16, 104 / 101, of 4096 333 / 299,
+    // although its column sums hold 24 registers of a lane in scratch, 6 without: those of the state between the passes, outside the loop.)
     const int32_t stages = p.chunk_keys / STAGE_KEYS;
     switch (a.rows_pad) {
         // two 32-row tiles per wavefront (one tile per wavefront with twice the wavefronts - four
@@ -996,7 +999,9 @@ hipError_t launch_score(const void* Q, const void* K, const ta_layout& lay, cons
             return launch_rg<4, 2, false, false>(a, p.units, rider, gathered, st);
         // 512 rows: two passes of 256 (eight row groups at once leave 128 registers per lane: spills, 3x slower), in kernels of
         // their own: the pass loop costs the column sums' main loop the registers that keep its two pipes busy (1.5 %)
-        default: return launch_rg<4, 2, true, true>(a, p.units, rider, gathered, st);
+        default:
+            if (stages >= 12) return launch_rg<4, 2, true, true>(a, p.units, rider, gathered, st);
+            return launch_rg<4, 2, true, false>(a, p.units, rider, gathered, st);
     }
 }
 
