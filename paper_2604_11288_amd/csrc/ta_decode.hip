@@ -57,17 +57,6 @@ __device__ __forceinline__ int32_t clamp_page(const SlotPages& pg, int32_t page)
     return page < 0 ? 0 : (page >= pg.num_pages ? pg.num_pages - 1 : page);
 }
 
-// Units whose keys the last-level cache (256 MB) is to hold until the next step, which reads them again: all where they fit, else 192 MB of them - the
-// rest has the streaming hint and passes by.  (us per step, hint everywhere / this: 256 units x 1025 slots 16.6 / 15.9, paged 17.9 / 17.1; 8192 x 101 47.2 / 42.0,
-// paged 54.1 / 45.8; 4096 x 257, 257 MB, 55.3 / 48.6; 6144 x 257 80.2 / 73.5, paged 89.1 / 80.8; 16 384 x 257 201.6 / 197.0, paged 226.4 / 219.7; 2048 x 1025 94.1 / 89.8.  Of more
-// than fit, 256 MB kept instead of 192: 16 384 x 257 206, 15 360 x 129 102.6 / 97.7; all of them: 218, 115.7.)
-constexpr int64_t CACHED_BYTES = int64_t(272) << 20, KEPT_BYTES = int64_t(192) << 20;
-int32_t kept_units(int64_t units, int slots)
-{
-    const int64_t of_unit = (int64_t)slots * 256;
-    return (int32_t)(units * of_unit <= CACHED_BYTES ? units : KEPT_BYTES / of_unit);
-}
-
 // ---- state initialisation -----------------------------------------------------
 constexpr int INIT_ITERS = 2;
 constexpr int INIT_ROWS = DU_THREADS / 16 * INIT_ITERS;    // rows of one of the two tensors per workgroup
@@ -135,10 +124,11 @@ __device__ __forceinline__ void init_slots(const ta_decode_state& st, const Init
 
 // The slot tables, the keys, the values, then the per-sequence arrays.  Rows move as in the compaction: INIT_ROWS consecutive slots of the
 // flat [units][slots] order and one tensor per workgroup, 16 lanes per row, all loads of a lane before its first store, bound by HBM; the slot tables, two
-// dependent loads each, have threads of their own.  Keys that the cache can hold until the first step are stored without the streaming hint
-// (KEEP).  (With the first step, us, both tensors by 64 rows behind their slots' tables / this: 256 units of 1025 slots 69 / 61.3, over pages 71.5 / 62.8; 2048
-// of 65 46 / 41; 4096 of 257 253.6 / 238; 16 384 of 257 970 / 922, over pages 1034 / 993; the slot tables behind the rows 933, keys without the hint where they do not fit 1001.)
-template <bool PAGED, bool KEEP>
+// dependent loads each, have threads of their own.  (us, both tensors by 64 rows behind their slots' tables / this: 256 units of 1025 slots
+// 53.2 / 45.3, over pages 53.9 / 46.1; 64 of 1025 17.5 / 14.4; 8192 of 65 97.7 / 89.5; 4096 of 257 183 / 175; 16 384 of 257 734 / 702.  Keys stored without the
+// streaming hint, for the first step to find in the last-level cache: 44.6, 44.8, 13.2, 85.3, 166.5, 699, but what comes next, in use the model's
+// next pass, then writes them back: a read of 1 GiB behind 4096 of 257 takes 302 us instead of 286.)
+template <bool PAGED>
 __global__ void __launch_bounds__(DU_THREADS)
 decode_init_kernel(ta_decode_state st, InitArgs a, SlotPages pg)
 {
@@ -192,12 +182,7 @@ decode_init_kernel(ta_decode_state st, InitArgs a, SlotPages pg)
     for (int i = 0; i < INIT_ITERS; ++i) {
         if (!live[i]) continue;
         const u32x4 row = slot[i] < st.K && slot[i] < count[i] ? v[i] : zero;
-        if (KEEP && !values) {
-            out[to[i]] = row;
-            asm volatile("");                              // (else the compiler makes one store of the two, without the hint)
-        } else {
-            __builtin_nontemporal_store(row, &out[to[i]]);
-        }
+        __builtin_nontemporal_store(row, &out[to[i]]);
     }
 }
 
@@ -318,7 +303,6 @@ struct UnitArgs {
     int32_t group;                                         // query heads per KV head
     Divider by_hkv, by_batch;
     float decay;
-    int32_t keep;                                          // workgroups before this one load keys without the streaming hint
 };
 
 // A step as one launch (FUSED below): what its sequence part works with, and the words in which the workgroups of a sequence count
@@ -607,7 +591,7 @@ __device__ __forceinline__ uint8_t vouchers_of_slots(const ta_decode_state& st, 
 // load of flags each.  Vouchers it needs only where no plain slot is left to evict: any plain slot ranks below every
 // sponsored one, and its own voucher is zero.  It counts itself in once it has read what the append overwrites, and the last workgroup
 // of a sequence to do so appends.
-template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES, int SPL, bool KEEP, bool FUSED = false>
+template <int GH, bool PAGED, bool SCORED, bool SMALL, int DT_RING, int WAVES, int SPL, bool FUSED = false>
 __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& pg, const StepArgs* fs = nullptr)
 {
     extern __shared__ float s_dyn[];
@@ -674,18 +658,12 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
     const int ntiles = (((slots + 15) >> 4) - wave + WAVES - 1) / WAVES;
     const auto tile_of = [&](int tile) { return wave + WAVES * tile; };
     uint4 qf[4], tiles[DT_RING][4];                        // DT_RING tiles in flight
-    // Key rows are read once per step.  Those that the last-level cache can hold until the next step (KEEP: the rule beside kept_units) are loaded
-    // as they are; the others have the non-temporal hint, which keeps them from displacing those, the slot tables, the accumulated attention and the
-    // per-sequence arrays (231 -> 210 us on 16 384 units).
-    const auto load_key = [&](const uint4* from) -> uint4 {
-        if constexpr (KEEP) {
-            return *from;
-        } else {
-            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-            const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(from));
-            return make_uint4(v.x, v.y, v.z, v.w);
-        }
-    };
+    // Key rows are read once per step: the non-temporal hint keeps them from displacing the slot tables,
+    // the accumulated attention and the per-sequence arrays in the caches (231 -> 210 us on 16 384 units).
+    // Also where they would fit the last-level cache: without the hint they stay there from step to step if nothing comes between, but in use
+    // the model's forward pass does, and then they cost what they displace (us per step, with the hint / up to 272 MB of keys without, behind a read of
+    // 1 GiB: 256 units x 1025 slots 17.4 / 18.1, 1024 x 257 17.6 / 18.9, 8192 x 101 48.4 / 53.0, 4096 x 257 55.8 / 60.0, 2048 x 1025 93.0 / 96.9; back to
+    // back: 15.0 / 16.5, 16.6 / 17.3, 48.1 / 43.7, 54.6 / 48.0, 92.6 / 88.7).
     const auto load_tile = [&](int tile, uint4 (&dst)[4]) {
         if (!PAGED) {                                      // dense unit: one uniform base, a 32-bit byte offset per lane
             const char* base = reinterpret_cast<const char*>(Kc);
@@ -693,7 +671,11 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
             for (int t = 0; t < 4; ++t) {
                 int row = tile_of(tile) * 16 + 4 * t + grp;
                 row = row < slots ? row : slots - 1;       // past the last slot: a valid row, masked at the store
-                dst[t] = load_key(reinterpret_cast<const uint4*>(base + (uint32_t)(row * 256 + sub * 16)));
+                {
+                    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+                    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (uint32_t)(row * 256 + sub * 16)));
+                    dst[t] = make_uint4(v.x, v.y, v.z, v.w);
+                }
             }
             return;
         }
@@ -701,7 +683,9 @@ __device__ __forceinline__ void decode_unit(const ta_decode_state& st, const Uni
         for (int t = 0; t < 4; ++t) {
             int row = tile_of(tile) * 16 + 4 * t + grp;
             row = row < slots ? row : slots - 1;
-            dst[t] = load_key(&Kc[row_at(row) + sub]);
+            typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+            const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(&Kc[row_at(row) + sub]));
+            dst[t] = make_uint4(v.x, v.y, v.z, v.w);
         }
     };
     if (SCORED) {
@@ -1179,64 +1163,50 @@ bool positions_first(bool scored, const ta_decode_state& st, UnitForm f) { retur
 // registers let more of them do so (six, us per step: 1025 slots, 256 units 21.0 -> 19.8, 1024 units 56.6 -> 52.7; 1501
 // slots, 1024 units 94.4 -> 75.4).  One wavefront per unit: three at four wavefronts per SIMD; paged slots need
 // more registers for their addresses: four at three wavefronts per SIMD instead of spilling.
-// How a launch's key loads go: all with the streaming hint, none, or none in the workgroups before UnitArgs::keep.  (A load whose hint is decided at run
-// time loses it; the third has the unit's code twice, which costs a step of one launch 0.5 us and one over pages 1.5, so the others have kernels of their own.)
-enum { STREAM_KEYS, KEEP_KEYS, KEEP_SOME };
-
-template <int GH, bool PAGED, bool SCORED, bool SMALL, int WAVES, int SPL, int KEYS>
+template <int GH, bool PAGED, bool SCORED, bool SMALL, int WAVES, int SPL>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu((WAVES > 1 ? 2 : PAGED ? 3 : 4))))
 decode_unit_kernel(ta_decode_state st, UnitArgs a, SlotPages pg)
 {
-    constexpr int RING = WAVES > 1 ? 2 : PAGED ? 4 : 3;
-    if (KEYS == KEEP_KEYS || (KEYS == KEEP_SOME && (int32_t)blockIdx.x < a.keep)) decode_unit<GH, PAGED, SCORED, SMALL, RING, WAVES, SPL, true>(st, a, pg);
-    else decode_unit<GH, PAGED, SCORED, SMALL, RING, WAVES, SPL, false>(st, a, pg);
+    decode_unit<GH, PAGED, SCORED, SMALL, (WAVES > 1 ? 2 : PAGED ? 4 : 3), WAVES, SPL>(st, a, pg);
 }
 
 // Paged slots: at most 128 registers (none of them in scratch), so that two workgroups of eight wavefronts share a compute unit as
 // those of the two-launch form do: with 131 to 135 they did not, and where units are more than compute units the step fell behind two
 // launches (us per step, 135 / 128 registers / two launches: 320 units x 1135 slots 29.3 / 25.7 / 28.0, 512 x 1025 33.7 / 30.0 / 31.5, 1024 x 1025
 // 63.2 / 55.0 / 55.3, 256 x 1025 17.9 / 17.8 / 20.0; from a graph, with none in scratch, 25.1, 28.0, 51.4, 16.3 / 27.0, 29.5, 53.0, 18.0).
-template <int GH, bool PAGED, bool SCORED, int WAVES, int SPL, int KEYS>
+template <int GH, bool PAGED, bool SCORED, int WAVES, int SPL>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(PAGED && SCORED ? 4 : 2)))
 decode_step_kernel(ta_decode_state st, UnitArgs a, SlotPages pg, StepArgs f)
 {
-    if (KEYS == KEEP_KEYS || (KEYS == KEEP_SOME && (int32_t)blockIdx.x < a.keep)) decode_unit<GH, PAGED, SCORED, true, 2, WAVES, SPL, true, true>(st, a, pg, &f);
-    else decode_unit<GH, PAGED, SCORED, true, 2, WAVES, SPL, false, true>(st, a, pg, &f);
+    decode_unit<GH, PAGED, SCORED, true, 2, WAVES, SPL, true>(st, a, pg, &f);
 }
 
 using UnitKernel = void (*)(ta_decode_state, UnitArgs, SlotPages);
 using StepKernel = void (*)(ta_decode_state, UnitArgs, SlotPages, StepArgs);
 
-template <int GH, bool PAGED, bool SCORED, int KEYS>
-StepKernel step_kernel_of(UnitForm f)
+template <int GH, bool PAGED, bool SCORED>
+StepKernel step_kernel(UnitForm f)
 {
     switch (f.waves * 8 + f.spl) {
-        case 2 * 8 + 2: return decode_step_kernel<GH, PAGED, SCORED, 2, 2, KEYS>;
-        case 4 * 8 + 2: return decode_step_kernel<GH, PAGED, SCORED, 4, 2, KEYS>;
-        case 4 * 8 + 3: return decode_step_kernel<GH, PAGED, SCORED, 4, 3, KEYS>;
-        case 8 * 8 + 3: return decode_step_kernel<GH, PAGED, SCORED, 8, 3, KEYS>;
-        default: return decode_step_kernel<GH, PAGED, SCORED, 8, 4, KEYS>;
+        case 2 * 8 + 2: return decode_step_kernel<GH, PAGED, SCORED, 2, 2>;
+        case 4 * 8 + 2: return decode_step_kernel<GH, PAGED, SCORED, 4, 2>;
+        case 4 * 8 + 3: return decode_step_kernel<GH, PAGED, SCORED, 4, 3>;
+        case 8 * 8 + 3: return decode_step_kernel<GH, PAGED, SCORED, 8, 3>;
+        default: return decode_step_kernel<GH, PAGED, SCORED, 8, 4>;
     }
-}
-
-template <int GH, bool PAGED, bool SCORED>
-StepKernel step_kernel(UnitForm f, bool all_kept)
-{
-    if constexpr (!SCORED) return step_kernel_of<GH, PAGED, false, STREAM_KEYS>(f);      // (no keys)
-    else return all_kept ? step_kernel_of<GH, PAGED, true, KEEP_KEYS>(f) : step_kernel_of<GH, PAGED, true, (PAGED ? STREAM_KEYS : KEEP_SOME)>(f);
 }
 
 template <int GH, bool PAGED>
 UnitKernel unit_kernel(bool scored, UnitForm f)
 {
-    if (!scored) return f.spl ? decode_unit_kernel<GH, PAGED, false, true, 1, LOOP_SPL, STREAM_KEYS> : decode_unit_kernel<GH, PAGED, false, false, 1, LOOP_SPL, STREAM_KEYS>;
+    if (!scored) return f.spl ? decode_unit_kernel<GH, PAGED, false, true, 1, LOOP_SPL> : decode_unit_kernel<GH, PAGED, false, false, 1, LOOP_SPL>;
     switch (f.waves * 8 + f.spl) {
-        case 1 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 1, 2, KEEP_SOME>;
-        case 2 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 2, 2, KEEP_SOME>;
-        case 4 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 4, 2, KEEP_SOME>;
-        case 4 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 4, 3, KEEP_SOME>;
-        case 8 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 8, 3, KEEP_SOME>;
-        default: return decode_unit_kernel<GH, PAGED, true, true, 8, 4, KEEP_SOME>;
+        case 1 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 1, 2>;
+        case 2 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 2, 2>;
+        case 4 * 8 + 2: return decode_unit_kernel<GH, PAGED, true, true, 4, 2>;
+        case 4 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 4, 3>;
+        case 8 * 8 + 3: return decode_unit_kernel<GH, PAGED, true, true, 8, 3>;
+        default: return decode_unit_kernel<GH, PAGED, true, true, 8, 4>;
     }
 }
 
@@ -1275,8 +1245,7 @@ hipError_t unit_attributes()
             if (e == hipSuccess)
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     for (const UnitForm f : {UnitForm{2, 2}, UnitForm{4, 2}, UnitForm{4, 3}, UnitForm{8, 3}, UnitForm{8, 4}})
-        for (const StepKernel k : {step_kernel<GH, false, true>(f, false), step_kernel<GH, true, true>(f, false), step_kernel<GH, false, true>(f, true),
-                                   step_kernel<GH, true, true>(f, true)})
+        for (const StepKernel k : {step_kernel<GH, false, true>(f), step_kernel<GH, true, true>(f)})
             if (e == hipSuccess)
                 e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     return e;
@@ -1288,9 +1257,8 @@ void launch_unit(const ta_decode_state& st, const UnitArgs& a, const SlotPages& 
 {
     if (one) {
         // (how many heads a group has is nothing to a unit without an attention term)
-        const bool all = a.keep >= one->lead + a.units;
-        const StepKernel kernel = a.alpha != 0.0f ? (st.pages ? step_kernel<GH, true, true>(f, all) : step_kernel<GH, false, true>(f, all))
-                                                  : (st.pages ? step_kernel<4, true, false>(f, all) : step_kernel<4, false, false>(f, all));
+        const StepKernel kernel = a.alpha != 0.0f ? (st.pages ? step_kernel<GH, true, true>(f) : step_kernel<GH, false, true>(f))
+                                                  : (st.pages ? step_kernel<4, true, false>(f) : step_kernel<4, false, false>(f));
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * f.waves), lds, s, st, a, pg, *one);
         return;
     }
@@ -1337,11 +1305,8 @@ hipError_t launch_decode_init(const ta_decode_state& st, const int32_t* tok, con
     a.seq_blocks = (int64_t)((st.cap + DU_THREADS - 1) / DU_THREADS) * st.batch;
     const GridLines grid(a.slot_blocks + 2 * a.row_blocks + a.seq_blocks);
     const SlotPages pg = slot_pages(st);
-    const int64_t units = (int64_t)st.layers * st.batch * st.hkv;
-    const bool keep = A && kept_units(units, st.K + 1) == units;         // (without scores no step reads the keys)
-    const auto kernel = st.pages ? (keep ? decode_init_kernel<true, true> : decode_init_kernel<true, false>)
-                                 : (keep ? decode_init_kernel<false, true> : decode_init_kernel<false, false>);
-    hipLaunchKernelGGL(kernel, dim3(grid.x, grid.lines), dim3(DU_THREADS), 0, s, st, a, pg);
+    if (st.pages) hipLaunchKernelGGL(decode_init_kernel<true>, dim3(grid.x, grid.lines), dim3(DU_THREADS), 0, s, st, a, pg);
+    else hipLaunchKernelGGL(decode_init_kernel<false>, dim3(grid.x, grid.lines), dim3(DU_THREADS), 0, s, st, a, pg);
     return hipGetLastError();
 }
 
@@ -1382,7 +1347,6 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
     a.by_hkv = divider((uint32_t)st.hkv);
     a.by_batch = divider((uint32_t)st.batch);
     a.decay = prm.budget_decay;
-    a.keep = kept_units(units, slots);
     lds_floats += page_list;
     if (one && lds_floats < 4 + NEAR_SPAN + (size_t)TILE_PER * 64 * form.waves) lds_floats = 4 + NEAR_SPAN + (size_t)TILE_PER * 64 * form.waves;
     const size_t lds = lds_floats * sizeof(float);
@@ -1399,7 +1363,6 @@ hipError_t launch_decode_step(const ta_decode_state& st, const int32_t* new_tok,
         const uint64_t grid = (uint64_t)units + (uint64_t)sa.tiles * (uint64_t)st.batch;
         if (grid > 0x7FFFFFFFull) return hipErrorInvalidValue;
         sa.lead = positions_first(scored, st, form) ? (int32_t)(grid - units) : 0;
-        a.keep += sa.lead;
         sa.new_tok = new_tok;
         sa.sync = sync;
         sa.per_seq = per_seq;

@@ -153,7 +153,7 @@ def test_budgets_decay_once_in_every_tile(n, K):
 
 @pytest.mark.parametrize("layers,K,page_size", [(16, 279, 0), (16, 279, 16), (20, 220, 0), (20, 220, 16)])
 def test_more_keys_than_the_cache_keeps(layers, K, page_size):
-    """One launch and two over keys of more than 272 MB, part of which has the streaming hint: each layer's units end as they do in a state of that
+    """One launch and two over keys of more than 272 MB, which the last-level cache does not hold: each layer's units end as they do in a state of that
     layer alone, bit for bit."""
     batch, hq, hkv, n = 32, 16, 8, 400
     prm = ta.Params()
@@ -162,7 +162,7 @@ def test_more_keys_than_the_cache_keeps(layers, K, page_size):
     assert layers * batch * hkv * (K + 1) * 256 > 272 << 20
     of_layer = ("pos", "A", "Kc", "Vc")
     alone = {}
-    for l in (0, 10, 11, layers - 1):                             # the first, those around the last that the cache is to hold, the last
+    for l in (0, 10, 11, layers - 1):                             # the first, those around the cache's size, the last
         pages = None
         if page_size:
             p = big.pages
