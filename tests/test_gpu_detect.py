@@ -120,7 +120,7 @@ def test_detect_forms_at_their_limits(m, n):
 @pytest.mark.parametrize("m", [32, 64, 128, 256])
 @pytest.mark.parametrize("n, dm", [(17000, 2080), (33600, 1056)])
 def test_detect_streamed_rows(n, dm, m):
-    # 64 MiB of hidden states and more (streaming loads), steps that start elsewhere in every workgroup, the last one half a step
+    # 64 MiB of hidden states and more (streaming loads), steps in parts that workgroups visit in different orders, the last step half a step
     assert n * dm * 2 >= 64 << 20
     h, W1, W2 = wl.make_detector_inputs(1, n, dm, m, seed=wl.BASE_SEED + n + m, p_anchor=0.1, device=DEV)
     conf, anchor, anchor_B = ta.ta_detect_anchors(h, W1, W2, ta.Params(), 0.3, True, 2.0)
@@ -130,6 +130,22 @@ def test_detect_streamed_rows(n, dm, m):
     got = conf.cpu().numpy()
     assert _close(got[:, rows], ref).all(), np.abs(got[:, rows] - ref).max()
     _check_decisions(got[:, rows], ref, anchor.cpu().numpy()[:, rows], anchor_B.cpu().numpy()[:, rows], 0.3, True, 15.0, 2.0)
+
+
+@pytest.mark.parametrize("m", [32, 64, 128, 256])
+def test_detect_streamed_strided_rows_of_unequal_lengths(m):
+    n, dm = 17000, 2080
+    h, W1, W2 = wl.make_detector_inputs(2, n // 2, dm, m, seed=wl.BASE_SEED + m, p_anchor=0.1, device=DEV, row_stride=dm + 32)
+    assert h.stride(1) == dm + 32 and n * dm * 2 >= 64 << 20
+    seq_len = np.array([n // 2 - 41, n // 2], np.int32)
+    conf, anchor, anchor_B = ta.ta_detect_anchors(h, W1, W2, ta.Params(), 0.3, True, 2.0, seq_len=_dev(seq_len))
+    torch.cuda.synchronize()
+    conf, anchor, anchor_B = conf.cpu().numpy(), anchor.cpu().numpy(), anchor_B.cpu().numpy()
+    assert not conf[0, seq_len[0]:].any() and not anchor[0, seq_len[0]:].any() and not anchor_B[0, seq_len[0]:].any()
+    rows = np.concatenate([np.arange(0, 70), np.arange(n // 2 - 111, n // 2 - 41)])
+    ref = _conf_ref(h[:, _dev(rows)], W1, W2)
+    assert _close(conf[:, rows], ref).all(), np.abs(conf[:, rows] - ref).max()
+    _check_decisions(conf[:, rows], ref, anchor[:, rows], anchor_B[:, rows], 0.3, True, 15.0, 2.0)
 
 
 @pytest.mark.parametrize("dm", [96, 1056, 2080, 4096, 4704])

@@ -82,6 +82,21 @@ def test_wide_rows_strided_and_ragged_sequences():
     _check(sim, anchor, x, C, 0.5, valid=valid)
 
 
+@pytest.mark.parametrize("E", [10, 60, 128, 200])
+@pytest.mark.parametrize("n, dm", [(17000, 2080), (33600, 1056)])
+def test_streamed_rows(n, dm, E):
+    # 64 MiB of rows and more (streaming loads), apart by more than their width, in two sequences of unequal lengths; the last step is half a step
+    assert n * dm * 2 >= 64 << 20
+    x, C = wl.make_embedding_inputs(n, dm, E, seed=wl.BASE_SEED + n + E, p_near=0.2, device=DEV, row_stride=dm + 32)
+    seq_len = np.array([n // 2, n // 2 - 37], np.int32)
+    sim, anchor = ta.ta_embed_anchors(x.view(2, n // 2, dm), C, 0.6, seq_len=_dev(seq_len))
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(0, 70), np.arange(n // 2 - 70, n // 2 + 70), np.arange(n - 70, n)]))
+    valid = (np.arange(n // 2)[None, :] < seq_len[:, None]).reshape(-1)[rows]
+    at = _dev(rows)
+    _check(sim.view(-1)[at], anchor.view(-1)[at], x[at], C, 0.6, valid=valid)
+
+
 def test_degenerate_vectors():
     dm = 64
     rng = np.random.default_rng(3)
