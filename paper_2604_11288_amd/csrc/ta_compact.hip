@@ -3,11 +3,15 @@
 // step).  Pure data movement, bound by HBM.
 //
 // A 256-byte row (d = 128 bf16) is moved by 16 lanes with one 16-byte load and one 16-byte store each, two rows in flight
-// per lane.  A workgroup takes 32 consecutive output rows of one unit and one of the two tensors: the first half of the launch
+// per lane.  A workgroup takes 32 consecutive rows of the flat [units][K] order and one of the two tensors: the first half of the launch
 // moves the keys, the second the values.  The memory's changes between reading and writing bound it, and these cost
-// least where few places are open at a time.  (us, 64 rows of both tensors per workgroup / this: 256 units x 1024 rows 46.6 / 44.2,
-// 1024 x 512 95 / 90, in one run of rows 96.5 / 83.3 = 6.4 TB/s read and written, 1024 x 777 141.5 / 132, 4096 x 100 80.8 / 73.4; one
-// tensor, 64 rows of 256 threads 45.5, 92.7, 88.8, 136.5, 76.5; 16 rows of 128 threads 43.9, 89.4, 85, 132.9, 69.7, but 2048 x 20 11.0 for 9.3.)
+// least where few places are open at a time.  (us, 64 rows of both tensors of one unit per workgroup / this: 256 units x 1000 rows 47.6 / 43.9,
+// 1024 x 512 94.6 / 88.3 = 6.1 TB/s read and written, 8192 x 200 306 / 270, over pages 329 / 286; one or four rows in flight per lane 49.8 and 45.8, 101 and
+// 91.8, 301 and 278.)
+// By flat rows, as units alone left the last workgroup of each with what does not fill it, half of them all but empty
+// at 33 rows: 32 rows of one unit per workgroup / this, 16 384 x 33 119 / 90, over pages 153 / 97, x 16 over pages 68 / 50, x 4 27.7 / 14.5, 65 536 x 8 over
+// pages 201 / 94, 2048 x 40 19.4 / 17.1; 32 rows of one unit take as long as before, 64 x 1024 13.2 / 13.3, 16 384 x 64 170 / 170, and some 0.3 us more with
+// one list for all units.  (Workgroups that lie within a unit in code of their own, with what follows from the unit uniform: 2 to 4 % slower.)
 #include "ta_gather.h"
 
 namespace ta {
@@ -24,47 +28,52 @@ compact_kernel(CompactArgs a)
 {
     const uint32_t block = blockIdx.z * GRID_LINE + blockIdx.x;
     if (block >= a.blocks) return;
-    const int32_t unit = (int32_t)divide(block, a.by_blocks);
-    const int32_t blk = (int32_t)block - unit * a.blocks_per_unit;
     const bool values = blockIdx.y != 0;
-    const int32_t pair = (int32_t)divide((uint32_t)unit, a.by_hkv), h = unit - pair * a.hkv;
-    const int32_t l = (int32_t)divide((uint32_t)pair, a.by_batch), b = pair - l * a.batch;
-    const int32_t sel = a.idx_shared ? b : unit;
+    const int64_t row0 = (int64_t)block * ROWS_PER_BLOCK;
+    const int32_t unit0 = a.rows <= 0x7FFFFFFF ? (int32_t)divide((uint32_t)row0, a.by_K) : (int32_t)(row0 / a.K);   // uniform
+    const int32_t slot0 = (int32_t)(row0 - (int64_t)unit0 * a.K);
     const int lane16 = threadIdx.x & 15;
-    const int32_t row0 = blk * ROWS_PER_BLOCK + (int32_t)(threadIdx.x >> 4);
-    const int32_t* idx = a.idx + (size_t)sel * (size_t)a.K;
-    int32_t p[COMPACT_ITERS];
+    int32_t unit[COMPACT_ITERS], r[COMPACT_ITERS], p[COMPACT_ITERS], count[COMPACT_ITERS];
+    int32_t h[COMPACT_ITERS], b[COMPACT_ITERS], l[COMPACT_ITERS];
 #pragma unroll
-    for (int j = 0; j < COMPACT_ITERS; ++j) {              // requested together with the count
-        const int32_t r = row0 + j * ROWS_PER_ITER;
-        p[j] = idx[r < a.K ? r : a.K - 1];
+    for (int j = 0; j < COMPACT_ITERS; ++j) {
+        const int32_t off = (int32_t)(threadIdx.x >> 4) + j * ROWS_PER_ITER, s = slot0 + off;
+        const bool in = row0 + off < a.rows;
+        const int32_t du = (int32_t)divide((uint32_t)s, a.by_K);
+        unit[j] = in ? unit0 + du : unit0;
+        r[j] = in ? s - du * a.K : 0;
+        const int32_t pair = (int32_t)divide((uint32_t)unit[j], a.by_hkv);
+        h[j] = unit[j] - pair * a.hkv;
+        l[j] = (int32_t)divide((uint32_t)pair, a.by_batch);
+        b[j] = pair - l[j] * a.batch;
+        const int32_t sel = a.idx_shared ? b[j] : unit[j];
+        p[j] = a.idx[(size_t)sel * (size_t)a.K + r[j]];
+        count[j] = in ? a.cnt[sel] : 0;
     }
-    int32_t cnt = a.cnt[sel];
-    cnt = cnt > a.K ? a.K : cnt;
-    if (blk * ROWS_PER_BLOCK >= cnt) return;              // whole block past the retained rows
-    const RowSource<PAGED, LAYERED> rows(a, l, b, h, lane16);
-    const u32x4* in = reinterpret_cast<const u32x4*>(LAYERED ? global_ptr(values ? a.Vin_l[l] : a.Kin_l[l]) : (values ? a.Vin : a.Kin));
-    u32x4* out = reinterpret_cast<u32x4*>(LAYERED ? global_ptr(values ? a.Vout_l[l] : a.Kout_l[l]) : (values ? a.Vout : a.Kout));
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < COMPACT_ITERS; ++j) any = any || r[j] < count[j];
+    if (__ballot(any) == 0ull) return;                     // the wavefront's rows are all past the retained ones
     u32x4 v[COMPACT_ITERS];
 #pragma unroll
     for (int j = 0; j < COMPACT_ITERS; ++j) {
-        const int32_t r = row0 + j * ROWS_PER_ITER;        // (past the last row: an index within the tensor, not stored)
-        const int32_t q = r < cnt ? p[j] : p[0];
+        const RowSource<PAGED, LAYERED> rows(a, l[j], b[j], h[j], lane16);
+        const u32x4* in = reinterpret_cast<const u32x4*>(LAYERED ? global_ptr(values ? a.Vin_l[l[j]] : a.Kin_l[l[j]]) : (values ? a.Vin : a.Kin));
+        const int32_t q = r[j] < count[j] ? p[j] : 0;      // (past the retained rows: a row of the tensor, not stored)
         v[j] = __builtin_nontemporal_load(&in[rows(q < 0 ? 0 : (q >= a.n ? a.n - 1 : q))]);
     }
     // The compacted rows are not read again by this pass: streaming stores keep them from
     // lingering in the caches as dirty lines that the next kernel's reads would have to evict.
-    const int64_t out_base = (int64_t)(LAYERED ? unit - l * a.hkv * a.batch : unit) * a.K * 16 + lane16;
 #pragma unroll
     for (int j = 0; j < COMPACT_ITERS; ++j) {
-        const int32_t r = row0 + j * ROWS_PER_ITER;
-        if (r >= cnt) continue;
-        int64_t off = out_base + (int64_t)r * 16;
+        if (r[j] >= count[j]) continue;
+        u32x4* out = reinterpret_cast<u32x4*>(LAYERED ? global_ptr(values ? a.Vout_l[l[j]] : a.Kout_l[l[j]]) : (values ? a.Vout : a.Kout));
+        int64_t off = ((int64_t)(LAYERED ? unit[j] - l[j] * a.hkv * a.batch : unit[j]) * a.K + r[j]) * 16 + lane16;
         if (DST_PAGED) {
-            const int32_t slot = r / a.d_page_size;
-            int32_t page = a.d_table[(size_t)b * a.d_max_pages + slot];
+            const int32_t slot = r[j] / a.d_page_size;
+            int32_t page = a.d_table[(size_t)b[j] * a.d_max_pages + slot];
             page = page < 0 ? 0 : (page >= a.d_num_pages ? a.d_num_pages - 1 : page);
-            off = l * a.d_layer + (int64_t)page * a.d_page + (int64_t)(r - slot * a.d_page_size) * a.d_pos + h * a.d_head + lane16;
+            off = l[j] * a.d_layer + (int64_t)page * a.d_page + (int64_t)(r[j] - slot * a.d_page_size) * a.d_pos + h[j] * a.d_head + lane16;
         }
         __builtin_nontemporal_store(v[j], &out[off]);
     }
@@ -164,9 +173,9 @@ CompactArgs make_compact_args(const void* Kin, const void* Vin, const int32_t* i
     a.n = lay.n;
     a.K = K;
     a.idx_shared = idx_shared;
-    a.blocks_per_unit = (K + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
-    a.blocks = (uint32_t)((int64_t)lay.layers * lay.batch * lay.hkv * a.blocks_per_unit);
-    a.by_blocks = divider((uint32_t)a.blocks_per_unit);
+    a.rows = (int64_t)lay.layers * lay.batch * lay.hkv * K;
+    a.blocks = (uint32_t)((a.rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK);
+    a.by_K = divider((uint32_t)K);
     a.by_hkv = divider((uint32_t)lay.hkv);
     a.by_batch = divider((uint32_t)lay.batch);
     return a;
@@ -178,7 +187,7 @@ hipError_t launch_compact(const void* Kin, const void* Vin, const int32_t* idx, 
                           const ta_paged_kv* dst_pg)
 {
     const CompactArgs a = make_compact_args(Kin, Vin, idx, cnt, lay, K, idx_shared, Kout, Vout, pg, lp, dst_pg);
-    const int64_t blocks = (int64_t)lay.layers * lay.batch * lay.hkv * a.blocks_per_unit;
+    const int64_t blocks = (a.rows + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK;
     if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;              // (Divider)
     const GridLines lines(blocks);
     const dim3 grid(lines.x, 2, lines.lines), block(COMPACT_THREADS);

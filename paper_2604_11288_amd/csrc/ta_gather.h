@@ -17,9 +17,9 @@ struct CompactArgs {
     int64_t s_layer, s_batch, s_head, s_pos;   // input strides in 16-byte units
     int32_t batch, hkv, n, K;
     int32_t idx_shared;
-    int32_t blocks_per_unit;
-    uint32_t blocks;                           // of either tensor
-    Divider by_blocks, by_hkv, by_batch;
+    int64_t rows;                              // units * K, of either tensor
+    uint32_t blocks;
+    Divider by_K, by_hkv, by_batch;
     // paged input: rows are addressed through the block table (s_batch unused, s_page per page)
     const int32_t* table;
     int64_t s_page;

@@ -72,13 +72,13 @@ def test_layers_scored_pass_equals_stacked_pass_and_oracle(n, batch, layers, K, 
         assert np.array_equal(wl.bf16_bits(got.Vout[l][b, g, :c]), ora.compact(v_rows, idx_ref))
 
 
-def test_layers_attention_free_pass_shares_one_retained_set():
+@pytest.mark.parametrize("K", [128, 77])         # (77: workgroups of the compaction reach from one layer's rows into the next's)
+def test_layers_attention_free_pass_shares_one_retained_set(K):
     w = wl.scaled(wl.CONFIGS["c3_ta_fast"], layers=4, batch=3, n=3000, hkv=2, ragged=(100, 3000), planted=8)
     td = wl.make_tokens(w)
     _, Kc, Vc = wl.make_qkv(w, device=DEV)
     prm = ta.Params(n_sink=w.n_sink, n_recent=w.n_recent, alpha=0.0)
     tok, seq = _dev(td.tok), _dev(td.seq_len)
-    K = 128
     ref = ta.ta_evict(tok, td.tab_ids, td.tab_len, None, Kc, Vc, K, prm, seq_len=seq)
     got = ta.ta_evict_layers(tok, td.tab_ids, td.tab_len, None, _scatter(Kc), _scatter(Vc), K, prm, seq_len=seq)
     torch.cuda.synchronize()

@@ -428,8 +428,53 @@ def test_compact_bit_exact_strided_and_shared():
         assert np.array_equal(wl.bf16_bits(Vo[l, b, h][:c]), ora.compact(wl.bf16_bits(V[l, b, h]), sidx[b][:c]))
 
 
+@pytest.mark.parametrize("K", [1, 7, 16, 31, 32, 33, 65, 150])
+@pytest.mark.parametrize("paged", [False, True])
+def test_compact_rows_of_several_units_in_a_workgroup(K, paged):
+    """Rows go to workgroups in the flat order of all units: counts from none to all, indices behind a count that are no positions, a last workgroup that
+    is not full; rows past a count stay as they were."""
+    layers, batch, hkv, n = 3, 5, 3, 200
+    g = torch.Generator(device=DEV).manual_seed(K)
+    Kin, Vin = (torch.randint(-30000, 30000, (layers, batch, hkv, n, 128), generator=g, device=DEV, dtype=torch.int16).view(torch.bfloat16) for _ in range(2))
+    idx = torch.rand((layers, batch, hkv, n), generator=g, device=DEV).topk(K, dim=-1).indices.sort(-1).values.to(torch.int32)
+    cnt = torch.randint(0, K + 1, (layers, batch, hkv), generator=g, device=DEV, dtype=torch.int32)
+    cnt[0, 0], cnt[1, 2], cnt[-1, -1] = K, 0, K
+    cnt[1, 0, 0] = K + 5                                             # clamped
+    live = torch.arange(K, device=DEV) < cnt[..., None]
+    want = [torch.where(live[..., None], t.view(torch.int16).gather(3, idx.long()[..., None].expand(-1, -1, -1, -1, 128)), 7) for t in (Kin, Vin)]
+    given = torch.where(live, idx, -1 << 30)
+    out = tuple(torch.full((layers, batch, hkv, K, 128), 7, dtype=torch.int16, device=DEV).view(torch.bfloat16) for _ in range(2))
+    if paged:
+        Kp, Vp, table, pages, strides = wl.make_paged(Kin, Vin, 16)
+        ta.ta_compact_paged(ta.PagedKV(Kp, Vp, table, 16, pages, strides, layers, batch, hkv, n), given, cnt, K, out=out)
+    else:
+        ta.ta_compact(Kin, Vin, given, cnt, K, out=out)
+    for o, w in zip(out, want):
+        assert torch.equal(o.view(torch.int16), w)
+
+
 def test_compact_more_workgroups_than_one_line():
-    # 2^23 workgroups of a tensor and a few more: a second line of the launch, all but empty
+    """A second line of the launch (2^23 workgroups of 32 rows and more): every layer of the destination's pages is the same one, and of 2^23 units
+    two have rows, in different heads, the first and the last."""
+    layers, hkv, K, n = (1 << 20) + 1, 8, 33, 40
+    Kin, Vin = (torch.randint(-30000, 30000, (1, 1, hkv, n, 128), dtype=torch.int16, device=DEV).view(torch.bfloat16).expand(layers, -1, -1, -1, -1) for _ in range(2))
+    idx, cnt = torch.zeros((layers, 1, hkv, K), dtype=torch.int32, device=DEV), torch.zeros((layers, 1, hkv), dtype=torch.int32, device=DEV)
+    at = torch.arange(n - K, n, device=DEV)
+    for l, h in ((0, 0), (layers - 1, hkv - 1)):
+        idx[l, 0, h], cnt[l, 0, h] = at.to(torch.int32), K
+    pool = [torch.full((1, 3, 11, hkv, 128), 7, dtype=torch.int16, device=DEV) for _ in range(2)]
+    dst = ta.PagedKV(pool[0].view(torch.bfloat16), pool[1].view(torch.bfloat16), torch.tensor([[2, 0, 1]], dtype=torch.int32, device=DEV), 11, 3,
+                     (0, 11 * hkv * 128, hkv * 128, 128), layers, 1, hkv, K)
+    ta.ta_compact_into_pages(Kin, Vin, idx, cnt, K, dst)
+    for t, p in zip((Kin, Vin), pool):
+        want = torch.full((33, hkv, 128), 7, dtype=torch.int16, device=DEV)
+        for h in (0, hkv - 1):
+            want[:, h] = t[0, 0, h, at].view(torch.int16)
+        assert torch.equal(p[0, [2, 0, 1]].view(33, hkv, 128), want)
+
+
+def test_compact_units_of_one_row():
+    # 2^23 units of one row and a few more
     layers, hkv = (1 << 20) + 1, 8
     K = torch.randint(-30000, 30000, (layers, 1, hkv, 1, 128), dtype=torch.int16, device=DEV).view(torch.bfloat16)
     V = K.flip(0)
