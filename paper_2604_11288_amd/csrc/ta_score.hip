@@ -258,9 +258,11 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 
     // Stages whose keys are all visible to every row: [0, nfast).  The column-sum sweep visits them in the reverse order of the
     // statistics sweep: what that sweep read last is the likeliest to still sit in the last-level cache.
-    // (Starting at a stage that differs from block to block, as an earlier form did, is no faster and costs its arithmetic.  Whole pass, us, with
-    // that / without: 8 units of 4096 keys 21.7 / 20.5, 256 of 16 384 with 64 rows 376 / 365, 2048 of 4096 794 / 785; full_model_4k 144.2 / 143.4,
-    // pooled_layers_8k 267.5 / 266.1, long_context_128k 4565 / 4540.)
+    // (Starting at a stage that differs from block to block, as an earlier form did, costs its arithmetic and is faster only where chunks of 1 MB lie 1 MB
+    // apart and all run at once.  Whole pass, us, with that / without: 8 units of 4096 keys 21.7 / 20.5, 256 of 16 384 with 64 rows 376 / 365, 2048 of
+    // 4096 794 / 785, 24 layers of 8192 keys, 256 rows, 267.5 / 266.1, one sequence of 131 072 4565 / 4540; one sweep, 512 units of 8192 keys 191 / 185, 128 of
+    // 32 768 194 / 185, 64 of 32 768 95 / 103, with 64 rows 32 of 65 536 89 / 95.  Every other chunk in the opposite order mends those, 102 and 91, and costs
+    // as much elsewhere: 256 rows, 64 of 32 768 keys 135 / 148, two sweeps, 128 rows, 256 of 16 384 350 / 363.)
     int nfast = min_lim >= key_lo + STAGE_KEYS - 1 ? (min_lim - key_lo + 1) / STAGE_KEYS : 0;
     nfast = nfast > nstages ? nstages : nfast;
     const auto stage_pos = [&](int s) { return COLSUM && s < nfast ? nfast - 1 - s : s; };

@@ -124,7 +124,7 @@ def test_whole_pass_with_given_lse():
                         ta.Params(n_sink=4, n_recent=4, alpha=0.0), seq_len=seq)
 
 
-@pytest.mark.parametrize("G, W, most, page_size", [(4, 32, 57, 0), (4, 64, 19, 0), (8, 64, 19, 0), (1, 512, 19, 0), (4, 32, 70, 64), (4, 64, 19, 128), (8, 64, 19, 64)])
+@pytest.mark.parametrize("G, W, most, page_size", [(4, 32, 57, 0), (4, 64, 19, 0), (8, 64, 19, 0), (1, 512, 19, 0), (4, 32, 57, 64), (4, 32, 70, 64), (4, 64, 19, 128), (8, 64, 19, 64)])
 def test_score_long_chunks_at_every_remainder(G, W, most, page_size):
     """Chunks of many stages, 128, 256 and 512 rows (two passes over a chunk; with other rows' limits in each where the window has as many), dense and over pages (of which 64 of a chunk are at hand, longer ones
     read the table): lengths whose fully visible stages end at every place of a turn of the main loop (four stages), at its start-up and
