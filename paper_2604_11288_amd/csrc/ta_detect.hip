@@ -99,24 +99,28 @@ __device__ __forceinline__ float add_squares(uint4 v, float acc)
 enum { MODE_MLP = 0, MODE_COSINE = 1 };
 
 // The order in which a wavefront visits its `steps` steps over the features.  Rows lie a power of two apart more often than not, so workgroups that
-// all begin at feature 0 read the same offset within their rows at the same time and crowd a few memory channels.  So the steps are dealt out, `chunk`
-// at a time, to 2^log parts, and neighbouring workgroups begin with different ones.  The sums of a part start from zero, and the parts' sums are added
+// all begin at feature 0 read the same offset within their rows at the same time and crowd a few memory channels.  So the steps lie in 2^log
+// parts, and neighbouring workgroups begin with different ones.  The sums of a part start from zero, and the parts' sums are added
 // up as a balanced tree (close_part).  A workgroup visits part (start ^ i) as the i-th: whatever its start, the same pairs of the tree meet, with at most
 // their operands exchanged, so a row's result does not depend, to the last bit, on where the row stands in the call.  (A start that wraps
 // round, each workgroup's another, spreads the reads further but adds up in as many orders.)
-// us, all at feature 0 / parts / wrapping starts: 128 256 rows of 4096, 16 concepts, four parts of four steps 187 / 150 = 7.0 TB/s / 148; 131 072
-// positions of 4096, 128 units, four parts of 1 KB 240 / 203 / 191, 32 768 62 / 54 / 50; 64 units, four parts 208 / 200 / 188; 65 536 of 4096, 32 units, eight
-// parts 95 / 87 / 85; 131 072 of 2048, 32 units 100 / 88 / 88.  Which chunk is best differs by form: with 4 KB, or 2 KB where W1 counts, between
-// the starts these crowd the channels of the L2 in turn (64 units, 2 KB 235; 128 units, two parts 4 KB apart 400).
+// us, all at feature 0 / parts / wrapping starts, d_model 4096: 128 256 rows, 16 concepts, four parts 187 / 150 = 7.0 TB/s / 148; 131 072 positions,
+// 128 units, four parts 236 / 192 / 190, 32 768 62 / 57 / 52; 32 units, eight parts 187 / 174 / 171; d_model 2048, 131 072 positions, four parts, 128 units
+// 130 / 121 / 99, 64 units 108 / 104 / 101, 32 units 101 / 91 / 92.  Where the wavefronts' parts begin 2 or 4 KB apart and W1 counts as much as h, they crowd the channels
+// of the L2 in turn: 64 units with four wavefronts, four parts 235 for 213 at feature 0 (steps dealt out one by one 200, but d_model 2048 22 for 18), so in
+// order; 128 units, two parts 402.  Rows that are no multiple of 4 KB apart gain nothing (d_model 3072, 131 072 positions of 32 units 139 / 144).
 struct Visit {
-    int steps, log, chunk, parts, base, start, part, at, left;   // at: this step; left: steps of its part, with this one
-    // The parts [base, base + parts).  (Workgroup b runs on XCD b mod 8: neighbours of an XCD start at different parts.)
-    __device__ __forceinline__ Visit(int n, int l, int c, int of = 1, int share = 0)
-        : steps(n), log(l), chunk(c), parts((1 << l) / of), base(share * parts), start((int)(blockIdx.x >> 3) & (parts - 1)), part(0) { open(); }
+    int steps, chunk, parts, base, start, part, at, left;  // at: this step; left: steps of its part, with this one
+    // The parts [base, base + parts) of 2^log.  (Workgroup b runs on XCD b mod 8: neighbours of an XCD start at different parts.)
+    __device__ __forceinline__ Visit(int n, int log, int of = 1, int share = 0)
+        : steps(n), chunk((n + (1 << log) - 1) >> log), parts((1 << log) / of), base(share * parts), start((int)(blockIdx.x >> 3) & (parts - 1)), part(0)
+    {
+        open();
+    }
     __device__ __forceinline__ int steps_in(int first, int count) const    // of that many parts that follow each other
     {
-        const int turn = chunk << log, turns = steps / turn, most = count * chunk, rest = steps - turns * turn - first * chunk;
-        return turns * most + (rest < 0 ? 0 : (rest > most ? most : rest));
+        const int rest = steps - first * chunk, most = count * chunk;
+        return rest < 0 ? 0 : (rest > most ? most : rest);
     }
     __device__ __forceinline__ int total() const { return steps_in(base, parts); }
     __device__ __forceinline__ void open()
@@ -128,7 +132,6 @@ struct Visit {
     {
         ++at;
         --left;
-        if (at % chunk == 0) at += (chunk << log) - chunk;
     }
     __device__ __forceinline__ bool last() const { return part + 1 == parts; }
     __device__ __forceinline__ void to_full()              // on to a part that has steps left, if there is one
@@ -152,7 +155,7 @@ __device__ __forceinline__ void close_part(const Visit& v, T (&acc)[N], T (&tree
         }
 #pragma unroll
         for (int l = 1; l < LOG; ++l) {
-            if (((v.part + 1) & ((1 << l) - 1)) && !v.last()) break;   // uniform
+            if ((v.part + 1) & ((1 << l) - 1)) break;      // uniform
 #pragma unroll
             for (int j = 0; j < N; ++j) {
                 tree[l][j] += tree[l - 1][j];
@@ -165,16 +168,11 @@ __device__ __forceinline__ void close_part(const Visit& v, T (&acc)[N], T (&tree
     }
 }
 
-// Rows of less than 4 KB are read in order: their parts would be too short to pay for the additions (20 000 positions of 1024, 128 units, four
-// parts / one 18.5 / 17.3 us).
-template <int LOG>
-__device__ __forceinline__ int parts_log(int dm) { return dm >= 2048 ? LOG : 0; }
-
 // ---- shared form: the wavefronts of a workgroup share every slice ---------------------------------------
 // TW: wavefront rows over the positions (64 TW positions per workgroup); HT: 32-unit hidden tiles
 // per wavefront; MH: wavefront columns over the hidden units (m = 32 HT MH); MODE: which epilogue; DT_RING: slice
-// buffers, loads run DT_RING - 1 slices ahead; STREAM: see launch_hint; LOG, CHUNK: see Visit
-template <int TW, int HT, int MH, int MODE, int DT_RING, bool STREAM, int LOG, int CHUNK>
+// buffers, loads run DT_RING - 1 slices ahead; STREAM: see launch_hint; LOG: see Visit
+template <int TW, int HT, int MH, int MODE, int DT_RING, bool STREAM, int LOG>
 __global__ void __launch_bounds__(64 * TW * MH, 2)
 detect_kernel(DetectArgs a)
 {
@@ -231,7 +229,7 @@ detect_kernel(DetectArgs a)
     const uint32_t half_back = ((lane & 7) ^ (lane >> 3)) >= 4 ? 64u : 0u;   // half a slice: the second half repeats the first
     const char* hbase = reinterpret_cast<const char*>(a.h) + tile0 * a.h_row_bytes;
     const char* wbase = reinterpret_cast<const char*>(a.W1);
-    Visit ahead(nstages, parts_log<LOG>(a.dm), CHUNK), now = ahead;      // the slice to request, the slice to work on
+    Visit ahead(nstages, LOG), now = ahead;                // the slice to request, the slice to work on
     ahead.to_full();
     const auto issue = [&](int i) {
         const uint32_t dst = lds0 + (uint32_t)(i % DT_RING) * BUF_BYTES;
@@ -446,7 +444,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // 40 us), and the partial sums of the WV wavefronts meet once, in LDS, after the last step.
 // PT: 16-position tiles of a workgroup; NT: 16-unit tiles of the hidden layer (concepts); WV wavefronts, each of which
 // contracts every SHARES-th step of 64 features; R: steps in flight per wavefront; PW: wavefronts that have such a share of the steps together, each
-// half of its parts (2: twice as many requests in flight where the workgroups are few; the sums are those of 1, bit for bit); LOG, CHUNK: see Visit
+// half of its parts (2: twice as many requests in flight where the workgroups are few; the sums are those of 1, bit for bit); LOG: see Visit
 template <int PT, int NT, int WV, int R, int PW>
 struct SplitShape {
     static constexpr int POS = 16 * PT, M = 16 * NT, THREADS = 64 * WV;
@@ -460,7 +458,7 @@ struct SplitShape {
     static constexpr int LDS_BYTES = UNITS * 16 + (M + THREADS + NORMS * M + NORMS * POS) * 4;
 };
 
-template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG, int CHUNK, int PW>
+template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG, int PW>
 __global__ void __launch_bounds__(64 * WV)
 detect_split_kernel(DetectArgs a)
 {
@@ -481,7 +479,7 @@ detect_split_kernel(DetectArgs a)
     constexpr int SHARES = WV / PW;                        // wavefront w: every SHARES-th step from step w % SHARES on, parts by w / SHARES
     constexpr int LOGW = PW == 2 ? LOG - 1 : LOG;
     const int share = wave % SHARES;
-    Visit ahead(nsteps > share ? (nsteps - share + SHARES - 1) / SHARES : 0, PW == 2 ? LOG : parts_log<LOG>(a.dm), CHUNK, PW, wave / SHARES);
+    Visit ahead(nsteps > share ? (nsteps - share + SHARES - 1) / SHARES : 0, LOG, PW, wave / SHARES);
     const int mine = ahead.total();
     Visit now = ahead;                                     // the step to work on; ahead: the step to request
     ahead.to_full();
@@ -691,7 +689,7 @@ detect_split_kernel(DetectArgs a)
     }
 }
 
-template <int TW, int HT, int MH, int MODE, int RING, bool STREAM, int LOG = 0, int CHUNK = 1>
+template <int TW, int HT, int MH, int MODE, int RING, bool STREAM, int LOG = 0>
 hipError_t launch_one(const DetectArgs& a, hipStream_t st)
 {
     constexpr int M = 32 * HT * MH;
@@ -699,27 +697,27 @@ hipError_t launch_one(const DetectArgs& a, hipStream_t st)
     const size_t lds = (size_t)RING * (DT_TOKENS + M) * 128 + (size_t)M * 4 + (size_t)(MH + 1) * DT_TOKENS * 4;
     static DeviceOnce setup;                               // dynamic LDS above 64 KB needs the attribute (per instantiation)
     const hipError_t attr_err = setup.run([&](int) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_kernel<TW, HT, MH, MODE, RING, STREAM, LOG, CHUNK>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_kernel<TW, HT, MH, MODE, RING, STREAM, LOG>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned blocks = (unsigned)((a.total + DT_TOKENS - 1) / DT_TOKENS);
-    hipLaunchKernelGGL((detect_kernel<TW, HT, MH, MODE, RING, STREAM, LOG, CHUNK>), dim3(blocks), dim3(64 * TW * MH), lds, st, a);
+    hipLaunchKernelGGL((detect_kernel<TW, HT, MH, MODE, RING, STREAM, LOG>), dim3(blocks), dim3(64 * TW * MH), lds, st, a);
     return hipGetLastError();
 }
 
-template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG = 0, int CHUNK = 1, int PW = 1>
+template <int PT, int NT, int WV, int R, int MODE, bool STREAM, int LOG = 0, int PW = 1>
 hipError_t launch_split(const DetectArgs& a, hipStream_t st)
 {
     using S = SplitShape<PT, NT, WV, R, PW>;
     static DeviceOnce setup;
     const hipError_t attr_err = setup.run([&](int) {
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, CHUNK, PW>),
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, PW>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES);
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned blocks = (unsigned)((a.total + S::POS - 1) / S::POS);
-    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, CHUNK, PW>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
+    hipLaunchKernelGGL((detect_split_kernel<PT, NT, WV, R, MODE, STREAM, LOG, PW>), dim3(blocks), dim3(S::THREADS), S::LDS_BYTES, st, a);
     return hipGetLastError();
 }
 
@@ -729,45 +727,48 @@ hipError_t launch_split(const DetectArgs& a, hipStream_t st)
 // that gives every compute unit at most one workgroup (16 positions up to 4096, 32 up to 8192, 64 up to 16384), then
 // the shared form where W1's traffic counts.  Measured at d_model 4096 where no other is given, launches of a graph over inputs in turn, in us, split /
 // shared form with three buffers / with two:
-//   128 units:  16384: 37 / - / 61;  24000: 64.6 / 52.0 / 65.8;  32768: 70.4 / 54.3 / 69.3;  40000: 98 / 102 / 85;  131072: 254 / 205 / 203;
-//               d_model 2048, 16500: 36.0 / 28.9 / 35.2;  24000: 38.5 / 29.9 / 36.3;  32768: 41.8 / 33.6 / 38.4;
+//   128 units:  16384: 37 / - / 61;  24000: 64.6 / 50.6 / 65.8;  32768: 70.4 / 56 / 69.3;  40000: 98 / 102 / 84;  131072: 254 / 205 / 192;
+//               d_model 2048, 16500: 36.0 / 28.9 / 35.2;  24000: 38.5 / 29.8 / 36.3;  32768: 41.8 / 33.6 / 38.4;
 //               d_model 1024, 16500: 21.3 / 17.5 / 19.6;  24000: 25.0 / 19.3 / 21.4;  32768: 25.9 / 18.0 / 21.3
 //   256 units:  8192: 42 / 64 / -;  16384: 75 / 66 / -;  32768: 147 / 82 / -;  131072: - / 320 (128 positions) / 284 (256)
 //   64 units, 64 positions with four wavefronts / 32:  16384: 29.8 / 36.8;  65536: 108 / 133;  131072: 210 / 256
-//   32 units, 64 positions with eight wavefronts / 32 with four:  16384: 25.9 / 28.5;  65536: 91.8 / 93.4;  262144: 340 = 6.3 TB/s / 346
-//   up to 16 concepts (cosine), 32 positions with four wavefronts / 16 with eight (two per share of the features):  512 rows 10.5 / 6.9;  4096:
-//               10.8 / 8.8;  6000: 14.0 / 15.3;  8000: 15.1 / 16.5;  32000: 45.2 / 47.6;  128256: 159 / 171;  d_model 2048, 4096: 7.8 / 6.7;  100000: 65 / 86
-template <int MODE, bool STREAM>
+//   32 units, 64 positions with eight wavefronts / 32 with four:  16384: 25.9 / 28.5;  65536: 90.7 / 93.4;  262144: 336 = 6.4 TB/s / 346
+//   up to 16 concepts (cosine), 32 positions with four wavefronts / 16 with eight (two per share of the features):  512 rows 10.5 / 6.7;  4096:
+//               10.8 / 8.8;  6000: 13.7 / 15.3;  8000: 15.1 / 16.5;  32000: 42 / 47.6;  128256: 150 / 171;  d_model 2048, 4096: 7.8 / 6.7;  100000: 65 / 86
+// Parts (Visit) for the streamed rows that crowd, and for up to 16 concepts at any number of rows from d_model 2048 on: with few rows they are in the
+// caches, and parts cost their additions (12 000 positions of 2048, 32 units 13.0 / 14.3).
+template <int MODE, bool STREAM, bool PARTS>
 hipError_t launch_width(const DetectArgs& a, hipStream_t st)
 {
     const int64_t P = a.total;
     const int64_t cus = compute_units();
+    constexpr int FOUR = PARTS ? 2 : 0, EIGHT = PARTS ? 3 : 0, FOUR_MLP = MODE == MODE_MLP ? FOUR : 0;
     // Rows of few steps: fewer wavefronts, so that each has several steps of its own to keep in flight (d_model 1024, 131072
     // positions: 32 units 52 us with four wavefronts, 56 with eight, 64 units 58 with two, 68 with four; d_model 2048: 100 / 108, 108 / 124).
     const bool narrow = a.dm <= 2048;
     if (MODE == MODE_COSINE && a.wrows <= 16) {            // (both forms of a d_model add up alike: a table's rows and a prompt's get the same results)
         if (a.dm < 2048) return launch_split<2, 1, 4, 2, MODE, STREAM>(a, st);
-        if (P <= 4096) return launch_split<1, 1, 8, 2, MODE, STREAM, 2, 4, 2>(a, st);
-        return launch_split<2, 1, 4, 2, MODE, STREAM, 2, 4>(a, st);
+        if (P <= 4096) return launch_split<1, 1, 8, 2, MODE, STREAM, 2, 2>(a, st);
+        return launch_split<2, 1, 4, 2, MODE, STREAM, 2>(a, st);
     }
     switch (a.m) {
         case 32:
             if (P <= 4096) return launch_split<1, 2, 8, 2, MODE, STREAM>(a, st);
-            if (P <= 8192) return launch_split<2, 2, 4, 2, MODE, STREAM, 2, 2>(a, st);
-            if (narrow && P > 24576) return launch_split<2, 2, 4, 2, MODE, STREAM, 2, 2>(a, st);
-            return launch_split<4, 2, 8, 1, MODE, STREAM, 3, 1>(a, st);
+            if (P <= 8192) return launch_split<2, 2, 4, 2, MODE, STREAM, FOUR>(a, st);
+            if (narrow && P > 24576) return launch_split<2, 2, 4, 2, MODE, STREAM, FOUR>(a, st);
+            return launch_split<4, 2, 8, 1, MODE, STREAM, EIGHT>(a, st);
         case 64:
             if (P <= 4096) return launch_split<1, 4, 4, 3, MODE, STREAM>(a, st);
             if (P <= 8192) return launch_split<2, 4, 4, 2, MODE, STREAM>(a, st);
-            if (narrow && P > 24576) return launch_split<4, 4, 2, 2, MODE, STREAM, 2, 4>(a, st);
-            return launch_split<4, 4, 4, 2, MODE, STREAM, 2, 1>(a, st);
+            if (narrow && P > 24576) return launch_split<4, 4, 2, 2, MODE, STREAM, FOUR>(a, st);
+            return launch_split<4, 4, 4, 2, MODE, STREAM>(a, st);
         case 128:
             if (P <= 4096) return launch_split<1, 8, 4, 2, MODE, STREAM>(a, st);
             if (P <= 8192) return launch_split<2, 8, 4, 1, MODE, STREAM>(a, st);
             if (P <= 64 * cus) return launch_split<4, 8, 4, 1, MODE, STREAM>(a, st);
             // 128 positions per workgroup; three buffers (one workgroup per compute unit) while that is one round of workgroups
-            if (P <= 128 * cus) return launch_one<2, 2, 2, MODE, 3, STREAM, 2, 8>(a, st);
-            return launch_one<2, 2, 2, MODE, 2, STREAM, 2, 8>(a, st);
+            if (P <= 128 * cus) return launch_one<2, 2, 2, MODE, 3, STREAM, FOUR_MLP>(a, st);
+            return launch_one<2, 2, 2, MODE, 2, STREAM, FOUR_MLP>(a, st);
         default:
             if (P <= 4096) return launch_split<1, 16, 4, 1, MODE, STREAM>(a, st);
             if (P <= 8192) return launch_split<2, 16, 4, 1, MODE, STREAM>(a, st);
@@ -784,7 +785,8 @@ template <int MODE>
 hipError_t launch_hint(const DetectArgs& a, hipStream_t st)
 {
     constexpr int64_t STREAM_BYTES = int64_t(64) << 20;
-    return a.total * a.dm * 2 >= STREAM_BYTES ? launch_width<MODE, true>(a, st) : launch_width<MODE, false>(a, st);
+    if (a.total * a.dm * 2 < STREAM_BYTES) return launch_width<MODE, false, false>(a, st);
+    return a.dm >= 2048 && a.h_row_bytes % 4096 == 0 ? launch_width<MODE, true, true>(a, st) : launch_width<MODE, true, false>(a, st);
 }
 
 }  // namespace
