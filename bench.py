@@ -48,7 +48,7 @@ SCORE_TRAFFIC = {
     "c4_long_context": {      # profiles/evict_pass_c4_long_context_K1024.txt
         "bytes_per_step": 69.40e9,
         "sources": {
-            "ta_score.hip": "c9833c5f370521858e13d09e585c09219f7b21e6638851fe95e9f635e620b5b0",
+            "ta_score.hip": "88738f8bd940863e1b0f623d2acf6360baa79bea818341c8ceef6c1bd7e5a692",
             "ta_score_common.h": "63db8ddf5fa51de1c9c0bba8099d89dd4e23ca91ac5c5163b227273ce568d4e2",
             "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
             "ta_order.h": "27e88482dbbf44b482f6d8f51f84bef8be18f49efa01d8c75eb2464c1f23b8d4",
@@ -57,7 +57,7 @@ SCORE_TRAFFIC = {
     "c2_full_model": {        # profiles/score_two_sweep_c2_full_model_K1024.txt
         "bytes_per_step": 559.4e6,
         "sources": {
-            "ta_score.hip": "c9833c5f370521858e13d09e585c09219f7b21e6638851fe95e9f635e620b5b0",
+            "ta_score.hip": "88738f8bd940863e1b0f623d2acf6360baa79bea818341c8ceef6c1bd7e5a692",
             "ta_score_common.h": "63db8ddf5fa51de1c9c0bba8099d89dd4e23ca91ac5c5163b227273ce568d4e2",
             "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
             "ta_order.h": "27e88482dbbf44b482f6d8f51f84bef8be18f49efa01d8c75eb2464c1f23b8d4",
