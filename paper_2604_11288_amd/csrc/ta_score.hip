@@ -124,8 +124,10 @@ struct RiderArgs {
 // RG row groups of RT 32-row MFMA tiles each per workgroup; 2 * RG wavefronts.
 // row_base: first of the 64 * RG rows this call works on (units with more rows than the widest workgroup's 256 take several
 // calls; more row groups would leave too few registers per lane)
-template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool TURNS>
-__device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], int32_t row_base);
+// ONE: both sweeps over a unit of one chunk are this workgroup's, one after the other: the first leaves the rows' constants in s_one and
+// the second finds them there.
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool TURNS, bool ONE = false>
+__device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], int32_t row_base, float* s_one = nullptr);
 
 // one tile per wavefront: four wavefronts per SIMD (at most 128 registers each)
 template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool PASSES, bool TURNS>
@@ -168,8 +170,43 @@ score_match_kernel(ScoreArgs a, RiderArgs r)
     }
 }
 
-template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool TURNS>
-__device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], const int32_t row_base)
+// Both sweeps over units of one chunk each, in one launch: a workgroup sweeps its unit twice.  The second sweep begins with what the
+// first has read last and finds in the last-level cache what all workgroups that run at once have read in between, the statistics stay
+// in LDS, and one workgroup's second sweep runs beside its neighbour's first: no end of a launch in the middle.
+template <int RG, int RT, bool PAGED, bool TURNS>
+__device__ __forceinline__ void score_once(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS])
+{
+    __shared__ float s_one[32 * RT * RG];
+    score_body<RG, RT, false, PAGED, false, TURNS, true>(a, s_k, 0, s_one);
+    __syncthreads();                                       // the constants are in LDS, and nobody uses the stages' memory
+    score_body<RG, RT, true, PAGED, true, TURNS, true>(a, s_k, 0, s_one);
+}
+
+template <int RG, int RT, bool PAGED, bool TURNS>
+__global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
+score_once_kernel(ScoreArgs a)
+{
+    __shared__ uint4 s_k[lds_stages(RG)][STAGE_UNITS];
+    score_once<RG, RT, PAGED, TURNS>(a, s_k);
+}
+
+template <int RG, int RT, bool PAGED, bool TURNS>
+__global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
+score_once_match_kernel(ScoreArgs a, RiderArgs r)
+{
+    __shared__ uint4 s_k[lds_stages(RG)][STAGE_UNITS];
+    if (blockIdx.x >= r.score_blocks) {
+        if (threadIdx.x >= MATCH_THREADS) return;          // a tile is the work of four wavefronts
+        const uint32_t t = blockIdx.x - r.score_blocks;
+        match_expand_tile(r.m, r.tab, (int32_t)(t % (uint32_t)r.m.tiles), (int32_t)(t / (uint32_t)r.m.tiles),
+                          (int)threadIdx.x, *reinterpret_cast<MatchLds*>(&s_k[0][0]));
+        return;
+    }
+    score_once<RG, RT, PAGED, TURNS>(a, s_k);
+}
+
+template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool TURNS, bool ONE>
+__device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS], const int32_t row_base, float* s_one)
 {
     constexpr int ROW_TILES = RT;
     constexpr int GROUP_ROWS = 32 * RT;                    // rows of one wavefront
@@ -199,7 +236,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     constexpr int FLUSH = TURN;                            // stages of a half
     __shared__ float s_part[COLSUM ? 2 * FLUSH : 1][RG][STAGE_KEYS];
 
-    const int tid = threadIdx.x;
+    int tid = threadIdx.x;
+    if constexpr (ONE) asm volatile("" : "+v"(tid));       // (nothing that follows from it is kept in registers from one sweep for the other)
     const int lane = tid & 63, wave = tid >> 6;
     const int c32 = lane & 31, hf = lane >> 5;
     const int rg = wave % RG, kt = wave / RG;              // row group, key tile of the stage
@@ -244,7 +282,8 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 
     if (key_lo >= nb) {
         // the whole chunk lies past the end of this sequence: nothing is visible
-        if constexpr (!COLSUM) {
+        if constexpr (!COLSUM && ONE) {
+        } else if constexpr (!COLSUM) {
             float* st = a.ws + (((size_t)unit * a.nchunks + chunk) * a.rows_pad) * 2;
             for (int r = tid; r < a.rows_pad; r += THREADS) {
                 st[r * 2] = -INFINITY;
@@ -374,7 +413,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                 if (v > -INFINITY) c = v * 1.4426950408889634f;
             }
         }
-        if (!a.lse) {                                      // uniform
+        if constexpr (ONE) {
+            if (r < a.rows) c = s_one[lr];
+        } else if (!a.lse) {                               // uniform
             // Two threads per row, each with half of the chunks, all loads in flight: one round trip however many chunks
             // there are, so that few units can be cut into many.
             static_assert(sizeof(s_part) >= sizeof(float2) * ROWS, "the second halves pass through the partial sums' memory");
@@ -750,8 +791,12 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
                 const float mf = fmaxf(m_run[t], mo);
                 float zf = 0.0f;
                 if (mf > -INFINITY) zf = z_run[t] * fast_exp2(m_run[t] - mf) + zo * fast_exp2(mo - mf);
-                st[(row_base + r) * 2] = mf;
-                st[(row_base + r) * 2 + 1] = zf;
+                if constexpr (ONE) {
+                    s_one[r] = zf > 0.0f ? mf + log2f(zf) : INFINITY;
+                } else {
+                    st[(row_base + r) * 2] = mf;
+                    st[(row_base + r) * 2 + 1] = zf;
+                }
             }
         }
     }
@@ -788,6 +833,33 @@ hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* r
     return hipGetLastError();
 }
 
+template <int RG, int RT, bool TURNS>
+hipError_t launch_once(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
+{
+    if (rider && RG == 1) {                                // (as in launch_sweep)
+        const hipError_t e = launch_match(rider->tok, a.seq_len, a.batch, a.n, *rider->tab, rider->anchor_B, rider->allow,
+                                          rider->anchor, rider->spons, rider->vouch, st);
+        if (e != hipSuccess) return e;
+        rider = nullptr;
+    }
+    if constexpr (RG > 1) {
+        if (rider) {
+            RiderArgs r;
+            r.m = make_match_args(rider->tok, a.seq_len, a.batch, a.n, rider->anchor_B, rider->allow, rider->anchor, rider->spons,
+                                  rider->vouch);
+            r.tab = *rider->tab;
+            r.score_blocks = blocks;
+            const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
+            if (a.table) hipLaunchKernelGGL((score_once_match_kernel<RG, RT, true, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            else hipLaunchKernelGGL((score_once_match_kernel<RG, RT, false, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            return hipGetLastError();
+        }
+    }
+    if (a.table) hipLaunchKernelGGL((score_once_kernel<RG, RT, true, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
+    else hipLaunchKernelGGL((score_once_kernel<RG, RT, false, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
+    return hipGetLastError();
+}
+
 template <int RG, int RT, bool PASSES, bool TURNS>
 hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_t gathered, hipStream_t st)
 {
@@ -820,6 +892,20 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
         if (stream) return launch_sweep<RG, RT, true, !PASSES, PASSES, TURNS>(a, blocks, with, st);
         return launch_sweep<RG, RT, true, false, PASSES, TURNS>(a, blocks, with, st);
     };
+    // One chunk per unit: no workgroup needs another one's statistics, and one launch does both sweeps (score_once).  (Whole pass, us, two
+    // launches / one.  128 rows: 512 units of 700 keys 62.1 / 56.4, of 3000 162.5 / 156.0, 1024 of 1500 187 / 170, paged 4096 of 1500..3001 534 /
+    // 478, 2048 of 5000 1012 / 949, of 2048..16 384 1772 / 1686, of 16 384 2947 / 2901; 64 rows, 2048 of 2000 489 / 454, of 2048..16 384 1835 /
+    // 1660; 256 rows, 256 of 1000 63.0 / 56.4, 2048 of 2000 756 / 707, of 8000 2404 / 2292.  No shape was slower.  The second sweep with the
+    // streaming hint, whatever is gathered next: 1024 of 3000 without / with it 313 / 294, 1024 of 1500 with 500 rows gathered 238 / 235, 512
+    // of 700 56.4 / 56.8.)
+    // Several chunks per unit in one launch, the workgroups of a unit waiting for each other's statistics, was measured as well: 256
+    // units of 4096 keys 144.7 / 139.9, 8 of 4096 18.1 / 19.4, 256 of 8000 201 / 211.
+    if constexpr (!PASSES) {
+        if (!a.lse && a.nchunks == 1) {
+            a.backwards = 0;
+            return launch_once<RG, RT, TURNS>(a, blocks, rider, st);
+        }
+    }
     if (a.lse) return column_sums(rider);                  // the row normalisers are given: column sums alone
     a.keep_place = 0x7FFFFFFF;
     a.keep_stage = 1024;

@@ -1,0 +1,73 @@
+"""Units of one chunk: both sweeps of the score step by the same workgroup, against the oracle.
+
+A unit has one chunk where there are many units, or fewer than 128 keys.  The lengths lie around a stage of 64 keys, around the window (the
+masked stages), and around the number of stages from which the main loop goes by whole turns (12 with 256 rows, 48 with up to 128).
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_11288_amd as ta
+from oracle import ta_oracle as ora
+from paper_2604_11288_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _close(got, ref):
+    return np.all(np.abs(got - ref) <= 1e-3 * np.abs(ref) + 1e-7)
+
+
+def _check(w, A, Q, K, lens, causal, units):
+    G = w.hq // w.hkv
+    for l, b, g in units:
+        nb = int(lens[b])
+        ref = ora.score(wl.bf16_bits(Q[l, b, g * G:(g + 1) * G]), wl.bf16_bits(K[l, b, g, :nb]), causal) if nb else np.zeros(0, np.float32)
+        got = A[l, b, g].cpu().numpy()
+        assert _close(got[:nb], ref), (l, b, g, nb)
+        assert not got[nb:].any(), (l, b, g, nb)
+
+
+@pytest.mark.parametrize("hq,window,n,lens", [
+    (8, 16, 127, (127, 1, 64, 0)),            # 32 rows, fewer than 128 keys; an empty sequence
+    (16, 32, 65, (65, 63, 33, 2)),            # 64 rows
+    (32, 32, 100, (100, 32, 31, 99)),         # 128 rows; as many keys as window rows, one fewer
+    (64, 32, 126, (126, 65, 5, 0)),           # 256 rows
+])
+def test_short_rows_match_the_oracle(hq, window, n, lens):
+    w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=2, batch=4, n=n, hq=hq, hkv=8, window=window)
+    Q, K, _ = wl.make_qkv(w, device=DEV, with_v=False)
+    seq = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    for causal in (True, False):
+        A = torch.full((2, 4, 8, n), float("nan"), device=DEV)
+        ta.ta_score(Q, K, ta.Params(causal=causal), seq_len=seq, A=A)
+        _check(w, A, Q, K, lens, causal, [(l, b, g) for l in range(2) for b in range(4) for g in (0, 7)])
+
+
+@pytest.mark.parametrize("hq,window,n,lens,paged", [
+    (8, 32, 700, None, False),                # 32 rows, workgroups of two wavefronts
+    (32, 32, 3008, (3008, 3007, 129, 0, 1500, 64, 2944, 31), False),      # 47 stages, ragged
+    (32, 32, 3137, (3137, 3073, 3072, 128, 1, 700, 3136, 3000), False),   # 50 stages: whole turns
+    (32, 32, 1500, (1500, 1499, 64, 63, 0, 800, 1472, 33), True),
+    (64, 32, 704, None, False),               # 256 rows, 11 stages
+    (64, 32, 833, (833, 768, 767, 40, 0, 64, 832, 500), True),            # 14 stages: whole turns
+])
+def test_many_units_match_the_oracle(hq, window, n, lens, paged):
+    w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=16, batch=8, n=n, hq=hq, hkv=8, window=window)
+    Q, K, _ = wl.make_qkv(w, device=DEV, with_v=False)
+    seq = torch.tensor(lens, dtype=torch.int32, device=DEV) if lens else None
+    prm = ta.Params()
+    if paged:
+        ps = 64
+        slots = (n + ps - 1) // ps
+        table = torch.randperm(8 * slots, generator=torch.Generator().manual_seed(n)).to(torch.int32).view(8, slots)
+        pool = torch.zeros((16, 8 * slots, ps, 8, 128), dtype=torch.bfloat16, device=DEV)
+        rows = torch.zeros((16, 8, slots * ps, 8, 128), dtype=torch.bfloat16, device=DEV)
+        rows[:, :, :n] = K.transpose(2, 3)
+        pool[:, table.view(-1).long().to(DEV)] = rows.view(16, 8 * slots, ps, 8, 128)
+        kv = ta.PagedKV(pool, pool, table.to(DEV), ps, 8 * slots, pool.stride()[:4], 16, 8, 8, n)
+        A = ta.ta_score_paged(Q, kv, prm, seq_len=seq)
+    else:
+        A = ta.ta_score(Q, K, prm, seq_len=seq)
+    _check(w, A, Q, K, lens or (n,) * 8, True, [(l, b, (3 * l + b) % 8) for l in (0, 9, 15) for b in range(8)])
