@@ -177,7 +177,8 @@ template <int RG, int RT, bool PAGED, bool TURNS>
 __device__ __forceinline__ void score_once(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS])
 {
     __shared__ float s_one[32 * RT * RG];
-    score_body<RG, RT, false, PAGED, false, TURNS, true>(a, s_k, 0, s_one);
+    // (the first sweep with the streaming hint where a unit may have more stages than a.keep_last: see the rule at the launch)
+    score_body<RG, RT, false, PAGED, RG == 1 || (RG == 2 && TURNS), TURNS, true>(a, s_k, 0, s_one);
     __syncthreads();                                       // the constants are in LDS, and nobody uses the stages' memory
     score_body<RG, RT, true, PAGED, true, TURNS, true>(a, s_k, 0, s_one);
 }
@@ -343,7 +344,9 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
         lane_off[j] = (uint32_t)(row * a.k_sp + ((lane & 15) ^ (row & 15))) * 16u;
     }
     // STREAM: with the streaming hint; in the first sweep up to this stage only, those from it on are for the last-level cache
-    const int keep_from = STREAM && !COLSUM && place < a.keep_place ? (int)(((uint64_t)nstages * (uint64_t)a.keep_stage) >> 10) : 0;
+    int keep_from = 0;
+    if constexpr (STREAM && !COLSUM && ONE) keep_from = nstages > a.keep_last ? nstages - a.keep_last : 0;
+    else if constexpr (STREAM && !COLSUM) keep_from = place < a.keep_place ? (int)(((uint64_t)nstages * (uint64_t)a.keep_stage) >> 10) : 0;
     auto stage_issue = [&](int s) {
         const int32_t key0 = key_lo + stage_pos(s) * STAGE_KEYS;
         const uint4* sbase = stage_base(key0);
@@ -895,14 +898,23 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
     // One chunk per unit: no workgroup needs another one's statistics, and one launch does both sweeps (score_once).  (Whole pass, us, two
     // launches / one.  128 rows: 512 units of 700 keys 62.1 / 56.4, of 3000 162.5 / 156.0, 1024 of 1500 187 / 170, paged 4096 of 1500..3001 534 /
     // 478, 2048 of 5000 1012 / 949, of 2048..16 384 1772 / 1686, of 16 384 2947 / 2901; 64 rows, 2048 of 2000 489 / 454, of 2048..16 384 1835 /
-    // 1660; 256 rows, 256 of 1000 63.0 / 56.4, 2048 of 2000 756 / 707, of 8000 2404 / 2292.  No shape was slower.  The second sweep with the
+    // 1660; 256 rows, 256 of 1000 63.0 / 56.4, 2048 of 2000 756 / 707, of 8000 2404 / 2292.  The second sweep with the
     // streaming hint, whatever is gathered next: 1024 of 3000 without / with it 313 / 294, 1024 of 1500 with 500 rows gathered 238 / 235, 512
     // of 700 56.4 / 56.8.)
+    // The first sweep, with up to 128 rows, has the hint as well but for the last keep_last stages of a unit: twice what a workgroup's share of
+    // the cache holds, 64 stages (1 MB), 42 with 64 rows.  Without it long units of 64 rows lose more to what the workgroups push out of the cache
+    // between a unit's sweeps than one launch gives.  (Whole pass, us, two launches / one without / with the hint: 64 rows, 512 units of 32 768 keys
+    // 1448 / 1506 / 1424, of 16 384 746 / 762 / 728, paged 1671 / 1688 / 1638 of 32 768, 2048 of 2048..16 384 1800 / 1685 / 1641; 128 rows, 512 of
+    // 8000 412 / 399 / 385, of 16 384 781 / 778 / 753, 2048 of 6000 1215 / 1150 / 1122, of 2048..16 384 1768 / 1706 / 1669.  With the share itself
+    // 4096 of 3000 1257 for 1241, with three times the share 512 of 8000 393, 2048 of 6000 1153.)  128 rows with fewer than 48 stages (no TURNS) would
+    // stream nothing and go without the test.
     // Several chunks per unit in one launch, the workgroups of a unit waiting for each other's statistics, was measured as well: 256
     // units of 4096 keys 144.7 / 139.9, 8 of 4096 18.1 / 19.4, 256 of 8000 201 / 211.
     if constexpr (!PASSES) {
         if (!a.lse && a.nchunks == 1) {
             a.backwards = 0;
+            const int64_t at_once = blocks < RESIDENT * compute_units() ? blocks : RESIDENT * compute_units();
+            a.keep_last = (int32_t)(2 * LLC_BYTES / (STAGE_KEYS * 256) / at_once);
             return launch_once<RG, RT, TURNS>(a, blocks, rider, st);
         }
     }

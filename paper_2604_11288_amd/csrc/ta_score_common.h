@@ -31,6 +31,7 @@ struct ScoreArgs {
     int32_t units;
     int32_t causal;
     int32_t keep_place, keep_stage;    // first sweep: units from this place on and stages from this 1024th on are for the cache
+    int32_t keep_last;                 // both sweeps in one launch: so many last stages of a unit's first sweep are for the cache
     int32_t backwards;                 // sweep 2 takes the units and chunks in the opposite order
     float scale_log2;                  // log2(e) / sqrt(d)
     // one tensor per layer: DEVICE tables of per-layer base addresses (layer l starts at Ql[l], Kl[l]

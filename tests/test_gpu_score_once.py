@@ -52,6 +52,11 @@ def test_short_rows_match_the_oracle(hq, window, n, lens):
     (32, 32, 1500, (1500, 1499, 64, 63, 0, 800, 1472, 33), True),
     (64, 32, 704, None, False),               # 256 rows, 11 stages
     (64, 32, 833, (833, 768, 767, 40, 0, 64, 832, 500), True),            # 14 stages: whole turns
+    # units longer than what the first sweep leaves to the cache (64 stages with 128 rows, 42 with 64), and units of just that length
+    (32, 32, 4500, (4500, 4097, 4096, 4160, 4224, 100, 0, 4095), False),
+    (32, 32, 4500, (4500, 4097, 4096, 4160, 4224, 100, 0, 4095), True),   # 71 pages: beyond 64 of a chunk the table is read
+    (16, 32, 2900, (2900, 2753, 2752, 2689, 2688, 64, 0, 2687), False),   # 64 rows, workgroups of two wavefronts
+    (8, 32, 4500, (4500, 4097, 4096, 2689, 2688, 64, 0, 4224), True),
 ])
 def test_many_units_match_the_oracle(hq, window, n, lens, paged):
     w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=16, batch=8, n=n, hq=hq, hkv=8, window=window)
