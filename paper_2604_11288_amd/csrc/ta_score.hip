@@ -173,25 +173,25 @@ score_match_kernel(ScoreArgs a, RiderArgs r)
 // Both sweeps over units of one chunk each, in one launch: a workgroup sweeps its unit twice.  The second sweep begins with what the
 // first has read last and finds in the last-level cache what all workgroups that run at once have read in between, the statistics stay
 // in LDS, and one workgroup's second sweep runs beside its neighbour's first: no end of a launch in the middle.
-template <int RG, int RT, bool PAGED, bool TURNS>
+template <int RG, int RT, bool PAGED, bool STREAM, bool TURNS>
 __device__ __forceinline__ void score_once(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS])
 {
     __shared__ float s_one[32 * RT * RG];
     // (the first sweep with the streaming hint where a unit may have more stages than a.keep_last: see the rule at the launch)
-    score_body<RG, RT, false, PAGED, RG == 1 || (RG == 2 && TURNS), TURNS, true>(a, s_k, 0, s_one);
+    score_body<RG, RT, false, PAGED, STREAM && (RG == 1 || (RG == 2 && TURNS)), TURNS, true>(a, s_k, 0, s_one);
     __syncthreads();                                       // the constants are in LDS, and nobody uses the stages' memory
-    score_body<RG, RT, true, PAGED, true, TURNS, true>(a, s_k, 0, s_one);
+    score_body<RG, RT, true, PAGED, STREAM, TURNS, true>(a, s_k, 0, s_one);
 }
 
-template <int RG, int RT, bool PAGED, bool TURNS>
+template <int RG, int RT, bool PAGED, bool STREAM, bool TURNS>
 __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_once_kernel(ScoreArgs a)
 {
     __shared__ uint4 s_k[lds_stages(RG)][STAGE_UNITS];
-    score_once<RG, RT, PAGED, TURNS>(a, s_k);
+    score_once<RG, RT, PAGED, STREAM, TURNS>(a, s_k);
 }
 
-template <int RG, int RT, bool PAGED, bool TURNS>
+template <int RG, int RT, bool PAGED, bool STREAM, bool TURNS>
 __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_once_match_kernel(ScoreArgs a, RiderArgs r)
 {
@@ -203,7 +203,7 @@ score_once_match_kernel(ScoreArgs a, RiderArgs r)
                           (int)threadIdx.x, *reinterpret_cast<MatchLds*>(&s_k[0][0]));
         return;
     }
-    score_once<RG, RT, PAGED, TURNS>(a, s_k);
+    score_once<RG, RT, PAGED, STREAM, TURNS>(a, s_k);
 }
 
 template <int RG, int RT, bool COLSUM, bool PAGED, bool STREAM, bool TURNS, bool ONE>
@@ -836,7 +836,7 @@ hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* r
     return hipGetLastError();
 }
 
-template <int RG, int RT, bool TURNS>
+template <int RG, int RT, bool STREAM, bool TURNS>
 hipError_t launch_once(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
 {
     if (rider && RG == 1) {                                // (as in launch_sweep)
@@ -853,13 +853,13 @@ hipError_t launch_once(const ScoreArgs& a, unsigned blocks, const MatchRider* ri
             r.tab = *rider->tab;
             r.score_blocks = blocks;
             const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
-            if (a.table) hipLaunchKernelGGL((score_once_match_kernel<RG, RT, true, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
-            else hipLaunchKernelGGL((score_once_match_kernel<RG, RT, false, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            if (a.table) hipLaunchKernelGGL((score_once_match_kernel<RG, RT, true, STREAM, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
+            else hipLaunchKernelGGL((score_once_match_kernel<RG, RT, false, STREAM, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
             return hipGetLastError();
         }
     }
-    if (a.table) hipLaunchKernelGGL((score_once_kernel<RG, RT, true, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
-    else hipLaunchKernelGGL((score_once_kernel<RG, RT, false, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
+    if (a.table) hipLaunchKernelGGL((score_once_kernel<RG, RT, true, STREAM, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
+    else hipLaunchKernelGGL((score_once_kernel<RG, RT, false, STREAM, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
     return hipGetLastError();
 }
 
@@ -898,9 +898,13 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
     // One chunk per unit: no workgroup needs another one's statistics, and one launch does both sweeps (score_once).  (Whole pass, us, two
     // launches / one.  128 rows: 512 units of 700 keys 62.1 / 56.4, of 3000 162.5 / 156.0, 1024 of 1500 187 / 170, paged 4096 of 1500..3001 534 /
     // 478, 2048 of 5000 1012 / 949, of 2048..16 384 1772 / 1686, of 16 384 2947 / 2901; 64 rows, 2048 of 2000 489 / 454, of 2048..16 384 1835 /
-    // 1660; 256 rows, 256 of 1000 63.0 / 56.4, 2048 of 2000 756 / 707, of 8000 2404 / 2292.  The second sweep with the
-    // streaming hint, whatever is gathered next: 1024 of 3000 without / with it 313 / 294, 1024 of 1500 with 500 rows gathered 238 / 235, 512
-    // of 700 56.4 / 56.8.)
+    // 1660; 256 rows, 256 of 1000 63.0 / 56.4, 2048 of 2000 756 / 707, of 8000 2404 / 2292.)
+    // The second sweep has the streaming hint: the cache is full of the keys of the workgroups that run at once, and what they read for the last time should
+    // not displace them.  Neither sweep has it where there are up to SMALL_BYTES of keys and a third of them or more is gathered next: the cache then has
+    // room for both.  (Whole pass, us, without / with, K rows gathered.  1024 of 3000 keys 313 / 294, of 1500, K = 1024 317 / 315, of 900, K = 500 187 / 183,
+    // 256 rows, 512 of 1500, K = 1024 211 / 207; 512 of 1900 140.6 / 140.2 with K = 500, 178.7 / 180.7 with 1024.  Up to SMALL_BYTES: 512 of 700, K = 600
+    // 95.0 / 97.3, of 1000, K = 800 123.0 / 124.9, paged 500..1000, K = 400 90.9 / 92.9, 256 rows, 256 of 1000, K = 500 72.2 / 75.0; but 512 of 1000, K = 250
+    // 83.3 / 83.1, of 700, K = 16 50.3 / 50.5, 1024 of 500, K = 128 98.5 / 97.6, and the scores alone, 512 of 180 15.1 / 14.2.)
     // The first sweep, with up to 128 rows, has the hint as well but for the last keep_last stages of a unit: twice what a workgroup's share of
     // the cache holds, 64 stages (1 MB), 42 with 64 rows.  Without it long units of 64 rows lose more to what the workgroups push out of the cache
     // between a unit's sweeps than one launch gives.  (Whole pass, us, two launches / one without / with the hint: 64 rows, 512 units of 32 768 keys
@@ -915,7 +919,11 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
             a.backwards = 0;
             const int64_t at_once = blocks < RESIDENT * compute_units() ? blocks : RESIDENT * compute_units();
             a.keep_last = (int32_t)(2 * LLC_BYTES / (STAGE_KEYS * 256) / at_once);
-            return launch_once<RG, RT, TURNS>(a, blocks, rider, st);
+            // (workgroups of two wavefronts, and units of 48 stages that have one chunk each, come with more keys than that)
+            if constexpr (RG == 4 || (RG == 2 && !TURNS)) {
+                if (bytes <= SMALL_BYTES && 3 * (int64_t)gathered >= a.n) return launch_once<RG, RT, false, TURNS>(a, blocks, rider, st);
+            }
+            return launch_once<RG, RT, true, TURNS>(a, blocks, rider, st);
         }
     }
     if (a.lse) return column_sums(rider);                  // the row normalisers are given: column sums alone

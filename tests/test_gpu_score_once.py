@@ -76,3 +76,45 @@ def test_many_units_match_the_oracle(hq, window, n, lens, paged):
     else:
         A = ta.ta_score(Q, K, prm, seq_len=seq)
     _check(w, A, Q, K, lens or (n,) * 8, True, [(l, b, (3 * l + b) % 8) for l in (0, 9, 15) for b in range(8)])
+
+
+@pytest.mark.parametrize("hq,layers,n,budget,page_size", [
+    (32, 2, 190, 100, 0),                     # keys for the cache, no hint: up to 128 MiB of keys, a third of them gathered
+    (32, 2, 190, 64, 64),                     # 64 * 3 >= 190
+    (32, 2, 190, 63, 64),                     # 63 * 3 < 190
+    (32, 8, 1000, 400, 64),                   # 131 072 000 bytes of keys, just below the line
+    (32, 8, 1048, 400, 64),                   # and 137 363 456, above it
+    (64, 2, 190, 100, 64),                    # 256 rows, three stages
+    (64, 4, 1000, 500, 0),                    # 16 stages: whole turns
+    (64, 4, 1000, 334, 64),
+    (64, 4, 1000, 333, 64),
+])
+def test_whole_pass_with_and_without_the_streaming_hint(hq, layers, n, budget, page_size):
+    # the match rides along behind the units' workgroups
+    w = wl.scaled(wl.CONFIGS["c2_full_model"], layers=layers, batch=8, n=n, hq=hq, hkv=8, window=32, planted=2)
+    td = wl.make_tokens(w, clean=False)
+    lens = (n, n - 1, 64, 129, 0, 31, n // 2, 128)
+    seq = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    Q, K, V = wl.make_qkv(w, device=DEV)
+    prm = ta.Params(n_sink=4, n_recent=4)
+    tok = torch.from_numpy(td.tok).to(DEV)
+    if page_size:
+        Kp, Vp, table, pages, strides = wl.make_paged(K, V, page_size)
+        kv = ta.PagedKV(Kp, Vp, table, page_size, pages, strides, layers, 8, 8, n)
+        plan = ta.EvictPlan(tok, td.tab_ids, td.tab_len, Q, None, None, budget, prm, seq_len=seq, paged=kv)
+    else:
+        plan = ta.EvictPlan(tok, td.tab_ids, td.tab_len, Q, K, V, budget, prm, seq_len=seq)
+    plan.A.fill_(float("nan"))
+    plan.run()
+    units = [(l, b, (3 * l + b) % 8) for l in (0, layers - 1) for b in range(8)]
+    _check(w, plan.A, Q, K, lens, True, units)
+    for l, b, g in units:
+        nb = lens[b]
+        a, s, v = ora.evict_sequence(td.tok[b, :nb], td.tab_ids, td.tab_len) if nb else (np.zeros(0, np.uint8), np.zeros(0, np.uint8), np.zeros(0, np.float32))
+        assert np.array_equal(plan.anchor[b, :nb].cpu().numpy(), a) and np.array_equal(plan.spons[b, :nb].cpu().numpy(), s), b
+        assert np.array_equal(plan.vouch[b, :nb].cpu().numpy(), v), b
+        sel = ora.select(plan.A[l, b, g, :nb].cpu().numpy(), a, s, v, budget, 4, 4) if nb else np.zeros(0, np.int32)
+        c = int(plan.cnt[l, b, g])
+        assert c == len(sel) and np.array_equal(plan.idx[l, b, g, :c].cpu().numpy(), sel), (l, b, g)
+        rows = torch.from_numpy(sel).long().to(DEV)
+        assert torch.equal(plan.Kout[l, b, g, :c], K[l, b, g][rows]) and torch.equal(plan.Vout[l, b, g, :c], V[l, b, g][rows]), (l, b, g)
