@@ -121,6 +121,17 @@ struct RiderArgs {
     uint32_t score_blocks;
 };
 
+// a workgroup past the score grid: its tile, in the stages' memory
+template <int STAGES>
+__device__ __forceinline__ void match_tile_of_block(const RiderArgs& r, uint4 (*s_k)[STAGE_UNITS])
+{
+    static_assert(sizeof(MatchLds) <= sizeof(uint4) * STAGES * STAGE_UNITS, "match tile must fit the stage ring");
+    if (threadIdx.x >= MATCH_THREADS) return;              // a tile is the work of four wavefronts
+    const uint32_t t = blockIdx.x - r.score_blocks;
+    match_expand_tile(r.m, r.tab, (int32_t)(t % (uint32_t)r.m.tiles), (int32_t)(t / (uint32_t)r.m.tiles),
+                      (int)threadIdx.x, *reinterpret_cast<MatchLds*>(&s_k[0][0]));
+}
+
 // RG row groups of RT 32-row MFMA tiles each per workgroup; 2 * RG wavefronts.
 // row_base: first of the 64 * RG rows this call works on (units with more rows than the widest workgroup's 256 take several
 // calls; more row groups would leave too few registers per lane)
@@ -152,12 +163,8 @@ __global__ void __launch_bounds__(128 * RG, RT == 1 ? 4 : 2)
 score_match_kernel(ScoreArgs a, RiderArgs r)
 {
     __shared__ uint4 s_k[lds_stages(RG)][STAGE_UNITS];
-    static_assert(sizeof(MatchLds) <= sizeof(uint4) * lds_stages(RG) * STAGE_UNITS, "match tile must fit the stage ring");
     if (blockIdx.x >= r.score_blocks) {
-        if (threadIdx.x >= MATCH_THREADS) return;          // a tile is the work of four wavefronts
-        const uint32_t t = blockIdx.x - r.score_blocks;
-        match_expand_tile(r.m, r.tab, (int32_t)(t % (uint32_t)r.m.tiles), (int32_t)(t / (uint32_t)r.m.tiles),
-                          (int)threadIdx.x, *reinterpret_cast<MatchLds*>(&s_k[0][0]));
+        match_tile_of_block<lds_stages(RG)>(r, s_k);
         return;
     }
     if constexpr (!PASSES) {
@@ -197,10 +204,7 @@ score_once_match_kernel(ScoreArgs a, RiderArgs r)
 {
     __shared__ uint4 s_k[lds_stages(RG)][STAGE_UNITS];
     if (blockIdx.x >= r.score_blocks) {
-        if (threadIdx.x >= MATCH_THREADS) return;          // a tile is the work of four wavefronts
-        const uint32_t t = blockIdx.x - r.score_blocks;
-        match_expand_tile(r.m, r.tab, (int32_t)(t % (uint32_t)r.m.tiles), (int32_t)(t / (uint32_t)r.m.tiles),
-                          (int)threadIdx.x, *reinterpret_cast<MatchLds*>(&s_k[0][0]));
+        match_tile_of_block<lds_stages(RG)>(r, s_k);
         return;
     }
     score_once<RG, RT, PAGED, STREAM, TURNS>(a, s_k);
@@ -283,15 +287,14 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
 
     if (key_lo >= nb) {
         // the whole chunk lies past the end of this sequence: nothing is visible
-        if constexpr (!COLSUM && ONE) {
-        } else if constexpr (!COLSUM) {
+        if constexpr (COLSUM) {
+            zero_share();
+        } else if constexpr (!ONE) {
             float* st = a.ws + (((size_t)unit * a.nchunks + chunk) * a.rows_pad) * 2;
             for (int r = tid; r < a.rows_pad; r += THREADS) {
                 st[r * 2] = -INFINITY;
                 st[r * 2 + 1] = 0.0f;
             }
-        } else {
-            zero_share();
         }
         return;
     }
@@ -805,58 +808,55 @@ __device__ __forceinline__ void score_body(const ScoreArgs& a, uint4 (*s_k)[STAG
     }
 }
 
+// Workgroups narrower than a match tile: the match runs as a launch of its own in front of the sweep.
+hipError_t match_in_front(const ScoreArgs& a, const MatchRider& m, hipStream_t st)
+{
+    return launch_match(m.tok, a.seq_len, a.batch, a.n, *m.tab, m.anchor_B, m.allow, m.anchor, m.spons, m.vouch, st);
+}
+
+RiderArgs rider_args(const ScoreArgs& a, const MatchRider& m, unsigned blocks)
+{
+    RiderArgs r;
+    r.m = make_match_args(m.tok, a.seq_len, a.batch, a.n, m.anchor_B, m.allow, m.anchor, m.spons, m.vouch);
+    r.tab = *m.tab;
+    r.score_blocks = blocks;
+    return r;
+}
+
 template <int RG, int RT, bool COLSUM, bool STREAM, bool PASSES, bool TURNS>
 hipError_t launch_sweep(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
 {
-    if (rider && RG == 1) {
-        // workgroups narrower than a match tile: the match runs as a launch of its own in front of the sweep
-        const hipError_t e = launch_match(rider->tok, a.seq_len, a.batch, a.n, *rider->tab, rider->anchor_B, rider->allow,
-                                          rider->anchor, rider->spons, rider->vouch, st);
-        if (e != hipSuccess) return e;
-        rider = nullptr;
-    }
-    if constexpr (RG > 1) {
+    if constexpr (RG == 1) {
         if (rider) {
-            RiderArgs r;
-            r.m = make_match_args(rider->tok, a.seq_len, a.batch, a.n, rider->anchor_B, rider->allow, rider->anchor, rider->spons,
-                                  rider->vouch);
-            r.tab = *rider->tab;
-            r.score_blocks = blocks;
-            const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
-            if (a.table) hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, true, STREAM, PASSES, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
-            else hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, false, STREAM, PASSES, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
-            return hipGetLastError();
+            const hipError_t e = match_in_front(a, *rider, st);
+            if (e != hipSuccess) return e;
         }
+    } else if (rider) {
+        const RiderArgs r = rider_args(a, *rider, blocks);
+        const dim3 grid(blocks + (unsigned)r.m.tiles * (unsigned)r.m.batch);
+        if (a.table) hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, true, STREAM, PASSES, TURNS>), grid, dim3(128 * RG), 0, st, a, r);
+        else hipLaunchKernelGGL((score_match_kernel<RG, RT, COLSUM, false, STREAM, PASSES, TURNS>), grid, dim3(128 * RG), 0, st, a, r);
+        return hipGetLastError();
     }
-    if (a.table) {
-        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true, STREAM, PASSES, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
-    } else {
-        hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false, STREAM, PASSES, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
-    }
+    if (a.table) hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, true, STREAM, PASSES, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
+    else hipLaunchKernelGGL((score_kernel<RG, RT, COLSUM, false, STREAM, PASSES, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
     return hipGetLastError();
 }
 
 template <int RG, int RT, bool STREAM, bool TURNS>
 hipError_t launch_once(const ScoreArgs& a, unsigned blocks, const MatchRider* rider, hipStream_t st)
 {
-    if (rider && RG == 1) {                                // (as in launch_sweep)
-        const hipError_t e = launch_match(rider->tok, a.seq_len, a.batch, a.n, *rider->tab, rider->anchor_B, rider->allow,
-                                          rider->anchor, rider->spons, rider->vouch, st);
-        if (e != hipSuccess) return e;
-        rider = nullptr;
-    }
-    if constexpr (RG > 1) {
+    if constexpr (RG == 1) {
         if (rider) {
-            RiderArgs r;
-            r.m = make_match_args(rider->tok, a.seq_len, a.batch, a.n, rider->anchor_B, rider->allow, rider->anchor, rider->spons,
-                                  rider->vouch);
-            r.tab = *rider->tab;
-            r.score_blocks = blocks;
-            const unsigned extra = (unsigned)r.m.tiles * (unsigned)r.m.batch;
-            if (a.table) hipLaunchKernelGGL((score_once_match_kernel<RG, RT, true, STREAM, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
-            else hipLaunchKernelGGL((score_once_match_kernel<RG, RT, false, STREAM, TURNS>), dim3(blocks + extra), dim3(128 * RG), 0, st, a, r);
-            return hipGetLastError();
+            const hipError_t e = match_in_front(a, *rider, st);
+            if (e != hipSuccess) return e;
         }
+    } else if (rider) {
+        const RiderArgs r = rider_args(a, *rider, blocks);
+        const dim3 grid(blocks + (unsigned)r.m.tiles * (unsigned)r.m.batch);
+        if (a.table) hipLaunchKernelGGL((score_once_match_kernel<RG, RT, true, STREAM, TURNS>), grid, dim3(128 * RG), 0, st, a, r);
+        else hipLaunchKernelGGL((score_once_match_kernel<RG, RT, false, STREAM, TURNS>), grid, dim3(128 * RG), 0, st, a, r);
+        return hipGetLastError();
     }
     if (a.table) hipLaunchKernelGGL((score_once_kernel<RG, RT, true, STREAM, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
     else hipLaunchKernelGGL((score_once_kernel<RG, RT, false, STREAM, TURNS>), dim3(blocks), dim3(128 * RG), 0, st, a);
