@@ -309,13 +309,30 @@ def test_score_bits_follow_the_workspace_only_at_the_stated_size(layers, hkv, n,
 
 @pytest.mark.parametrize("window,layers,batch", [(16, 4, 97), (13, 5, 60), (32, 3, 90), (32, 4, 60), (64, 2, 70)])
 def test_score_more_workgroups_than_run_at_once(window, layers, batch):
-    # the second sweep takes units and chunks in the opposite order; 64 rows and fewer have workgroups of their own.  Some
-    # lengths take the order of ragged sequences (up to 64 of them)
+    # units of one chunk: a workgroup does both sweeps.  64 rows and fewer have workgroups of their own.  Some lengths take the
+    # order of ragged sequences (up to 64 of them)
     w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=layers, batch=batch, n=333, hq=8, hkv=2, window=window)
     units = [(l, b, g) for l in (0, layers - 1) for b in (0, 1, batch // 2, batch - 1) for g in (0, 1)]
     _check_score(w, units=units)
     lens = np.random.default_rng(batch).integers(0, 334, size=batch).astype(np.int32)
     _check_score(w, seq_len=lens, units=units)
+
+
+@pytest.mark.parametrize("window", [32, 16, 64])       # 128, 64 and 256 rows
+@pytest.mark.parametrize("layers,batch,n", [
+    (6, 43, 4096),       # 258 units of four chunks, 258 MiB of keys: the first sweep streams two units and leaves 256 to the cache
+    (8, 40, 4096),       # 320 of four chunks: 64 and 256
+    (4, 64, 4500),       # 256 units, 281 MiB; two chunks up to 128 rows, all at once: the last stages of each are left to the cache
+])
+def test_score_chunks_of_more_keys_than_the_cache_holds(window, layers, batch, n):
+    # a launch per sweep; with more workgroups than run at once the second sweep takes units and chunks in the opposite order
+    w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=layers, batch=batch, n=n, hq=4, hkv=1, window=window)
+    places = (0, 1, 2, 3, 63, 64, 65, layers * batch // 2, layers * batch - 2, layers * batch - 1)
+    _check_score(w, units=[(p // batch, p % batch, 0) for p in places])
+    lens = np.random.default_rng(n + batch).integers(0, n + 1, size=batch).astype(np.int32)
+    lens[5], lens[7] = 0, n
+    by_length = np.argsort(-lens, kind="stable")       # the order in which the sequences are taken
+    _check_score(w, seq_len=lens, units=[(l, int(by_length[r]), 0) for l in (0, layers - 1) for r in (0, 1, 8, batch // 2, batch - 2, batch - 1)])
 
 
 # --------------------------------------------------------------------------

@@ -1,7 +1,7 @@
 """Units of one chunk: both sweeps of the score step by the same workgroup, against the oracle.
 
-A unit has one chunk where there are many units, or fewer than 128 keys.  The lengths lie around a stage of 64 keys, around the window (the
-masked stages), and around the number of stages from which the main loop goes by whole turns (12 with 256 rows, 48 with up to 128).
+A unit has one chunk where there are many units, or up to 192 keys (two chunks take four stages of 64).  The lengths lie around a stage, around
+the window (the masked stages), and around the number of stages from which the main loop goes by whole turns (12 with 256 rows, 48 with up to 128).
 """
 import numpy as np
 import pytest
@@ -34,6 +34,11 @@ def _check(w, A, Q, K, lens, causal, units):
     (16, 32, 65, (65, 63, 33, 2)),            # 64 rows
     (32, 32, 100, (100, 32, 31, 99)),         # 128 rows; as many keys as window rows, one fewer
     (64, 32, 126, (126, 65, 5, 0)),           # 256 rows
+    (32, 32, 128, (128, 127, 65, 64)),
+    (8, 16, 192, (192, 191, 129, 128)),       # the longest of few units that have one chunk
+    (32, 32, 192, (192, 191, 129, 128)),
+    (64, 32, 192, (192, 191, 129, 128)),
+    (32, 32, 193, (193, 192, 129, 0)),        # two chunks
 ])
 def test_short_rows_match_the_oracle(hq, window, n, lens):
     w = wl.scaled(wl.CONFIGS["c1_single_layer"], layers=2, batch=4, n=n, hq=hq, hkv=8, window=window)
@@ -78,18 +83,25 @@ def test_many_units_match_the_oracle(hq, window, n, lens, paged):
     _check(w, A, Q, K, lens or (n,) * 8, True, [(l, b, (3 * l + b) % 8) for l in (0, 9, 15) for b in range(8)])
 
 
-@pytest.mark.parametrize("hq,layers,n,budget,page_size", [
-    (32, 2, 190, 100, 0),                     # keys for the cache, no hint: up to 128 MiB of keys, a third of them gathered
-    (32, 2, 190, 64, 64),                     # 64 * 3 >= 190
-    (32, 2, 190, 63, 64),                     # 63 * 3 < 190
-    (32, 8, 1000, 400, 64),                   # 131 072 000 bytes of keys, just below the line
-    (32, 8, 1048, 400, 64),                   # and 137 363 456, above it
-    (64, 2, 190, 100, 64),                    # 256 rows, three stages
-    (64, 4, 1000, 500, 0),                    # 16 stages: whole turns
-    (64, 4, 1000, 334, 64),
-    (64, 4, 1000, 333, 64),
+@pytest.mark.parametrize("hq,layers,n,budget,form", [
+    (32, 2, 190, 100, "dense"),               # keys for the cache, no hint: up to 128 MiB of keys, a third of them gathered
+    (32, 2, 190, 64, "pages of 64"),          # 64 * 3 >= 190
+    (32, 2, 190, 63, "pages of 64"),          # 63 * 3 < 190
+    (32, 8, 1000, 400, "pages of 64"),        # 131 072 000 bytes of keys, just below the line
+    (32, 8, 1048, 400, "pages of 64"),        # and 137 363 456, above it
+    (32, 8, 3200, 64, "dense"),               # 50 stages: whole turns
+    (32, 8, 3200, 64, "pages of 192"),        # a page size that is no power of two
+    (32, 8, 700, 64, "layers"),
+    (16, 8, 1100, 64, "pages of 64"),         # 64 rows: narrow workgroups, the match in front of them
+    (16, 8, 4500, 64, "layers"),
+    (64, 2, 190, 100, "pages of 64"),         # 256 rows, three stages
+    (64, 4, 1000, 500, "dense"),              # 16 stages: whole turns
+    (64, 4, 1000, 334, "pages of 64"),
+    (64, 4, 1000, 333, "pages of 64"),
+    (64, 8, 1100, 64, "layers"),
+    (64, 16, 640, 64, "pages of 192"),        # ten stages
 ])
-def test_whole_pass_with_and_without_the_streaming_hint(hq, layers, n, budget, page_size):
+def test_whole_pass_over_units_of_one_chunk(hq, layers, n, budget, form):
     # the match rides along behind the units' workgroups
     w = wl.scaled(wl.CONFIGS["c2_full_model"], layers=layers, batch=8, n=n, hq=hq, hkv=8, window=32, planted=2)
     td = wl.make_tokens(w, clean=False)
@@ -98,7 +110,10 @@ def test_whole_pass_with_and_without_the_streaming_hint(hq, layers, n, budget, p
     Q, K, V = wl.make_qkv(w, device=DEV)
     prm = ta.Params(n_sink=4, n_recent=4)
     tok = torch.from_numpy(td.tok).to(DEV)
-    if page_size:
+    if form == "layers":
+        plan = ta.LayerEvictPlan(tok, td.tab_ids, td.tab_len, list(Q), list(K), list(V), budget, prm, seq_len=seq)
+    elif form != "dense":
+        page_size = int(form.split()[-1])
         Kp, Vp, table, pages, strides = wl.make_paged(K, V, page_size)
         kv = ta.PagedKV(Kp, Vp, table, page_size, pages, strides, layers, 8, 8, n)
         plan = ta.EvictPlan(tok, td.tab_ids, td.tab_len, Q, None, None, budget, prm, seq_len=seq, paged=kv)
@@ -117,4 +132,4 @@ def test_whole_pass_with_and_without_the_streaming_hint(hq, layers, n, budget, p
         c = int(plan.cnt[l, b, g])
         assert c == len(sel) and np.array_equal(plan.idx[l, b, g, :c].cpu().numpy(), sel), (l, b, g)
         rows = torch.from_numpy(sel).long().to(DEV)
-        assert torch.equal(plan.Kout[l, b, g, :c], K[l, b, g][rows]) and torch.equal(plan.Vout[l, b, g, :c], V[l, b, g][rows]), (l, b, g)
+        assert torch.equal(plan.Kout[l][b, g, :c], K[l, b, g][rows]) and torch.equal(plan.Vout[l][b, g, :c], V[l, b, g][rows]), (l, b, g)
