@@ -48,8 +48,8 @@ SCORE_TRAFFIC = {
     "c4_long_context": {      # profiles/evict_pass_c4_long_context_K1024.txt
         "bytes_per_step": 69.33e9,
         "sources": {
-            "ta_score.hip": "07aeb64ec7f0d5c82a708ed28f3763de9f149ceb528deeb8655eeef4a812beb0",
-            "ta_score_common.h": "63db8ddf5fa51de1c9c0bba8099d89dd4e23ca91ac5c5163b227273ce568d4e2",
+            "ta_score.hip": "5a3eafc05654037a54b626d80772b520a2d310872eb3fca826e87ab13e5ddfe8",
+            "ta_score_common.h": "9e01b38df6ccd759cb53f083b31064f168af204204f6eee2e614bab2f01405f4",
             "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
             "ta_order.h": "27e88482dbbf44b482f6d8f51f84bef8be18f49efa01d8c75eb2464c1f23b8d4",
         },
@@ -57,8 +57,8 @@ SCORE_TRAFFIC = {
     "c2_full_model": {        # profiles/score_two_sweep_c2_full_model_K1024.txt
         "bytes_per_step": 559.4e6,
         "sources": {
-            "ta_score.hip": "88738f8bd940863e1b0f623d2acf6360baa79bea818341c8ceef6c1bd7e5a692",
-            "ta_score_common.h": "63db8ddf5fa51de1c9c0bba8099d89dd4e23ca91ac5c5163b227273ce568d4e2",
+            "ta_score.hip": "5a3eafc05654037a54b626d80772b520a2d310872eb3fca826e87ab13e5ddfe8",
+            "ta_score_common.h": "9e01b38df6ccd759cb53f083b31064f168af204204f6eee2e614bab2f01405f4",
             "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
             "ta_order.h": "27e88482dbbf44b482f6d8f51f84bef8be18f49efa01d8c75eb2464c1f23b8d4",
         },

@@ -14,7 +14,8 @@
 //   sweep 2 (colsum) : merge the chunk statistics of a row into one constant
 //                      c_r = m_r + log2 Z_r, recompute S, p = 2^(s - c_r),
 //                      sum p over the rows -> A
-// Both sweeps are one kernel template.  A workgroup owns one chunk of keys of
+// Both sweeps are one kernel template, a launch each; a unit of one chunk needs no other workgroup's statistics, and
+// its workgroup does both in one launch, its rows' constants in LDS (score_once).  A workgroup owns one chunk of keys of
 // one unit and streams it through LDS in 64-key stages: a ring of four 16 KB
 // buffers (three for units of at most 64 rows) filled by direct global->LDS loads
 // issued as many stages ahead but one (no staging registers), 16-byte chunks XOR-swizzled by row so that the
@@ -178,8 +179,8 @@ score_match_kernel(ScoreArgs a, RiderArgs r)
 }
 
 // Both sweeps over units of one chunk each, in one launch: a workgroup sweeps its unit twice.  The second sweep begins with what the
-// first has read last and finds in the last-level cache what all workgroups that run at once have read in between, the statistics stay
-// in LDS, and one workgroup's second sweep runs beside its neighbour's first: no end of a launch in the middle.
+// first has read last, the statistics stay in LDS, and there is no end of a launch in the middle: the second sweeps of some
+// workgroups run beside the first ones of others (on the same compute unit with up to 128 rows; with 256 a workgroup fills one).
 template <int RG, int RT, bool PAGED, bool STREAM, bool TURNS>
 __device__ __forceinline__ void score_once(const ScoreArgs& a, uint4 (*s_k)[STAGE_UNITS])
 {
@@ -871,23 +872,24 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
     a.units = (int32_t)units;
     const unsigned blocks = (unsigned)(8ll * ((units + 7) / 8) * a.nchunks);
     // More workgroups than run at once: the second sweep takes them in the opposite order, so that it begins with the keys that
-    // the first has read last and that the last-level cache (256 MB) still holds.  (Two sweeps, 128 rows, us: 512 units of 2048
-    // keys 115 -> 107, 1024 of 2048 224 -> 211, 1024 of 4096 419 -> 410, ragged 1024 of 1500..3001 249 -> 233; 256 rows, 192
-    // units of 8192 keys 283 -> 271.)  Where all run at once the stages of each do that already, and the ragged ones should
-    // keep the longest first (512 of 1500..3001: 126 -> 129).
+    // the first has read last and that the last-level cache (256 MB) still holds.  (Whole pass, us, units of several chunks, in the same order / the
+    // opposite: 320 units of 4096 keys, K = 1024 190 / 184, 384 of 8000 309 / 305, 320 of 16 384 491 / 491, with 64 rows 486 / 493, 256 rows, 192 units of
+    // 8192 248 / 249; ragged ones lose by it, 320 of 2048..8192 178 / 182, 336 of 4096..16 384 410 / 422.)  Where all run at once the stages of each do that
+    // already.
     constexpr int64_t RESIDENT = RG == 1 ? 3 : (RG == 2 ? 2 : 1);       // workgroups per compute unit, by their stage rings
     const bool rounds = blocks > RESIDENT * compute_units();
     a.backwards = !a.lse && rounds;
     // Keys that will not be read again are loaded with the streaming hint, which leaves less to evict: those of the only or the
     // second sweep, and in the first all but the last LLC_BYTES, which the second will begin with - of the last units or, where all
-    // run at once, of the last stages of each.  (Counted as if every sequence had n keys.  The last units of a ragged batch are
-    // its shortest: of 2048 units of 2048..16384 keys some 40 MB are kept, not 256.)  (Two sweeps, 128 rows, us: 256 units of 16 384 keys 396 -> 379, ragged 2048 of
-    // 2048..16384 1815 -> 1739, ragged 1024 of 1500..3001 238 -> 228; one sweep: 256 units of 4096 keys 59 -> 52, of 16 384
-    // 208 -> 195.  Streaming both sweeps of 256 units of 4096 keys: 5 % slower.)  Not below SMALL_BYTES, where the keys may
+    // run at once, of the last stages of each.  (Counted as if every sequence had n keys.  The last units of a ragged batch are its shortest, of
+    // which less is kept.)  (Whole pass, us, units of several chunks, the first sweep without / with: 320 units of 4096 keys 151 / 150, 384 of 8000 318 / 305,
+    // 320 of 16 384 507 / 491, with 64 rows 522 / 493, 256 of 16 384 389 / 383, with 64 rows 385 / 368, ragged 336 of 4096..16 384 438 / 422, but 320 of
+    // 2048..8192 180 / 182; the second: 384 of 8000 317 / 305, 256 of 16 384 401 / 383, 320 of 4096 149.8 / 149.9; one sweep: 256 units of 4096 keys 59 / 52,
+    // of 16 384 208 / 195.  Streaming both sweeps of 256 units of 4096 keys: 5 % slower.)  Not below SMALL_BYTES, where the keys may
     // be in the caches (64 units of 4096 keys 31 -> 33), and not the first sweep of 256 rows, which is bound by arithmetic
     // and loses more to the test than it gains; passes over a chunk's rows read its keys several times.  Where an eighth of the
-    // keys or more is gathered next and the cache holds a good part of them, the second sweep leaves them there (evict pass
-    // over 256 units of 4096 keys, 1024 rows 152 -> 147).
+    // keys or more is gathered next and the cache holds a good part of them, the second sweep leaves them there (evict pass,
+    // 1024 rows gathered, over 256 units of 4096 keys 151 -> 145, over 320 186.2 -> 184.4).  Units of one chunk have rules of their own, below.
     constexpr int64_t LLC_BYTES = int64_t(256) << 20, SMALL_BYTES = int64_t(128) << 20;
     const int64_t bytes = units * a.n * 256;
     const bool stream = !PASSES && bytes > SMALL_BYTES && !(gathered >= a.n / 8 && bytes <= 2 * LLC_BYTES);
@@ -896,9 +898,9 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
         return launch_sweep<RG, RT, true, false, PASSES, TURNS>(a, blocks, with, st);
     };
     // One chunk per unit: no workgroup needs another one's statistics, and one launch does both sweeps (score_once).  (Whole pass, us, two
-    // launches / one.  128 rows: 512 units of 700 keys 62.1 / 56.4, of 3000 162.5 / 156.0, 1024 of 1500 187 / 170, paged 4096 of 1500..3001 534 /
-    // 478, 2048 of 5000 1012 / 949, of 2048..16 384 1772 / 1686, of 16 384 2947 / 2901; 64 rows, 2048 of 2000 489 / 454, of 2048..16 384 1835 /
-    // 1660; 256 rows, 256 of 1000 63.0 / 56.4, 2048 of 2000 756 / 707, of 8000 2404 / 2292.)
+    // launches / one.  128 rows: 512 units of 700 keys 62.1 / 56.4, of 3000 162.5 / 156.0, 1024 of 1500 187 / 170, paged 2048 of 1500..3001 534 /
+    // 491, 4096 968 / 871, 2048 of 5000 1012 / 949, of 2048..16 384 1772 / 1686; 64 rows, 2048 of 2000 489 / 454, of 2048..16 384 1835 / 1660;
+    // 256 rows, 256 of 1000 63.0 / 56.4, 2048 of 2000 756 / 707, of 8000 2404 / 2292.)
     // The second sweep has the streaming hint: the cache is full of the keys of the workgroups that run at once, and what they read for the last time should
     // not displace them.  Neither sweep has it where there are up to SMALL_BYTES of keys and a third of them or more is gathered next: the cache then has
     // room for both.  (Whole pass, us, without / with, K rows gathered.  1024 of 3000 keys 313 / 294, of 1500, K = 1024 317 / 315, of 900, K = 500 187 / 183,
@@ -909,9 +911,9 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
     // the cache holds, 64 stages (1 MB), 42 with 64 rows.  Without it long units of 64 rows lose more to what the workgroups push out of the cache
     // between a unit's sweeps than one launch gives.  (Whole pass, us, two launches / one without / with the hint: 64 rows, 512 units of 32 768 keys
     // 1448 / 1506 / 1424, of 16 384 746 / 762 / 728, paged 1671 / 1688 / 1638 of 32 768, 2048 of 2048..16 384 1800 / 1685 / 1641; 128 rows, 512 of
-    // 8000 412 / 399 / 385, of 16 384 781 / 778 / 753, 2048 of 6000 1215 / 1150 / 1122, of 2048..16 384 1768 / 1706 / 1669.  With the share itself
-    // 4096 of 3000 1257 for 1241, with three times the share 512 of 8000 393, 2048 of 6000 1153.)  128 rows with fewer than 48 stages (no TURNS) would
-    // stream nothing and go without the test.
+    // 8000 412 / 399 / 385, of 16 384 781 / 778 / 753, 2048 of 6000 1215 / 1150 / 1122, of 16 384 2991 / 2996 / 2966, of 2048..16 384 1768 / 1706 /
+    // 1669.  With the share itself 4096 of 3000 1257 for 1241, with three times the share 512 of 8000 393, 2048 of 6000 1153.)  128 rows with fewer than
+    // 48 stages (no TURNS) would stream nothing and go without the test.
     // Several chunks per unit in one launch, the workgroups of a unit waiting for each other's statistics, was measured as well: 256
     // units of 4096 keys 144.7 / 139.9, 8 of 4096 18.1 / 19.4, 256 of 8000 201 / 211.
     if constexpr (!PASSES) {
@@ -919,7 +921,7 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
             a.backwards = 0;
             const int64_t at_once = blocks < RESIDENT * compute_units() ? blocks : RESIDENT * compute_units();
             a.keep_last = (int32_t)(2 * LLC_BYTES / (STAGE_KEYS * 256) / at_once);
-            // (workgroups of two wavefronts, and units of 48 stages that have one chunk each, come with more keys than that)
+            // (a pass takes workgroups of two wavefronts, and one chunk of 48 stages per unit, only with more keys than that)
             if constexpr (RG == 4 || (RG == 2 && !TURNS)) {
                 if (bytes <= SMALL_BYTES && 3 * (int64_t)gathered >= a.n) return launch_once<RG, RT, false, TURNS>(a, blocks, rider, st);
             }
