@@ -48,7 +48,7 @@ SCORE_TRAFFIC = {
     "c4_long_context": {      # profiles/evict_pass_c4_long_context_K1024.txt
         "bytes_per_step": 69.33e9,
         "sources": {
-            "ta_score.hip": "5a3eafc05654037a54b626d80772b520a2d310872eb3fca826e87ab13e5ddfe8",
+            "ta_score.hip": "3ddad88ebe2531b1b1ebc91e0f550d5828b2d8277bba805e79e860cd471a6314",
             "ta_score_common.h": "9e01b38df6ccd759cb53f083b31064f168af204204f6eee2e614bab2f01405f4",
             "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
             "ta_order.h": "27e88482dbbf44b482f6d8f51f84bef8be18f49efa01d8c75eb2464c1f23b8d4",
@@ -57,7 +57,7 @@ SCORE_TRAFFIC = {
     "c2_full_model": {        # profiles/score_two_sweep_c2_full_model_K1024.txt
         "bytes_per_step": 559.4e6,
         "sources": {
-            "ta_score.hip": "5a3eafc05654037a54b626d80772b520a2d310872eb3fca826e87ab13e5ddfe8",
+            "ta_score.hip": "3ddad88ebe2531b1b1ebc91e0f550d5828b2d8277bba805e79e860cd471a6314",
             "ta_score_common.h": "9e01b38df6ccd759cb53f083b31064f168af204204f6eee2e614bab2f01405f4",
             "ta_match_device.h": "82dda095d1ab2432b8e6ae137ab7828a7d0152ac0ac0fa90e6949b25039a4a81",
             "ta_order.h": "27e88482dbbf44b482f6d8f51f84bef8be18f49efa01d8c75eb2464c1f23b8d4",

@@ -897,6 +897,18 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
         if (stream) return launch_sweep<RG, RT, true, !PASSES, PASSES, TURNS>(a, blocks, with, st);
         return launch_sweep<RG, RT, true, false, PASSES, TURNS>(a, blocks, with, st);
     };
+    if (a.lse) return column_sums(rider);                  // the row normalisers are given: column sums alone
+    if (PASSES || a.nchunks > 1) {
+        a.keep_place = 0x7FFFFFFF;
+        a.keep_stage = 1024;
+        if (rounds) a.keep_place = (int32_t)(units - units * LLC_BYTES / bytes);
+        else a.keep_stage = (int32_t)(1024 - 1024 * LLC_BYTES / bytes);
+        constexpr bool FIRST = RG < 4;
+        const hipError_t e = FIRST && bytes > LLC_BYTES ? launch_sweep<RG, RT, false, FIRST, PASSES, TURNS>(a, blocks, rider, st)
+                                                        : launch_sweep<RG, RT, false, false, PASSES, TURNS>(a, blocks, rider, st);
+        if (e != hipSuccess) return e;
+        return column_sums(nullptr);
+    }
     // One chunk per unit: no workgroup needs another one's statistics, and one launch does both sweeps (score_once).  (Whole pass, us, two
     // launches / one.  128 rows: 512 units of 700 keys 62.1 / 56.4, of 3000 162.5 / 156.0, 1024 of 1500 187 / 170, paged 2048 of 1500..3001 534 /
     // 491, 4096 968 / 871, 2048 of 5000 1012 / 949, of 2048..16 384 1772 / 1686; 64 rows, 2048 of 2000 489 / 454, of 2048..16 384 1835 / 1660;
@@ -916,28 +928,19 @@ hipError_t launch_rg(ScoreArgs a, int64_t units, const MatchRider* rider, int32_
     // 48 stages (no TURNS) would stream nothing and go without the test.
     // Several chunks per unit in one launch, the workgroups of a unit waiting for each other's statistics, was measured as well: 256
     // units of 4096 keys 144.7 / 139.9, 8 of 4096 18.1 / 19.4, 256 of 8000 201 / 211.
+    // (These instances come last: the compiler emits kernels in the order of use here, and the two launches of a pass run 0.5 % faster with less code
+    // between them: 256 units of 4096 keys, K = 1024 146.1 -> 145.3.)
     if constexpr (!PASSES) {
-        if (!a.lse && a.nchunks == 1) {
-            a.backwards = 0;
-            const int64_t at_once = blocks < RESIDENT * compute_units() ? blocks : RESIDENT * compute_units();
-            a.keep_last = (int32_t)(2 * LLC_BYTES / (STAGE_KEYS * 256) / at_once);
-            // (a pass takes workgroups of two wavefronts, and one chunk of 48 stages per unit, only with more keys than that)
-            if constexpr (RG == 4 || (RG == 2 && !TURNS)) {
-                if (bytes <= SMALL_BYTES && 3 * (int64_t)gathered >= a.n) return launch_once<RG, RT, false, TURNS>(a, blocks, rider, st);
-            }
-            return launch_once<RG, RT, true, TURNS>(a, blocks, rider, st);
+        a.backwards = 0;
+        const int64_t at_once = blocks < RESIDENT * compute_units() ? blocks : RESIDENT * compute_units();
+        a.keep_last = (int32_t)(2 * LLC_BYTES / (STAGE_KEYS * 256) / at_once);
+        // (a pass takes workgroups of two wavefronts, and one chunk of 48 stages per unit, only with more keys than that)
+        if constexpr (RG == 4 || (RG == 2 && !TURNS)) {
+            if (bytes <= SMALL_BYTES && 3 * (int64_t)gathered >= a.n) return launch_once<RG, RT, false, TURNS>(a, blocks, rider, st);
         }
+        return launch_once<RG, RT, true, TURNS>(a, blocks, rider, st);
     }
-    if (a.lse) return column_sums(rider);                  // the row normalisers are given: column sums alone
-    a.keep_place = 0x7FFFFFFF;
-    a.keep_stage = 1024;
-    if (rounds) a.keep_place = (int32_t)(units - units * LLC_BYTES / bytes);
-    else a.keep_stage = (int32_t)(1024 - 1024 * LLC_BYTES / bytes);
-    constexpr bool FIRST = RG < 4;
-    const hipError_t e = FIRST && bytes > LLC_BYTES ? launch_sweep<RG, RT, false, FIRST, PASSES, TURNS>(a, blocks, rider, st)
-                                                    : launch_sweep<RG, RT, false, false, PASSES, TURNS>(a, blocks, rider, st);
-    if (e != hipSuccess) return e;
-    return column_sums(nullptr);
+    return hipErrorInvalidValue;                           // (not reached)
 }
 
 }  // namespace
